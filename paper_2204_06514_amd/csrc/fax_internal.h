@@ -60,10 +60,16 @@ struct GemmArgs {
   // Scratch for splitting the contraction (fp32-output form only): gemm_split_ws_bytes(M, N, K)
   // bytes, or NULL to forbid the split.
   void* split_ws = nullptr;
+  // Internal buffers only: the rows of A, as stored, are readable up to the next multiple of 8 elements
+  // (zeros there if the contraction runs along them) / B stored [N, K] has only this many rows (0: N);
+  // the columns of C beyond them hold nothing meaningful.
+  bool a_padded = false;
+  int b_rows = 0;
 };
 int gemm(const GemmArgs& g, hipStream_t s);
 int gemm_simt(const GemmArgs& g, hipStream_t s);
 bool gemm_mfma_supported(const GemmArgs& g);
+bool gemm_edge_supported(const GemmArgs& g);
 // A weight-gradient product of a narrow model has few output tiles and a very long contraction
 // (K = all tokens): it is then cut into K ranges, each a full set of tiles writing its own fp32
 // partial product (and partial column sums), summed afterwards in a fixed order.  The plan (tile
@@ -79,6 +85,8 @@ int gemm_tile_walk_query(int M, int N, int K, bool f32_out, int* tm, int* tn, in
 // Predicted duration of gemm() on this shape from the same cost model (host only), microseconds.
 double gemm_time_estimate_us(int M, int N, int K, bool f32_out);
 int gemm_mfma(const GemmArgs& g, hipStream_t s);
+struct EpiArgs;
+int gemm_mfma_edge(const GemmArgs& g, const EpiArgs& e, const GemmSplitPlan& plan, hipStream_t s);
 
 // ---- LayerNorm, column sums ---------------------------------------------------------------
 int ln_fwd(int dtype, int rows, int D, const void* x, const void* gamma, const void* beta, float eps,
@@ -297,6 +305,7 @@ struct EpiArgs {
   size_t split_stride;  // in elements
   size_t colsum_stride; // likewise for the column sums: range r writes colsum + r * colsum_stride
   int group;            // tile rows per column-major group of the tile walk (MFMA kernel)
+  int a_lim, b_lim;     // masked-edge form of the MFMA kernel: extent of op(A) along M, of op(B) along N, that may be read
 };
 
 template <typename T>

@@ -61,17 +61,30 @@ struct TileLds {
 // (four rows, two apart), bit 3 of kr to bit 0.
 __device__ __forceinline__ int mc_swizzle(int kr) { return ((kr & 3) << 1) | ((kr >> 3) & 1); }
 
-template <int ROWS, bool KC>
-__device__ __forceinline__ unsigned slab_lane_offset(int ld, int b) {
+// EDGE: the operand ends `lim` rows (KC) or columns (MC, at least 8 of them) after the slab's first; a
+// lane whose chunk lies beyond fetches the last one instead: finite or not, what it brings only
+// reaches outputs that are not stored.
+template <int ROWS, bool KC, bool EDGE>
+__device__ __forceinline__ unsigned slab_lane_offset(int ld, int b, int lim) {
   if (KC) {
     const int row = b >> 7, pc = (b >> 4) & 7;
-    return (unsigned)(row * ld + ((pc ^ ((row >> 1) & 7)) << 3)) * 2u;
+    const int chunk = pc ^ ((row >> 1) & 7);
+    return (unsigned)((EDGE ? min(row, lim - 1) : row) * ld + (chunk << 3)) * 2u;
   }
   constexpr int RB = ROWS * 2;  // bytes per k-row
   const int kr = b / RB, pc = (b % RB) >> 4;
   const int lc = (((pc >> 1) ^ mc_swizzle(kr)) << 1) | (pc & 1);
-  return (unsigned)(kr * ld + (lc << 3)) * 2u;
+  return (unsigned)(kr * ld + (EDGE ? min(lc << 3, lim - 8) : lc << 3)) * 2u;
 }
+// First contraction index, within the slab, of that chunk.
+template <int ROWS, bool KC>
+__device__ __forceinline__ int slab_lane_k(int b) {
+  if (KC) return (((b >> 4) & 7) ^ ((b >> 8) & 7)) << 3;
+  return b / (ROWS * 2);
+}
+
+// Where lanes of an EDGE kernel fetch from whose contraction index lies beyond the end.
+static __device__ const uint4 gemm_zero16 = {0u, 0u, 0u, 0u};
 
 // One MFMA operand (8 bf16 per lane) for the 32 rows starting at rb, k-step ks (16 wide).
 template <int ROWS, bool KC>
@@ -200,7 +213,16 @@ __host__ __device__ inline void tile_walk(int id, int tiles_m, int tiles_n, int 
   tn_i = (id % per_group) / gsz;
 }
 
-template <int BM, int BN, bool A_KC, bool B_KC, int EM>
+// EDGE = false: M, N are multiples of the tile, K of the slab.  EDGE = true: any M, N, K.  Rows and
+// columns beyond the operands' ends are fetched from their last row or column group (e.a_lim, e.b_lim:
+// how far the operands reach) and never stored; contraction indices beyond K are fetched as zeros
+// for both operands, by the last slab's loads only (a wave-uniform branch around each load: the
+// full slabs keep the scalar-base addressing).  Tiles inside the output keep the unmasked epilogue.
+// Bound like the plain form by the rounds of tiles, padding included.  Against the scalar kernel that
+// these shapes ran on before, a block at 3000 tokens x 1200 wide (F = 4800): forward products 1440 ->
+// 180 us, input gradients 1610 -> 152, weight gradients with their bias sums 2470 -> 200, FFN-in with
+// the GELU epilogue 680 -> 136, GELU' 528 -> 57.
+template <int BM, int BN, bool A_KC, bool B_KC, int EM, bool EDGE>
 __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, const bf16_t* __restrict__ A, int lda,
                                                         const bf16_t* __restrict__ B, int ldb, EpiArgs e, int tiles_m,
                                                         int tiles_n) {
@@ -235,27 +257,48 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   // +16 lane.  The global address of a segment is (uniform slab base) + (this lane's offset,
   // fixed for the whole kernel), so stepping along K is scalar arithmetic only.
   constexpr int NSA = LA::NSEG, NSB = LB::NSEG;
+  // (EDGE: where the tile lies against the operands' ends matters as well; recomputed per tile)
   unsigned a_lane_off[NSA], b_lane_off[NSB];
+  auto set_lane_offsets = [&](int tm, int tn) {
+    int lane_o = lane;
+    if (EDGE) asm volatile("" : "+v"(lane_o));  // opaque: the parts of the offsets that no tile changes are not worth a register each
 #pragma unroll
-  for (int q = 0; q < NSA; q++) a_lane_off[q] = slab_lane_offset<BM, A_KC>(lda, (wave * NSA + q) * 1024 + lane * 16);
+    for (int q = 0; q < NSA; q++)
+      a_lane_off[q] = slab_lane_offset<BM, A_KC, EDGE>(lda, (wave * NSA + q) * 1024 + lane_o * 16, e.a_lim - tm * BM);
 #pragma unroll
-  for (int q = 0; q < NSB; q++) b_lane_off[q] = slab_lane_offset<BN, B_KC>(ldb, (wave * NSB + q) * 1024 + lane * 16);
+    for (int q = 0; q < NSB; q++)
+      b_lane_off[q] = slab_lane_offset<BN, B_KC, EDGE>(ldb, (wave * NSB + q) * 1024 + lane_o * 16, e.b_lim - tn * BN);
+  };
+  if (!EDGE) set_lane_offsets(0, 0);
   const size_t a_kstride = A_KC ? 1 : (size_t)lda, b_kstride = B_KC ? 1 : (size_t)ldb;
   const unsigned smem_addr = lds_addr(smem);
   auto a_tile_of = [&](int tm_i) { return A + (A_KC ? (size_t)tm_i * BM * lda : (size_t)tm_i * BM); };
   auto b_tile_of = [&](int tn_i) { return B + (B_KC ? (size_t)tn_i * BN * ldb : (size_t)tn_i * BN); };
-  // segment q of the A (B) slab at k0 of the tile at `tile_base` -> A (B) buffer number `buf`
-  auto dma_a_from = [&](const bf16_t* tile_base, int q, int k0, int buf) {
-    lds_dma16(tile_base + k0 * a_kstride, a_lane_off[q], smem_addr + buf * LA::BYTES + (wave * NSA + q) * 1024);
+  // segment q of the A (B) slab at k0 of the tile at `tile_base` -> A (B) buffer number `buf`; of the
+  // slab's contraction indices only the first `k_left` exist (EDGE)
+  auto dma_from = [&](const bf16_t* slab, unsigned lane_off, auto lane_k, int seg, int k_left, unsigned dst) {
+    if (EDGE && k_left < GK) {
+      int lane_t = lane;  // opaque: what is derived from it is rarely needed and must not occupy registers in the main loop
+      asm volatile("" : "+v"(lane_t));
+      const char* p = reinterpret_cast<const char*>(slab) + lane_off;
+      lds_dma16(lane_k(seg * 1024 + lane_t * 16) < k_left ? (const void*)p : (const void*)&gemm_zero16, dst);
+    } else {
+      lds_dma16(slab, lane_off, dst);
+    }
   };
-  auto dma_b_from = [&](const bf16_t* tile_base, int q, int k0, int buf) {
-    lds_dma16(tile_base + k0 * b_kstride, b_lane_off[q], smem_addr + B_BASE + buf * LB::BYTES + (wave * NSB + q) * 1024);
+  auto dma_a_from = [&](const bf16_t* tile_base, int q, int k0, int buf, int k_left) {
+    dma_from(tile_base + k0 * a_kstride, a_lane_off[q], slab_lane_k<BM, A_KC>, wave * NSA + q, k_left,
+             smem_addr + buf * LA::BYTES + (wave * NSA + q) * 1024);
+  };
+  auto dma_b_from = [&](const bf16_t* tile_base, int q, int k0, int buf, int k_left) {
+    dma_from(tile_base + k0 * b_kstride, b_lane_off[q], slab_lane_k<BN, B_KC>, wave * NSB + q, k_left,
+             smem_addr + B_BASE + buf * LB::BYTES + (wave * NSB + q) * 1024);
   };
   // With the contraction split (fp32-output form) the work items are (K range, tile) pairs: item
   // v is tile v % nt over slabs [r nkt / splits, (r + 1) nkt / splits), r = v / nt, nkt = K / GK,
   // and writes the partial product r (and the partial column sums r).
   const int splits = e.splits > 1 ? e.splits : 1;
-  const int nk_total = K / GK;
+  const int nk_total = EDGE ? (K + GK - 1) / GK : K / GK;
   auto k_range = [&](int item, int& first, int& count) {
     const int r = item / nt;
     first = (int)((unsigned)r * (unsigned)nk_total / (unsigned)splits);  // r < 32, nk_total < 2^25
@@ -263,14 +306,14 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   };
   // A tile starts with slab 0 in A[0], B[0] and slab 1 in A[1], B[1].  Everything but B of slab 1
   // can be requested while the previous tile's epilogue still uses A[2] and B[1].
-  auto request_first_slabs = [&](const bf16_t* a_base, const bf16_t* b_base, int nk) {
+  auto request_first_slabs = [&](const bf16_t* a_base, const bf16_t* b_base, int nk, int k_left) {
 #pragma unroll
-    for (int q = 0; q < NSA; q++) dma_a_from(a_base, q, 0, 0);
+    for (int q = 0; q < NSA; q++) dma_a_from(a_base, q, 0, 0, k_left);
 #pragma unroll
-    for (int q = 0; q < NSB; q++) dma_b_from(b_base, q, 0, 0);
+    for (int q = 0; q < NSB; q++) dma_b_from(b_base, q, 0, 0, k_left);
     if (nk > 1) {
 #pragma unroll
-      for (int q = 0; q < NSA; q++) dma_a_from(a_base, q, GK, 1);
+      for (int q = 0; q < NSA; q++) dma_a_from(a_base, q, GK, 1, k_left - GK);
     }
   };
 
@@ -279,9 +322,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   tile_of(blockIdx.x % nt, tm_i, tn_i);
   k_range(blockIdx.x, k_first, nk_item);
   size_t k_begin = (size_t)k_first * GK;
-  request_first_slabs(a_tile_of(tm_i) + k_begin * a_kstride, b_tile_of(tn_i) + k_begin * b_kstride, nk_item);
+  if (EDGE) set_lane_offsets(tm_i, tn_i);
+  request_first_slabs(a_tile_of(tm_i) + k_begin * a_kstride, b_tile_of(tn_i) + k_begin * b_kstride, nk_item, K - k_first * GK);
   for (int tile = blockIdx.x; tile < nt * splits; tile += gridDim.x) {
   const int nk = nk_item;
+  const int k_end = K - k_first * GK;  // contraction indices from this item's first to the end of the operands
   const int m0 = tm_i * BM, n0 = tn_i * BN;
   const bf16_t* const a_tile = a_tile_of(tm_i) + k_begin * a_kstride;
   const bf16_t* const b_tile = b_tile_of(tn_i) + k_begin * b_kstride;
@@ -290,8 +335,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
     et.C = (float*)e.C + (size_t)(tile / nt) * e.split_stride;
     if (EM & EM_COLSUM) et.colsum = e.colsum + (size_t)(tile / nt) * e.colsum_stride;
   }
-  auto dma_a = [&](int q, int k0, int buf) { dma_a_from(a_tile, q, k0, buf); };
-  auto dma_b = [&](int q, int k0, int buf) { dma_b_from(b_tile, q, k0, buf); };
+  auto dma_a = [&](int q, int k0, int buf) { dma_a_from(a_tile, q, k0, buf, k_end - k0); };
+  auto dma_b = [&](int q, int k0, int buf) { dma_b_from(b_tile, q, k0, buf, k_end - k0); };
   lds_dma_wait();   // slab 0 and A of slab 1 (requested a whole epilogue ago, except for the first tile)
   __syncthreads();  // ... are visible; every wave is done with the previous tile's epilogue staging
   if (nk > 1) {
@@ -468,7 +513,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
         for (int j = 0; j < TN; j++) {
           const float v = cs[j] + xch[j * 32 + lane];
           float* o = et.colsum + n0 + wn + j * 32 + lane;
-          *o = e.accumulate ? *o + v : v;
+          if (!EDGE || n0 + wn + j * 32 + lane < N) *o = e.accumulate ? *o + v : v;
         }
       }
     }
@@ -479,19 +524,26 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
     tile_of(next % nt, tm_i, tn_i);
     k_range(next, k_first, nk_item);
     k_begin = (size_t)k_first * GK;
-    request_first_slabs(a_tile_of(tm_i) + k_begin * a_kstride, b_tile_of(tn_i) + k_begin * b_kstride, nk_item);
+    if (EDGE) set_lane_offsets(tm_i, tn_i);
+    request_first_slabs(a_tile_of(tm_i) + k_begin * a_kstride, b_tile_of(tn_i) + k_begin * b_kstride, nk_item, K - k_first * GK);
   }
   // (lane index through an opaque copy: otherwise everything derived from it below is hoisted out of
   // the tile loop and kept in registers across the main loop, which has none to spare)
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));
+  // MASK: the tile reaches beyond the output; side inputs are fetched from clamped places (no branch
+  // around a load), stores are predicated.
+  auto epilogue = [&](auto mask_c) {
+  constexpr bool MASK = decltype(mask_c)::value;
   const int c4 = (lane_e % LPR) * 4;
   const int rsub = lane_e / LPR;
   const int ncol = n0 + wn + c4;
+  const int ncol_r = MASK ? min(ncol, N - 4) : ncol;  // where the side inputs are read
+  auto mrow_r = [&](int m) { return MASK ? min(m, M - 1) : m; };
   constexpr bool F32 = em_kind(EM) == EK_F32, DG = em_dgelu(EM);
   constexpr bool SIDE = !F32 && (DG || (EM & EM_RES));  // a bf16 side input: pre-activation U or residual R
   float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (!F32 && e.bias) bias = ld_bf16x4(e.bias, ncol);
+  if (!F32 && e.bias) bias = ld_bf16x4(e.bias, ncol_r);
   const bf16_t* sp = (const bf16_t*)(DG ? e.U : e.R);
   const int lds_ = DG ? e.ldu : e.ldr;
   // the side input of 32 rows is requested one round ahead: the loads fly while the previous
@@ -501,7 +553,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
     if (SIDE) {
 #pragma unroll
       for (int k = 0; k < NIT; k++)
-        dst[k] = *reinterpret_cast<const bf16x4*>(sp + (size_t)(m0 + wm + i * 32 + rsub + k * RPI) * lds_ + ncol);
+        dst[k] = *reinterpret_cast<const bf16x4*>(sp + (size_t)mrow_r(m0 + wm + i * 32 + rsub + k * RPI) * lds_ + ncol_r);
     }
   };
   side_request(0, side[0]);
@@ -530,7 +582,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
       for (int u = 0; u < BATCH; u++) {
         const int row = (k0 + u) * RPI + rsub;
         a[u] = *reinterpret_cast<const float4*>(wbuf + row * WC + (((c4 >> 2) ^ (row & 7)) << 2));
-        if (ADD_C) old_c[u] = *reinterpret_cast<const float4*>((const float*)et.C + (size_t)(mrow + (k0 + u) * RPI) * e.ldc + ncol);
+        if (ADD_C) old_c[u] = *reinterpret_cast<const float4*>((const float*)et.C + (size_t)mrow_r(mrow + (k0 + u) * RPI) * e.ldc + ncol_r);
       }
 #pragma unroll
       for (int u = 0; u < BATCH; u++) {
@@ -541,15 +593,55 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
           const bf16x4 v = side[i & 1][k0 + u];
           sd = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
         }
-        mfma_epilogue4<EM>(et, mrow + (k0 + u) * RPI, ncol, a[u], bias, sd);
+        const int m = mrow + (k0 + u) * RPI;
+        if (!MASK || (m < M && ncol < N)) mfma_epilogue4<EM>(et, m, ncol, a[u], bias, sd);
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
+  };  // epilogue
+  if constexpr (EDGE) {
+    if (m0 + BM > M || n0 + BN > N) epilogue(T_{});
+    else epilogue(F_{});
+  } else {
+    epilogue(F_{});
+  }
   }  // tile loop
   lds_dma_wait();  // nothing is in flight here; stated for whoever reads the assembly in a straight line
+}
+
+template <int BM, int BN, bool A_KC, bool B_KC, int EM, bool EDGE = false>
+static int launch_mfma(const GemmArgs& g, const EpiArgs& e, hipStream_t s) {
+  constexpr size_t lds = 3 * (size_t)TileLds<BM, A_KC>::BYTES + 2 * (size_t)TileLds<BN, B_KC>::BYTES;  // 160 KB at 256^2; also covers the epilogue's staging
+  auto kern = gemm_mfma_kernel<BM, BN, A_KC, B_KC, EM, EDGE>;
+  static bool configured = false;  // benign race: the attribute is idempotent
+  if (!configured) {
+    FAX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    configured = true;
+  }
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  static int n_cu = 0;  // benign race: same value from every thread
+  if (n_cu == 0) {
+    int dev = 0, v = 0;
+    FAX_HIP(hipGetDevice(&dev));
+    FAX_HIP(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
+    n_cu = v > 0 ? v : 256;
+  }
+  const int items = tiles_m * tiles_n * (e.splits > 1 ? e.splits : 1);
+  // Persistent: one workgroup per CU.  A 128^2 workgroup needs 80 KB of LDS and under 256 registers,
+  // so two fit on a CU; they share its LDS bandwidth, which bounds that kernel, and gain little
+  // (measured: +-0.4 % with many tiles) except when that saves a second round for a few left-over
+  // tiles (320 tiles: -4 % on the whole step).
+  const int slots = (BM == 128 && items <= 2 * n_cu) ? 2 * n_cu : n_cu;
+  const int grid = items < slots ? items : slots;
+  EpiArgs ek = e;
+  if (ek.group == 0 && grid != 256) ek.group = 4;  // the side-by-side walk is written for 8 XCDs x 32 workgroups
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, s, g.M, g.N, g.K, (const bf16_t*)g.A, g.lda,
+                     (const bf16_t*)g.B, g.ldb, ek, tiles_m, tiles_n);
+  FAX_LAUNCH_CHECK("gemm_mfma");
+  return FAX_OK;
 }
 
 }  // namespace fax

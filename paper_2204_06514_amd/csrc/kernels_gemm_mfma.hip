@@ -50,8 +50,8 @@ static constexpr TileClass kTiles[] = {{256, 256, 1.55, 0.48, 1.10, 7.0, 8.0},
 // partly filled (a 128^2 launch of at most two per CU runs them side by side, at shared LDS
 // bandwidth); folding s partial products costs a launch plus their bytes, written once and read once.
 static double tile_time_us(const TileClass& tc, int M, int N, int K, bool f32_out, int s) {
-  const int slabs = (K / GK + s - 1) / s;
-  const long long items = (long long)(M / tc.m) * (N / tc.n) * s;
+  const int slabs = ((K + GK - 1) / GK + s - 1) / s;
+  const long long items = (long long)((M + tc.m - 1) / tc.m) * ((N + tc.n - 1) / tc.n) * s;
   const double epi = f32_out ? tc.epi_f32_us : tc.epi_bf16_us;
   auto round_us = [&](double busy_share) {
     return slabs * std::max(tc.floor_us, tc.full_us * (tc.idle_share + (1.0 - tc.idle_share) * busy_share)) + epi;
@@ -69,18 +69,22 @@ static double tile_time_us(const TileClass& tc, int M, int N, int K, bool f32_ou
   return t;
 }
 
+// Shapes whose tiles and slabs all come out whole; the others take the masked-edge form of the kernel.
+static bool tiles_whole(int M, int N, int K) { return M % 128 == 0 && N % 128 == 0 && K % GK == 0; }
+
 // Tile class (and, when `may_split`, number of K ranges) with the smallest predicted time; a
-// smaller tile or a split has to be 3 % better than what is already chosen.  tile_m = 0: no class
-// divides the shape.  The 256 x 128 class is used for bf16 outputs only: on weight-gradient
+// smaller tile or a split has to be 3 % better than what is already chosen.  `edge`: the masked-edge
+// form, for which every class will do and the padding counts as work; otherwise tile_m = 0 says that
+// no class divides the shape.  The 256 x 128 class is used for bf16 outputs only: on weight-gradient
 // products (both operands through the LDS transpose read, with or without K ranges) it measured
 // 10-50 % above this model.
-static GemmSplitPlan plan_tiles(int M, int N, int K, bool f32_out, bool may_split) {
+static GemmSplitPlan plan_tiles(int M, int N, int K, bool f32_out, bool may_split, bool edge = false) {
   GemmSplitPlan best{0, 0, 1};
-  if (M <= 0 || N <= 0 || K <= 0 || K % GK) return best;
-  const int nkt = K / GK;
+  if (M <= 0 || N <= 0 || K <= 0 || (K % GK && !edge)) return best;
+  const int nkt = (K + GK - 1) / GK;
   double best_t = 1e30;
   for (const TileClass& tc : kTiles) {
-    if (M % tc.m || N % tc.n) continue;
+    if ((M % tc.m || N % tc.n) && !edge) continue;
     if (f32_out && tc.m != tc.n) continue;
     for (int s = 1; s <= (may_split ? 32 : 1) && (s == 1 || nkt / s >= 8); s++) {
       const double t = tile_time_us(tc, M, N, K, f32_out, s);
@@ -93,7 +97,7 @@ static GemmSplitPlan plan_tiles(int M, int N, int K, bool f32_out, bool may_spli
   return best;
 }
 
-GemmSplitPlan gemm_split_plan(int M, int N, int K) { return plan_tiles(M, N, K, true, true); }
+GemmSplitPlan gemm_split_plan(int M, int N, int K) { return plan_tiles(M, N, K, true, true, !tiles_whole(M, N, K)); }
 
 // One dimension an odd multiple of 128 and the rest big enough to fill the chip with 256^2 tiles:
 // the product is computed as two, the bulk on 256^2 tiles and the last 128 rows (1) or columns (2)
@@ -138,20 +142,19 @@ static size_t split_ws_bytes_1(int M, int N, int K) {
 }
 
 size_t gemm_split_ws_bytes(int M, int N, int K) {
-  if (tail_dim(M, N) == 1) return std::max(split_ws_bytes_1(M - 128, N, K), split_ws_bytes_1(128, N, K));
+  if (tiles_whole(M, N, K) && tail_dim(M, N) == 1) return std::max(split_ws_bytes_1(M - 128, N, K), split_ws_bytes_1(128, N, K));
   return split_ws_bytes_1(M, N, K);  // a column strip keeps the leading dimension of C: no split there
 }
 
 static double time_estimate_1(int M, int N, int K, bool f32_out) {
-  const GemmSplitPlan plan = plan_tiles(M, N, K, f32_out, f32_out);
-  if (plan.tile_m == 0) return 2.0 * M * N * K / 15.0e6;  // the scalar kernel: about 15 TFLOP/s
+  const GemmSplitPlan plan = plan_tiles(M, N, K, f32_out, f32_out, !tiles_whole(M, N, K));
   for (const TileClass& tc : kTiles)
     if (tc.m == plan.tile_m && tc.n == plan.tile_n) return 3.0 + tile_time_us(tc, M, N, K, f32_out, plan.splits);
   return 0.0;
 }
 
 double gemm_time_estimate_us(int M, int N, int K, bool f32_out) {
-  switch (tail_dim(M, N)) {
+  switch (tiles_whole(M, N, K) ? tail_dim(M, N) : 0) {
     case 1: return time_estimate_1(M - 128, N, K, f32_out) + time_estimate_1(128, N, K, f32_out);
     case 2: return time_estimate_1(M, N - 128, K, f32_out) + time_estimate_1(M, 128, K, f32_out);
   }
@@ -159,7 +162,8 @@ double gemm_time_estimate_us(int M, int N, int K, bool f32_out) {
 }
 
 
-bool gemm_mfma_supported(const GemmArgs& g) {
+// What both forms of the kernel ask of a product, apart from its sizes.
+static bool mfma_layout_ok(const GemmArgs& g) {
   if (g.dtype != FAX_BF16) return false;
   if (g.c_f32 && (g.bias || g.R || g.C2 || g.epi != EPI_NONE)) return false;  // fp32 C is the plain weight-gradient form
   if (g.colsum && !(g.c_f32 && g.ta && !g.tb)) return false;  // the column sums of B ride only on that form, A [K, M], B [K, N]
@@ -169,7 +173,7 @@ bool gemm_mfma_supported(const GemmArgs& g) {
   if (g.epi == EPI_DGELU && (g.ta || !g.tb || g.R)) return false;
   // the second output likewise: forward orientation only
   if (g.epi == EPI_NONE && g.C2 && (g.ta || g.tb)) return false;
-  if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.K % GK != 0) return false;
+  if (g.M <= 0 || g.N <= 0 || g.K <= 0) return false;
   if (g.lda % 8 || g.ldb % 8 || !aligned16(g.A) || !aligned16(g.B)) return false;
   if (g.c_f32) {  // the epilogue moves four columns at a time: 16-byte fp32 units ...
     if (g.ldc % 4 || !aligned16(g.C)) return false;
@@ -178,39 +182,24 @@ bool gemm_mfma_supported(const GemmArgs& g) {
     if (!vec_ok(g.C, g.ldc) || !vec_ok(g.C2, g.ldc2) || !vec_ok(g.R, g.ldr) || !vec_ok(g.U, g.ldu) || !vec_ok(g.bias, 4))
       return false;
   }
-  return g.M % 128 == 0 && g.N % 128 == 0;  // the smallest tile class
+  return true;
 }
 
-template <int BM, int BN, bool A_KC, bool B_KC, int EM>
-static int launch_mfma(const GemmArgs& g, const EpiArgs& e, hipStream_t s) {
-  constexpr size_t lds = 3 * (size_t)TileLds<BM, A_KC>::BYTES + 2 * (size_t)TileLds<BN, B_KC>::BYTES;  // 160 KB at 256^2; also covers the epilogue's staging
-  auto kern = gemm_mfma_kernel<BM, BN, A_KC, B_KC, EM>;
-  static bool configured = false;  // benign race: the attribute is idempotent
-  if (!configured) {
-    FAX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    configured = true;
-  }
-  const int tiles_m = g.M / BM, tiles_n = g.N / BN;
-  static int n_cu = 0;  // benign race: same value from every thread
-  if (n_cu == 0) {
-    int dev = 0, v = 0;
-    FAX_HIP(hipGetDevice(&dev));
-    FAX_HIP(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
-    n_cu = v > 0 ? v : 256;
-  }
-  const int items = tiles_m * tiles_n * (e.splits > 1 ? e.splits : 1);
-  // Persistent: one workgroup per CU.  A 128^2 workgroup needs 80 KB of LDS and under 256 registers,
-  // so two fit on a CU; they share its LDS bandwidth, which bounds that kernel, and gain little
-  // (measured: +-0.4 % with many tiles) except when that saves a second round for a few left-over
-  // tiles (320 tiles: -4 % on the whole step).
-  const int slots = (BM == 128 && items <= 2 * n_cu) ? 2 * n_cu : n_cu;
-  const int grid = items < slots ? items : slots;
-  EpiArgs ek = e;
-  if (ek.group == 0 && grid != 256) ek.group = 4;  // the side-by-side walk is written for 8 XCDs x 32 workgroups
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, s, g.M, g.N, g.K, (const bf16_t*)g.A, g.lda,
-                     (const bf16_t*)g.B, g.ldb, ek, tiles_m, tiles_n);
-  FAX_LAUNCH_CHECK("gemm_mfma");
-  return FAX_OK;
+bool gemm_mfma_supported(const GemmArgs& g) {
+  return mfma_layout_ok(g) && tiles_whole(g.M, g.N, g.K);  // 128: the smallest tile class
+}
+
+// The masked-edge form moves the operands in whole 16-byte chunks and the output in groups of four
+// columns, so what is contiguous in memory has to be a multiple of those (the rows of an operand the
+// caller has padded may end inside one); the orientations are those of forward, input-gradient and
+// weight-gradient products.
+bool gemm_edge_supported(const GemmArgs& g) {
+  if (!mfma_layout_ok(g) || g.N % 4) return false;
+  if (g.c_f32 ? !g.ta || g.tb : g.ta) return false;
+  if (g.tb && !g.ta && (g.R || g.C2)) return false;
+  const bool a_whole = g.a_padded || (g.ta ? g.M : g.K) % 8 == 0;
+  const bool b_whole = (g.tb ? g.K : g.N) % 8 == 0;
+  return a_whole && b_whole;
 }
 
 template <int BM, int BN>
@@ -257,7 +246,8 @@ static const void* offset(const void* p, size_t elements, size_t elem_bytes) {
 static void* offset(void* p, size_t elements, size_t elem_bytes) { return p ? (char*)p + elements * elem_bytes : nullptr; }
 
 int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
-  if (const int td = tail_dim(g0.M, g0.N)) {
+  const bool edge = !tiles_whole(g0.M, g0.N, g0.K);
+  if (const int td = edge ? 0 : tail_dim(g0.M, g0.N)) {
     const size_t cb = g0.c_f32 ? 4 : 2;
     for (int part = 0; part < 2; part++) {
       GemmArgs h = g0;
@@ -288,7 +278,7 @@ int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
   GemmArgs g = g0;
   // Split the contraction?  Only the fp32-output form, with scratch from the caller and C stored
   // densely; the partial products (and partial column sums) are then folded in a fixed order.
-  const GemmSplitPlan plan = plan_tiles(g.M, g.N, g.K, g.c_f32, g.c_f32 && g.split_ws && g.ldc == g.N);
+  const GemmSplitPlan plan = plan_tiles(g.M, g.N, g.K, g.c_f32, g.c_f32 && g.split_ws && g.ldc == g.N, edge);
   if (plan.tile_m == 0) {
     set_error("gemm_mfma: %d x %d x %d fits no tile class", g.M, g.N, g.K);
     return FAX_ERR_UNSUPPORTED;
@@ -304,8 +294,10 @@ int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
   }
   EpiArgs e{g.bias, g.R, g.ldr, g.C, g.ldc, g.C2, g.ldc2, g.U, g.ldu, g.epi, g.gelu_form, g.c_f32 ? 1 : 0,
             g.accumulate ? 1 : 0, g.colsum, splits, mn, (size_t)g.N,
-            walk_group(g.M / plan.tile_m, g.N / plan.tile_n, g.K, splits)};
-  if (plan.tile_n == 256) FAX_TRY((dispatch<256, 256>(g, e, s)));
+            walk_group((g.M + plan.tile_m - 1) / plan.tile_m, (g.N + plan.tile_n - 1) / plan.tile_n, g.K, splits),
+            g.ta ? (g.M + 7) / 8 * 8 : g.M, g.b_rows ? g.b_rows : g.N};
+  if (edge) FAX_TRY(gemm_mfma_edge(g, e, plan, s));
+  else if (plan.tile_n == 256) FAX_TRY((dispatch<256, 256>(g, e, s)));
   else if (plan.tile_m == 256) FAX_TRY((dispatch<256, 128>(g, e, s)));
   else FAX_TRY((dispatch<128, 128>(g, e, s)));
   if (splits > 1) {

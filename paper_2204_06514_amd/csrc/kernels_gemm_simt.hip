@@ -96,9 +96,9 @@ int gemm(const GemmArgs& g, hipStream_t s) {
   if (!timing_on()) return gemm_dispatch(g, s);
   // name the variant the way the kernel templates are instantiated: operand orientation
   // (k = contraction index contiguous, m = row/column index contiguous) and epilogue
-  const bool mfma = g.path != PATH_SIMT && gemm_mfma_supported(g);
+  const char* form = g.path == PATH_SIMT ? "scalar" : gemm_mfma_supported(g) ? "mfma" : g.path == PATH_AUTO && gemm_edge_supported(g) ? "edge" : "scalar";
   char name[64];
-  snprintf(name, sizeof(name), "gemm_%s_A%c_B%c_%s", mfma ? "mfma" : "scalar", g.ta ? 'm' : 'k', g.tb ? 'k' : 'm',
+  snprintf(name, sizeof(name), "gemm_%s_A%c_B%c_%s", form, g.ta ? 'm' : 'k', g.tb ? 'k' : 'm',
            g.c_f32 ? "f32out" : g.epi == EPI_GELU ? "gelu" : g.epi == EPI_DGELU ? "dgelu" : "store");
   Timed t(name, WORK_FLOP, 2.0 * g.M * g.N * g.K, s);
   return gemm_dispatch(g, s);
@@ -110,9 +110,7 @@ static int gemm_dispatch(const GemmArgs& g, hipStream_t s) {
     set_error("fax_gemm: shape M=%d N=%d K=%d (dtype %d) does not tile for the MFMA kernel", g.M, g.N, g.K, g.dtype);
     return FAX_ERR_UNSUPPORTED;
   }
-  if (mfma) {
-    return gemm_mfma(g, s);
-  }
+  if (mfma || (g.path == PATH_AUTO && gemm_edge_supported(g))) return gemm_mfma(g, s);
   if (g.colsum) {
     // no fused form here: take the column sums of B [K, N] in a pass of their own
     if (g.tb || !g.colsum_ws) {
