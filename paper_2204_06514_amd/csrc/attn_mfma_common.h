@@ -144,13 +144,37 @@ __device__ __forceinline__ float sum32(float v) {
 template <typename T>
 __device__ __forceinline__ void settle(T& v) { asm volatile("" : "+v"(v)); }
 
+// ---- the masked-edge form (EDGE) ------------------------------------------------------------------
+// Every kernel here exists in two forms.  The plain one needs S a multiple of 128 and a head width of
+// 64 or 128.  The masked-edge one takes any S and any head width up to 128 that is a multiple of 8: it
+// computes at the next width DW of 64, 96, 128 with LDS rows of 64 or 128 elements.  LDS is cleared
+// once; after that a lane whose chunk lies beyond the head width or whose row lies beyond the
+// sequence simply does not load (the execution mask leaves its 16 bytes of LDS alone), so columns
+// beyond the head width stay zero, rows beyond the sequence hold zeros or an earlier tile's rows, and
+// nothing is read out of bounds.  Queries and keys held in registers are zero there.  Keys beyond the
+// sequence come after every query and fall to the causal mask; queries beyond it are masked by
+// dK/dV.  Probabilities and dS enter their second products as two bf16 numbers (value and
+// remainder: 2^-17 instead of 2^-9), because these shapes' probabilities were never rounded to 16
+// bits: the scalar kernels that remain for wider and odd heads keep them in fp32.
+template <int DW> constexpr int row_width() { return DW <= 64 ? 64 : 128; }
+__device__ __forceinline__ uint4 edge_load16(const bf16_t* p, bool ok) {
+  return ok ? *reinterpret_cast<const uint4*>(p) : make_uint4(0u, 0u, 0u, 0u);
+}
+__device__ __forceinline__ void clear_lds(char* smem, int bytes) {
+  for (int o = threadIdx.x * 16; o < bytes; o += 256 * 16) *reinterpret_cast<uint4*>(smem + o) = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+}
+
 // Store a transposed 32(d) x 32(row) accumulator set: lane owns one row, DH/32 tiles of 16 d's.
-template <int DH>
-__device__ __forceinline__ void store_rows(bf16_t* __restrict__ dst, const f32x16 (&acc)[DH / 32], float mul, int g) {
+// EDGE: only the columns below `width`.
+template <int DH, bool EDGE = false>
+__device__ __forceinline__ void store_rows(bf16_t* __restrict__ dst, const f32x16 (&acc)[DH / 32], float mul, int g,
+                                           int width = DH) {
 #pragma unroll
   for (int dt = 0; dt < DH / 32; dt++)
 #pragma unroll
     for (int q = 0; q < 4; q++) {
+      if (EDGE && dt * 32 + q * 8 >= width) continue;
       bf16x4 o;
 #pragma unroll
       for (int r = 0; r < 4; r++) o[r] = (__bf16)(acc[dt][q * 4 + r] * mul);
@@ -161,15 +185,18 @@ __device__ __forceinline__ void store_rows(bf16_t* __restrict__ dst, const f32x1
 // Segment i of this wave's share of a 64 x DH tile (see tile_dma above), as one load instruction:
 // wave-uniform tile address in scalar registers plus a per-lane byte offset that depends only on
 // the lane, the segment and the row stride, so the compiler computes it once per kernel and a load
-// costs no vector arithmetic.  `wave` must be wave-uniform (readfirstlane).
-template <int DH>
-__device__ __forceinline__ void tile_dma_seg(unsigned lds, const bf16_t* __restrict__ src, size_t ld, int wave, int i) {
+// costs no vector arithmetic.  `wave` must be wave-uniform (readfirstlane).  EDGE: only the first
+// `rows` rows and `chunks` chunks exist.
+template <int DH, bool EDGE = false>
+__device__ __forceinline__ void tile_dma_seg(unsigned lds, const bf16_t* __restrict__ src, size_t ld, int wave, int i,
+                                             int rows = TR, int chunks = DH / 8) {
   constexpr int NCH = DH / 8, RPI = 64 / NCH;
   const int lane = threadIdx.x & 63;
   const int seg = wave * (DH / 32) + i;
   const int row = seg * RPI + lane / NCH;
   const int chunk = (lane % NCH) ^ swz<DH>(row);
-  lds_dma16(src, (unsigned)(((size_t)row * ld + chunk * 8) * sizeof(bf16_t)), lds + seg * 1024u);
+  if (!EDGE || (row < rows && chunk < chunks))
+    lds_dma16(src, (unsigned)(((size_t)row * ld + chunk * 8) * sizeof(bf16_t)), lds + seg * 1024u);
 }
 
 // Workgroup -> (pair of 128-row tiles, batch-head) for the three kernels.  Under the causal mask

@@ -234,8 +234,9 @@ static int attention_fwd(int dtype, int B, int S, int H, int dh, const void* qkv
     set_error("attention: dtype %d, S=%d, dh=%d is not covered by the MFMA kernel", dtype, S, dh);
     return FAX_ERR_UNSUPPORTED;
   }
-  const bool mfma = ok && path != PATH_SIMT;
-  Timed t_(mfma ? "attention_fwd_mfma" : "attention_fwd_scalar", WORK_FLOP, 2.0 * B * H * (double)S * S * dh, s);
+  // PATH_MFMA asks for the plain form; the masked-edge form is the library's own choice
+  const bool mfma = path == PATH_MFMA || (path == PATH_AUTO && attn_edge_supported(dtype, B, S, H, dh));
+  Timed t_(!mfma ? "attention_fwd_scalar" : ok ? "attention_fwd_mfma" : "attention_fwd_edge", WORK_FLOP, 2.0 * B * H * (double)S * S * dh, s);
   if (mfma) return attn_fwd_mfma(B, S, H, dh, qkv, ctx, lse, s);
   return attn_fwd_simt(dtype, B, S, H, dh, qkv, ctx, lse, s);
 }
@@ -248,8 +249,9 @@ static int attention_bwd(int dtype, int B, int S, int H, int dh, const void* qkv
     set_error("attention: dtype %d, S=%d, dh=%d is not covered by the MFMA kernel", dtype, S, dh);
     return FAX_ERR_UNSUPPORTED;
   }
-  const bool mfma = ok && path != PATH_SIMT;
-  Timed t_(mfma ? "attention_bwd_mfma" : "attention_bwd_scalar", WORK_FLOP, 4.0 * B * H * (double)S * S * dh, s);
+  // PATH_MFMA asks for the plain form; the masked-edge form is the library's own choice
+  const bool mfma = path == PATH_MFMA || (path == PATH_AUTO && attn_edge_supported(dtype, B, S, H, dh));
+  Timed t_(!mfma ? "attention_bwd_scalar" : ok ? "attention_bwd_mfma" : "attention_bwd_edge", WORK_FLOP, 4.0 * B * H * (double)S * S * dh, s);
   if (mfma) return attn_bwd_mfma(B, S, H, dh, qkv, ctx, lse, dctx, dqkv, delta, s, split);
   return attn_bwd_simt(dtype, B, S, H, dh, qkv, ctx, lse, dctx, dqkv, delta, s);
 }

@@ -114,7 +114,8 @@ int attn_bwd_simt(int dtype, int B, int S, int H, int dh, const void* qkv, const
                   const void* dctx, void* dqkv, float* delta, hipStream_t s);
 // delta[b,h,i] = sum_d dctx[b,i,h,d] ctx[b,i,h,d]
 int attn_delta(int dtype, int B, int S, int H, int dh, const void* ctx, const void* dctx, float* delta, hipStream_t s);
-bool attn_mfma_supported(int dtype, int B, int S, int H, int dh);
+bool attn_mfma_supported(int dtype, int B, int S, int H, int dh);  // the plain form of the matrix-core kernels
+bool attn_edge_supported(int dtype, int B, int S, int H, int dh);  // plain or masked-edge form
 int attn_fwd_mfma(int B, int S, int H, int dh, const void* qkv, void* ctx, float* lse, hipStream_t s);
 // Optional: scratch for the dQ kernel's own copy of delta ([B,H,S] fp32) and a second stream with two
 // events; given them, and few enough workgroups (attn_bwd_side_by_side), dQ and dK/dV run side by side.

@@ -47,15 +47,17 @@ __device__ __forceinline__ int swz16(int row) {
 }
 
 // Segment i of this wave's share of a 64 x DH tile, as tile_dma_seg() but with the swizzle above.
-template <int DH>
-__device__ __forceinline__ void tile_dma_seg16(unsigned lds, const bf16_t* __restrict__ src, size_t ld, int wave, int i) {
+template <int DH, bool EDGE>
+__device__ __forceinline__ void tile_dma_seg16(unsigned lds, const bf16_t* __restrict__ src, size_t ld, int wave, int i, int rows,
+                                               int chunks) {
   constexpr int NCH = DH / 8, RPI = 64 / NCH;
   static_assert(NCH == 16, "the swizzle is written for 16 chunks per row");
   const int lane = threadIdx.x & 63;
   const int seg = wave * (DH / 32) + i;
   const int row = seg * RPI + lane / NCH;
   const int chunk = (lane % NCH) ^ swz16(row);
-  lds_dma16(src, (unsigned)(((size_t)row * ld + chunk * 8) * sizeof(bf16_t)), lds + seg * 1024u);
+  if (!EDGE || (row < rows && chunk < chunks))
+    lds_dma16(src, (unsigned)(((size_t)row * ld + chunk * 8) * sizeof(bf16_t)), lds + seg * 1024u);
 }
 
 // First operand, 16 rows rb..rb+15 of the tile (rb a multiple of 16), k-step ks (32 columns).
@@ -87,35 +89,38 @@ __device__ __forceinline__ bf16x8 frag_cols16(const char* lds, int cb, int r0, i
   return __builtin_bit_cast(bf16x8, v);
 }
 
-template <int DH>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int H, int BH, const bf16_t* __restrict__ qkv,
+template <int DW, bool EDGE>
+__global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
                                                                      const float* __restrict__ lse,
                                                                      const float* __restrict__ delta,
                                                                      const bf16_t* __restrict__ dctx,
                                                                      bf16_t* __restrict__ dqkv) {
-  constexpr int KS = DH / 32;   // k-steps of the score products
-  constexpr int DT = DH / 16;   // 16-wide d tiles of dK^T, dV^T
+  constexpr int DH = row_width<DW>();  // row length in LDS
+  constexpr int KS = DW / 32;   // k-steps of the score products
+  constexpr int DT = DW / 16;   // 16-wide d tiles of dK^T, dV^T
   constexpr int TB = TR * DH * 2;
   constexpr int LD_OFF = 2 * TB, STAGE = 2 * TB + 4 * 256;  // Q tile | dO tile | lse and delta (see tile_load)
   constexpr int N = 4 * KS;     // MFMAs per phase and half: {S, dP} x two query groups x KS, or {dV, dK} x DT
-  constexpr int LEAD = 8;       // fragments in flight
+  constexpr int LEAD = N % 8 == 0 ? 8 : 6;  // fragments in flight
   constexpr int NSEG = DH / 32;
   static_assert(N == 2 * DT && N % LEAD == 0 && 2 * NSEG + 1 <= N, "slot plan");
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int n_kt = S / TR;      // 64-key tiles
+  const int n_kt = EDGE ? (S + TR - 1) / TR : S / TR;  // 64-key tiles
   int pair, bh;
   pair_of_tiles(n_kt, BH, pair, bh);
   const int b = bh / H, h = bh % H;
-  const int Hd = H * DH;
+  const int hw = EDGE ? dh : DW, nch = hw / 8;  // head width, in elements and in 16-byte chunks
+  const int Hd = H * hw;
   const size_t ld = 3 * (size_t)Hd;
-  const bf16_t* base = qkv + (size_t)b * S * ld + h * DH;
-  const bf16_t* dob = dctx + (size_t)b * S * Hd + h * DH;
+  const bf16_t* base = qkv + (size_t)b * S * ld + h * hw;
+  const bf16_t* dob = dctx + (size_t)b * S * Hd + h * hw;
   const float* lrow = lse + ((size_t)b * H + h) * S;
   const float* drow = delta + ((size_t)b * H + h) * S;
   const int lane = threadIdx.x & 63, gq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const float c = rsqrtf((float)DH) * LOG2E;
+  const float c = rsqrtf((float)hw) * LOG2E;
   const unsigned sm = lds_addr(smem);
+  if (EDGE) clear_lds(smem, 2 * STAGE);
 
   for (int pass = 0; pass < 2; pass++) {
     const int kt = pass == 0 ? pair : n_kt - 1 - pair;
@@ -124,8 +129,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
     bf16x8 kf[KS], vf[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
-      kf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(base + (size_t)jk * ld + Hd + ks * 32 + gq * 8));
-      vf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(base + (size_t)jk * ld + 2 * Hd + ks * 32 + gq * 8));
+      const bool ok = !EDGE || (jk < S && ks * 4 + gq < nch);
+      const bf16_t *kp = base + (size_t)jk * ld + Hd + ks * 32 + gq * 8, *vp = kp + Hd;
+      kf[ks] = __builtin_bit_cast(bf16x8, EDGE ? edge_load16(kp, ok) : *reinterpret_cast<const uint4*>(kp));
+      vf[ks] = __builtin_bit_cast(bf16x8, EDGE ? edge_load16(vp, ok) : *reinterpret_cast<const uint4*>(vp));
     }
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) { settle(kf[ks]); settle(vf[ks]); }
@@ -136,15 +143,15 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
       for (int r = 0; r < 4; r++) dk[dt][r] = dv[dt][r] = 0.f;
 
     const int i_first = kt * TR;           // first query that meets these keys: the tile on the diagonal
-    const int n_q = (S - i_first) / TR;
+    const int n_q = EDGE ? (S - i_first + TR - 1) / TR : (S - i_first) / TR;
     // Tile of queries i0.. into buffer `buf`, one load instruction per call: this wave's NSEG
     // segments of Q (i < NSEG), of dO (i < 2 NSEG), and its 16 lse and 16 delta values (lanes 0-15
     // lse, 16-31 delta, 32-63 the same again: one 4-byte load instruction moves 64 lanes).
     auto tile_load = [&](int i0, int buf, int i) {
       const unsigned st = sm + buf * STAGE;
-      if (i < NSEG) tile_dma_seg16<DH>(st, base + (size_t)i0 * ld, ld, wave, i);
-      else if (i < 2 * NSEG) tile_dma_seg16<DH>(st + TB, dob + (size_t)i0 * Hd, (size_t)Hd, wave, i - NSEG);
-      else lds_dma4(((lane & 16) ? drow : lrow) + i0 + wave * 16 + (lane & 15), st + LD_OFF + wave * 256);
+      if (i < NSEG) tile_dma_seg16<DH, EDGE>(st, base + (size_t)i0 * ld, ld, wave, i, S - i0, nch);
+      else if (i < 2 * NSEG) tile_dma_seg16<DH, EDGE>(st + TB, dob + (size_t)i0 * Hd, (size_t)Hd, wave, i - NSEG, S - i0, nch);
+      else if (!EDGE || i0 + wave * 16 + (lane & 15) < S) lds_dma4(((lane & 16) ? drow : lrow) + i0 + wave * 16 + (lane & 15), st + LD_OFF + wave * 256);
     };
     bf16x8 f[LEAD];  // one ring for both kinds of fragment: slot i reloads the register it has just used
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -182,7 +189,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
           if (it == 0 && i <= 2 * NSEG) tile_load(i0n, (t + 1) & 1, i);
           __builtin_amdgcn_sched_barrier(0);
         }
-        bf16x8 pb, db;
+        bf16x8 pb, db, pl, dl;  // P and dS; EDGE: and what bf16 leaves of them
         __builtin_amdgcn_s_setprio(0);
 #pragma unroll
         for (int qg = 0; qg < 2; qg++) {
@@ -190,10 +197,15 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
 #pragma unroll
           for (int r = 0; r < 4; r++) {
             float p = __builtin_amdgcn_exp2f(fmaf(sc[qg][r], c, -LOG2E * f4_get(l4, r)));
-            if (MASK && jk > i0h + qg * 16 + gq * 4 + r) p = 0.f;
-            const float d = p * (dp[qg][r] - f4_get(d4, r));
+            const int i = i0h + qg * 16 + gq * 4 + r;
+            if (MASK && (jk > i || (EDGE && i >= S))) p = 0.f;
+            const float d = EDGE && MASK && i >= S ? 0.f : p * (dp[qg][r] - f4_get(d4, r));
             pb[qg * 4 + r] = (__bf16)p;
             db[qg * 4 + r] = (__bf16)d;
+            if (EDGE) {
+              pl[qg * 4 + r] = (__bf16)(p - (float)(__bf16)p);
+              dl[qg * 4 + r] = (__bf16)(d - (float)(__bf16)d);
+            }
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -203,6 +215,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
           const int dt = i / 2;
           if (i % 2 == 0) dv[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], pb, dv[dt], 0, 0, 0);
           else dk[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], db, dk[dt], 0, 0, 0);
+          if (EDGE && i % 2 == 0) dv[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], pl, dv[dt], 0, 0, 0);
+          if (EDGE && i % 2 != 0) dk[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], dl, dk[dt], 0, 0, 0);
           if (i + LEAD < N) f[i % LEAD] = col_frag(it, i + LEAD);
           else if (it == 0) f[i % LEAD] = row_frag(1, i + LEAD - N);  // the second half's first rows
           __builtin_amdgcn_sched_barrier(0);
@@ -218,13 +232,16 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
     lds_dma_wait();
     __syncthreads();
     tile(T_{}, 0);  // the tile on the diagonal; every later query comes after all of this workgroup's keys
-    for (int t = 1; t < n_q; t++) tile(F_{}, t);
+    for (int t = 1; t < (EDGE ? n_q - 1 : n_q); t++) tile(F_{}, t);
+    if (EDGE && n_q > 1) tile(T_{}, n_q - 1);  // may reach past S
 
+    if (EDGE && jk >= S) continue;
     // a lane owns one key row and, per d tile, the four consecutive d's 16 dt + 4 g + 0..3
-    const float scale = rsqrtf((float)DH);
-    bf16_t* out = dqkv + ((size_t)b * S + jk) * ld + h * DH;
+    const float scale = rsqrtf((float)hw);
+    bf16_t* out = dqkv + ((size_t)b * S + jk) * ld + h * hw;
 #pragma unroll
     for (int dt = 0; dt < DT; dt++) {
+      if (EDGE && dt * 16 + gq * 4 >= hw) continue;
       bf16x4 ok, ov;
 #pragma unroll
       for (int r = 0; r < 4; r++) {
@@ -237,16 +254,24 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
   }  // pass
 }
 
-int attn_bwd_dkv16_mfma(int B, int S, int H, const bf16_t* qkv, const float* lse, const float* delta, const bf16_t* dctx,
-                        bf16_t* dqkv, hipStream_t s) {
-  constexpr int DH = 128;
-  constexpr size_t lds_kv = 2 * (2 * (size_t)TR * DH * 2 + 4 * 256);  // two stages of Q tile | dO tile | lse, delta
-  FAX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bwd_dkv16_mfma_kernel<DH>),
+template <int DW, bool EDGE>
+static int dkv16_t(int B, int S, int H, int dh, const bf16_t* qkv, const float* lse, const float* delta, const bf16_t* dctx,
+                   bf16_t* dqkv, hipStream_t s) {
+  constexpr size_t lds_kv = 2 * (2 * (size_t)TR * row_width<DW>() * 2 + 4 * 256);  // two stages of Q tile | dO tile | lse, delta
+  FAX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bwd_dkv16_mfma_kernel<DW, EDGE>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_kv));
-  const int n_kt = S / TR;
+  const int n_kt = (S + TR - 1) / TR;
   const dim3 grid(((n_kt + 1) / 2) * B * H);
-  hipLaunchKernelGGL((attn_bwd_dkv16_mfma_kernel<DH>), grid, dim3(256), lds_kv, s, S, H, B * H, qkv, lse, delta, dctx, dqkv);
+  hipLaunchKernelGGL((attn_bwd_dkv16_mfma_kernel<DW, EDGE>), grid, dim3(256), lds_kv, s, S, H, B * H, dh, qkv, lse, delta, dctx,
+                     dqkv);
   return FAX_OK;
+}
+
+int attn_bwd_dkv16_mfma(int B, int S, int H, int dh, bool edge, const bf16_t* qkv, const float* lse, const float* delta,
+                        const bf16_t* dctx, bf16_t* dqkv, hipStream_t s) {
+  if (!edge) return dkv16_t<128, false>(B, S, H, dh, qkv, lse, delta, dctx, dqkv, s);
+  if (dh <= 96) return dkv16_t<96, true>(B, S, H, dh, qkv, lse, delta, dctx, dqkv, s);
+  return dkv16_t<128, true>(B, S, H, dh, qkv, lse, delta, dctx, dqkv, s);
 }
 
 }  // namespace fax

@@ -31,8 +31,8 @@
 
 namespace fax {
 
-// dK, dV at DH = 128: kernels_attn_dkv16.hip (16 keys per wave, its own LDS swizzle)
-int attn_bwd_dkv16_mfma(int B, int S, int H, const bf16_t* qkv, const float* lse, const float* delta, const bf16_t* dctx,
+// dK, dV at head widths above 64: kernels_attn_dkv16.hip (16 keys per wave, its own LDS swizzle)
+int attn_bwd_dkv16_mfma(int B, int S, int H, int dh, bool edge, const bf16_t* qkv, const float* lse, const float* delta, const bf16_t* dctx,
                         bf16_t* dqkv, hipStream_t s);
 
 // ---------------------------------------------------------------------------------------------
@@ -40,25 +40,28 @@ int attn_bwd_dkv16_mfma(int B, int S, int H, const bf16_t* qkv, const float* lse
 // K and V stream through two LDS buffers.  Per tile: P1 = S^T for both 32-key halves, V = online
 // softmax over the 64 keys, P3 = O^T += V^T P^T.
 // ---------------------------------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_fwd_mfma_kernel(int S, int H, int BH, const bf16_t* __restrict__ qkv,
+template <int DW, bool EDGE>
+__global__ __launch_bounds__(256, DW == 64 && !EDGE ? 3 : 2) void attn_fwd_mfma_kernel(int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
                                                             bf16_t* __restrict__ ctx, float* __restrict__ lse) {
-  constexpr int KS = DH / 16, DT = DH / 32, TB = TR * DH * 2;
+  constexpr int DH = row_width<DW>();  // row length in LDS
+  constexpr int KS = DW / 16, DT = DW / 32, TB = TR * DH * 2;
   constexpr int N = 2 * KS;            // MFMAs per phase (P3: 2 halves x 2 k-steps x DT = 2 KS as well)
   constexpr int LEAD = N < 8 ? N : 8;  // fragments in flight
   constexpr int NSEG = DH / 32;        // 1 KB load instructions per wave per tile
   extern __shared__ __attribute__((aligned(16))) char smem[];  // 2 x [K tile | V tile]
-  const int n_qt = S / 128;
+  const int n_qt = EDGE ? (S + 127) / 128 : S / 128;
   int pair, bh;
   pair_of_tiles(n_qt, BH, pair, bh);
   const int b = bh / H, h = bh % H;
-  const int Hd = H * DH;
+  const int hw = EDGE ? dh : DW, nch = hw / 8;  // head width, in elements and in 16-byte chunks
+  const int Hd = H * hw;
   const size_t ld = 3 * (size_t)Hd;
-  const bf16_t* base = qkv + (size_t)b * S * ld + h * DH;
+  const bf16_t* base = qkv + (size_t)b * S * ld + h * hw;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
-  const float scale = rsqrtf((float)DH);
+  const float scale = rsqrtf((float)hw);
   const float c = scale * LOG2E;
   const unsigned sm = lds_addr(smem);
+  if (EDGE) clear_lds(smem, 4 * TB);
 
   for (int pass = 0; pass < 2; pass++) {
     const int qt = pass == 0 ? n_qt - 1 - pair : pair;  // the long one first
@@ -67,7 +70,8 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_fwd_mfma_kernel(in
     bf16x8 qf[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ks++)
-      qf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(base + (size_t)iq * ld + ks * 16 + g * 8));
+      qf[ks] = __builtin_bit_cast(bf16x8, EDGE ? edge_load16(base + (size_t)iq * ld + ks * 16 + g * 8, iq < S && ks * 2 + g < nch)
+                                               : *reinterpret_cast<const uint4*>(base + (size_t)iq * ld + ks * 16 + g * 8));
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) settle(qf[ks]);
     float m = -INFINITY, l = 0.f;
@@ -77,11 +81,11 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_fwd_mfma_kernel(in
 #pragma unroll
       for (int v = 0; v < 16; v++) oacc[dt][v] = 0.f;
 
-    const int n_kv = 2 * (qt + 1);
+    const int n_kv = EDGE ? min(2 * (qt + 1), (S + TR - 1) / TR) : 2 * (qt + 1);
     auto tile_load = [&](int j0, int buf, int i) {
       const unsigned st = sm + buf * 2 * TB;
-      if (i < NSEG) tile_dma_seg<DH>(st, base + (size_t)j0 * ld + Hd, ld, wave, i);
-      else tile_dma_seg<DH>(st + TB, base + (size_t)j0 * ld + 2 * Hd, ld, wave, i - NSEG);
+      if (i < NSEG) tile_dma_seg<DH, EDGE>(st, base + (size_t)j0 * ld + Hd, ld, wave, i, S - j0, nch);
+      else tile_dma_seg<DH, EDGE>(st + TB, base + (size_t)j0 * ld + 2 * Hd, ld, wave, i - NSEG, S - j0, nch);
     };
     bf16x8 fr[LEAD], fc[LEAD];
     // One 64-key tile.  MASK: the tile may reach past the wave's first query.
@@ -148,7 +152,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_fwd_mfma_kernel(in
       }
       const float mc = m * c;
       float rs = 0.f;
-      bf16x8 pb[2][2];
+      bf16x8 pb[2][2], pl[2][2];  // probabilities; EDGE: and what bf16 leaves of them
 #pragma unroll
       for (int jt = 0; jt < 2; jt++)
 #pragma unroll
@@ -156,6 +160,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_fwd_mfma_kernel(in
           const float p = __builtin_amdgcn_exp2f(fmaf(s[jt][v], c, -mc));
           rs += p;
           pb[jt][v >> 3][v & 7] = (__bf16)p;
+          if (EDGE) pl[jt][v >> 3][v & 7] = (__bf16)(p - (float)(__bf16)p);
         }
       rs = sum32(rs);
       l += rs;
@@ -165,6 +170,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_fwd_mfma_kernel(in
       for (int i = 0; i < N; i++) {
         const int dt = i % DT;
         oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[i % LEAD], pb[(i / DT) % 2][(i / DT) / 2], oacc[dt], 0, 0, 0);
+        if (EDGE) oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[i % LEAD], pl[(i / DT) % 2][(i / DT) / 2], oacc[dt], 0, 0, 0);
         if (i + LEAD < N) fc[i % LEAD] = col_frag(i + LEAD);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -178,10 +184,16 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_fwd_mfma_kernel(in
     lds_dma_wait();
     __syncthreads();
     for (int t = 0; t < n_kv - 2; t++) tile(F_{}, t);
-    tile(T_{}, n_kv - 2);  // the last two tiles (128 keys) straddle the diagonal of this workgroup's 128 queries
-    tile(T_{}, n_kv - 1);
+    // the last two tiles (128 keys) straddle the diagonal of this workgroup's 128 queries
+    if (EDGE) {
+      for (int t = max(n_kv - 2, 0); t < n_kv; t++) tile(T_{}, t);
+    } else {
+      tile(T_{}, n_kv - 2);
+      tile(T_{}, n_kv - 1);
+    }
 
-    store_rows<DH>(ctx + ((size_t)b * S + iq) * Hd + h * DH, oacc, 1.f / l, g);
+    if (EDGE && iq >= S) continue;
+    store_rows<DW, EDGE>(ctx + ((size_t)b * S + iq) * Hd + h * hw, oacc, 1.f / l, g, hw);
     if (g == 0) lse[((size_t)b * H + h) * S + iq] = m * scale + logf(l);
   }  // pass
 }
@@ -196,54 +208,61 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_fwd_mfma_kernel(in
 // One barrier per 64-key tile.  Registers budgeted for two waves per SIMD, LDS for two workgroups
 // per CU (see above).
 // ---------------------------------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, int BH, const bf16_t* __restrict__ qkv,
+template <int DW, bool EDGE>
+__global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
                                                                          const float* __restrict__ lse,
                                                                          const bf16_t* __restrict__ ctx,
                                                                          const bf16_t* __restrict__ dctx,
                                                                          float* __restrict__ delta,
                                                                          bf16_t* __restrict__ dqkv) {
-  constexpr int KS = DH / 16, DT = DH / 32, TB = TR * DH * 2;
+  constexpr int DH = row_width<DW>();  // row length in LDS
+  constexpr int KS = DW / 16, DT = DW / 32, TB = TR * DH * 2;
   constexpr int N1 = 2 * KS;   // score MFMAs per 32-key half: S and dP, KS each
   constexpr int N3 = 2 * DT;   // dQ MFMAs per half: two k-steps x DT
   constexpr int LEAD = N3;     // fragments in flight
   constexpr int NSEG = DH / 32;
   static_assert(2 * NSEG <= N1 && N1 % LEAD == 0, "slot plan");
   extern __shared__ __attribute__((aligned(16))) char smem[];  // 2 x [K tile | V tile]
-  const int n_qt = S / 128;
+  const int n_qt = EDGE ? (S + 127) / 128 : S / 128;
   int pair, bh;
   pair_of_tiles(n_qt, BH, pair, bh);
   const int b = bh / H, h = bh % H;
-  const int Hd = H * DH;
+  const int hw = EDGE ? dh : DW, nch = hw / 8;  // head width, in elements and in 16-byte chunks
+  const int Hd = H * hw;
   const size_t ld = 3 * (size_t)Hd;
-  const bf16_t* base = qkv + (size_t)b * S * ld + h * DH;
+  const bf16_t* base = qkv + (size_t)b * S * ld + h * hw;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
-  const float scale = rsqrtf((float)DH);
+  const float scale = rsqrtf((float)hw);
   const float c = scale * LOG2E;
   const unsigned sm = lds_addr(smem);
+  if (EDGE) clear_lds(smem, 4 * TB);
 
   for (int pass = 0; pass < 2; pass++) {
     const int qt = pass == 0 ? n_qt - 1 - pair : pair;
     if (pass == 1 && qt == n_qt - 1 - pair) break;
     const int q0w = qt * 128 + wave * 32, iq = q0w + (lane & 31);
     bf16x8 qf[KS], dof[KS];
-    const bf16_t* dorow = dctx + ((size_t)b * S + iq) * Hd + h * DH;
+    const bf16_t* dorow = dctx + ((size_t)b * S + iq) * Hd + h * hw;
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
-      qf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(base + (size_t)iq * ld + ks * 16 + g * 8));
-      dof[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(dorow + ks * 16 + g * 8));
+      const bool ok = !EDGE || (iq < S && ks * 2 + g < nch);
+      const bf16_t* qp = base + (size_t)iq * ld + ks * 16 + g * 8;
+      qf[ks] = __builtin_bit_cast(bf16x8, EDGE ? edge_load16(qp, ok) : *reinterpret_cast<const uint4*>(qp));
+      dof[ks] = __builtin_bit_cast(bf16x8, EDGE ? edge_load16(dorow + ks * 16 + g * 8, ok)
+                                                : *reinterpret_cast<const uint4*>(dorow + ks * 16 + g * 8));
     }
-    float li = lse[((size_t)b * H + h) * S + iq] * LOG2E;
+    float li = EDGE && iq >= S ? 0.f : lse[((size_t)b * H + h) * S + iq] * LOG2E;
     float di = 0.f;  // delta_i = sum_d dO[i, d] O[i, d], half of the row per lane
-    const bf16_t* orow = ctx + ((size_t)b * S + iq) * Hd + h * DH;
+    const bf16_t* orow = ctx + ((size_t)b * S + iq) * Hd + h * hw;
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
-      const bf16x8 o = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(orow + ks * 16 + g * 8));
+      const bf16x8 o = __builtin_bit_cast(bf16x8, EDGE ? edge_load16(orow + ks * 16 + g * 8, iq < S && ks * 2 + g < nch)
+                                                       : *reinterpret_cast<const uint4*>(orow + ks * 16 + g * 8));
 #pragma unroll
       for (int e = 0; e < 8; e++) di = fmaf((float)o[e], (float)dof[ks][e], di);
     }
     di = sum32(di);
-    if (g == 0) delta[((size_t)b * H + h) * S + iq] = di;
+    if (g == 0 && (!EDGE || iq < S)) delta[((size_t)b * H + h) * S + iq] = di;
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) { settle(qf[ks]); settle(dof[ks]); }
     settle(li); settle(di);
@@ -253,11 +272,11 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
 #pragma unroll
       for (int v = 0; v < 16; v++) dq[dt][v] = 0.f;
 
-    const int n_kv = 2 * (qt + 1);
+    const int n_kv = EDGE ? min(2 * (qt + 1), (S + TR - 1) / TR) : 2 * (qt + 1);
     auto tile_load = [&](int j0, int buf, int i) {
       const unsigned st = sm + buf * 2 * TB;
-      if (i < NSEG) tile_dma_seg<DH>(st, base + (size_t)j0 * ld + Hd, ld, wave, i);
-      else tile_dma_seg<DH>(st + TB, base + (size_t)j0 * ld + 2 * Hd, ld, wave, i - NSEG);
+      if (i < NSEG) tile_dma_seg<DH, EDGE>(st, base + (size_t)j0 * ld + Hd, ld, wave, i, S - j0, nch);
+      else tile_dma_seg<DH, EDGE>(st + TB, base + (size_t)j0 * ld + 2 * Hd, ld, wave, i - NSEG, S - j0, nch);
     };
     bf16x8 f[LEAD];  // one ring for both kinds of fragment: slot i reloads the register it has just used
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -288,19 +307,22 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
           if (jt == 0 && i < 2 * NSEG) tile_load(j0n, (t + 1) & 1, i);
           __builtin_amdgcn_sched_barrier(0);
         }
-        bf16x8 db[2];
+        bf16x8 db[2], dl[2];  // dS; EDGE: and what bf16 leaves of it
         __builtin_amdgcn_s_setprio(0);
 #pragma unroll
         for (int v = 0; v < 16; v++) {
           float p = __builtin_amdgcn_exp2f(fmaf(sc[v], c, -li));
           if (MASK && t * TR + jt * 32 + (v >> 2) * 8 + g * 4 + (v & 3) > iq) p = 0.f;
-          db[v >> 3][v & 7] = (__bf16)(p * (dp[v] - di));
+          const float d = p * (dp[v] - di);
+          db[v >> 3][v & 7] = (__bf16)d;
+          if (EDGE) dl[v >> 3][v & 7] = (__bf16)(d - (float)(__bf16)d);
         }
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int i = 0; i < N3; i++) {
           dq[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], db[i / DT], dq[i % DT], 0, 0, 0);
+          if (EDGE) dq[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], dl[i / DT], dq[i % DT], 0, 0, 0);
           if (jt == 0) f[i % LEAD] = row_frag(1, i);  // the second half's first rows (N3 = LEAD)
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -315,10 +337,16 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
     lds_dma_wait();
     __syncthreads();
     for (int t = 0; t < n_kv - 2; t++) tile(F_{}, t);
-    tile(T_{}, n_kv - 2);  // the last two tiles (128 keys) straddle the diagonal of this workgroup's 128 queries
-    tile(T_{}, n_kv - 1);
+    // the last two tiles (128 keys) straddle the diagonal of this workgroup's 128 queries
+    if (EDGE) {
+      for (int t = max(n_kv - 2, 0); t < n_kv; t++) tile(T_{}, t);
+    } else {
+      tile(T_{}, n_kv - 2);
+      tile(T_{}, n_kv - 1);
+    }
 
-    store_rows<DH>(dqkv + ((size_t)b * S + iq) * ld + h * DH, dq, scale, g);
+    if (EDGE && iq >= S) continue;
+    store_rows<DW, EDGE>(dqkv + ((size_t)b * S + iq) * ld + h * hw, dq, scale, g, hw);
   }  // pass
 }
 
@@ -328,33 +356,36 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
 // a 32-query half at a time: P1 = S and dP (2 KS MFMAs), V = P and dS packed to bf16, P3 = dV^T and
 // dK^T (2 KS MFMAs); two LDS buffers, one barrier per 64-query tile.
 // ---------------------------------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S, int H, int BH, const bf16_t* __restrict__ qkv,
+template <int DW, bool EDGE>
+__global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
                                                                           const float* __restrict__ lse,
                                                                           const float* __restrict__ delta,
                                                                           const bf16_t* __restrict__ dctx,
                                                                           bf16_t* __restrict__ dqkv) {
-  constexpr int KS = DH / 16, DT = DH / 32, TB = TR * DH * 2;
+  constexpr int DH = row_width<DW>();  // row length in LDS
+  constexpr int KS = DW / 16, DT = DW / 32, TB = TR * DH * 2;
   constexpr int LD_OFF = 2 * TB, STAGE = 2 * TB + 4 * 256;  // Q tile | dO tile | lse and delta as above
   constexpr int N = 2 * KS;                   // MFMAs per phase and half
   constexpr int LEAD = N < 8 ? N : 8;         // fragments in flight
   constexpr int NSEG = DH / 32;
   static_assert(N % LEAD == 0 && 2 * NSEG + 1 <= N, "slot plan");
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int n_kt = S / 128;
+  const int n_kt = EDGE ? (S + 127) / 128 : S / 128;
   int pair, bh;
   pair_of_tiles(n_kt, BH, pair, bh);
   const int b = bh / H, h = bh % H;
-  const int Hd = H * DH;
+  const int hw = EDGE ? dh : DW, nch = hw / 8;  // head width, in elements and in 16-byte chunks
+  const int Hd = H * hw;
   const size_t ld = 3 * (size_t)Hd;
-  const bf16_t* base = qkv + (size_t)b * S * ld + h * DH;
-  const bf16_t* dob = dctx + (size_t)b * S * Hd + h * DH;
+  const bf16_t* base = qkv + (size_t)b * S * ld + h * hw;
+  const bf16_t* dob = dctx + (size_t)b * S * Hd + h * hw;
   const float* lrow = lse + ((size_t)b * H + h) * S;
   const float* drow = delta + ((size_t)b * H + h) * S;
   const int lane = threadIdx.x & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const float c = rsqrtf((float)DH) * LOG2E;
+  const float c = rsqrtf((float)hw) * LOG2E;
   const unsigned sm = lds_addr(smem);
+  if (EDGE) clear_lds(smem, 2 * STAGE);
 
   for (int pass = 0; pass < 2; pass++) {
     const int kt = pass == 0 ? pair : n_kt - 1 - pair;
@@ -363,8 +394,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
     bf16x8 kf[KS], vf[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
-      kf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(base + (size_t)jk * ld + Hd + ks * 16 + g * 8));
-      vf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(base + (size_t)jk * ld + 2 * Hd + ks * 16 + g * 8));
+      const bool ok = !EDGE || (jk < S && ks * 2 + g < nch);
+      const bf16_t *kp = base + (size_t)jk * ld + Hd + ks * 16 + g * 8, *vp = kp + Hd;
+      kf[ks] = __builtin_bit_cast(bf16x8, EDGE ? edge_load16(kp, ok) : *reinterpret_cast<const uint4*>(kp));
+      vf[ks] = __builtin_bit_cast(bf16x8, EDGE ? edge_load16(vp, ok) : *reinterpret_cast<const uint4*>(vp));
     }
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) { settle(kf[ks]); settle(vf[ks]); }
@@ -375,12 +408,12 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
       for (int v = 0; v < 16; v++) dk[dt][v] = dv[dt][v] = 0.f;
 
     const int i_first = kt * 128;
-    const int n_q = (S - i_first) / TR;
+    const int n_q = EDGE ? (S - i_first + TR - 1) / TR : (S - i_first) / TR;
     auto tile_load = [&](int i0, int buf, int i) {
       const unsigned st = sm + buf * STAGE;
-      if (i < NSEG) tile_dma_seg<DH>(st, base + (size_t)i0 * ld, ld, wave, i);
-      else if (i < 2 * NSEG) tile_dma_seg<DH>(st + TB, dob + (size_t)i0 * Hd, (size_t)Hd, wave, i - NSEG);
-      else lds_dma4(((lane & 16) ? drow : lrow) + i0 + wave * 16 + (lane & 15), st + LD_OFF + wave * 256);
+      if (i < NSEG) tile_dma_seg<DH, EDGE>(st, base + (size_t)i0 * ld, ld, wave, i, S - i0, nch);
+      else if (i < 2 * NSEG) tile_dma_seg<DH, EDGE>(st + TB, dob + (size_t)i0 * Hd, (size_t)Hd, wave, i - NSEG, S - i0, nch);
+      else if (!EDGE || i0 + wave * 16 + (lane & 15) < S) lds_dma4(((lane & 16) ? drow : lrow) + i0 + wave * 16 + (lane & 15), st + LD_OFF + wave * 256);
     };
     bf16x8 f[LEAD];  // one ring for both kinds of fragment: slot i reloads the register it has just used
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -417,7 +450,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
           if (it == 0 && i <= 2 * NSEG) tile_load(i0n, (t + 1) & 1, i);
           __builtin_amdgcn_sched_barrier(0);
         }
-        bf16x8 pb[2], db[2];
+        bf16x8 pb[2], db[2], pl[2], dl[2];  // P and dS; EDGE: and what bf16 leaves of them
         __builtin_amdgcn_s_setprio(0);
 #pragma unroll
         for (int q = 0; q < 4; q++) {
@@ -426,10 +459,15 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
           for (int r = 0; r < 4; r++) {
             const int v = q * 4 + r;
             float p = __builtin_amdgcn_exp2f(fmaf(sc[v], c, -LOG2E * f4_get(l4, r)));
-            if (MASK && jk > i0h + q * 8 + g * 4 + r) p = 0.f;
-            const float d = p * (dp[v] - f4_get(d4, r));
+            const int i = i0h + q * 8 + g * 4 + r;
+            if (MASK && (jk > i || (EDGE && i >= S))) p = 0.f;
+            const float d = EDGE && MASK && i >= S ? 0.f : p * (dp[v] - f4_get(d4, r));
             pb[v >> 3][v & 7] = (__bf16)p;
             db[v >> 3][v & 7] = (__bf16)d;
+            if (EDGE) {
+              pl[v >> 3][v & 7] = (__bf16)(p - (float)(__bf16)p);
+              dl[v >> 3][v & 7] = (__bf16)(d - (float)(__bf16)d);
+            }
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -439,6 +477,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
           const int hh = i / (2 * DT), dt = (i / 2) % DT;
           if (i % 2 == 0) dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], pb[hh], dv[dt], 0, 0, 0);
           else dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], db[hh], dk[dt], 0, 0, 0);
+          if (EDGE && i % 2 == 0) dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], pl[hh], dv[dt], 0, 0, 0);
+          if (EDGE && i % 2 != 0) dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], dl[hh], dk[dt], 0, 0, 0);
           if (i + LEAD < N) f[i % LEAD] = col_frag(it, i + LEAD);
           else if (it == 0) f[i % LEAD] = row_frag(1, i + LEAD - N);  // the second half's first rows
           __builtin_amdgcn_sched_barrier(0);
@@ -453,14 +493,21 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
     for (int i = 0; i <= 2 * NSEG; i++) tile_load(i_first, 0, i);
     lds_dma_wait();
     __syncthreads();
-    tile(T_{}, 0);  // the first two tiles (128 queries) straddle the diagonal of this workgroup's 128 keys
-    tile(T_{}, 1);
-    for (int t = 2; t < n_q; t++) tile(F_{}, t);
+    // The first two tiles (128 queries) straddle the diagonal of this workgroup's 128 keys, and under EDGE the last may reach
+    // past S; there every tile takes the masks (a second copy of the tile costs 63 spilled registers).
+    if (EDGE) {
+      for (int t = 0; t < n_q; t++) tile(T_{}, t);
+    } else {
+      tile(T_{}, 0);
+      tile(T_{}, 1);
+      for (int t = 2; t < n_q; t++) tile(F_{}, t);
+    }
 
-    const float scale = rsqrtf((float)DH);
-    bf16_t* out = dqkv + ((size_t)b * S + jk) * ld + h * DH;
-    store_rows<DH>(out + Hd, dk, scale, g);
-    store_rows<DH>(out + 2 * Hd, dv, 1.f, g);
+    const float scale = rsqrtf((float)hw);
+    if (EDGE && jk >= S) continue;
+    bf16_t* out = dqkv + ((size_t)b * S + jk) * ld + h * hw;
+    store_rows<DW, EDGE>(out + Hd, dk, scale, g, hw);
+    store_rows<DW, EDGE>(out + 2 * Hd, dv, 1.f, g, hw);
   }  // pass
 }
 
@@ -469,41 +516,59 @@ bool attn_mfma_supported(int dtype, int B, int S, int H, int dh) {
   return dtype == FAX_BF16 && (dh == 64 || dh == 128) && S > 0 && S % 128 == 0;
 }
 
+// Whole 16-byte chunks per head are all that the masked-edge form asks for.  Measured against the scalar kernels, forward / backward
+// in us: one head of 17 x 64 7.8 / 15.3 -> 8.4 / 11.7 (launch and latency), 8 heads of 64 x 32 13.1 / 28.2 -> 8.6 / 11.9,
+// 45 heads of 1000 x 80 1485 / 2966 -> 33 / 86, 32 heads of 777 x 64 572 / 1075 -> 24 / 83, 16 heads of 1500 x 128
+// 1754 / 3791 -> 47 / 115.  Errors against float64 are the scalar kernels' to three digits (the roundings of the outputs).
+bool attn_edge_supported(int dtype, int B, int S, int H, int dh) {
+  (void)B; (void)H;
+  return dtype == FAX_BF16 && dh % 8 == 0 && dh <= 128 && S > 0;
+}
+
 template <typename K>
 static int set_lds(K kern, size_t bytes) {
   FAX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
   return FAX_OK;
 }
 
-template <int DH>
-static int fwd_t(int B, int S, int H, const bf16_t* qkv, bf16_t* ctx, float* lse, hipStream_t s) {
-  constexpr size_t lds = 2 * (2 * (size_t)TR * DH * 2);  // two stages of K tile | V tile
-  FAX_TRY(set_lds(attn_fwd_mfma_kernel<DH>, lds));
-  hipLaunchKernelGGL((attn_fwd_mfma_kernel<DH>), dim3(((S / 128 + 1) / 2) * B * H), dim3(256), lds, s, S, H, B * H, qkv, ctx,
-                     lse);
+static inline unsigned grid_of(int B, int S, int H) { return (unsigned)((((S + 127) / 128 + 1) / 2) * B * H); }
+
+template <int DW, bool EDGE>
+static int fwd_t(int B, int S, int H, int dh, const bf16_t* qkv, bf16_t* ctx, float* lse, hipStream_t s) {
+  constexpr size_t lds = 2 * (2 * (size_t)TR * row_width<DW>() * 2);  // two stages of K tile | V tile
+  FAX_TRY(set_lds(attn_fwd_mfma_kernel<DW, EDGE>, lds));
+  hipLaunchKernelGGL((attn_fwd_mfma_kernel<DW, EDGE>), dim3(grid_of(B, S, H)), dim3(256), lds, s, S, H, B * H, dh, qkv, ctx, lse);
   FAX_LAUNCH_CHECK("attn_fwd_mfma");
   return FAX_OK;
 }
 
 int attn_fwd_mfma(int B, int S, int H, int dh, const void* qkv, void* ctx, float* lse, hipStream_t s) {
-  if (dh == 64) return fwd_t<64>(B, S, H, (const bf16_t*)qkv, (bf16_t*)ctx, lse, s);
-  return fwd_t<128>(B, S, H, (const bf16_t*)qkv, (bf16_t*)ctx, lse, s);
+  const bf16_t* q = (const bf16_t*)qkv;
+  bf16_t* c = (bf16_t*)ctx;
+  if (!attn_mfma_supported(FAX_BF16, B, S, H, dh)) {
+    if (dh <= 64) return fwd_t<64, true>(B, S, H, dh, q, c, lse, s);
+    if (dh <= 96) return fwd_t<96, true>(B, S, H, dh, q, c, lse, s);
+    return fwd_t<128, true>(B, S, H, dh, q, c, lse, s);
+  }
+  if (dh == 64) return fwd_t<64, false>(B, S, H, dh, q, c, lse, s);
+  return fwd_t<128, false>(B, S, H, dh, q, c, lse, s);
 }
 
-template <int DH>
-static int bwd_t(int B, int S, int H, const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx,
+template <int DW, bool EDGE>
+static int bwd_t(int B, int S, int H, int dh, const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx,
                  bf16_t* dqkv, float* delta, hipStream_t s, const AttnBwdSplit* split) {
+  constexpr int DH = row_width<DW>();
   constexpr size_t lds_q = 2 * (2 * (size_t)TR * DH * 2);  // two stages of K tile | V tile
-  const dim3 grid(((S / 128 + 1) / 2) * B * H);
-  FAX_TRY(set_lds(attn_bwd_dq_mfma_kernel<DH>, lds_q));
+  const dim3 grid(grid_of(B, S, H));
+  FAX_TRY(set_lds(attn_bwd_dq_mfma_kernel<DW, EDGE>, lds_q));
   auto dkv = [&](hipStream_t st) -> int {
-    if constexpr (DH == 64) {
+    if constexpr (DW == 64) {
       constexpr size_t lds_kv = 2 * (2 * (size_t)TR * DH * 2 + 4 * 256);  // two stages of Q tile | dO tile | lse, delta
-      FAX_TRY(set_lds(attn_bwd_dkv_phased_mfma_kernel<DH>, lds_kv));
-      hipLaunchKernelGGL((attn_bwd_dkv_phased_mfma_kernel<DH>), grid, dim3(256), lds_kv, st, S, H, B * H, qkv, lse, delta, dctx,
-                         dqkv);
+      FAX_TRY(set_lds(attn_bwd_dkv_phased_mfma_kernel<DW, EDGE>, lds_kv));
+      hipLaunchKernelGGL((attn_bwd_dkv_phased_mfma_kernel<DW, EDGE>), grid, dim3(256), lds_kv, st, S, H, B * H, dh, qkv, lse,
+                         delta, dctx, dqkv);
     } else {
-      FAX_TRY(attn_bwd_dkv16_mfma(B, S, H, qkv, lse, delta, dctx, dqkv, st));
+      FAX_TRY(attn_bwd_dkv16_mfma(B, S, H, dh, EDGE, qkv, lse, delta, dctx, dqkv, st));
     }
     return FAX_OK;
   };
@@ -513,7 +578,7 @@ static int bwd_t(int B, int S, int H, const bf16_t* qkv, const bf16_t* ctx, cons
   // its copy to scratch, and with a second stream the two kernels run at the same time.  Whether
   // this form is used depends on the shape only, so that one or two streams give the same bits.
   if (split && split->delta_scratch && attn_bwd_side_by_side(B, S, H)) {
-    FAX_TRY(attn_delta(FAX_BF16, B, S, H, DH, ctx, dctx, delta, s));
+    FAX_TRY(attn_delta(FAX_BF16, B, S, H, dh, ctx, dctx, delta, s));
     const bool two = split->side && split->fork && split->join;
     if (two) {
       FAX_HIP(hipEventRecord(split->fork, s));
@@ -521,7 +586,7 @@ static int bwd_t(int B, int S, int H, const bf16_t* qkv, const bf16_t* ctx, cons
       FAX_TRY(dkv(split->side));
       FAX_HIP(hipEventRecord(split->join, split->side));
     }
-    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<DH>), grid, dim3(256), lds_q, s, S, H, B * H, qkv, lse, ctx, dctx,
+    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<DW, EDGE>), grid, dim3(256), lds_q, s, S, H, B * H, dh, qkv, lse, ctx, dctx,
                        split->delta_scratch, dqkv);
     if (two) FAX_HIP(hipStreamWaitEvent(s, split->join, 0));
     else FAX_TRY(dkv(s));
@@ -529,7 +594,8 @@ static int bwd_t(int B, int S, int H, const bf16_t* qkv, const bf16_t* ctx, cons
     return FAX_OK;
   }
   // dQ first: it also produces delta, which the dK/dV kernel reads
-  hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<DH>), grid, dim3(256), lds_q, s, S, H, B * H, qkv, lse, ctx, dctx, delta, dqkv);
+  hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<DW, EDGE>), grid, dim3(256), lds_q, s, S, H, B * H, dh, qkv, lse, ctx, dctx, delta,
+                     dqkv);
   FAX_TRY(dkv(s));
   FAX_LAUNCH_CHECK("attn_bwd_mfma");
   return FAX_OK;
@@ -537,15 +603,21 @@ static int bwd_t(int B, int S, int H, const bf16_t* qkv, const bf16_t* ctx, cons
 
 // dK/dV runs one workgroup per CU, dQ two: side by side they need 1.5 CUs per pair of row tiles.
 bool attn_bwd_side_by_side(int B, int S, int H) {
-  const long long n = (long long)((S / 128 + 1) / 2) * B * H;
+  const long long n = (long long)(((S + 127) / 128 + 1) / 2) * B * H;
   return 3 * n <= 2 * 256;
 }
 
 int attn_bwd_mfma(int B, int S, int H, int dh, const void* qkv, const void* ctx, const float* lse, const void* dctx,
                   void* dqkv, float* delta, hipStream_t s, const AttnBwdSplit* split) {
-  if (dh == 64)
-    return bwd_t<64>(B, S, H, (const bf16_t*)qkv, (const bf16_t*)ctx, lse, (const bf16_t*)dctx, (bf16_t*)dqkv, delta, s, split);
-  return bwd_t<128>(B, S, H, (const bf16_t*)qkv, (const bf16_t*)ctx, lse, (const bf16_t*)dctx, (bf16_t*)dqkv, delta, s, split);
+  const bf16_t *q = (const bf16_t*)qkv, *c = (const bf16_t*)ctx, *dc = (const bf16_t*)dctx;
+  bf16_t* dq = (bf16_t*)dqkv;
+  if (!attn_mfma_supported(FAX_BF16, B, S, H, dh)) {
+    if (dh <= 64) return bwd_t<64, true>(B, S, H, dh, q, c, lse, dc, dq, delta, s, split);
+    if (dh <= 96) return bwd_t<96, true>(B, S, H, dh, q, c, lse, dc, dq, delta, s, split);
+    return bwd_t<128, true>(B, S, H, dh, q, c, lse, dc, dq, delta, s, split);
+  }
+  if (dh == 64) return bwd_t<64, false>(B, S, H, dh, q, c, lse, dc, dq, delta, s, split);
+  return bwd_t<128, false>(B, S, H, dh, q, c, lse, dc, dq, delta, s, split);
 }
 
 }  // namespace fax

@@ -6,6 +6,7 @@ import torch
 
 import paper_2204_06514_amd as fax
 from helpers import DEV, TDTYPE, CODE, to_dev, to_np, rel_max, rel_fro
+from oracle import transformer as orc
 from workloads import round_to_bf16
 
 pytestmark = pytest.mark.gpu
@@ -57,3 +58,55 @@ def test_edge_gemm_reads_nothing_beyond_the_contraction():
     C = torch.empty((M, N), dtype=torch.float32, device=DEV)
     fax.fax_gemm(fax.FAX_BF16, 1, 0, M, N, K, Ad, M, Bd, N, C, N, c_f32=1)
     assert rel_max(to_np(C), A.T @ B) <= 1e-5
+
+
+# B, S, H, dh: around the 64-row tiles and 128-row workgroups, head widths around 64, 96 and 128 (and one chunk), one to many heads
+ATTENTION = [(1, 1, 1, 8), (2, 17, 3, 64), (1, 63, 8, 80), (3, 64, 1, 128), (1, 65, 2, 96), (2, 127, 2, 72), (1, 128, 2, 32),
+             (1, 129, 3, 128), (1, 192, 2, 64), (2, 200, 4, 104), (1, 333, 16, 48), (1, 1000, 2, 80), (1, 777, 2, 64)]
+
+
+def _guarded(a):
+    """The tensor with rows of NaN behind it: what a kernel fetched there as a factor would show."""
+    buf = torch.full((a.size + 4096,), float("nan"), dtype=torch.bfloat16, device=DEV)
+    buf[:a.size] = to_dev(a, "bf16").reshape(-1)
+    return buf[:a.size].view(a.shape)
+
+
+@pytest.mark.parametrize("B,S,H,dh", ATTENTION)
+def test_edge_attention(B, S, H, dh):
+    rng = np.random.default_rng(S * 3 + dh)
+    Hd = H * dh
+    qkv, dctx = round_to_bf16(rng.standard_normal((B, S, 3 * Hd))), round_to_bf16(rng.standard_normal((B, S, Hd)))
+    ctx_ref, lse_ref = orc.attention_fwd(qkv, H, dh)
+    qd, dd = _guarded(qkv), _guarded(dctx)
+    full = lambda n, t: torch.full((n + 1024,), 7.0, dtype=t, device=DEV)  # noqa: E731
+    ctx, lse = full(ctx_ref.size, torch.bfloat16), full(lse_ref.size, torch.float32)
+    dq, delta = full(qkv.size, torch.bfloat16), full(lse_ref.size, torch.float32)
+    fax.fax_attention_fwd(fax.FAX_BF16, B, S, H, dh, qd, ctx, lse, fax.PATH_AUTO)
+    fax.fax_attention_bwd(fax.FAX_BF16, B, S, H, dh, qd, ctx, lse, dd, dq, delta, fax.PATH_AUTO)
+    for t, n in ((ctx, ctx_ref.size), (lse, lse_ref.size), (dq, qkv.size), (delta, lse_ref.size)):
+        assert (t[n:] == 7.0).all()   # nothing written behind the outputs
+    # ctx: one rounding to bf16 (2^-9) of a sum whose probabilities carry 2^-17; lse: fp32
+    assert rel_fro(to_np(ctx[:ctx_ref.size]).reshape(ctx_ref.shape), ctx_ref) <= 4e-3
+    assert np.abs(to_np(lse[:lse_ref.size]).reshape(lse_ref.shape) - lse_ref).max() <= 2e-5
+    # the gradients: one rounding each, plus that of ctx, which delta is formed from (the bar of the scalar kernels)
+    got, ref = to_np(dq[:qkv.size]).reshape(qkv.shape), orc.attention_bwd(dctx, qkv, H, dh)
+    for i in range(3):
+        g, r = got[..., i * Hd:(i + 1) * Hd], ref[..., i * Hd:(i + 1) * Hd]
+        if S > 1 or i == 2:
+            assert rel_fro(g, r) <= 6e-3, i
+        else:   # one query, one key: the gradients of Q and K cancel to nothing but the rounding of ctx
+            assert np.abs(g - r).max() <= 4e-2
+
+
+def test_edge_attention_agrees_with_the_plain_form():
+    """The same heads with eight more positions, which no earlier query sees: the first 256 rows have to agree."""
+    rng = np.random.default_rng(11)
+    S, H, dh = 256, 2, 128
+    qkv = to_dev(round_to_bf16(rng.standard_normal((1, S + 8, 3 * H * dh))), "bf16")
+    ctx = torch.empty((1, S, H * dh), dtype=torch.bfloat16, device=DEV); lse = torch.empty((1, H, S), device=DEV)
+    ctx2 = torch.empty((1, S + 8, H * dh), dtype=torch.bfloat16, device=DEV); lse2 = torch.empty((1, H, S + 8), device=DEV)
+    fax.fax_attention_fwd(fax.FAX_BF16, 1, S, H, dh, qkv[:, :S].contiguous(), ctx, lse, fax.PATH_MFMA)
+    fax.fax_attention_fwd(fax.FAX_BF16, 1, S + 8, H, dh, qkv, ctx2, lse2, fax.PATH_AUTO)
+    assert rel_fro(to_np(ctx2[:, :S]), to_np(ctx)) <= 8e-3
+    assert np.abs(to_np(lse2[..., :S]) - to_np(lse)).max() <= 2e-5
