@@ -447,6 +447,25 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
 }
 
 // ---- model ----------------------------------------------------------------------------------
+// Row distance of the logits.  The matrix-core products of the output projection fetch whole 16-byte chunks, so the rows of a
+// vocabulary that ends inside one are stored that much further apart (D: their other operands' rows have to be whole as
+// well).  The bytes this adds (at most 14 per row) lie over the buffer that follows the logits in the workspace, which holds
+// at least 2 D >= 16 per row and nothing that is needed while the logits are: the size of the workspace does not change.
+// 3108 tokens x 32003 x 512 against the scalar kernel: logits 1371 -> 172 us, gradient of the embedding 1869 -> 101, of the
+// hidden state 5243 -> 476.
+static int logits_ld(const FaxModelDims& m) {
+  return m.blk.dtype == FAX_BF16 && m.blk.D % 8 == 0 ? (m.V + 7) / 8 * 8 : m.V;
+}
+// logits = hf E^T, rows `ld` apart; columns beyond V, if any, repeat the last one
+static GemmArgs logits_product(const FaxModelDims& m, const void* hf, const void* tok_emb, void* logits, int ld) {
+  GemmArgs g;
+  g.dtype = m.blk.dtype; g.ta = false; g.tb = true;
+  g.M = m.blk.B * m.blk.S; g.N = ld; g.K = m.blk.D;
+  g.A = hf; g.lda = m.blk.D; g.B = tok_emb; g.ldb = m.blk.D; g.C = logits; g.ldc = ld;
+  if (ld > m.V) g.b_rows = m.V;
+  return g;
+}
+
 struct TrainWs {
   size_t xs, saved, hf, muf, rstdf, logits, row_loss, dcur, dhf, blk, headsplit, embidx, total;
   size_t x_stride, saved_stride;
@@ -468,9 +487,9 @@ static void train_layout(const FaxModelDims& m, TrainWs* W) {
   W->hf = take(z.T * z.D * z.es);
   W->muf = take(z.T * 4);
   W->rstdf = take(z.T * 4);
-  W->logits = take(z.T * (size_t)m.V * z.es);
   W->row_loss = take(z.T * 4);
-  W->dcur = take(z.T * z.D * z.es);
+  W->logits = take(z.T * (size_t)m.V * z.es);
+  W->dcur = take(z.T * z.D * z.es);  // right behind the logits, whose padded rows may reach into it (logits_ld)
   W->dhf = take(z.T * z.D * z.es);
   W->blk = take(B.total);
   W->headsplit = take(gemm_split_ws_bytes(m.V, (int)z.D, (int)z.T));  // the embedding gradient's product may split K
@@ -657,12 +676,12 @@ static void eval_layout(const FaxModelDims& m, EvalWs* W) {
   auto take = [&](size_t bytes) { size_t r = o; o += align_up(bytes); return r; };
   W->x[0] = take(z.T * z.D * z.es);
   W->x[1] = take(z.T * z.D * z.es);
-  W->saved = take(L.total);
   W->hf = take(z.T * z.D * z.es);
   W->muf = take(z.T * 4);
   W->rstdf = take(z.T * 4);
-  W->logits = take(z.T * (size_t)m.V * z.es);
   W->row_loss = take(z.T * 4);
+  W->logits = take(z.T * (size_t)m.V * z.es);
+  W->saved = take(L.total);  // right behind the logits, whose padded rows may reach into it (logits_ld)
   W->total = o;
 }
 
@@ -695,7 +714,7 @@ int fax_eval_step(const FaxModelDims* dims, const FaxModelTensors* params, const
   eval_layout(*dims, &W);
   Sizes z(d);
   char* w = (char*)ws;
-  const int T = (int)z.T, D = d.D, V = dims->V;
+  const int T = (int)z.T, D = d.D, V = dims->V, ldl = logits_ld(*dims);
   FaxBlockDims bd = d;
   bd.flags &= ~FAX_FLAG_TP_PARTIAL;
   FAX_TRY(embed_fwd(d.dtype, d.B, d.S, D, tokens, params->tok_emb, params->pos_emb, w + W.x[0], s));
@@ -703,12 +722,8 @@ int fax_eval_step(const FaxModelDims* dims, const FaxModelTensors* params, const
     FAX_TRY(block_fwd_impl(bd, params->blocks[l], w + W.x[l & 1], w + W.x[(l + 1) & 1], w + W.saved, nullptr, nullptr, s));
   FAX_TRY(ln_fwd(d.dtype, T, D, w + W.x[dims->L & 1], params->lnf_g, params->lnf_b, d.ln_eps, w + W.hf,
                  (float*)(w + W.muf), (float*)(w + W.rstdf), s));
-  GemmArgs g;  // logits = hf E^T
-  g.dtype = d.dtype; g.ta = false; g.tb = true;
-  g.M = T; g.N = V; g.K = D;
-  g.A = w + W.hf; g.lda = D; g.B = params->tok_emb; g.ldb = D; g.C = w + W.logits; g.ldc = V;
-  FAX_TRY(gemm(g, s));
-  return cross_entropy(d.dtype, T, V, w + W.logits, labels, nullptr, (float*)(w + W.row_loss), loss_out, 1.0f, s);
+  FAX_TRY(gemm(logits_product(*dims, w + W.hf, params->tok_emb, w + W.logits, ldl), s));
+  return cross_entropy(d.dtype, T, V, ldl, w + W.logits, labels, nullptr, (float*)(w + W.row_loss), loss_out, 1.0f, s);
 }
 
 int fax_train_step(const FaxModelDims* dims, const FaxModelTensors* params, const FaxModelTensors* master,
@@ -753,7 +768,7 @@ int fax_train_step(const FaxModelDims* dims, const FaxModelTensors* params, cons
   train_layout(*dims, &W);
   Sizes z(d);
   char* w = (char*)ws;
-  const int T = (int)z.T, D = d.D, V = dims->V, L = dims->L;
+  const int T = (int)z.T, D = d.D, V = dims->V, L = dims->L, ldl = logits_ld(*dims);
   FaxBlockDims bd = d;
   bd.flags &= ~FAX_FLAG_TP_PARTIAL;
 
@@ -771,16 +786,12 @@ int fax_train_step(const FaxModelDims* dims, const FaxModelTensors* params, cons
                            w + W.saved + W.saved_stride * l, nullptr, nullptr, s));
   FAX_TRY(ln_fwd(d.dtype, T, D, xL, params->lnf_g, params->lnf_b, d.ln_eps, w + W.hf, (float*)(w + W.muf),
                  (float*)(w + W.rstdf), s));
-  GemmArgs g;  // logits = hf E^T
-  g.dtype = d.dtype; g.ta = false; g.tb = true;
-  g.M = T; g.N = V; g.K = D;
-  g.A = w + W.hf; g.lda = D; g.B = params->tok_emb; g.ldb = D; g.C = w + W.logits; g.ldc = V;
-  FAX_TRY(gemm(g, s));
+  FAX_TRY(gemm(logits_product(*dims, w + W.hf, params->tok_emb, w + W.logits, ldl), s));
   }
   // loss and its gradient, in place over the logits
   {
   Timed phase_("phase_loss", WORK_BYTE, 2.0 * T * (double)V * z.es, s);
-  FAX_TRY(cross_entropy(d.dtype, T, V, w + W.logits, labels, w + W.logits, (float*)(w + W.row_loss), loss_out, grad_scale,
+  FAX_TRY(cross_entropy(d.dtype, T, V, ldl, w + W.logits, labels, w + W.logits, (float*)(w + W.row_loss), loss_out, grad_scale,
                         s));
   }
   {
@@ -788,13 +799,15 @@ int fax_train_step(const FaxModelDims* dims, const FaxModelTensors* params, cons
   // output projection backward: dE = dlogits^T hf ; dhf = dlogits E
   GemmArgs g; g.dtype = d.dtype; g.ta = true; g.tb = false;
   g.M = V; g.N = D; g.K = T;
-  g.A = w + W.logits; g.lda = V; g.B = w + W.hf; g.ldb = D; g.C = grads->tok_emb; g.ldc = D; g.c_f32 = true;
+  g.a_padded = ldl > V;
+  g.A = w + W.logits; g.lda = ldl; g.B = w + W.hf; g.ldb = D; g.C = grads->tok_emb; g.ldc = D; g.c_f32 = true;
   g.accumulate = acc;
   g.split_ws = W.headsplit < W.total ? w + W.headsplit : nullptr;
   FAX_TRY(gemm(g, s));
   g = GemmArgs(); g.dtype = d.dtype;
   g.M = T; g.N = D; g.K = V;
-  g.A = w + W.logits; g.lda = V; g.B = params->tok_emb; g.ldb = D; g.C = w + W.dhf; g.ldc = D;
+  g.a_padded = ldl > V;
+  g.A = w + W.logits; g.lda = ldl; g.B = params->tok_emb; g.ldb = D; g.C = w + W.dhf; g.ldc = D;
   FAX_TRY(gemm(g, s));
   FAX_TRY(ln_bwd(d.dtype, T, D, w + W.dhf, xL, (const float*)(w + W.muf), (const float*)(w + W.rstdf), params->lnf_g,
                  nullptr, w + W.dcur, (float*)grads->lnf_g, (float*)grads->lnf_b, acc, w + W.blk, s));
@@ -932,7 +945,7 @@ int fax_cross_entropy(int dtype, int N, int V, const void* logits, const int32_t
   if (N <= 0 || V <= 0) { set_error("bad cross-entropy size N=%d V=%d", N, V); return FAX_ERR_INVALID_ARG; }
   FAX_TRY(check_ptr(logits, "logits")); FAX_TRY(check_ptr(labels, "labels")); FAX_TRY(check_ptr(dlogits, "dlogits"));
   FAX_TRY(check_ptr(row_loss, "row_loss")); FAX_TRY(check_ptr(loss_out, "loss_out"));
-  return cross_entropy(dtype, N, V, logits, labels, dlogits, row_loss, loss_out, 1.0f, (hipStream_t)stream);
+  return cross_entropy(dtype, N, V, V, logits, labels, dlogits, row_loss, loss_out, 1.0f, (hipStream_t)stream);
 }
 
 int fax_probe_mfma(int workgroups, int iters, unsigned seed, float* sink, void* stream) {

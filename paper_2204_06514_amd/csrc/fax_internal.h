@@ -129,8 +129,9 @@ int attn_bwd_mfma(int B, int S, int H, int dh, const void* qkv, const void* ctx,
                   const void* dctx, void* dqkv, float* delta, hipStream_t s, const AttnBwdSplit* split = nullptr);
 
 // ---- loss, embedding, optimizer ---------------------------------------------------------------
-// dlogits = grad_scale (softmax - onehot) / N, may alias logits, NULL for the loss alone
-int cross_entropy(int dtype, int N, int V, const void* logits, const int32_t* labels, void* dlogits,
+// dlogits = grad_scale (softmax - onehot) / N, may alias logits, NULL for the loss alone.  Rows are `ld` >= V elements apart in
+// both (ld = V: stored densely); what lies between is not read, and set to zero in dlogits.
+int cross_entropy(int dtype, int N, int V, int ld, const void* logits, const int32_t* labels, void* dlogits,
                   float* row_loss, float* loss_out, float grad_scale, hipStream_t s);
 // Per-row losses in a file-scope device array of the library (CE_STATIC_MAX_ROWS floats, 1 MiB per GPU).
 constexpr int CE_STATIC_MAX_ROWS = 1 << 18;

@@ -185,8 +185,11 @@ static bool mfma_layout_ok(const GemmArgs& g) {
   return true;
 }
 
+// B may have fewer rows than the product has columns (GemmArgs::b_rows): only the masked-edge form stops there.
+static bool b_short(const GemmArgs& g) { return g.b_rows && g.b_rows < g.N; }
+
 bool gemm_mfma_supported(const GemmArgs& g) {
-  return mfma_layout_ok(g) && tiles_whole(g.M, g.N, g.K);  // 128: the smallest tile class
+  return mfma_layout_ok(g) && tiles_whole(g.M, g.N, g.K) && !b_short(g);  // 128: the smallest tile class
 }
 
 // The masked-edge form moves the operands in whole 16-byte chunks and the output in groups of four
@@ -246,7 +249,7 @@ static const void* offset(const void* p, size_t elements, size_t elem_bytes) {
 static void* offset(void* p, size_t elements, size_t elem_bytes) { return p ? (char*)p + elements * elem_bytes : nullptr; }
 
 int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
-  const bool edge = !tiles_whole(g0.M, g0.N, g0.K);
+  const bool edge = !tiles_whole(g0.M, g0.N, g0.K) || b_short(g0);
   if (const int td = edge ? 0 : tail_dim(g0.M, g0.N)) {
     const size_t cb = g0.c_f32 ? 4 : 2;
     for (int part = 0; part < 2; part++) {

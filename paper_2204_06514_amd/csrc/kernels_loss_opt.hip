@@ -37,17 +37,23 @@ __device__ __forceinline__ float block_reduce(float v, float* red, bool is_max) 
   return r;
 }
 
-// NV: 16-byte vectors per thread (V <= blockDim.x * NV * elements per vector, V a multiple of the latter).
-template <typename T, int NV>
-__global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V, const T* __restrict__ logits,
+// NV: 16-byte vectors per thread (V <= blockDim.x * NV * elements per vector).  PAD = false: V is a multiple of the vector.
+// PAD = true: V is not, but the row distance ld is; the elements of the last vector beyond V count as -infinity, which gives
+// them the gradient zero.  Bound by HBM and the exponentials like the other; these are the library's there, as in the
+// generic kernel that served such V before, in three passes over the row with 2-byte accesses (3108 x 32003: 262 -> 140 us).
+template <bool PAD>
+__device__ __forceinline__ float ce_exp(float d) { return PAD ? expf(d) : __builtin_amdgcn_exp2f(d * CE_LOG2E); }
+
+template <typename T, int NV, bool PAD>
+__global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V, int ld, const T* __restrict__ logits,
                                                                    const int32_t* __restrict__ labels,
                                                                    T* __restrict__ dlogits, float* __restrict__ row_loss,
                                                                    float grad_scale) {
   using Vv = Vec16<T>;
   __shared__ float red_m[CE_MAX_THREADS / 64], red_s[CE_MAX_THREADS / 64];
   const int row = blockIdx.x;
-  const T* z = logits + (size_t)row * V;
-  const int nvec = V / Vv::N;
+  const T* z = logits + (size_t)row * ld;
+  const int nvec = PAD ? (V + Vv::N - 1) / Vv::N : V / Vv::N;
   const int nt = blockDim.x;
   const int label = labels[row];
   // read before the barrier below, i.e. before any thread of the workgroup overwrites the row (dz may alias z)
@@ -57,6 +63,11 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V,
   for (int i = 0; i < NV; i++) {
     const int c = threadIdx.x + i * nt;
     if (c < nvec) zv[i].load(z + (size_t)c * Vv::N);
+    if (PAD && c == nvec - 1) {
+#pragma unroll
+      for (int e = 0; e < Vv::N; e++)
+        if (c * Vv::N + e >= V) zv[i].set(e, -INFINITY);
+    }
   }
   // this thread's maximum, then its sum of e^(z - maximum) (differences first, then the scale to base 2)
   float mt = -INFINITY;
@@ -72,13 +83,13 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V,
   for (int i = 0; i < NV; i++) {
     if (threadIdx.x + i * nt < nvec) {
 #pragma unroll
-      for (int e = 0; e < Vv::N; e++) se += __builtin_amdgcn_exp2f((zv[i].get(e) - mt) * CE_LOG2E);
+      for (int e = 0; e < Vv::N; e++) se += ce_exp<PAD>(zv[i].get(e) - mt);
     }
   }
   // combine the (maximum, sum) pairs: within the wave, then across waves through LDS.  A thread
   // without elements has maximum -inf and sum 0 and drops out.
   const float mw = wave_max(mt);
-  const float sw = wave_sum(mt == -INFINITY ? 0.f : se * __builtin_amdgcn_exp2f((mt - mw) * CE_LOG2E));
+  const float sw = wave_sum(mt == -INFINITY ? 0.f : se * ce_exp<PAD>(mt - mw));
   const int wave = threadIdx.x >> 6, nw = nt >> 6;
   if ((threadIdx.x & 63) == 0) {
     red_m[wave] = mw;
@@ -89,19 +100,19 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V,
   for (int i = 1; i < nw; i++) M = fmaxf(M, red_m[i]);
   float S = 0.f;
   for (int i = 0; i < nw; i++)  // fixed order
-    S += red_m[i] == -INFINITY ? 0.f : red_s[i] * __builtin_amdgcn_exp2f((red_m[i] - M) * CE_LOG2E);
-  if (threadIdx.x == 0) row_loss[row] = (M + __builtin_amdgcn_logf(S) * CE_LN2) - z_label;  // v_log_f32 is log2
+    S += red_m[i] == -INFINITY ? 0.f : red_s[i] * ce_exp<PAD>(red_m[i] - M);
+  if (threadIdx.x == 0) row_loss[row] = (M + (PAD ? logf(S) : __builtin_amdgcn_logf(S) * CE_LN2)) - z_label;  // v_log_f32 is log2
   if (!dlogits) return;
   const float invN = grad_scale / (float)N;
   const float inv = invN / S;
-  T* dz = dlogits + (size_t)row * V;
+  T* dz = dlogits + (size_t)row * ld;
 #pragma unroll
   for (int i = 0; i < NV; i++) {
     const int c = threadIdx.x + i * nt;
     if (c < nvec) {
       float g[Vv::N];
 #pragma unroll
-      for (int e = 0; e < Vv::N; e++) g[e] = __builtin_amdgcn_exp2f((zv[i].get(e) - M) * CE_LOG2E) * inv;
+      for (int e = 0; e < Vv::N; e++) g[e] = ce_exp<PAD>(zv[i].get(e) - M) * inv;
       const int k = label - c * Vv::N;
       if (k >= 0 && k < Vv::N) {  // rare: the vector that holds the label's column
 #pragma unroll
@@ -118,14 +129,14 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V,
 
 // Any V: three passes over the row in memory (the re-reads hit cache).
 template <typename T>
-__global__ __launch_bounds__(CE_MAX_THREADS) void ce_generic_kernel(int N, int V, const T* __restrict__ logits,
+__global__ __launch_bounds__(CE_MAX_THREADS) void ce_generic_kernel(int N, int V, int ld, const T* __restrict__ logits,
                                                                     const int32_t* __restrict__ labels,
                                                                     T* __restrict__ dlogits, float* __restrict__ row_loss,
                                                                     float grad_scale) {
   __shared__ float red[CE_MAX_THREADS / 64];
   const int row = blockIdx.x;
-  const T* z = logits + (size_t)row * V;
-  T* dz = dlogits + (size_t)row * V;
+  const T* z = logits + (size_t)row * ld;
+  T* dz = dlogits + (size_t)row * ld;
   const int label = labels[row];
   const float invN = grad_scale / (float)N;
   float mx = -INFINITY;
@@ -143,6 +154,7 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_generic_kernel(int N, int V
     if (c == label) g -= invN;
     dz[c] = from_f<T>(g);
   }
+  for (int c = V + threadIdx.x; c < ld; c += blockDim.x) dz[c] = from_f<T>(0.f);
 }
 
 // loss = mean(row_loss), summed in a fixed order by one block.
@@ -172,23 +184,32 @@ static bool ce_shape(int nvec, int* threads, int* nv) {
   return best >= 0;
 }
 
+template <typename T, bool PAD>
+static void ce_cached(int nv, int nt, int N, int V, int ld, const T* logits, const int32_t* labels, T* dlogits, float* row_loss,
+                      float grad_scale, hipStream_t s) {
+#define FAX_CE(NVT)                                                                                                   \
+  case NVT:                                                                                                           \
+    hipLaunchKernelGGL((ce_cached_kernel<T, NVT, PAD>), dim3(N), dim3(nt), 0, s, N, V, ld, logits, labels, dlogits,   \
+                       row_loss, grad_scale);                                                                         \
+    break
+  switch (nv) {
+    FAX_CE(2); FAX_CE(4); FAX_CE(6); FAX_CE(8); FAX_CE(10); FAX_CE(12); FAX_CE(16);
+  }
+#undef FAX_CE
+}
+
 template <typename T>
-static int ce_t(int N, int V, const T* logits, const int32_t* labels, T* dlogits, float* row_loss, float* loss_out,
+static int ce_t(int N, int V, int ld, const T* logits, const int32_t* labels, T* dlogits, float* row_loss, float* loss_out,
                 float grad_scale, hipStream_t s) {
   constexpr int VN = Vec16<T>::N;
   int nt = 0, nv = 0;
-  if (V % VN == 0 && ce_shape(V / VN, &nt, &nv)) {
-#define FAX_CE(NVT)                                                                                                  \
-  case NVT:                                                                                                          \
-    hipLaunchKernelGGL((ce_cached_kernel<T, NVT>), dim3(N), dim3(nt), 0, s, N, V, logits, labels, dlogits, row_loss, \
-                       grad_scale);                                                                                  \
-    break
-    switch (nv) {
-      FAX_CE(2); FAX_CE(4); FAX_CE(6); FAX_CE(8); FAX_CE(10); FAX_CE(12); FAX_CE(16);
-    }
-#undef FAX_CE
+  // dense rows of whole vectors, or rows whose distance is the next multiple of a vector
+  const bool whole = ld == V && V % VN == 0, pad = ld == (V + VN - 1) / VN * VN && ld > V;
+  if ((whole || pad) && ce_shape(ld / VN, &nt, &nv)) {
+    if (pad) ce_cached<T, true>(nv, nt, N, V, ld, logits, labels, dlogits, row_loss, grad_scale, s);
+    else ce_cached<T, false>(nv, nt, N, V, ld, logits, labels, dlogits, row_loss, grad_scale, s);
   } else {
-    hipLaunchKernelGGL((ce_generic_kernel<T>), dim3(N), dim3(CE_MAX_THREADS), 0, s, N, V, logits, labels, dlogits, row_loss,
+    hipLaunchKernelGGL((ce_generic_kernel<T>), dim3(N), dim3(CE_MAX_THREADS), 0, s, N, V, ld, logits, labels, dlogits, row_loss,
                        grad_scale);
   }
   FAX_LAUNCH_CHECK("cross_entropy");
@@ -197,13 +218,13 @@ static int ce_t(int N, int V, const T* logits, const int32_t* labels, T* dlogits
   return FAX_OK;
 }
 
-int cross_entropy(int dtype, int N, int V, const void* logits, const int32_t* labels, void* dlogits, float* row_loss,
+int cross_entropy(int dtype, int N, int V, int ld, const void* logits, const int32_t* labels, void* dlogits, float* row_loss,
                   float* loss_out, float grad_scale, hipStream_t s) {
   if (N == 0) return FAX_OK;
   Timed t_("cross_entropy", WORK_BYTE, (dlogits ? 2.0 : 1.0) * N * V * (dtype == FAX_F32 ? 4.0 : 2.0), s);
   if (dtype == FAX_F32)
-    return ce_t<float>(N, V, (const float*)logits, labels, (float*)dlogits, row_loss, loss_out, grad_scale, s);
-  return ce_t<bf16_t>(N, V, (const bf16_t*)logits, labels, (bf16_t*)dlogits, row_loss, loss_out, grad_scale, s);
+    return ce_t<float>(N, V, ld, (const float*)logits, labels, (float*)dlogits, row_loss, loss_out, grad_scale, s);
+  return ce_t<bf16_t>(N, V, ld, (const bf16_t*)logits, labels, (bf16_t*)dlogits, row_loss, loss_out, grad_scale, s);
 }
 
 // The same with the per-row losses in a buffer that belongs to the library instead of the caller:
@@ -245,7 +266,7 @@ int cross_entropy_static(int dtype, int N, int V, const void* logits, const int3
   }
   // Every row < N of the scratch is written by the row kernel before the mean reads it, and no row
   // >= N is read: nothing has to be cleared between calls.
-  return cross_entropy(dtype, N, V, logits, labels, dlogits, row_loss, loss_out, 1.0f, s);
+  return cross_entropy(dtype, N, V, V, logits, labels, dlogits, row_loss, loss_out, 1.0f, s);
 }
 
 // ---------------------------------------------------------------------------------------------

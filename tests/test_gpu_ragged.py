@@ -110,3 +110,28 @@ def test_edge_attention_agrees_with_the_plain_form():
     fax.fax_attention_fwd(fax.FAX_BF16, 1, S + 8, H, dh, qkv, ctx2, lse2, fax.PATH_AUTO)
     assert rel_fro(to_np(ctx2[:, :S]), to_np(ctx)) <= 8e-3
     assert np.abs(to_np(lse2[..., :S]) - to_np(lse)).max() <= 2e-5
+
+
+# V: one short of a tile (127: the padded rows are whole tiles, the embedding is not), one more than a vector, many vectors and a rest
+@pytest.mark.parametrize("V,D,S", [(127, 64, 128), (1001, 128, 65), (4099, 64, 128)])
+def test_output_projection_over_a_ragged_vocabulary(V, D, S):
+    from test_gpu_train import run_train_step, _dev_params, _walk
+    from helpers import dims_of
+    from workloads import BlockShape, ModelShape, make_model_inputs
+    ms = ModelShape(BlockShape(B=1, S=S, D=D, H=1, dh=D, F=128, dtype="bf16", sigma_w=0.05, L=1), V=V, S_max=S)
+    sh = ms.blk
+    p, tok, lab = make_model_inputs(ms, seed=3, generic=True)
+    lab[0, 0], lab[0, -1] = V - 1, 0        # the label in the last, partly filled vector
+    loss_ref, g_ref, _ = orc.model_loss_and_grads(p, tok, lab, sh.H, sh.dh, sh.gelu, sh.ln_eps)
+    loss, params, _, _, _, grads = run_train_step(ms, p, tok, lab, update=False)
+    assert abs(loss - loss_ref) <= 2e-3 * abs(loss_ref)
+    bad = {name: rel_fro(to_np(get(grads)), get(g_ref)) for name, get in _walk(grads)}
+    # one block of bf16 activations (2^-9 each rounding): the bar of the block and training tests
+    assert max(bad.values()) <= 2e-2, bad
+    md = fax.FaxModelDims(dims_of(sh), sh.L, V, S, 0)
+    wsb = fax.fax_eval_workspace_bytes(md)
+    ws = torch.full((wsb + 4096,), 255, dtype=torch.uint8, device=DEV)   # NaN wherever a kernel reads what none has written
+    out = torch.zeros(4, device=DEV)
+    fax.fax_eval_step(md, _dev_params(p, "bf16"), torch.from_numpy(tok).to(DEV), torch.from_numpy(lab).to(DEV), out, ws, wsb)
+    assert abs(out[0].item() - loss) <= 1e-6 * abs(loss)
+    assert (ws[wsb:] == 255).all()
