@@ -236,7 +236,9 @@ static int attention_fwd(int dtype, int B, int S, int H, int dh, const void* qkv
   }
   // PATH_MFMA asks for the plain form; the masked-edge form is the library's own choice
   const bool mfma = path == PATH_MFMA || (path == PATH_AUTO && attn_edge_supported(dtype, B, S, H, dh));
-  Timed t_(!mfma ? "attention_fwd_scalar" : ok ? "attention_fwd_mfma" : "attention_fwd_edge", WORK_FLOP, 2.0 * B * H * (double)S * S * dh, s);
+  const bool f32 = path == PATH_AUTO && attn_f32_supported(dtype, dh, qkv, ctx, nullptr, nullptr);
+  Timed t_(f32 ? "attention_fwd_mfma32" : !mfma ? "attention_fwd_scalar" : ok ? "attention_fwd_mfma" : "attention_fwd_edge", WORK_FLOP, 2.0 * B * H * (double)S * S * dh, s);
+  if (f32) return attn_fwd_f32(B, S, H, dh, qkv, ctx, lse, s);
   if (mfma) return attn_fwd_mfma(B, S, H, dh, qkv, ctx, lse, s);
   return attn_fwd_simt(dtype, B, S, H, dh, qkv, ctx, lse, s);
 }
@@ -251,7 +253,9 @@ static int attention_bwd(int dtype, int B, int S, int H, int dh, const void* qkv
   }
   // PATH_MFMA asks for the plain form; the masked-edge form is the library's own choice
   const bool mfma = path == PATH_MFMA || (path == PATH_AUTO && attn_edge_supported(dtype, B, S, H, dh));
-  Timed t_(!mfma ? "attention_bwd_scalar" : ok ? "attention_bwd_mfma" : "attention_bwd_edge", WORK_FLOP, 4.0 * B * H * (double)S * S * dh, s);
+  const bool f32 = path == PATH_AUTO && attn_f32_supported(dtype, dh, qkv, ctx, dctx, dqkv);
+  Timed t_(f32 ? "attention_bwd_mfma32" : !mfma ? "attention_bwd_scalar" : ok ? "attention_bwd_mfma" : "attention_bwd_edge", WORK_FLOP, 4.0 * B * H * (double)S * S * dh, s);
+  if (f32) return attn_bwd_f32(B, S, H, dh, qkv, ctx, lse, dctx, dqkv, delta, s);
   if (mfma) return attn_bwd_mfma(B, S, H, dh, qkv, ctx, lse, dctx, dqkv, delta, s, split);
   return attn_bwd_simt(dtype, B, S, H, dh, qkv, ctx, lse, dctx, dqkv, delta, s);
 }

@@ -68,6 +68,8 @@ struct GemmArgs {
 };
 int gemm(const GemmArgs& g, hipStream_t s);
 int gemm_simt(const GemmArgs& g, hipStream_t s);
+bool gemm_f32_supported(const GemmArgs& g);
+int gemm_f32(const GemmArgs& g, hipStream_t s);
 bool gemm_mfma_supported(const GemmArgs& g);
 bool gemm_edge_supported(const GemmArgs& g);
 // A weight-gradient product of a narrow model has few output tiles and a very long contraction
@@ -114,6 +116,10 @@ int attn_bwd_simt(int dtype, int B, int S, int H, int dh, const void* qkv, const
                   const void* dctx, void* dqkv, float* delta, hipStream_t s);
 // delta[b,h,i] = sum_d dctx[b,i,h,d] ctx[b,i,h,d]
 int attn_delta(int dtype, int B, int S, int H, int dh, const void* ctx, const void* dctx, float* delta, hipStream_t s);
+bool attn_f32_supported(int dtype, int dh, const void* qkv, const void* ctx, const void* dctx, const void* dqkv);
+int attn_fwd_f32(int B, int S, int H, int dh, const void* qkv, void* ctx, float* lse, hipStream_t s);
+int attn_bwd_f32(int B, int S, int H, int dh, const void* qkv, const void* ctx, const float* lse, const void* dctx, void* dqkv,
+                 float* delta, hipStream_t s);
 bool attn_mfma_supported(int dtype, int B, int S, int H, int dh);  // the plain form of the matrix-core kernels
 bool attn_edge_supported(int dtype, int B, int S, int H, int dh);  // plain or masked-edge form
 int attn_fwd_mfma(int B, int S, int H, int dh, const void* qkv, void* ctx, float* lse, hipStream_t s);

@@ -1,5 +1,5 @@
-// Causal attention with scalar FMAs: the fp32 path, and the fallback for head widths the MFMA
-// kernel does not cover.  One wavefront per query row (forward, dQ) or per key row (dK, dV);
+// Causal attention with scalar FMAs: the fallback for head widths and alignments that the matrix-core kernels do not
+// cover, and the form a caller gets by asking for it.  One wavefront per query row (forward, dQ) or per key row (dK, dV);
 // scores are never materialised: a 64-key chunk at a time with a running max and sum.
 // No atomics: every output element has exactly one writer.
 #include "fax_internal.h"

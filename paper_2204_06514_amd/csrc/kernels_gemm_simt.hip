@@ -1,5 +1,5 @@
-// Scalar-FMA GEMM: true fp32 multiply-add for the fp32 workloads, and the fallback for bf16
-// shapes that the MFMA kernel's tiles do not divide.  Any M, N, K, any operand orientation.
+// Scalar-FMA GEMM: the fallback for what neither matrix-core form takes (bf16 operands that 16-byte loads do not fit, fp32
+// with both operands transposed), and the form a caller gets by asking for it.  Any M, N, K, any operand orientation.
 // 64x64x16 tile, 256 threads, 4x4 outputs per thread, operands staged through LDS as fp32.
 #include <cstdio>
 
@@ -96,7 +96,8 @@ int gemm(const GemmArgs& g, hipStream_t s) {
   if (!timing_on()) return gemm_dispatch(g, s);
   // name the variant the way the kernel templates are instantiated: operand orientation
   // (k = contraction index contiguous, m = row/column index contiguous) and epilogue
-  const char* form = g.path == PATH_SIMT ? "scalar" : gemm_mfma_supported(g) ? "mfma" : g.path == PATH_AUTO && gemm_edge_supported(g) ? "edge" : "scalar";
+  const char* form = g.path == PATH_SIMT ? "scalar" : gemm_mfma_supported(g) ? "mfma" : g.path == PATH_AUTO && gemm_edge_supported(g) ? "edge" :
+                     g.path == PATH_AUTO && gemm_f32_supported(g) ? "mfma32" : "scalar";
   char name[64];
   snprintf(name, sizeof(name), "gemm_%s_A%c_B%c_%s", form, g.ta ? 'm' : 'k', g.tb ? 'k' : 'm',
            g.c_f32 ? "f32out" : g.epi == EPI_GELU ? "gelu" : g.epi == EPI_DGELU ? "dgelu" : "store");
@@ -111,6 +112,7 @@ static int gemm_dispatch(const GemmArgs& g, hipStream_t s) {
     return FAX_ERR_UNSUPPORTED;
   }
   if (mfma || (g.path == PATH_AUTO && gemm_edge_supported(g))) return gemm_mfma(g, s);
+  if (g.path == PATH_AUTO && gemm_f32_supported(g)) return gemm_f32(g, s);
   if (g.colsum) {
     // no fused form here: take the column sums of B [K, N] in a pass of their own
     if (g.tb || !g.colsum_ws) {

@@ -1,0 +1,124 @@
+"""The fp32 kernels on the matrix cores at the sizes where they can go wrong: around every tile class, single rows, contractions
+that end inside a slab, operands that no 16-byte load fits, head widths around 32, 64, 96 and 128; masked rows that are not finite."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2204_06514_amd as fax
+import helpers
+from helpers import DEV, to_dev, to_np, rel_max
+from oracle import transformer as orc
+from workloads import BlockShape, make_block_inputs, PARAM_NAMES
+
+pytestmark = pytest.mark.gpu
+EPS = 2.0 ** -24  # one fp32 rounding
+
+
+def _f32(a):
+    return a.astype(np.float32).astype(np.float64)
+
+
+def _padded(a, rows, cols):
+    """The matrix in the corner of a larger one filled with NaN: what a kernel fetched there as a factor would show."""
+    buf = torch.full((a.shape[0] + rows, a.shape[1] + cols), float("nan"), dtype=torch.float32, device=DEV)
+    buf[:a.shape[0], :a.shape[1]] = to_dev(a, "f32")
+    return buf
+
+
+# M, N, K; in this order the 32 x 32 tiles, the 64 x 64, the 128 x 64 and the 128 x 128
+GEMM = [(31, 33, 127), (33, 32, 129), (1, 64, 260), (65, 100, 128), (1, 1, 1), (1000, 1000, 72), (960, 1024, 64), (520, 2052, 33),
+        (1100, 1003, 33), (2049, 516, 64), (2047, 4100, 32), (1023, 2052, 97), (2048, 4096, 31)]
+
+
+@pytest.mark.parametrize("M,N,K", GEMM)
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+@pytest.mark.parametrize("pad", [0, 3, 4])  # rows of the operands longer than the product: 3 takes the vector loads away
+def test_gemm_f32_tiles_and_edges(M, N, K, ta, tb, pad):
+    rng = np.random.default_rng(M + N + K)
+    A, B = _f32(rng.standard_normal((K, M) if ta else (M, K))), _f32(rng.standard_normal((N, K) if tb else (K, N)))
+    bias, R = _f32(rng.standard_normal(N)), _f32(rng.standard_normal((M, N)))
+    Ad, Bd = _padded(A, 1, pad), _padded(B, 1, pad)
+    C = torch.full((M + 1, N), 7.0, dtype=torch.float32, device=DEV)
+    args = (fax.FAX_F32, ta, tb, M, N, K, Ad, Ad.shape[1], Bd, Bd.shape[1], C, N)
+    fax.fax_gemm(*args, bias=to_dev(bias, "f32"), residual=to_dev(R, "f32"), ldr=N)
+    a, b = A.T if ta else A, B.T if tb else B
+    ref = a @ b
+    # K products and sums in any order, then two more sums: at most K + 2 roundings of what the magnitudes add up to
+    size = np.abs(a) @ np.abs(b)
+    assert (np.abs(to_np(C[:M]) - (ref + bias + R)) <= (K + 2) * EPS * (size + np.abs(bias) + np.abs(R))).all()
+    fax.fax_gemm(*args, c_f32=1)
+    fax.fax_gemm(*args, c_f32=1, accumulate=1)
+    assert (np.abs(to_np(C[:M]) - 2 * ref) <= 2 * (K + 1) * EPS * size).all()
+    assert (C[M] == 7.0).all()  # nothing beyond the last row
+
+
+def test_gemm_f32_without_a_contraction():
+    bias = torch.arange(40, dtype=torch.float32, device=DEV)
+    C = torch.full((3, 40), 7.0, dtype=torch.float32, device=DEV)
+    fax.fax_gemm(fax.FAX_F32, 0, 0, 3, 40, 0, None, 0, None, 40, C, 40, bias=bias)
+    assert (C == bias).all()
+
+
+# every epilogue and the column sums, in small and in larger tiles
+@pytest.mark.parametrize("shape", [dict(B=1, S=65, D=68, H=1, dh=36, F=132), dict(B=2, S=520, D=260, H=2, dh=64, F=2052),
+                                   dict(B=3, S=333, D=257, H=4, dh=33, F=1030)])
+@pytest.mark.parametrize("gelu", ["tanh", "erf"])
+def test_block_f32(shape, gelu):
+    sh = BlockShape(dtype="f32", sigma_w=0.05, gelu=gelu, **shape)
+    p, x, dy = make_block_inputs(sh, seed=1, generic=True)
+    out = helpers.run_block(sh, p, x, dy)
+    y, c = orc.block_fwd(x, p, sh.H, sh.dh, sh.gelu, sh.ln_eps)
+    dx, g, _ = orc.block_bwd(dy, c, p)
+    worst = {k: rel_max(a, b) for k, a, b in [("y", out["y"], y), ("dx", out["dx"], dx)] + [(k, out["grads"][k], g[k]) for k in PARAM_NAMES]}
+    assert max(worst.values()) <= helpers.TOL_F32, worst
+
+
+# B, S, H, dh: one and several tiles for each of the four waves, the last one full, nearly empty and nearly full
+ATTENTION = [(1, 1, 1, 4), (2, 31, 3, 32), (1, 32, 2, 20), (3, 33, 1, 64), (1, 127, 2, 36), (2, 128, 1, 96), (1, 129, 3, 80),
+             (1, 161, 2, 128), (2, 200, 2, 100), (1, 515, 2, 64)]
+
+
+def _attention(B, S, H, dh, qkv, dctx):
+    qd, gd = _padded(qkv.reshape(B * S, -1), 40, 0), _padded(dctx.reshape(B * S, -1), 40, 0)
+    ctx = torch.full((B * S + 1, H * dh), 7.0, dtype=torch.float32, device=DEV)
+    lse = torch.empty((B, H, S), dtype=torch.float32, device=DEV)
+    dq = torch.full((B * S + 1, 3 * H * dh), 7.0, dtype=torch.float32, device=DEV)
+    fax.fax_attention_fwd(fax.FAX_F32, B, S, H, dh, qd, ctx, lse)
+    fax.fax_attention_bwd(fax.FAX_F32, B, S, H, dh, qd, ctx, lse, gd, dq, torch.empty_like(lse))
+    assert (ctx[-1] == 7.0).all() and (dq[-1] == 7.0).all()
+    return to_np(ctx[:-1]).reshape(B, S, H, dh), to_np(lse), to_np(dq[:-1]).reshape(B, S, 3, H, dh)
+
+
+def _reference(B, S, H, dh, qkv, dctx):
+    t = torch.from_numpy(qkv.reshape(B, S, 3, H, dh)).requires_grad_(True)
+    q, k, v = t.permute(2, 0, 3, 1, 4)
+    sc = (q @ k.transpose(-1, -2) / dh ** 0.5).masked_fill(torch.ones(S, S, dtype=torch.bool).triu(1), -float("inf"))
+    ctx = (torch.softmax(sc, -1) @ v).permute(0, 2, 1, 3)
+    ctx.backward(torch.from_numpy(dctx.reshape(B, S, H, dh)))
+    return ctx.detach().numpy(), torch.logsumexp(sc, -1).detach().numpy(), t.grad.numpy()
+
+
+@pytest.mark.parametrize("B,S,H,dh", ATTENTION)
+def test_attention_f32_tiles_and_edges(B, S, H, dh):
+    rng = np.random.default_rng(S + dh)
+    qkv, dctx = _f32(rng.standard_normal((B, S, 3 * H * dh))), _f32(rng.standard_normal((B, S, H * dh)))
+    for got, ref in zip(_attention(B, S, H, dh, qkv, dctx), _reference(B, S, H, dh, qkv, dctx)):
+        assert rel_max(got, ref) <= helpers.TOL_F32
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("part", [0, 1, 2])
+def test_attention_f32_masked_rows_stay_out(part, bad):
+    """A query, key or value that is not finite must not reach what the causal mask keeps it from, inside its tile and out."""
+    B, S, H, dh, at = 1, 100, 2, 64, 45
+    rng = np.random.default_rng(part)
+    qkv, dctx = _f32(rng.standard_normal((B, S, 3, H, dh))), _f32(rng.standard_normal((B, S, H * dh)))
+    clean = _attention(B, S, H, dh, qkv, dctx)
+    qkv[0, at, part, :, 5] = bad
+    got = _attention(B, S, H, dh, qkv, dctx)
+    assert np.array_equal(got[0][0, :at], clean[0][0, :at])              # earlier outputs
+    assert np.array_equal(got[2][0, :at, 0], clean[2][0, :at, 0])        # earlier dQ
+    assert not np.isfinite(got[0][0, at]).all()
+    if part == 0:                                                        # a query reaches the keys up to its own position only
+        assert np.array_equal(got[2][0, at + 1:, 1:], clean[2][0, at + 1:, 1:])
+        assert not np.isfinite(got[2][0, at, 1:]).all()
