@@ -451,22 +451,27 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
 }
 
 // ---- model ----------------------------------------------------------------------------------
-// Row distance of the logits.  The matrix-core products of the output projection fetch whole 16-byte chunks, so the rows of a
-// vocabulary that ends inside one are stored that much further apart (D: their other operands' rows have to be whole as
-// well).  The bytes this adds (at most 14 per row) lie over the buffer that follows the logits in the workspace, which holds
-// at least 2 D >= 16 per row and nothing that is needed while the logits are: the size of the workspace does not change.
-// 3108 tokens x 32003 x 512 against the scalar kernel: logits 1371 -> 172 us, gradient of the embedding 1869 -> 101, of the
-// hidden state 5243 -> 476.
+// Row distance of the logits.  The matrix-core products of the output projection and the loss fetch whole 16-byte chunks, so the
+// rows of a vocabulary that ends inside one are stored further apart (D: their other operands' rows have to be whole as
+// well): at the next multiple of 128 bytes, because the products fetch 128 bytes of a row at a time and rows that start inside
+// a cache line cost two lines each.  The bytes this adds (at most 126 per row) lie over the buffer that follows the logits in the
+// workspace, which holds at least one row of D per row and nothing that is needed while the logits are: the size of the workspace
+// does not change.  3108 tokens x 32003 x 512 in bf16: gradient of the hidden state 5243 us on the scalar kernel, 462 with rows of
+// 32008, 322 with rows of 32064.
 static int logits_ld(const FaxModelDims& m) {
-  return m.blk.dtype == FAX_BF16 && m.blk.D % 8 == 0 ? (m.V + 7) / 8 * 8 : m.V;
+  const int chunk = m.blk.dtype == FAX_BF16 ? 8 : 4, line = chunk * 8;
+  if (m.blk.D % chunk) return m.V;
+  const int unit = m.blk.D >= line ? line : chunk;
+  return (m.V + unit - 1) / unit * unit;
 }
-// logits = hf E^T, rows `ld` apart; columns beyond V, if any, repeat the last one
+// logits = hf E^T, rows `ld` apart; in bf16 the columns up to the next multiple of 8 repeat the last one (the kernel
+// stores whole groups of four), and nothing is stored beyond
 static GemmArgs logits_product(const FaxModelDims& m, const void* hf, const void* tok_emb, void* logits, int ld) {
   GemmArgs g;
   g.dtype = m.blk.dtype; g.ta = false; g.tb = true;
-  g.M = m.blk.B * m.blk.S; g.N = ld; g.K = m.blk.D;
+  g.M = m.blk.B * m.blk.S; g.N = g.dtype == FAX_BF16 && ld > m.V ? (m.V + 7) / 8 * 8 : m.V; g.K = m.blk.D;
   g.A = hf; g.lda = m.blk.D; g.B = tok_emb; g.ldb = m.blk.D; g.C = logits; g.ldc = ld;
-  if (ld > m.V) g.b_rows = m.V;
+  if (g.N > m.V) g.b_rows = m.V;
   return g;
 }
 

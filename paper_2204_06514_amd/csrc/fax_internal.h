@@ -60,7 +60,7 @@ struct GemmArgs {
   // Scratch for splitting the contraction (fp32-output form only): gemm_split_ws_bytes(M, N, K)
   // bytes, or NULL to forbid the split.
   void* split_ws = nullptr;
-  // Internal buffers only: the rows of A, as stored, are readable up to the next multiple of 8 elements
+  // Internal buffers only: the rows of A, as stored, are readable up to the next multiple of 16 bytes
   // (zeros there if the contraction runs along them) / B stored [N, K] has only this many rows (0: N);
   // the columns of C beyond them hold nothing meaningful.
   bool a_padded = false;
@@ -136,7 +136,8 @@ int attn_bwd_mfma(int B, int S, int H, int dh, const void* qkv, const void* ctx,
 
 // ---- loss, embedding, optimizer ---------------------------------------------------------------
 // dlogits = grad_scale (softmax - onehot) / N, may alias logits, NULL for the loss alone.  Rows are `ld` >= V elements apart in
-// both (ld = V: stored densely); what lies between is not read, and set to zero in dlogits.
+// both (ld = V: stored densely); what lies between is not used, and set to zero in dlogits up to the next multiple of 16
+// bytes at least, where ld is one.
 int cross_entropy(int dtype, int N, int V, int ld, const void* logits, const int32_t* labels, void* dlogits,
                   float* row_loss, float* loss_out, float grad_scale, hipStream_t s);
 // Per-row losses in a file-scope device array of the library (CE_STATIC_MAX_ROWS floats, 1 MiB per GPU).
@@ -313,7 +314,7 @@ struct EpiArgs {
   size_t split_stride;  // in elements
   size_t colsum_stride; // likewise for the column sums: range r writes colsum + r * colsum_stride
   int group;            // tile rows per column-major group of the tile walk (MFMA kernel)
-  int a_lim, b_lim;     // masked-edge form of the MFMA kernel: extent of op(A) along M, of op(B) along N, that may be read
+  int a_lim, b_lim;     // masked-edge form of the MFMA kernel: extent of op(A) along M, of op(B) along N, that may be read (fp32 kernel: a_lim, along A's rows as stored)
 };
 
 template <typename T>

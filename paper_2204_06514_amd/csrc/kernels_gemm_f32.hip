@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(int M, int N, int K, c
   float4 ra[SA::CHUNKS], rb[SB::CHUNKS];  // the slab on its way from memory to LDS
   auto request = [&](int k0) {
 #pragma unroll
-    for (int i = 0; i < SA::CHUNKS; i++) ra[i] = chunk_load<BM, BK, !TA, VEC>(A, lda, M, K, m0, k0, tid + i * 256);
+    for (int i = 0; i < SA::CHUNKS; i++) ra[i] = chunk_load<BM, BK, !TA, VEC>(A, lda, TA ? e.a_lim : M, TA ? K : e.a_lim, m0, k0, tid + i * 256);
 #pragma unroll
     for (int i = 0; i < SB::CHUNKS; i++) rb[i] = chunk_load<BN, BK, TB, VEC>(B, ldb, N, K, n0, k0, tid + i * 256);
   };
@@ -337,8 +337,10 @@ bool gemm_f32_supported(const GemmArgs& g) {
 
 int gemm_f32(const GemmArgs& g, hipStream_t s) {
   auto vec_ok = [](const void* p, int ld, int extent) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && ld % 4 == 0 && extent % 4 == 0; };
-  const bool vec = vec_ok(g.A, g.lda, g.ta ? g.M : g.K) && vec_ok(g.B, g.ldb, g.tb ? g.K : g.N);
-  const EpiArgs e{g.bias, g.R, g.ldr, g.C, g.ldc, g.C2, g.ldc2, g.U, g.ldu, g.epi, g.gelu_form, 1, g.accumulate ? 1 : 0, g.colsum};
+  const int a_row = g.ta ? g.M : g.K, a_lim = g.a_padded ? (a_row + 3) / 4 * 4 : a_row;  // how far A's rows may be read
+  const bool vec = vec_ok(g.A, g.lda, a_lim) && vec_ok(g.B, g.ldb, g.tb ? g.K : g.N);
+  EpiArgs e{g.bias, g.R, g.ldr, g.C, g.ldc, g.C2, g.ldc2, g.U, g.ldu, g.epi, g.gelu_form, 1, g.accumulate ? 1 : 0, g.colsum};
+  e.a_lim = a_lim;
   const int cls = gemm_f32_class(g.M, g.N, g.K);
   return vec ? dispatch_f32_class<true>(cls, g, e, s) : dispatch_f32_class<false>(cls, g, e, s);
 }

@@ -38,7 +38,7 @@ __device__ __forceinline__ float block_reduce(float v, float* red, bool is_max) 
 }
 
 // NV: 16-byte vectors per thread (V <= blockDim.x * NV * elements per vector).  PAD = false: V is a multiple of the vector.
-// PAD = true: V is not, but the row distance ld is; the elements of the last vector beyond V count as -infinity, which gives
+// PAD = true: V is not, but the row distance ld >= V is; the elements of the last vector beyond V count as -infinity, which gives
 // them the gradient zero.  Bound by HBM and the exponentials like the other; these are the library's there, as in the
 // generic kernel that served such V before, in three passes over the row with 2-byte accesses (3108 x 32003: 262 -> 140 us).
 template <bool PAD>
@@ -203,10 +203,9 @@ static int ce_t(int N, int V, int ld, const T* logits, const int32_t* labels, T*
                 float grad_scale, hipStream_t s) {
   constexpr int VN = Vec16<T>::N;
   int nt = 0, nv = 0;
-  // dense rows of whole vectors, or rows whose distance is the next multiple of a vector
-  const bool whole = ld == V && V % VN == 0, pad = ld == (V + VN - 1) / VN * VN && ld > V;
-  if ((whole || pad) && ce_shape(ld / VN, &nt, &nv)) {
-    if (pad) ce_cached<T, true>(nv, nt, N, V, ld, logits, labels, dlogits, row_loss, grad_scale, s);
+  // rows that start on a vector and have room for whole ones; those that end inside one take the padded form
+  if (ld % VN == 0 && ce_shape((V + VN - 1) / VN, &nt, &nv)) {
+    if (V % VN) ce_cached<T, true>(nv, nt, N, V, ld, logits, labels, dlogits, row_loss, grad_scale, s);
     else ce_cached<T, false>(nv, nt, N, V, ld, logits, labels, dlogits, row_loss, grad_scale, s);
   } else {
     hipLaunchKernelGGL((ce_generic_kernel<T>), dim3(N), dim3(CE_MAX_THREADS), 0, s, N, V, ld, logits, labels, dlogits, row_loss,

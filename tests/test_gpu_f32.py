@@ -122,3 +122,29 @@ def test_attention_f32_masked_rows_stay_out(part, bad):
     if part == 0:                                                        # a query reaches the keys up to its own position only
         assert np.array_equal(got[2][0, at + 1:, 1:], clean[2][0, at + 1:, 1:])
         assert not np.isfinite(got[2][0, at, 1:]).all()
+
+
+# V: one short of and one more than a vector, rows shorter than a cache line (D = 12: stored at the next vector instead), many vectors
+@pytest.mark.parametrize("V,D,S", [(127, 64, 33), (1001, 64, 65), (37, 12, 20), (4099, 68, 40)])
+def test_output_projection_f32_over_a_ragged_vocabulary(V, D, S):
+    from test_gpu_train import run_train_step, _dev_params, _walk
+    from helpers import dims_of
+    from workloads import ModelShape, make_model_inputs
+    ms = ModelShape(BlockShape(B=1, S=S, D=D, H=1, dh=D, F=128, dtype="f32", sigma_w=0.05, L=1), V=V, S_max=S)
+    sh = ms.blk
+    p, tok, lab = make_model_inputs(ms, seed=3, generic=True)
+    lab[0, 0], lab[0, -1] = V - 1, 0        # the label in the last, partly filled vector
+    loss_ref, g_ref, _ = orc.model_loss_and_grads(p, tok, lab, sh.H, sh.dh, sh.gelu, sh.ln_eps)
+    loss, params, _, _, _, grads = run_train_step(ms, p, tok, lab, update=False)
+    assert abs(loss - loss_ref) <= 1e-5 * abs(loss_ref)
+    bad = {name: rel_max(to_np(get(grads)), get(g_ref)) for name, get in _walk(grads)}
+    for name in [n for n in bad if n.endswith("bqkv")]:
+        del bad[name]                       # its key third is zero but for rounding
+    assert max(bad.values()) <= 1e-5, bad
+    md = fax.FaxModelDims(dims_of(sh), sh.L, V, S, 0)
+    wsb = fax.fax_eval_workspace_bytes(md)
+    ws = torch.full((wsb + 4096,), 255, dtype=torch.uint8, device=DEV)   # NaN wherever a kernel reads what none has written
+    out = torch.zeros(4, device=DEV)
+    fax.fax_eval_step(md, _dev_params(p, "f32"), torch.from_numpy(tok).to(DEV), torch.from_numpy(lab).to(DEV), out, ws, wsb)
+    assert abs(out[0].item() - loss) <= 1e-6 * abs(loss)
+    assert (ws[wsb:] == 255).all()
