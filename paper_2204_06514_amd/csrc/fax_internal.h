@@ -77,8 +77,9 @@ bool gemm_edge_supported(const GemmArgs& g);
 // partial product (and partial column sums), summed afterwards in a fixed order.  The plan (tile
 // class, number of ranges; 1 = no split) comes from a small cost model of the kernel.
 struct GemmSplitPlan {
-  int tile_m, tile_n;  // 256 x 256, 256 x 128 or 128 x 128; 0: no tile class divides the shape
+  int tile_m, tile_n;  // 256 x 256, 256 x 128, 128 x 128 or 64 x 64; 0: no tile class divides the shape
   int splits;
+  bool deep;           // the form of kernels_gemm_deep.hip
 };
 GemmSplitPlan gemm_split_plan(int M, int N, int K);
 size_t gemm_split_ws_bytes(int M, int N, int K);
@@ -89,6 +90,7 @@ double gemm_time_estimate_us(int M, int N, int K, bool f32_out);
 int gemm_mfma(const GemmArgs& g, hipStream_t s);
 struct EpiArgs;
 int gemm_mfma_edge(const GemmArgs& g, const EpiArgs& e, const GemmSplitPlan& plan, hipStream_t s);
+int gemm_mfma_deep(const GemmArgs& g, const EpiArgs& e, const GemmSplitPlan& plan, hipStream_t s);
 
 // ---- LayerNorm, column sums ---------------------------------------------------------------
 int ln_fwd(int dtype, int rows, int D, const void* x, const void* gamma, const void* beta, float eps,

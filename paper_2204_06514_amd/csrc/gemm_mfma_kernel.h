@@ -59,7 +59,12 @@ struct TileLds {
 // blocks the LDS serves in one pass, (0, 1) or (0, 2), their eight 32-byte pieces must fall into
 // eight different groups of the 256-byte bank window: bits 0-1 of kr go to bits 1-2 of the XOR
 // (four rows, two apart), bit 3 of kr to bit 0.
-__device__ __forceinline__ int mc_swizzle(int kr) { return ((kr & 3) << 1) | ((kr >> 3) & 1); }
+// A 64-wide operand has four groups per k-row and two k-rows per bank window: bit 0 of kr picks the half of the window
+// already, bit 1 goes to bit 1 of the XOR.
+template <int ROWS>
+__device__ __forceinline__ int mc_swizzle(int kr) {
+  return ROWS == 64 ? (kr & 2) | ((kr >> 3) & 1) : ((kr & 3) << 1) | ((kr >> 3) & 1);
+}
 
 // EDGE: the operand ends `lim` rows (KC) or columns (MC, at least 8 of them) after the slab's first; a
 // lane whose chunk lies beyond fetches the last one instead: finite or not, what it brings only
@@ -73,7 +78,7 @@ __device__ __forceinline__ unsigned slab_lane_offset(int ld, int b, int lim) {
   }
   constexpr int RB = ROWS * 2;  // bytes per k-row
   const int kr = b / RB, pc = (b % RB) >> 4;
-  const int lc = (((pc >> 1) ^ mc_swizzle(kr)) << 1) | (pc & 1);
+  const int lc = (((pc >> 1) ^ mc_swizzle<ROWS>(kr)) << 1) | (pc & 1);
   return (unsigned)(kr * ld + (EDGE ? min(lc << 3, lim - 8) : lc << 3)) * 2u;
 }
 // First contraction index, within the slab, of that chunk.
@@ -98,7 +103,7 @@ __device__ __forceinline__ bf16x8 frag_load(const char* lds, int rb, int ks, int
     const int blk = lane >> 4, i = lane & 15;
     const int kr = ks * 16 + (blk >> 1) * 8 + (i >> 2);  // kr + 4 has the same swizzle
     const int col = rb + (blk & 1) * 16 + (i & 3) * 4;
-    const char* p = lds + kr * (ROWS * 2) + (((col >> 4) ^ mc_swizzle(kr)) << 5) + (col & 15) * 2;
+    const char* p = lds + kr * (ROWS * 2) + (((col >> 4) ^ mc_swizzle<ROWS>(kr)) << 5) + (col & 15) * 2;
     typedef __attribute__((address_space(3))) short4v lds_s4;
     const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p));
     const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p + 4 * ROWS * 2));
@@ -211,6 +216,93 @@ __host__ __device__ inline void tile_walk(int id, int tiles_m, int tiles_n, int 
   const int gsz = group < tiles_m - gm0 ? group : tiles_m - gm0;
   tm_i = gm0 + (id % per_group) % gsz;
   tn_i = (id % per_group) / gsz;
+}
+
+// Epilogue of one wave's TM x TN accumulators, whose first element is C[mw][nw].  The wave turns 32 rows of its tile at a time
+// through LDS (fp32, `wbuf`: 32 x 32 TN floats of its own) and reads them
+// back row-wise, four consecutive columns per lane, so that a row of the wave tile leaves as
+// one contiguous run and bias, residual and the GELU side inputs move as 8-byte vectors.  On
+// the way in a lane writes the 16-byte units it owns (row l & 31); the 16-byte chunk index is
+// XOR-ed with (row & 7) so that neither those writes (8 lanes = 8 rows, same chunk) nor the
+// row-wise reads (8 lanes = 8 consecutive chunks) collide on LDS banks.  Reads are issued eight
+// rows ahead of the arithmetic and stores that consume them.
+// MASK: the tile reaches beyond the output; side inputs are fetched from clamped places (no branch
+// around a load), stores are predicated.  `et`: the epilogue operands of this work item (e of the launch).
+template <int EM, bool MASK, int TM, int TN>
+__device__ __forceinline__ void tile_epilogue(const EpiArgs& e, const EpiArgs& et, const f32x16 (&acc)[TM][TN], float* wbuf,
+                                              int mw, int nw, int M, int N, int lane_e) {
+  constexpr int WC = TN * 32;     // columns of the wave tile
+  constexpr int LPR = WC / 4;     // lanes per row on the way out
+  constexpr int RPI = 64 / LPR;   // rows per store instruction
+  constexpr int NIT = 32 / RPI;   // store instructions per 32 rows
+  constexpr int BATCH = NIT < 8 ? NIT : 8;
+  static_assert(NIT % BATCH == 0, "batching of the read-back");
+  const int c4 = (lane_e % LPR) * 4;
+  const int rsub = lane_e / LPR;
+  const int ncol = nw + c4;
+  const int ncol_r = MASK ? min(ncol, N - 4) : ncol;  // where the side inputs are read
+  auto mrow_r = [&](int m) { return MASK ? min(m, M - 1) : m; };
+  constexpr bool F32 = em_kind(EM) == EK_F32, DG = em_dgelu(EM);
+  constexpr bool SIDE = !F32 && (DG || (EM & EM_RES));  // a bf16 side input: pre-activation U or residual R
+  float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (!F32 && e.bias) bias = ld_bf16x4(e.bias, ncol_r);
+  const bf16_t* sp = (const bf16_t*)(DG ? e.U : e.R);
+  const int lds_ = DG ? e.ldu : e.ldr;
+  // the side input of 32 rows is requested one round ahead: the loads fly while the previous
+  // rows turn through LDS
+  bf16x4 side[2][SIDE ? NIT : 1];
+  auto side_request = [&](int i, bf16x4 (&dst)[SIDE ? NIT : 1]) {
+    if (SIDE) {
+#pragma unroll
+      for (int k = 0; k < NIT; k++)
+        dst[k] = *reinterpret_cast<const bf16x4*>(sp + (size_t)mrow_r(mw + i * 32 + rsub + k * RPI) * lds_ + ncol_r);
+    }
+  };
+  side_request(0, side[0]);
+#pragma unroll
+  for (int i = 0; i < TM; i++) {
+    const int mrow = mw + i * 32 + rsub;
+    if (i + 1 < TM) side_request(i + 1, side[(i + 1) & 1]);
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        const int row = lane_e & 31;
+        const int chunk = j * 8 + g * 2 + (lane_e >> 5);
+        const f32x16& t = acc[i][j];
+        *reinterpret_cast<float4*>(wbuf + row * WC + ((chunk ^ (row & 7)) << 2)) =
+            make_float4(t[g * 4], t[g * 4 + 1], t[g * 4 + 2], t[g * 4 + 3]);
+      }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int k0 = 0; k0 < NIT; k0 += BATCH) {
+      constexpr bool ADD_C = F32 && (EM & EM_RES);
+      float4 a[BATCH], old_c[ADD_C ? BATCH : 1];
+#pragma unroll
+      for (int u = 0; u < BATCH; u++) {
+        const int row = (k0 + u) * RPI + rsub;
+        a[u] = *reinterpret_cast<const float4*>(wbuf + row * WC + (((c4 >> 2) ^ (row & 7)) << 2));
+        if (ADD_C) old_c[u] = *reinterpret_cast<const float4*>((const float*)et.C + (size_t)mrow_r(mrow + (k0 + u) * RPI) * e.ldc + ncol_r);
+      }
+#pragma unroll
+      for (int u = 0; u < BATCH; u++) {
+        float4 sd = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (ADD_C) {
+          sd = old_c[u];
+        } else if (SIDE) {
+          const bf16x4 v = side[i & 1][k0 + u];
+          sd = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+        }
+        const int m = mrow + (k0 + u) * RPI;
+        if (!MASK || (m < M && ncol < N)) mfma_epilogue4<EM>(et, m, ncol, a[u], bias, sd);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
 }
 
 // EDGE = false: M, N are multiples of the tile, K of the slab.  EDGE = true: any M, N, K.  Rows and
@@ -488,20 +580,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   }
   lds_dma_wait();  // the re-requested last slab: nothing may be in flight when LDS is reused or the wave ends
 
-  // Epilogue.  Each wave turns 32 rows of its tile at a time through LDS (fp32) and reads them
-  // back row-wise, four consecutive columns per lane, so that a row of the wave tile leaves as
-  // one contiguous run and bias, residual and the GELU side inputs move as 8-byte vectors.  On
-  // the way in a lane writes the 16-byte units it owns (row l & 31); the 16-byte chunk index is
-  // XOR-ed with (row & 7) so that neither those writes (8 lanes = 8 rows, same chunk) nor the
-  // row-wise reads (8 lanes = 8 consecutive chunks) collide on LDS banks.  Reads are issued eight
-  // rows ahead of the arithmetic and stores that consume them.  The staging areas are A[2] (waves
-  // 0, 1) and B[1] (waves 2, 3): A[0], A[1] and B[0] are already receiving the next tile.
+  // Epilogue (tile_epilogue).  The staging areas are A[2] (waves 0, 1) and B[1] (waves 2, 3): A[0], A[1] and B[0] are
+  // already receiving the next tile.
   constexpr int WC = TN * 32;     // columns of the wave tile
-  constexpr int LPR = WC / 4;     // lanes per row on the way out
-  constexpr int RPI = 64 / LPR;   // rows per store instruction
-  constexpr int NIT = 32 / RPI;   // store instructions per 32 rows
-  constexpr int BATCH = NIT < 8 ? NIT : 8;
-  static_assert(NIT % BATCH == 0, "batching of the read-back");
   static_assert(2 * 32 * WC * 4 <= LA::BYTES && 2 * 32 * WC * 4 <= LB::BYTES, "two waves stage in one slab buffer");
   __syncthreads();                // every wave is done with the operand slabs
   float* wbuf = reinterpret_cast<float*>(smem + (wave < 2 ? 2 * LA::BYTES : B_BASE + LB::BYTES)) + (wave & 1) * 32 * WC;
@@ -540,76 +621,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   // the tile loop and kept in registers across the main loop, which has none to spare)
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));
-  // MASK: the tile reaches beyond the output; side inputs are fetched from clamped places (no branch
-  // around a load), stores are predicated.
   auto epilogue = [&](auto mask_c) {
-  constexpr bool MASK = decltype(mask_c)::value;
-  const int c4 = (lane_e % LPR) * 4;
-  const int rsub = lane_e / LPR;
-  const int ncol = n0 + wn + c4;
-  const int ncol_r = MASK ? min(ncol, N - 4) : ncol;  // where the side inputs are read
-  auto mrow_r = [&](int m) { return MASK ? min(m, M - 1) : m; };
-  constexpr bool F32 = em_kind(EM) == EK_F32, DG = em_dgelu(EM);
-  constexpr bool SIDE = !F32 && (DG || (EM & EM_RES));  // a bf16 side input: pre-activation U or residual R
-  float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (!F32 && e.bias) bias = ld_bf16x4(e.bias, ncol_r);
-  const bf16_t* sp = (const bf16_t*)(DG ? e.U : e.R);
-  const int lds_ = DG ? e.ldu : e.ldr;
-  // the side input of 32 rows is requested one round ahead: the loads fly while the previous
-  // rows turn through LDS
-  bf16x4 side[2][SIDE ? NIT : 1];
-  auto side_request = [&](int i, bf16x4 (&dst)[SIDE ? NIT : 1]) {
-    if (SIDE) {
-#pragma unroll
-      for (int k = 0; k < NIT; k++)
-        dst[k] = *reinterpret_cast<const bf16x4*>(sp + (size_t)mrow_r(m0 + wm + i * 32 + rsub + k * RPI) * lds_ + ncol_r);
-    }
-  };
-  side_request(0, side[0]);
-#pragma unroll
-  for (int i = 0; i < TM; i++) {
-    const int mrow = m0 + wm + i * 32 + rsub;
-    if (i + 1 < TM) side_request(i + 1, side[(i + 1) & 1]);
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int g = 0; g < 4; g++) {
-        const int row = lane_e & 31;
-        const int chunk = j * 8 + g * 2 + (lane_e >> 5);
-        const f32x16& t = acc[i][j];
-        *reinterpret_cast<float4*>(wbuf + row * WC + ((chunk ^ (row & 7)) << 2)) =
-            make_float4(t[g * 4], t[g * 4 + 1], t[g * 4 + 2], t[g * 4 + 3]);
-      }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int k0 = 0; k0 < NIT; k0 += BATCH) {
-      constexpr bool ADD_C = F32 && (EM & EM_RES);
-      float4 a[BATCH], old_c[ADD_C ? BATCH : 1];
-#pragma unroll
-      for (int u = 0; u < BATCH; u++) {
-        const int row = (k0 + u) * RPI + rsub;
-        a[u] = *reinterpret_cast<const float4*>(wbuf + row * WC + (((c4 >> 2) ^ (row & 7)) << 2));
-        if (ADD_C) old_c[u] = *reinterpret_cast<const float4*>((const float*)et.C + (size_t)mrow_r(mrow + (k0 + u) * RPI) * e.ldc + ncol_r);
-      }
-#pragma unroll
-      for (int u = 0; u < BATCH; u++) {
-        float4 sd = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (ADD_C) {
-          sd = old_c[u];
-        } else if (SIDE) {
-          const bf16x4 v = side[i & 1][k0 + u];
-          sd = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
-        }
-        const int m = mrow + (k0 + u) * RPI;
-        if (!MASK || (m < M && ncol < N)) mfma_epilogue4<EM>(et, m, ncol, a[u], bias, sd);
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
+    tile_epilogue<EM, decltype(mask_c)::value, TM, TN>(e, et, acc, wbuf, m0 + wm, n0 + wn, M, N, lane_e);
   };  // epilogue
   if constexpr (EDGE) {
     if (m0 + BM > M || n0 + BN > N) epilogue(T_{});

@@ -29,22 +29,26 @@ static int walk_group(int tiles_m, int tiles_n, int K, int splits) {
 // itself sizes its grid from the device's own CU count, see launch_mfma).
 static constexpr int kCUs = 256;
 
-// Tile classes of the kernel, largest first, and what a workgroup pays per 64-wide K slab and per
-// tile (microseconds, fitted to timings of this kernel).  The slab time is given for a full chip
-// (`full_us`) and falls with the share of busy CUs towards `floor_us`: with fewer CUs busy the
-// clock is higher (256^2: 1.55 us with all CUs busy, 1.15 with half of them) and each gets more of
+// Tile classes, largest first, and what a workgroup pays per 64-wide K slab and per
+// tile (microseconds, fitted to timings with operands that come from memory, as the previous kernel or the optimizer left them).
+// The slab time is given for a full chip (`full_us`) and falls with the share of busy CUs towards `floor_us`: with fewer CUs
+// busy the clock is higher (256^2: 1.55 us with all CUs busy, 1.1 with half of them) and each gets more of
 // the L2s' bandwidth, which is what bounds the 256 x 128 class on a full chip (13.7 TB/s into LDS
-// over all CUs: 0.89 us a slab on 256 CUs, 0.64 on 160).  The smaller the tile, the more LDS
+// over all CUs: 0.90 us a slab on 256 CUs, 0.78 on 50).  The smaller the tile, the more LDS
 // fragment traffic per flop (4 + 4 fragments per 16 MFMAs at 256^2, 4 + 2 per 8 at 256 x 128,
-// 2 + 2 per 4 at 128^2).
+// 2 + 2 per 4 at 128^2).  Measured and predicted, us: 3108 x 512 x 2048 41 / 30 / 26 / 17 / 19 in the five classes' order,
+// predicted 43 / 29 / 24 / 17 / 28; 3000 x 1200 x 4800 87 / 63 / 53 / 68 / 88, predicted 90 / 63 / 53 / 65 / 116.
 struct TileClass {
   int m, n;
+  bool deep;  // kernels_gemm_deep.hip: any shape
   double full_us, idle_share, floor_us;  // slab time = max(floor, full * (idle_share + (1 - idle_share) * busy share))
   double epi_bf16_us, epi_f32_us;
 };
-static constexpr TileClass kTiles[] = {{256, 256, 1.55, 0.48, 1.10, 7.0, 8.0},
-                                       {256, 128, 0.89, 0.25, 0.64, 4.0, 4.5},
-                                       {128, 128, 0.66, 1.00, 0.66, 3.0, 3.0}};
+static constexpr TileClass kTiles[] = {{256, 256, false, 1.55, 0.48, 1.10, 7.0, 8.0},
+                                       {256, 128, false, 0.90, 0.25, 0.78, 4.0, 4.5},
+                                       {128, 128, false, 0.66, 1.00, 0.66, 3.0, 3.0},
+                                       {128, 64, true, 0.42, 0.85, 0.37, 3.5, 3.5},
+                                       {64, 64, true, 0.36, 0.75, 0.28, 3.5, 3.5}};
 
 // Predicted duration of one launch: workgroups run in rounds of one per CU, the last one possibly
 // partly filled (a 128^2 launch of at most two per CU runs them side by side, at shared LDS
@@ -57,8 +61,11 @@ static double tile_time_us(const TileClass& tc, int M, int N, int K, bool f32_ou
     return slabs * std::max(tc.floor_us, tc.full_us * (tc.idle_share + (1.0 - tc.idle_share) * busy_share)) + epi;
   };
   double t;
-  if (tc.m == 128 && items > kCUs && items <= 2 * kCUs && !f32_out) {
+  if (tc.m == 128 && !tc.deep && items > kCUs && items <= 2 * kCUs && !(f32_out && s > 1)) {
     t = 1.6 * round_us(1.0);
+  } else if (tc.m == 64) {  // two workgroups per CU: one's epilogue runs behind the other's products
+    const long long rounds = (items + kCUs - 1) / kCUs;
+    t = rounds * (round_us(items < kCUs ? (double)items / kCUs : 1.0) - 2.0) + 2.0;
   } else {
     // (weight-gradient products, both operands through the LDS transpose read, gain nothing from a
     // partly filled round: every round at the full-chip price reproduces their measured plans)
@@ -78,26 +85,26 @@ static bool tiles_whole(int M, int N, int K) { return M % 128 == 0 && N % 128 ==
 // no class divides the shape.  The 256 x 128 class is used for bf16 outputs only: on weight-gradient
 // products (both operands through the LDS transpose read, with or without K ranges) it measured
 // 10-50 % above this model.
-static GemmSplitPlan plan_tiles(int M, int N, int K, bool f32_out, bool may_split, bool edge = false) {
-  GemmSplitPlan best{0, 0, 1};
+static GemmSplitPlan plan_tiles(int M, int N, int K, bool f32_out, bool may_split, bool edge, bool deep) {
+  GemmSplitPlan best{0, 0, 1, false};
   if (M <= 0 || N <= 0 || K <= 0 || (K % GK && !edge)) return best;
   const int nkt = (K + GK - 1) / GK;
   double best_t = 1e30;
   for (const TileClass& tc : kTiles) {
-    if ((M % tc.m || N % tc.n) && !edge) continue;
-    if (f32_out && tc.m != tc.n) continue;
+    if (tc.deep ? !deep : (M % tc.m || N % tc.n) && !edge) continue;
+    if (f32_out && tc.m != tc.n && !tc.deep) continue;
     for (int s = 1; s <= (may_split ? 32 : 1) && (s == 1 || nkt / s >= 8); s++) {
       const double t = tile_time_us(tc, M, N, K, f32_out, s);
       if (t < best_t * 0.97) {
         best_t = t;
-        best = GemmSplitPlan{tc.m, tc.n, s};
+        best = GemmSplitPlan{tc.m, tc.n, s, tc.deep};
       }
     }
   }
   return best;
 }
 
-GemmSplitPlan gemm_split_plan(int M, int N, int K) { return plan_tiles(M, N, K, true, true, !tiles_whole(M, N, K)); }
+GemmSplitPlan gemm_split_plan(int M, int N, int K) { return plan_tiles(M, N, K, true, true, !tiles_whole(M, N, K), true); }
 
 // One dimension an odd multiple of 128 and the rest big enough to fill the chip with 256^2 tiles:
 // the product is computed as two, the bulk on 256^2 tiles and the last 128 rows (1) or columns (2)
@@ -114,9 +121,10 @@ static int tail_dim(int M, int N) {
 GemmSplitPlan gemm_plan_query(int M, int N, int K, bool f32_out, int* tail) {
   const int td = tail_dim(M, N);
   *tail = td;
-  if (td == 1) return plan_tiles(M - 128, N, K, f32_out, f32_out);
-  if (td == 2) return plan_tiles(M, N - 128, K, f32_out, false);  // the strip keeps C's leading dimension: no split
-  return plan_tiles(M, N, K, f32_out, f32_out);
+  const bool deep = tiles_whole(M, N, K);
+  if (td == 1) return plan_tiles(M - 128, N, K, f32_out, f32_out, false, deep);
+  if (td == 2) return plan_tiles(M, N - 128, K, f32_out, false, false, deep);  // the strip keeps C's leading dimension: no split
+  return plan_tiles(M, N, K, f32_out, f32_out, false, deep);
 }
 
 // The tile walk of the main launch of a product (not of the 128-wide strip an odd multiple of 128
@@ -129,7 +137,7 @@ int gemm_tile_walk_query(int M, int N, int K, bool f32_out, int* tm, int* tn, in
   int grp = walk_group(tiles_m, tiles_n, K, plan.splits);
   const int nt = tiles_m * tiles_n;
   const int slots = (plan.tile_m == 128 && nt * plan.splits <= 2 * kCUs) ? 2 * kCUs : kCUs;
-  if (grp == 0 && (nt < slots ? nt : slots) != 256) grp = 4;  // as launch_mfma decides
+  if (grp == 0 && (plan.deep || (nt < slots ? nt : slots) != 256)) grp = 4;  // as launch_mfma and launch_deep decide
   *group = grp; *count = nt;
   for (int id = 0; id < nt && id < capacity; id++) tile_walk(id, tiles_m, tiles_n, grp, tm[id], tn[id]);
   return 0;
@@ -147,9 +155,9 @@ size_t gemm_split_ws_bytes(int M, int N, int K) {
 }
 
 static double time_estimate_1(int M, int N, int K, bool f32_out) {
-  const GemmSplitPlan plan = plan_tiles(M, N, K, f32_out, f32_out, !tiles_whole(M, N, K));
+  const GemmSplitPlan plan = plan_tiles(M, N, K, f32_out, f32_out, !tiles_whole(M, N, K), true);
   for (const TileClass& tc : kTiles)
-    if (tc.m == plan.tile_m && tc.n == plan.tile_n) return 3.0 + tile_time_us(tc, M, N, K, f32_out, plan.splits);
+    if (tc.m == plan.tile_m && tc.n == plan.tile_n && tc.deep == plan.deep) return 3.0 + tile_time_us(tc, M, N, K, f32_out, plan.splits);
   return 0.0;
 }
 
@@ -281,7 +289,8 @@ int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
   GemmArgs g = g0;
   // Split the contraction?  Only the fp32-output form, with scratch from the caller and C stored
   // densely; the partial products (and partial column sums) are then folded in a fixed order.
-  const GemmSplitPlan plan = plan_tiles(g.M, g.N, g.K, g.c_f32, g.c_f32 && g.split_ws && g.ldc == g.N, edge);
+  const GemmSplitPlan plan = plan_tiles(g.M, g.N, g.K, g.c_f32, g.c_f32 && g.split_ws && g.ldc == g.N, edge,
+                                        gemm_edge_supported(g));
   if (plan.tile_m == 0) {
     set_error("gemm_mfma: %d x %d x %d fits no tile class", g.M, g.N, g.K);
     return FAX_ERR_UNSUPPORTED;
@@ -299,7 +308,8 @@ int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
             g.accumulate ? 1 : 0, g.colsum, splits, mn, (size_t)g.N,
             walk_group((g.M + plan.tile_m - 1) / plan.tile_m, (g.N + plan.tile_n - 1) / plan.tile_n, g.K, splits),
             g.ta ? (g.M + 7) / 8 * 8 : g.M, g.b_rows ? g.b_rows : g.N};
-  if (edge) FAX_TRY(gemm_mfma_edge(g, e, plan, s));
+  if (plan.deep) FAX_TRY(gemm_mfma_deep(g, e, plan, s));
+  else if (edge) FAX_TRY(gemm_mfma_edge(g, e, plan, s));
   else if (plan.tile_n == 256) FAX_TRY((dispatch<256, 256>(g, e, s)));
   else if (plan.tile_m == 256) FAX_TRY((dispatch<256, 128>(g, e, s)));
   else FAX_TRY((dispatch<128, 128>(g, e, s)));

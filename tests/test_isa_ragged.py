@@ -1,5 +1,6 @@
 """The assembly-level checks of test_isa_hazards.py for the masked-edge GEMM flavours (CPU only)."""
 import os
+import re
 
 from test_isa_hazards import ROOT, _assembly, scan
 
@@ -10,3 +11,17 @@ def test_edge_gemm_loads_are_waited_for(tmp_path):
     n, bad = scan(_assembly(tmp_path, os.path.join(CSRC, "kernels_gemm_edge.hip")))
     assert n >= 36, n   # twelve flavours at three tile classes
     assert not bad, {k: v[:3] for k, v in bad.items()}
+
+
+def test_deep_gemm_assembly_blocks(tmp_path):
+    """The blocks hold only loads into LDS, waits and barriers, and every wait in front of a barrier leaves zero to three whole
+    slabs' loads in flight (a slab: three instructions a wave at 128 x 64, two at 64 x 64).  How many are in flight where is not
+    followed here: whole and cut slabs are requested on two branches, which a walk in straight line counts both."""
+    text = _assembly(tmp_path, os.path.join(CSRC, "kernels_gemm_deep.hip"))
+    n, bad = scan(text, r"_ZN3fax16gemm_deep_kernel")
+    assert n == 24, n   # twelve flavours at two tile classes
+    assert not [p for v in bad.values() for p in v if "possibly in flight" not in p]
+    for k in re.split(r"\n(?=_ZN3fax16gemm_deep_kernel[^\n]*:\s)", text)[1:]:
+        slab = 3 if "ILi128ELi64E" in k.split(":")[0] else 2
+        waits = re.findall(r"#ASMSTART\s+s_waitcnt vmcnt\((\d+)\)\s+s_barrier\s", k)
+        assert set(waits) == {str(i * slab) for i in range(4)}, waits
