@@ -339,15 +339,22 @@ static int side_stream(SideStream** out) {
 
 // When every product of the backward pass is a whole number of rounds of one workgroup per CU
 // (the 4096-wide block: 256 to 2048 tiles each), the second stream has nothing to fill and the
-// kernels would only take turns: everything then stays on the caller's stream.
+// kernels would only take turns: everything then stays on the caller's stream.  Likewise when the products are so short
+// that the host cannot keep up: the ten events and waits of the second stream cost it some 85 us a call, on top of the 40 of
+// the launches (fp32 block of 128 tokens x 128: 161 us with the second stream, 95 without; bf16, 512 tokens x 256: 192
+// and 165; where the products' estimate is 150 us, 3108 tokens x 512, it gains 5 %, at 420 us, 2048 x 5120 shares, 5 %).
 static bool use_side_stream(const FaxBlockDims& d) {
   if (d.flags & FAX_FLAG_SINGLE_STREAM) return false;
-  if (d.dtype != FAX_BF16) return true;
   Sizes z(d);
   const int T = (int)z.T, D = d.D, Hd = (int)z.Hd, F = d.F;
   const int shapes[8][4] = {{F, D, T, 1}, {D, F, T, 1}, {Hd, D, T, 1}, {D, 3 * Hd, T, 1},
                             {T, F, D, 0}, {T, D, F, 0}, {T, Hd, D, 0}, {T, D, 3 * Hd, 0}};
   constexpr long long kCUs = 256;
+  double us = 0.0;
+  for (const auto& g : shapes)
+    us += d.dtype == FAX_BF16 ? gemm_time_estimate_us(g[0], g[1], g[2], g[3] != 0) : 5.0 + 2.0 * g[0] * g[1] * g[2] / 90.0e6;
+  if (us < 110.0) return false;
+  if (d.dtype != FAX_BF16) return true;
   for (const auto& g : shapes) {
     int tail = 0;
     const GemmSplitPlan p = gemm_plan_query(g[0], g[1], g[2], g[3] != 0, &tail);
