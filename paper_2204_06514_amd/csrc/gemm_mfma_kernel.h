@@ -141,6 +141,28 @@ __device__ __forceinline__ void gelu_tanh_both(float u, float& g, float& dg) {
   dg = fmaf(fmaf(-g, sg, g), fmaf(0.21406445f, u2, 1.5957691216057308f), sg);
 }
 
+// erf-form GELU.  With x = |u| / sqrt(2), erfc(x) / 2 = e^(-x^2) Q(t), t = 1 / (1 + 0.33 x), Q a polynomial of degree 8 without
+// constant term fitted here to the smallest largest relative error over x < 9.5 (8.2e-8); e^(-x^2) = e^(-u^2 / 2) is the
+// density's exponential as well, so value and derivative share one v_exp_f32 and one v_rcp_f32: 26 issue slots per element
+// where the library's erf and exp are over a hundred with both of their branches.  The lower tail has no cancellation
+// (1 + erf loses it below u = -3); elsewhere the error is that of fp32 sums near 1 either way (4e-8 of the values' norm).  The
+// FFN-in product of 3000 tokens x 4800 x 1200: 154 -> 59 us.
+__device__ __forceinline__ void gelu_erf_both(float u, float& g, float& dg) {
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.23334524f, fabsf(u), 1.f));
+  const float e = __builtin_amdgcn_exp2f(u * u * -0.72134752f);
+  float q = fmaf(-0.067964382f, t, 0.23134403f);
+  q = fmaf(q, t, -0.17771934f);
+  q = fmaf(q, t, 0.20627069f);
+  q = fmaf(q, t, 0.022505369f);
+  q = fmaf(q, t, 0.10096190f);
+  q = fmaf(q, t, 0.091418624f);
+  q = fmaf(q, t, 0.093183056f);
+  const float c = q * t * e;
+  const float cdf = u < 0.f ? c : 1.f - c;
+  g = u * cdf;
+  dg = fmaf(u * 0.39894228f, e, cdf);
+}
+
 // Four consecutive columns n..n+3 of row m at once: 8-byte bf16 loads and stores.
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 __device__ __forceinline__ float4 ld_bf16x4(const void* base, size_t idx) {
@@ -181,10 +203,8 @@ __device__ __forceinline__ void mfma_epilogue4(const EpiArgs& e, int m, int n, f
       gelu_tanh_both(a.x, g.x, dg.x); gelu_tanh_both(a.y, g.y, dg.y);
       gelu_tanh_both(a.z, g.z, dg.z); gelu_tanh_both(a.w, g.w, dg.w);
     } else {
-      g = make_float4(gelu_f(a.x, FAX_GELU_ERF), gelu_f(a.y, FAX_GELU_ERF), gelu_f(a.z, FAX_GELU_ERF),
-                      gelu_f(a.w, FAX_GELU_ERF));
-      dg = make_float4(gelu_grad_f(a.x, FAX_GELU_ERF), gelu_grad_f(a.y, FAX_GELU_ERF), gelu_grad_f(a.z, FAX_GELU_ERF),
-                       gelu_grad_f(a.w, FAX_GELU_ERF));
+      gelu_erf_both(a.x, g.x, dg.x); gelu_erf_both(a.y, g.y, dg.y);
+      gelu_erf_both(a.z, g.z, dg.z); gelu_erf_both(a.w, g.w, dg.w);
     }
     st_bf16x4(e.C, (size_t)m * e.ldc + n, dg);
     st_bf16x4(e.C2, (size_t)m * e.ldc2 + n, g);
