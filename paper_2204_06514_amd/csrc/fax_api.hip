@@ -395,7 +395,7 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
     g.A = act; g.lda = lda; g.B = grad; g.ldb = ldb; g.C = out; g.ldc = Ndim; g.c_f32 = true; g.accumulate = acc;
     g.colsum = (float*)bias_grad; g.colsum_ws = red_w;
     g.split_ws = W.splitk < W.total ? ws + W.splitk : nullptr;
-    return gemm(g, sw);
+    return g;
   };
   auto dgrad = [&](const void* grad, int lda, int Ndim, const void* w, int ldw, int Kdim, void* out) {
     GemmArgs g;  // out[T, Kdim] = grad[T, Ndim] w[Kdim, Ndim]^T
@@ -403,6 +403,13 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
     g.M = T; g.N = Kdim; g.K = Ndim;
     g.A = grad; g.lda = lda; g.B = w; g.ldb = ldw; g.C = out; g.ldc = Kdim;
     return g;
+  };
+  // a layer's two products: on one stream each, or, on the caller's stream, in one launch where that is offered
+  auto both = [&](const GemmArgs& w, const GemmArgs& g, bool mark_w2) -> int {
+    if (!side && gemm_pair_supported(w, g)) return gemm_pair(w, g, s);
+    FAX_TRY(gemm(w, sw));
+    if (side && mark_w2) FAX_HIP(hipEventRecord(side->w2_done, side->s));
+    return gemm(g, s);
   };
   // main stream records `e` once the tensor the next weight gradient reads is complete; the side stream waits for it
   auto hand_over = [&](hipEvent_t SideStream::*e) -> int {
@@ -414,25 +421,21 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
 
   // feed-forward output projection
   FAX_TRY(hand_over(&SideStream::fork));  // everything enqueued before this call (dy, saved, ...) is visible to the side stream
-  FAX_TRY(wgrad(saved + L.a, F, F, dy, D, D, gr.w2, gr.b2));
-  if (side) FAX_HIP(hipEventRecord(side->w2_done, side->s));
   {
     GemmArgs g = dgrad(dy, D, D, p.w2, D, F, du);  // du = (dy W2^T) * gelu'(u)
     g.epi = EPI_DGELU; g.U = saved + L.dgelu; g.ldu = F;
-    FAX_TRY(gemm(g, s));
+    FAX_TRY(both(wgrad(saved + L.a, F, F, dy, D, D, gr.w2, gr.b2), g, true));
   }
   // feed-forward input projection
   FAX_TRY(hand_over(&SideStream::du));
-  FAX_TRY(wgrad(saved + L.h2, D, D, du, F, F, gr.w1, gr.b1));
-  FAX_TRY(gemm(dgrad(du, F, F, p.w1, F, D, dh2), s));
+  FAX_TRY(both(wgrad(saved + L.h2, D, D, du, F, F, gr.w1, gr.b1), dgrad(du, F, F, p.w1, F, D, dh2), false));
   // LN2 and the residual branch: dx1 = dy + LN2'(dh2)
   FAX_TRY(ln_bwd(d.dtype, T, D, dh2, saved + L.x1, (const float*)(saved + L.mu2), (const float*)(saved + L.rstd2),
                  p.ln2_g, dy, dx1, (float*)gr.ln2_g, (float*)gr.ln2_b, acc, red, s, side ? side->s : nullptr,
                  side ? side->ln2 : nullptr));
   // attention output projection
   FAX_TRY(hand_over(&SideStream::dx1));
-  FAX_TRY(wgrad(saved + L.ctx, Hd, Hd, dx1, D, D, gr.wo, gr.bo));
-  FAX_TRY(gemm(dgrad(dx1, D, D, p.wo, D, Hd, dctx), s));
+  FAX_TRY(both(wgrad(saved + L.ctx, Hd, Hd, dx1, D, D, gr.wo, gr.bo), dgrad(dx1, D, D, p.wo, D, Hd, dctx), false));
   // attention
   const AttnBwdSplit split{(float*)(ws + W.delta2), side ? side->s : nullptr, side ? side->attn_fork : nullptr,
                            side ? side->attn_join : nullptr};
@@ -440,8 +443,7 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
                         dqkv, delta, PATH_AUTO, s, &split));
   // QKV projection
   FAX_TRY(hand_over(&SideStream::dqkv));
-  FAX_TRY(wgrad(saved + L.h1, D, D, dqkv, 3 * Hd, 3 * Hd, gr.wqkv, gr.bqkv));
-  FAX_TRY(gemm(dgrad(dqkv, 3 * Hd, 3 * Hd, p.wqkv, 3 * Hd, D, dh1), s));
+  FAX_TRY(both(wgrad(saved + L.h1, D, D, dqkv, 3 * Hd, 3 * Hd, gr.wqkv, gr.bqkv), dgrad(dqkv, 3 * Hd, 3 * Hd, p.wqkv, 3 * Hd, D, dh1), false));
   // LN1 and the residual branch: dx = dx1 + LN1'(dh1).  dx may be the buffer dy came in: the first
   // weight gradient, which reads dy, has to be through with it.
   if (side) FAX_HIP(hipStreamWaitEvent(s, side->w2_done, 0));

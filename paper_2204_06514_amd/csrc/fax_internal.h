@@ -91,6 +91,11 @@ int gemm_mfma(const GemmArgs& g, hipStream_t s);
 struct EpiArgs;
 int gemm_mfma_edge(const GemmArgs& g, const EpiArgs& e, const GemmSplitPlan& plan, hipStream_t s);
 int gemm_mfma_deep(const GemmArgs& g, const EpiArgs& e, const GemmSplitPlan& plan, hipStream_t s);
+int gemm_mfma_deep_pair(const GemmArgs& wg, const EpiArgs& we, const GemmSplitPlan& wp, const GemmArgs& dg, const EpiArgs& de,
+                        const GemmSplitPlan& dp, hipStream_t s);
+// A weight-gradient product (with column sums) and an input-gradient product that do not depend on each other, in one launch.
+bool gemm_pair_supported(const GemmArgs& w, const GemmArgs& d);
+int gemm_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s);
 
 // ---- LayerNorm, column sums ---------------------------------------------------------------
 int ln_fwd(int dtype, int rows, int D, const void* x, const void* gamma, const void* beta, float eps,

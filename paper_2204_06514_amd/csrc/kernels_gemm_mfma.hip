@@ -256,6 +256,40 @@ static const void* offset(const void* p, size_t elements, size_t elem_bytes) {
 }
 static void* offset(void* p, size_t elements, size_t elem_bytes) { return p ? (char*)p + elements * elem_bytes : nullptr; }
 
+static EpiArgs epi_args(const GemmArgs& g, const GemmSplitPlan& plan) {
+  return EpiArgs{g.bias, g.R, g.ldr, g.C, g.ldc, g.C2, g.ldc2, g.U, g.ldu, g.epi, g.gelu_form, g.c_f32 ? 1 : 0,
+                 g.accumulate ? 1 : 0, g.colsum, plan.splits, (size_t)g.M * g.N, (size_t)g.N,
+                 walk_group((g.M + plan.tile_m - 1) / plan.tile_m, (g.N + plan.tile_n - 1) / plan.tile_n, g.K, plan.splits),
+                 g.ta ? (g.M + 7) / 8 * 8 : g.M, g.b_rows ? g.b_rows : g.N};
+}
+
+// The plan gemm_mfma() would launch, if that is the small-tile form in one launch.
+static bool deep_alone(const GemmArgs& g, GemmSplitPlan* plan) {
+  if (g.path != PATH_AUTO || !gemm_edge_supported(g)) return false;
+  const bool edge = !tiles_whole(g.M, g.N, g.K) || b_short(g);
+  if (!edge && tail_dim(g.M, g.N)) return false;
+  *plan = plan_tiles(g.M, g.N, g.K, g.c_f32, g.c_f32 && g.split_ws && g.ldc == g.N, edge, true);
+  return plan->deep && plan->splits == 1;
+}
+
+// The pair takes one launch where both products take the small-tile form by themselves, undivided: those leave CUs idle or last
+// little longer than a launch.  The results are the same bits.  (Larger tiles fill the chip alone.)
+bool gemm_pair_supported(const GemmArgs& w, const GemmArgs& d) {
+  GemmSplitPlan wp, dp;
+  return w.c_f32 && w.ta && !w.tb && w.colsum && !d.c_f32 && !d.ta && d.tb && !d.C2 && !d.R && !d.bias &&
+         (d.epi == EPI_NONE || d.epi == EPI_DGELU) && deep_alone(w, &wp) && deep_alone(d, &dp);
+}
+
+int gemm_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s) {
+  GemmSplitPlan wp, dp;
+  if (!deep_alone(w, &wp) || !deep_alone(d, &dp)) {
+    set_error("gemm_pair: not two products of the small-tile form");
+    return FAX_ERR_UNSUPPORTED;
+  }
+  Timed t("gemm_mfma_pair", WORK_FLOP, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, s);
+  return gemm_mfma_deep_pair(w, epi_args(w, wp), wp, d, epi_args(d, dp), dp, s);
+}
+
 int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
   const bool edge = !tiles_whole(g0.M, g0.N, g0.K) || b_short(g0);
   if (const int td = edge ? 0 : tail_dim(g0.M, g0.N)) {
@@ -304,10 +338,7 @@ int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
     if (g.colsum) g.colsum = part_cs;
     g.accumulate = false;
   }
-  EpiArgs e{g.bias, g.R, g.ldr, g.C, g.ldc, g.C2, g.ldc2, g.U, g.ldu, g.epi, g.gelu_form, g.c_f32 ? 1 : 0,
-            g.accumulate ? 1 : 0, g.colsum, splits, mn, (size_t)g.N,
-            walk_group((g.M + plan.tile_m - 1) / plan.tile_m, (g.N + plan.tile_n - 1) / plan.tile_n, g.K, splits),
-            g.ta ? (g.M + 7) / 8 * 8 : g.M, g.b_rows ? g.b_rows : g.N};
+  const EpiArgs e = epi_args(g, plan);
   if (plan.deep) FAX_TRY(gemm_mfma_deep(g, e, plan, s));
   else if (edge) FAX_TRY(gemm_mfma_edge(g, e, plan, s));
   else if (plan.tile_n == 256) FAX_TRY((dispatch<256, 256>(g, e, s)));

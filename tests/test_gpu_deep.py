@@ -68,3 +68,39 @@ def test_block_on_deep_tiles(shape, gelu):
     dx, g, _ = orc.block_bwd(dy, c, p)
     worst = {k: rel_fro(a, b) for k, a, b in [("y", out["y"], y), ("dx", out["dx"], dx)] + [(k, out["grads"][k], g[k]) for k in PARAM_NAMES]}
     assert max(worst.values()) <= helpers.TOL_BF16, worst
+
+
+# A layer's weight and input gradient in one launch (small products, one stream): the bits that fax_gemm gives from the same tensors in
+# launches of their own.  Whole and cut slabs, 64- and 128-row tiles of either product, gradients stored and added to.
+@pytest.mark.parametrize("shape", [dict(B=2, S=256, D=256, H=4, dh=64, F=1024), dict(B=1, S=100, D=200, H=2, dh=72, F=520),
+                                   dict(B=1, S=1, D=64, H=1, dh=64, F=72), dict(B=1, S=65, D=512, H=8, dh=64, F=2048)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_paired_gradients(shape, accumulate):
+    sh = BlockShape(dtype="bf16", sigma_w=0.03, gelu="tanh", **shape)
+    p, x, dy = make_block_inputs(sh, seed=3, generic=True)
+    init = {k: np.full(p[k].shape, 0.5) for k in PARAM_NAMES} if accumulate else None
+    out = helpers.run_block(sh, p, x, dy, accumulate=accumulate, grads_init=init)
+    T, sv, bw = sh.T, out["saved"], out["bwd"]
+
+    def gemm(ta, tb, M, N, K, A, B, f32):
+        C = torch.full((M, N), 0.5, dtype=torch.float32 if f32 else torch.bfloat16, device=DEV)
+        Ad, Bd = to_dev(A, "bf16"), to_dev(B, "bf16")
+        fax.fax_gemm(fax.FAX_BF16, ta, tb, M, N, K, Ad, Ad.shape[1], Bd, Bd.shape[1], C, N, c_f32=f32,
+                     accumulate=int(accumulate and f32))
+        return to_np(C)
+
+    dy2 = dy.reshape(T, sh.D)
+    for name, act, grad in [("w2", sv["a"], dy2), ("w1", sv["h2"], bw["du"]), ("wo", sv["ctx"], bw["dx1"]),
+                            ("wqkv", sv["h1"], bw["dqkv"])]:
+        ref = gemm(1, 0, act.shape[1], grad.shape[1], T, act, grad, 1)
+        assert np.array_equal(out["grads"][name].reshape(ref.shape), ref), name
+    for name, grad, w in [("dh2", bw["du"], p["w1"]), ("dctx", bw["dx1"], p["wo"]), ("dh1", bw["dqkv"], p["wqkv"])]:
+        w = np.asarray(w).reshape(-1, grad.shape[1])
+        ref = gemm(0, 1, T, w.shape[0], grad.shape[1], grad, w, 0)
+        assert np.array_equal(bw[name], ref), name
+    y, c = orc.block_fwd(x, p, sh.H, sh.dh, sh.gelu, sh.ln_eps)
+    dx, g, _ = orc.block_bwd(dy, c, p)
+    add = 0.5 if accumulate else 0.0
+    worst = {k: rel_fro(out["grads"][k] - add, g[k]) for k in PARAM_NAMES}
+    worst["dx"] = rel_fro(out["dx"], dx)
+    assert max(worst.values()) <= helpers.TOL_BF16, worst

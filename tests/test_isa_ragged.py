@@ -21,7 +21,14 @@ def test_deep_gemm_assembly_blocks(tmp_path):
     n, bad = scan(text, r"_ZN3fax16gemm_deep_kernel")
     assert n == 24, n   # twelve flavours at two tile classes
     assert not [p for v in bad.values() for p in v if "possibly in flight" not in p]
-    for k in re.split(r"\n(?=_ZN3fax16gemm_deep_kernel[^\n]*:\s)", text)[1:]:
-        slab = 3 if "ILi128ELi64E" in k.split(":")[0] else 2
+    n, bad = scan(text, r"_ZN3fax21gemm_deep_pair_kernel")
+    assert n == 16, n   # two tile classes and two flavours of either product
+    assert not [p for v in bad.values() for p in v if "possibly in flight" not in p]
+    for k in re.split(r"\n(?=_ZN3fax(?:16gemm_deep|21gemm_deep_pair)_kernel[^\n]*:\s)", text)[1:]:
+        name = k.split(":")[0]
+        if "pair" in name:
+            slabs = {3 if t == "128" else 2 for t in re.findall(r"Li(128|64)E", name)}
+        else:
+            slabs = {3 if "ILi128ELi64E" in name else 2}
         waits = re.findall(r"#ASMSTART\s+s_waitcnt vmcnt\((\d+)\)\s+s_barrier\s", k)
-        assert set(waits) == {str(i * slab) for i in range(4)}, waits
+        assert set(waits) == {str(i * slab) for i in range(4) for slab in slabs}, waits
