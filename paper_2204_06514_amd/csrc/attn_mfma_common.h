@@ -31,10 +31,9 @@
 #pragma once
 #include <type_traits>
 
-#include "fax_internal.h"
+#include "attn_rows.h"
 
 namespace fax {
-
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -156,6 +155,13 @@ __device__ __forceinline__ void settle(T& v) { asm volatile("" : "+v"(v)); }
 // dK/dV.  Probabilities and dS enter their second products as two bf16 numbers (value and
 // remainder: 2^-17 instead of 2^-9), because these shapes' probabilities were never rounded to 16
 // bits: the scalar kernels that remain for wider and odd heads keep them in fp32.
+//
+// A masked pair, and a pair with a row of LDS beyond the sequence, enters the second product as a zero
+// factor, which an infinity or NaN on the other side turns into NaN.  So every row whose sums hold
+// one is computed again by the scalar kernels' row (attn_rows.h), which touches no masked pair: a row
+// that had to be NaN is NaN again, one that did not is what those kernels give.  The check is an FMA
+// per accumulator register and pass, about 1 % of the shortest pass's vector work; the second
+// computation costs what the scalar kernels cost, for those rows alone.
 template <int DW> constexpr int row_width() { return DW <= 64 ? 64 : 128; }
 __device__ __forceinline__ uint4 edge_load16(const bf16_t* p, bool ok) {
   return ok ? *reinterpret_cast<const uint4*>(p) : make_uint4(0u, 0u, 0u, 0u);
@@ -180,6 +186,16 @@ __device__ __forceinline__ void store_rows(bf16_t* __restrict__ dst, const f32x1
       for (int r = 0; r < 4; r++) o[r] = (__bf16)(acc[dt][q * 4 + r] * mul);
       *reinterpret_cast<bf16x4*>(dst + dt * 32 + q * 8 + g * 4) = o;
     }
+}
+
+// `sum` (zero to begin with) becomes NaN if an accumulator is an infinity or NaN.
+template <typename V, int N>
+__device__ __forceinline__ float not_finite(const V (&acc)[N], float sum) {
+#pragma unroll
+  for (int t = 0; t < N; t++)
+#pragma unroll
+    for (unsigned v = 0; v < sizeof(V) / sizeof(float); v++) sum = fmaf(acc[t][v], 0.f, sum);
+  return sum;
 }
 
 // Segment i of this wave's share of a 64 x DH tile (see tile_dma above), as one load instruction:

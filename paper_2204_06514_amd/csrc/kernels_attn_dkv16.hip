@@ -235,21 +235,40 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
     for (int t = 1; t < (EDGE ? n_q - 1 : n_q); t++) tile(F_{}, t);
     if (EDGE && n_q > 1) tile(T_{}, n_q - 1);  // may reach past S
 
-    if (EDGE && jk >= S) continue;
+    bool store = true;
+    unsigned again = 0;  // keys to compute a second time, by their lane among the first sixteen
+    if (EDGE) {
+      store = jk < S;
+      const unsigned long long odd = __builtin_amdgcn_ballot_w64(store && not_finite(dv, not_finite(dk, 0.f)) != 0.f);
+      again = (unsigned)(odd | (odd >> 16) | (odd >> 32) | (odd >> 48)) & 0xffffu;
+      store = store && !((again >> (lane & 15)) & 1);
+    }
     // a lane owns one key row and, per d tile, the four consecutive d's 16 dt + 4 g + 0..3
     const float scale = rsqrtf((float)hw);
     bf16_t* out = dqkv + ((size_t)b * S + jk) * ld + h * hw;
+    if (!EDGE || store) {
 #pragma unroll
-    for (int dt = 0; dt < DT; dt++) {
-      if (EDGE && dt * 16 + gq * 4 >= hw) continue;
-      bf16x4 ok, ov;
+      for (int dt = 0; dt < DT; dt++) {
+        if (EDGE && dt * 16 + gq * 4 >= hw) continue;
+        bf16x4 ok, ov;
 #pragma unroll
-      for (int r = 0; r < 4; r++) {
-        ok[r] = (__bf16)(dk[dt][r] * scale);
-        ov[r] = (__bf16)dv[dt][r];
+        for (int r = 0; r < 4; r++) {
+          ok[r] = (__bf16)(dk[dt][r] * scale);
+          ov[r] = (__bf16)dv[dt][r];
+        }
+        *reinterpret_cast<bf16x4*>(out + Hd + dt * 16 + gq * 4) = ok;
+        *reinterpret_cast<bf16x4*>(out + 2 * Hd + dt * 16 + gq * 4) = ov;
       }
-      *reinterpret_cast<bf16x4*>(out + Hd + dt * 16 + gq * 4) = ok;
-      *reinterpret_cast<bf16x4*>(out + 2 * Hd + dt * 16 + gq * 4) = ov;
+    }
+    if (EDGE) {
+      for (; again; again &= again - 1) {
+        int lane_r = lane;
+        settle(lane_r);
+        const int j = kt * TR + wave * 16 + __builtin_ctz(again);
+        const bf16_t* kp = base + (size_t)j * ld + Hd;
+        bf16_t* kout = dqkv + ((size_t)b * S + j) * ld + h * hw + Hd;
+        attn_bwd_dkv_row<2>(kp, kp + Hd, j, S, lane_r, base, ld, dob, Hd, hw, lrow, drow, kout, kout + Hd);
+      }
     }
   }  // pass
 }

@@ -192,9 +192,27 @@ __global__ __launch_bounds__(256, DW == 64 && !EDGE ? 3 : 2) void attn_fwd_mfma_
       tile(T_{}, n_kv - 1);
     }
 
-    if (EDGE && iq >= S) continue;
-    store_rows<DW, EDGE>(ctx + ((size_t)b * S + iq) * Hd + h * hw, oacc, 1.f / l, g, hw);
-    if (g == 0) lse[((size_t)b * H + h) * S + iq] = m * scale + logf(l);
+    bool store = true;
+    unsigned again = 0;  // rows to compute a second time, by their lane in the lower half
+    if (EDGE) {
+      store = iq < S;
+      const unsigned long long odd = __builtin_amdgcn_ballot_w64(store && not_finite(oacc, l * 0.f) != 0.f);
+      again = (unsigned)odd | (unsigned)(odd >> 32);
+      store = store && !((again >> (lane & 31)) & 1);
+    }
+    if (store) {
+      store_rows<DW, EDGE>(ctx + ((size_t)b * S + iq) * Hd + h * hw, oacc, 1.f / l, g, hw);
+      if (g == 0) lse[((size_t)b * H + h) * S + iq] = m * scale + logf(l);
+    }
+    if (EDGE) {
+      for (; again; again &= again - 1) {
+        int lane_r = lane;
+        settle(lane_r);  // nothing derived from it here is worth a register in the loops above
+        const int i = q0w + __builtin_ctz(again);
+        attn_fwd_row<(DW + 63) / 64>(base + (size_t)i * ld, i, lane_r, base, ld, Hd, hw, ctx + ((size_t)b * S + i) * Hd + h * hw,
+                                               lse + ((size_t)b * H + h) * S + i);
+      }
+    }
   }  // pass
 }
 
@@ -345,8 +363,25 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
       tile(T_{}, n_kv - 1);
     }
 
-    if (EDGE && iq >= S) continue;
-    store_rows<DW, EDGE>(dqkv + ((size_t)b * S + iq) * ld + h * hw, dq, scale, g, hw);
+    bool store = true;
+    unsigned again = 0;  // as in the forward kernel
+    if (EDGE) {
+      store = iq < S;
+      const unsigned long long odd = __builtin_amdgcn_ballot_w64(store && not_finite(dq, 0.f) != 0.f);
+      again = (unsigned)odd | (unsigned)(odd >> 32);
+      store = store && !((again >> (lane & 31)) & 1);
+    }
+    if (store) store_rows<DW, EDGE>(dqkv + ((size_t)b * S + iq) * ld + h * hw, dq, scale, g, hw);
+    if (EDGE) {
+      for (; again; again &= again - 1) {
+        int lane_r = lane;
+        settle(lane_r);
+        const int r = __builtin_ctz(again), i = q0w + r;
+        attn_bwd_dq_row<(DW + 63) / 64>(base + (size_t)i * ld, dctx + ((size_t)b * S + i) * Hd + h * hw, i, lane_r,
+                                                  lse[((size_t)b * H + h) * S + i], __shfl(di, r, 64), base, ld, Hd, hw,
+                                                  dqkv + ((size_t)b * S + i) * ld + h * hw);
+      }
+    }
   }  // pass
 }
 
@@ -504,10 +539,29 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
     }
 
     const float scale = rsqrtf((float)hw);
-    if (EDGE && jk >= S) continue;
+    bool store = true;
+    unsigned again = 0;  // as in the forward kernel
+    if (EDGE) {
+      store = jk < S;
+      const unsigned long long odd = __builtin_amdgcn_ballot_w64(store && not_finite(dv, not_finite(dk, 0.f)) != 0.f);
+      again = (unsigned)odd | (unsigned)(odd >> 32);
+      store = store && !((again >> (lane & 31)) & 1);
+    }
     bf16_t* out = dqkv + ((size_t)b * S + jk) * ld + h * hw;
-    store_rows<DW, EDGE>(out + Hd, dk, scale, g, hw);
-    store_rows<DW, EDGE>(out + 2 * Hd, dv, 1.f, g, hw);
+    if (!EDGE || store) {
+      store_rows<DW, EDGE>(out + Hd, dk, scale, g, hw);
+      store_rows<DW, EDGE>(out + 2 * Hd, dv, 1.f, g, hw);
+    }
+    if (EDGE) {
+      for (; again; again &= again - 1) {
+        int lane_r = lane;
+        settle(lane_r);
+        const int j = j0w + __builtin_ctz(again);
+        const bf16_t* kp = base + (size_t)j * ld + Hd;
+        bf16_t* kout = dqkv + ((size_t)b * S + j) * ld + h * hw + Hd;
+        attn_bwd_dkv_row<(DW + 63) / 64>(kp, kp + Hd, j, S, lane_r, base, ld, dob, Hd, hw, lrow, drow, kout, kout + Hd);
+      }
+    }
   }  // pass
 }
 

@@ -1,19 +1,12 @@
 // Causal attention with scalar FMAs: the fallback for head widths and alignments that the matrix-core kernels do not
 // cover, and the form a caller gets by asking for it.  One wavefront per query row (forward, dQ) or per key row (dK, dV);
-// scores are never materialised: a 64-key chunk at a time with a running max and sum.
+// the rows themselves are in attn_rows.h.
 // No atomics: every output element has exactly one writer.
-#include "fax_internal.h"
+#include "attn_rows.h"
 
 namespace fax {
 
 static constexpr int AT_MAXDH = 256;  // lane owns d = lane + 64 r, r < 4
-
-template <typename T>
-__device__ __forceinline__ float dot_row(const float* __restrict__ a, const T* __restrict__ row, int dh) {
-  float s = 0.f;
-  for (int d = 0; d < dh; d++) s = fmaf(a[d], to_f(row[d]), s);
-  return s;
-}
 
 template <typename T>
 __global__ __launch_bounds__(256) void attn_fwd_simt_kernel(int S, int H, int dh, const T* __restrict__ qkv,
@@ -28,38 +21,8 @@ __global__ __launch_bounds__(256) void attn_fwd_simt_kernel(int S, int H, int dh
     for (int d = lane; d < dh; d += 64) qs[wave][d] = to_f(base[(size_t)i * ld + d]);
   __syncthreads();
   if (i >= S) return;
-  const float scale = rsqrtf((float)dh);
-  float m = -INFINITY, l = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int j0 = 0; j0 <= i; j0 += 64) {
-    const int j = j0 + lane;
-    const bool ok = j <= i;
-    float sc = ok ? dot_row<T>(qs[wave], base + (size_t)j * ld + Hd, dh) * scale : -INFINITY;
-    const float mn = fmaxf(m, wave_max(sc));
-    const float p = ok ? expf(sc - mn) : 0.f;
-    const float corr = expf(m - mn);
-    l = l * corr + wave_sum(p);
-#pragma unroll
-    for (int r = 0; r < 4; r++) acc[r] *= corr;
-    const int nj = min(64, i - j0 + 1);
-    for (int jj = 0; jj < nj; jj++) {
-      const float pj = __shfl(p, jj, 64);
-      const T* vr = base + (size_t)(j0 + jj) * ld + 2 * Hd;
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int d = lane + 64 * r;
-        if (d < dh) acc[r] = fmaf(pj, to_f(vr[d]), acc[r]);
-      }
-    }
-    m = mn;
-  }
-  T* out = ctx + ((size_t)b * S + i) * Hd + h * dh;
-  const float inv = 1.f / l;
-#pragma unroll
-  for (int r = 0; r < 4; r++) {
-    const int d = lane + 64 * r;
-    if (d < dh) out[d] = from_f<T>(acc[r] * inv);
-  }
-  if (lane == 0) lse[((size_t)b * H + h) * S + i] = m + logf(l);
+  attn_fwd_row<AT_MAXDH / 64>(qs[wave], i, lane, base, ld, Hd, dh, ctx + ((size_t)b * S + i) * Hd + h * dh,
+                              lse + ((size_t)b * H + h) * S + i);
 }
 
 // delta[b,h,i] = sum_d dO[i,d] O[i,d]
@@ -96,35 +59,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_simt_kernel(int S, int H, int
     }
   __syncthreads();
   if (i >= S) return;
-  const float scale = rsqrtf((float)dh);
-  const float li = lse[((size_t)b * H + h) * S + i], di = delta[((size_t)b * H + h) * S + i];
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int j0 = 0; j0 <= i; j0 += 64) {
-    const int j = j0 + lane;
-    float ds = 0.f;
-    if (j <= i) {
-      const float sc = dot_row<T>(qs[wave], base + (size_t)j * ld + Hd, dh) * scale;
-      const float p = expf(sc - li);
-      const float dp = dot_row<T>(dos[wave], base + (size_t)j * ld + 2 * Hd, dh);
-      ds = p * (dp - di);
-    }
-    const int nj = min(64, i - j0 + 1);
-    for (int jj = 0; jj < nj; jj++) {
-      const float dsj = __shfl(ds, jj, 64);
-      const T* kr = base + (size_t)(j0 + jj) * ld + Hd;
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int d = lane + 64 * r;
-        if (d < dh) acc[r] = fmaf(dsj, to_f(kr[d]), acc[r]);
-      }
-    }
-  }
-  T* out = dqkv + ((size_t)b * S + i) * ld + h * dh;
-#pragma unroll
-  for (int r = 0; r < 4; r++) {
-    const int d = lane + 64 * r;
-    if (d < dh) out[d] = from_f<T>(acc[r] * scale);
-  }
+  attn_bwd_dq_row<AT_MAXDH / 64>(qs[wave], dos[wave], i, lane, lse[((size_t)b * H + h) * S + i], delta[((size_t)b * H + h) * S + i],
+                                 base, ld, Hd, dh, dqkv + ((size_t)b * S + i) * ld + h * dh);
 }
 
 template <typename T>
@@ -147,43 +83,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_simt_kernel(int S, int H, in
     }
   __syncthreads();
   if (j >= S) return;
-  const float scale = rsqrtf((float)dh);
-  const float* lrow = lse + ((size_t)b * H + h) * S;
-  const float* drow = delta + ((size_t)b * H + h) * S;
-  float ak[4] = {0.f, 0.f, 0.f, 0.f}, av[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int i0 = j; i0 < S; i0 += 64) {
-    const int i = i0 + lane;
-    float p = 0.f, ds = 0.f;
-    if (i < S) {
-      const float sc = dot_row<T>(ks[wave], base + (size_t)i * ld, dh) * scale;
-      p = expf(sc - lrow[i]);
-      const float dp = dot_row<T>(vs[wave], dob + (size_t)i * Hd, dh);
-      ds = p * (dp - drow[i]);
-    }
-    const int ni = min(64, S - i0);
-    for (int ii = 0; ii < ni; ii++) {
-      const float pi = __shfl(p, ii, 64), dsi = __shfl(ds, ii, 64);
-      const T* qr = base + (size_t)(i0 + ii) * ld;
-      const T* dor = dob + (size_t)(i0 + ii) * Hd;
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int d = lane + 64 * r;
-        if (d < dh) {
-          av[r] = fmaf(pi, to_f(dor[d]), av[r]);
-          ak[r] = fmaf(dsi, to_f(qr[d]), ak[r]);
-        }
-      }
-    }
-  }
   T* out = dqkv + ((size_t)b * S + j) * ld + h * dh;
-#pragma unroll
-  for (int r = 0; r < 4; r++) {
-    const int d = lane + 64 * r;
-    if (d < dh) {
-      out[Hd + d] = from_f<T>(ak[r] * scale);
-      out[2 * Hd + d] = from_f<T>(av[r]);
-    }
-  }
+  attn_bwd_dkv_row<AT_MAXDH / 64>(ks[wave], vs[wave], j, S, lane, base, ld, dob, Hd, dh, lse + ((size_t)b * H + h) * S,
+                                  delta + ((size_t)b * H + h) * S, out + Hd, out + 2 * Hd);
 }
 
 int attn_delta(int dtype, int B, int S, int H, int dh, const void* ctx, const void* dctx, float* delta, hipStream_t s) {
