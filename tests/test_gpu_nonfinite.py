@@ -5,8 +5,9 @@ import pytest
 import torch
 
 import paper_2204_06514_amd as fax
-from helpers import DEV, TDTYPE, CODE, to_dev, to_np
-from workloads import round_to_bf16
+from helpers import DEV, TDTYPE, CODE, dims_of, to_dev, to_np
+from test_gpu_train import run_train_step, _dev_params
+from workloads import BlockShape, ModelShape, make_model_inputs, round_to_bf16
 
 pytestmark = pytest.mark.gpu
 NAN, INF = float("nan"), float("inf")
@@ -54,3 +55,24 @@ def test_bf16_attention_of_any_length(B, S, H, dh, at, part, bad):
     assert np.isfinite(ref["ctx"][0, :at]).all() and np.isfinite(ref["dqkv"][0, :at, 0]).all()
     # two roundings to bf16 (2^-9) of the same sums; the gradients also carry those of two ctx, which delta is formed from
     _agree(got, ref, 1e-2)
+
+
+# The loss over a vocabulary that ends inside a 16-byte vector (first two: with one element, the only one of its thread), and over a
+# whole one: a logit that is NaN makes its row's loss and gradient NaN wherever it stands.
+@pytest.mark.parametrize("V,col", [(121, 120), (1001, 1000), (1001, 3), (1024, 1019)])
+def test_a_nan_logit_reaches_the_loss(V, col):
+    ms = ModelShape(BlockShape(B=1, S=64, D=64, H=1, dh=64, F=128, dtype="bf16", sigma_w=0.05, L=1), V=V, S_max=64)
+    p, tok, lab = make_model_inputs(ms, seed=1, generic=True)
+    last = np.arange(8) + col // 8 * 8
+    nan = last[last < V] if V % 8 == 0 else [col]     # all that the thread has
+    p["tok_emb"][nan] = NAN
+    tok, lab = np.full_like(tok, 1), np.full_like(lab, 2)
+    loss, _, _, _, _, grads = run_train_step(ms, p, tok, lab, update=False)
+    assert np.isnan(loss)
+    # every row's gradient is NaN, the hidden states' with it, and every row of the embedding's
+    assert np.isnan(to_np(grads["lnf_g"])).all() and np.isnan(to_np(grads["tok_emb"])[:V]).all()
+    md = fax.FaxModelDims(dims_of(ms.blk), 1, V, 64, 0)
+    ws = torch.empty(fax.fax_eval_workspace_bytes(md), dtype=torch.uint8, device=DEV)
+    out = torch.zeros(4, device=DEV)
+    fax.fax_eval_step(md, _dev_params(p, "bf16"), torch.from_numpy(tok).to(DEV), torch.from_numpy(lab).to(DEV), out, ws, ws.numel())
+    assert np.isnan(out[0].item())
