@@ -152,9 +152,14 @@ __device__ __forceinline__ void settle(T& v) { asm volatile("" : "+v"(v)); }
 // beyond the head width stay zero, rows beyond the sequence hold zeros or an earlier tile's rows, and
 // nothing is read out of bounds.  Queries and keys held in registers are zero there.  Keys beyond the
 // sequence come after every query and fall to the causal mask; queries beyond it are masked by
-// dK/dV.  Probabilities and dS enter their second products as two bf16 numbers (value and
-// remainder: 2^-17 instead of 2^-9), because these shapes' probabilities were never rounded to 16
-// bits: the scalar kernels that remain for wider and odd heads keep them in fp32.
+// dK/dV.  Probabilities and dS enter their second products as three bf16 numbers (value, remainder and what
+// is left of that: all 24 bits of the fp32 number), and exponents come from differences of scaled scores
+// (edge_exp), because these shapes' probabilities are fp32 numbers in the scalar kernels, and remain so there for wider
+// and odd heads.  Where a sum cancels to 1e-4 of its terms, two numbers (2^-17) left 2-3 % of error in ctx and 3-4 % in
+// dV; three leave 0.17 and 0.34, the scalar kernels 0.17 and 0.31.  The third costs a product in three: forward / backward
+// of 32 heads of 777 x 64 24.0 / 84.3 -> 28.4 / 93.5 us, 45 heads of 1000 x 80 34.2 / 85.8 -> 40.5 / 101.5.  The terms of the
+// next eight keys or queries are formed between the MFMAs of the present ones (formed ahead, all at once: 5 % of the
+// block at 3000 tokens x 1200 instead of 3.7).
 //
 // A masked pair, and a pair with a row of LDS beyond the sequence, enters the second product as a zero
 // factor, which an infinity or NaN on the other side turns into NaN.  So every row whose sums hold
@@ -165,6 +170,21 @@ __device__ __forceinline__ void settle(T& v) { asm volatile("" : "+v"(v)); }
 template <int DW> constexpr int row_width() { return DW <= 64 ? 64 : 128; }
 __device__ __forceinline__ uint4 edge_load16(const bf16_t* p, bool ok) {
   return ok ? *reinterpret_cast<const uint4*>(p) : make_uint4(0u, 0u, 0u, 0u);
+}
+// e^(score * scale - ref): the difference first, rounded once relative to itself, then the step to base 2.  (One FMA with both
+// factors folded in rounds relative to ref instead, for the whole row alike.)
+__device__ __forceinline__ float edge_exp(float score, float scale, float ref) {
+  return __builtin_amdgcn_exp2f(fmaf(score, scale, -ref) * LOG2E);
+}
+// (x, y) = p[0] + p[1] + p[2], elements 2 n and 2 n + 1 of each
+__device__ __forceinline__ void split3(float x, float y, bf16x8 (&p)[3], int n) {
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    p[k][2 * n] = (__bf16)x;
+    p[k][2 * n + 1] = (__bf16)y;
+    x -= (float)p[k][2 * n];
+    y -= (float)p[k][2 * n + 1];
+  }
 }
 __device__ __forceinline__ void clear_lds(char* smem, int bytes) {
   for (int o = threadIdx.x * 16; o < bytes; o += 256 * 16) *reinterpret_cast<uint4*>(smem + o) = make_uint4(0u, 0u, 0u, 0u);

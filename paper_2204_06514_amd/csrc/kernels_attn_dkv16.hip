@@ -118,7 +118,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
   const float* drow = delta + ((size_t)b * H + h) * S;
   const int lane = threadIdx.x & 63, gq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const float c = rsqrtf((float)hw) * LOG2E;
+  const float scale = rsqrtf((float)hw);
+  const float c = scale * LOG2E;
   const unsigned sm = lds_addr(smem);
   if (EDGE) clear_lds(smem, 2 * STAGE);
 
@@ -164,8 +165,12 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
       auto row_frag = [&](int it, int i) {
         return frag_rows16<DH>(i % 2 ? st + TB : st, it * 32 + ((i / 2) / KS) * 16, (i / 2) % KS, lane);
       };
-      // P3 slot i of half it: dV (dO^T) or dK (Q^T) by bit 0, d tile i / 2
-      auto col_frag = [&](int it, int i) { return frag_cols16<DH>(i % 2 ? st : st + TB, (i / 2) * 16, it * 32, lane); };
+      // P3 slot i of half it: dV (dO^T) or dK (Q^T) by bit 0, d tile i / 2; EDGE: all of dV, then dK, whose factors are formed
+      // meanwhile, d tile i % DT
+      auto col_frag = [&](int it, int i) {
+        if (EDGE) return frag_cols16<DH>(i >= DT ? st : st + TB, (i % DT) * 16, it * 32, lane);
+        return frag_cols16<DH>(i % 2 ? st : st + TB, (i / 2) * 16, it * 32, lane);
+      };
       // lse / delta of the queries 32 it + 16 qg + 4 g + 0..3 that this lane meets in the accumulators of query group qg
       auto stat4 = [&](int it, int qg, int which) {
         const int row = it * 32 + qg * 16 + gq * 4;
@@ -189,34 +194,49 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
           if (it == 0 && i <= 2 * NSEG) tile_load(i0n, (t + 1) & 1, i);
           __builtin_amdgcn_sched_barrier(0);
         }
-        bf16x8 pb, db, pl, dl;  // P and dS; EDGE: and what bf16 leaves of them
+        bf16x8 pb[EDGE ? 3 : 1], db[EDGE ? 3 : 1];  // P and dS; EDGE: in three terms, those of dS between the MFMAs of dV
         __builtin_amdgcn_s_setprio(0);
 #pragma unroll
         for (int qg = 0; qg < 2; qg++) {
           const float4 l4 = stat4(it, qg, 0), d4 = stat4(it, qg, 1);
 #pragma unroll
           for (int r = 0; r < 4; r++) {
-            float p = __builtin_amdgcn_exp2f(fmaf(sc[qg][r], c, -LOG2E * f4_get(l4, r)));
+            float p = EDGE ? edge_exp(sc[qg][r], scale, f4_get(l4, r)) : __builtin_amdgcn_exp2f(fmaf(sc[qg][r], c, -LOG2E * f4_get(l4, r)));
             const int i = i0h + qg * 16 + gq * 4 + r;
             if (MASK && (jk > i || (EDGE && i >= S))) p = 0.f;
             const float d = EDGE && MASK && i >= S ? 0.f : p * (dp[qg][r] - f4_get(d4, r));
-            pb[qg * 4 + r] = (__bf16)p;
-            db[qg * 4 + r] = (__bf16)d;
             if (EDGE) {
-              pl[qg * 4 + r] = (__bf16)(p - (float)(__bf16)p);
-              dl[qg * 4 + r] = (__bf16)(d - (float)(__bf16)d);
+              sc[qg][r] = p;
+              dp[qg][r] = d;
+            } else {
+              pb[0][qg * 4 + r] = (__bf16)p;
+              db[0][qg * 4 + r] = (__bf16)d;
             }
           }
+        }
+        if constexpr (EDGE) {
+#pragma unroll
+          for (int n = 0; n < 4; n++) split3(sc[n / 2][n % 2 * 2], sc[n / 2][n % 2 * 2 + 1], pb, n);
         }
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int i = 0; i < N; i++) {
-          const int dt = i / 2;
-          if (i % 2 == 0) dv[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], pb, dv[dt], 0, 0, 0);
-          else dk[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], db, dk[dt], 0, 0, 0);
-          if (EDGE && i % 2 == 0) dv[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], pl, dv[dt], 0, 0, 0);
-          if (EDGE && i % 2 != 0) dk[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], dl, dk[dt], 0, 0, 0);
+          if constexpr (EDGE) {
+            const int dt = i % DT;
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+              if (i < DT) dv[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], pb[k], dv[dt], 0, 0, 0);
+              else dk[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], db[k], dk[dt], 0, 0, 0);
+            }
+#pragma unroll
+            for (int n = 0; n < 4; n++)
+              if (n * DT / 4 == i) split3(dp[n / 2][n % 2 * 2], dp[n / 2][n % 2 * 2 + 1], db, n);
+          } else {
+            const int dt = i / 2;
+            if (i % 2 == 0) dv[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], pb[0], dv[dt], 0, 0, 0);
+            else dk[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i % LEAD], db[0], dk[dt], 0, 0, 0);
+          }
           if (i + LEAD < N) f[i % LEAD] = col_frag(it, i + LEAD);
           else if (it == 0) f[i % LEAD] = row_frag(1, i + LEAD - N);  // the second half's first rows
           __builtin_amdgcn_sched_barrier(0);
@@ -244,7 +264,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv16_mfma_kernel(int S, int 
       store = store && !((again >> (lane & 15)) & 1);
     }
     // a lane owns one key row and, per d tile, the four consecutive d's 16 dt + 4 g + 0..3
-    const float scale = rsqrtf((float)hw);
     bf16_t* out = dqkv + ((size_t)b * S + jk) * ld + h * hw;
     if (!EDGE || store) {
 #pragma unroll

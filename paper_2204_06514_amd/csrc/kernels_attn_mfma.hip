@@ -140,9 +140,11 @@ __global__ __launch_bounds__(256, DW == 64 && !EDGE ? 3 : 2) void attn_fwd_mfma_
       // MAX_LAG octaves above it, which after the first few tiles is rare.  Probabilities are then
       // at most 2^MAX_LAG instead of 1; numerator, denominator and lse all use the same m, so
       // the result is the same softmax.
-      const float mn = fmaxf(m, mx);  // finite: key 0 is visible to every query and comes in the first tile
-      if (__builtin_amdgcn_ballot_w64((mn - m) * c > MAX_LAG) != 0) {
-        const float corr = __builtin_amdgcn_exp2f((m - mn) * c);
+      // EDGE: m is in units of the scaled score.
+      const float mn = fmaxf(m, EDGE ? mx * scale : mx);  // finite: key 0 is visible to every query and comes in the first tile
+      const float octaves = EDGE ? LOG2E : c;
+      if (__builtin_amdgcn_ballot_w64((mn - m) * octaves > MAX_LAG) != 0) {
+        const float corr = __builtin_amdgcn_exp2f((m - mn) * octaves);
         l *= corr;
 #pragma unroll
         for (int dt = 0; dt < DT; dt++)
@@ -152,25 +154,42 @@ __global__ __launch_bounds__(256, DW == 64 && !EDGE ? 3 : 2) void attn_fwd_mfma_
       }
       const float mc = m * c;
       float rs = 0.f;
-      bf16x8 pb[2][2], pl[2][2];  // probabilities; EDGE: and what bf16 leaves of them
+      bf16x8 pb[2][2];  // probabilities (EDGE: pc below, from the fp32 numbers in s)
 #pragma unroll
       for (int jt = 0; jt < 2; jt++)
 #pragma unroll
         for (int v = 0; v < 16; v++) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(s[jt][v], c, -mc));
+          const float p = EDGE ? edge_exp(s[jt][v], scale, m) : __builtin_amdgcn_exp2f(fmaf(s[jt][v], c, -mc));
           rs += p;
-          pb[jt][v >> 3][v & 7] = (__bf16)p;
-          if (EDGE) pl[jt][v >> 3][v & 7] = (__bf16)(p - (float)(__bf16)p);
+          if (EDGE) s[jt][v] = p;
+          else pb[jt][v >> 3][v & 7] = (__bf16)p;
         }
       rs = sum32(rs);
       l += rs;
+      bf16x8 pc[2][3];  // EDGE: eight keys' probabilities in three terms, and the next eight's as they are formed between the MFMAs
+      if constexpr (EDGE) {
+#pragma unroll
+        for (int n = 0; n < 4; n++) split3(s[0][2 * n], s[0][2 * n + 1], pc[0], n);
+      }
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int i = 0; i < N; i++) {
-        const int dt = i % DT;
-        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[i % LEAD], pb[(i / DT) % 2][(i / DT) / 2], oacc[dt], 0, 0, 0);
-        if (EDGE) oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[i % LEAD], pl[(i / DT) % 2][(i / DT) / 2], oacc[dt], 0, 0, 0);
+        const int dt = i % DT, ch = i / DT;
+        if constexpr (EDGE) {
+#pragma unroll
+          for (int k = 0; k < 3; k++) {
+            oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[i % LEAD], pc[ch & 1][k], oacc[dt], 0, 0, 0);
+#pragma unroll
+            for (int n = 0; n < 4; n++) {
+              const int v = (ch + 1) / 2 * 8 + 2 * n;
+              if (ch < 3 && n * 3 * DT / 4 == dt * 3 + k) split3(s[(ch + 1) % 2][v], s[(ch + 1) % 2][v + 1], pc[(ch + 1) & 1], n);
+            }
+            if (k < 2) __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[i % LEAD], pb[ch % 2][ch / 2], oacc[dt], 0, 0, 0);
+        }
         if (i + LEAD < N) fc[i % LEAD] = col_frag(i + LEAD);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -202,7 +221,7 @@ __global__ __launch_bounds__(256, DW == 64 && !EDGE ? 3 : 2) void attn_fwd_mfma_
     }
     if (store) {
       store_rows<DW, EDGE>(ctx + ((size_t)b * S + iq) * Hd + h * hw, oacc, 1.f / l, g, hw);
-      if (g == 0) lse[((size_t)b * H + h) * S + iq] = m * scale + logf(l);
+      if (g == 0) lse[((size_t)b * H + h) * S + iq] = EDGE ? m + logf(l) : m * scale + logf(l);
     }
     if (EDGE) {
       for (; again; again &= again - 1) {
@@ -269,7 +288,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
       dof[ks] = __builtin_bit_cast(bf16x8, EDGE ? edge_load16(dorow + ks * 16 + g * 8, ok)
                                                 : *reinterpret_cast<const uint4*>(dorow + ks * 16 + g * 8));
     }
-    float li = EDGE && iq >= S ? 0.f : lse[((size_t)b * H + h) * S + iq] * LOG2E;
+    float li = EDGE ? (iq >= S ? 0.f : lse[((size_t)b * H + h) * S + iq]) : lse[((size_t)b * H + h) * S + iq] * LOG2E;
     float di = 0.f;  // delta_i = sum_d dO[i, d] O[i, d], half of the row per lane
     const bf16_t* orow = ctx + ((size_t)b * S + iq) * Hd + h * hw;
 #pragma unroll
@@ -325,22 +344,36 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
           if (jt == 0 && i < 2 * NSEG) tile_load(j0n, (t + 1) & 1, i);
           __builtin_amdgcn_sched_barrier(0);
         }
-        bf16x8 db[2], dl[2];  // dS; EDGE: and what bf16 leaves of it
+        bf16x8 db[2], dc[2][3];  // dS; EDGE: in three terms, the second eight keys' formed between the first one's MFMAs
         __builtin_amdgcn_s_setprio(0);
 #pragma unroll
         for (int v = 0; v < 16; v++) {
-          float p = __builtin_amdgcn_exp2f(fmaf(sc[v], c, -li));
+          float p = EDGE ? edge_exp(sc[v], scale, li) : __builtin_amdgcn_exp2f(fmaf(sc[v], c, -li));
           if (MASK && t * TR + jt * 32 + (v >> 2) * 8 + g * 4 + (v & 3) > iq) p = 0.f;
           const float d = p * (dp[v] - di);
-          db[v >> 3][v & 7] = (__bf16)d;
-          if (EDGE) dl[v >> 3][v & 7] = (__bf16)(d - (float)(__bf16)d);
+          if (EDGE) dp[v] = d;
+          else db[v >> 3][v & 7] = (__bf16)d;
+        }
+        if constexpr (EDGE) {
+#pragma unroll
+          for (int n = 0; n < 4; n++) split3(dp[2 * n], dp[2 * n + 1], dc[0], n);
         }
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int i = 0; i < N3; i++) {
-          dq[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], db[i / DT], dq[i % DT], 0, 0, 0);
-          if (EDGE) dq[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], dl[i / DT], dq[i % DT], 0, 0, 0);
+          if constexpr (EDGE) {
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+              dq[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], dc[i / DT][k], dq[i % DT], 0, 0, 0);
+#pragma unroll
+              for (int n = 0; n < 4; n++)
+                if (n * 3 * DT / 4 == i * 3 + k) split3(dp[8 + 2 * n], dp[9 + 2 * n], dc[1], n);
+              if (k < 2) __builtin_amdgcn_sched_barrier(0);
+            }
+          } else {
+            dq[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], db[i / DT], dq[i % DT], 0, 0, 0);
+          }
           if (jt == 0) f[i % LEAD] = row_frag(1, i);  // the second half's first rows (N3 = LEAD)
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -418,7 +451,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
   const float* drow = delta + ((size_t)b * H + h) * S;
   const int lane = threadIdx.x & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const float c = rsqrtf((float)hw) * LOG2E;
+  const float scale = rsqrtf((float)hw);
+  const float c = scale * LOG2E;
   const unsigned sm = lds_addr(smem);
   if (EDGE) clear_lds(smem, 2 * STAGE);
 
@@ -459,8 +493,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
       const int i0n = i_first + min(t + 1, n_q - 1) * TR;  // past the end: the last tile again, into the buffer nobody reads
       // P1 slot i of half it: S (Q rows x K) or dP (dO rows x V) by bit 0, k-step i / 2
       auto row_frag = [&](int it, int i) { return frag_rows<DH>(i % 2 ? st + TB : st, it * 32, i / 2, lane); };
-      // P3 slot i: dV (dO^T) or dK (Q^T) by bit 0, d-tile (i / 2) % DT, k-step i / (2 DT)
+      // P3 slot i: dV (dO^T) or dK (Q^T) by bit 0, d-tile (i / 2) % DT, k-step i / (2 DT); EDGE: all of dV, then dK, whose factors are
+      // formed meanwhile, d-tile i % DT, k-step (i / DT) % 2
       auto col_frag = [&](int it, int i) {
+        if (EDGE) return frag_cols<DH>(i >= 2 * DT ? st : st + TB, (i % DT) * 32, it * 32 + ((i / DT) % 2) * 16, lane);
         return frag_cols<DH>(i % 2 ? st : st + TB, ((i / 2) % DT) * 32, it * 32 + (i / (2 * DT)) * 16, lane);
       };
       // lse / delta of the rows 32 it + 8 q + 4 g + 0..3 that this lane meets in accumulator group q
@@ -485,7 +521,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
           if (it == 0 && i <= 2 * NSEG) tile_load(i0n, (t + 1) & 1, i);
           __builtin_amdgcn_sched_barrier(0);
         }
-        bf16x8 pb[2], db[2], pl[2], dl[2];  // P and dS; EDGE: and what bf16 leaves of them
+        bf16x8 pb[2], db[2], pc[2][3];  // P and dS; EDGE: eight queries' P or dS in three terms, and the next eight's
         __builtin_amdgcn_s_setprio(0);
 #pragma unroll
         for (int q = 0; q < 4; q++) {
@@ -493,27 +529,46 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
 #pragma unroll
           for (int r = 0; r < 4; r++) {
             const int v = q * 4 + r;
-            float p = __builtin_amdgcn_exp2f(fmaf(sc[v], c, -LOG2E * f4_get(l4, r)));
+            float p = EDGE ? edge_exp(sc[v], scale, f4_get(l4, r)) : __builtin_amdgcn_exp2f(fmaf(sc[v], c, -LOG2E * f4_get(l4, r)));
             const int i = i0h + q * 8 + g * 4 + r;
             if (MASK && (jk > i || (EDGE && i >= S))) p = 0.f;
             const float d = EDGE && MASK && i >= S ? 0.f : p * (dp[v] - f4_get(d4, r));
-            pb[v >> 3][v & 7] = (__bf16)p;
-            db[v >> 3][v & 7] = (__bf16)d;
             if (EDGE) {
-              pl[v >> 3][v & 7] = (__bf16)(p - (float)(__bf16)p);
-              dl[v >> 3][v & 7] = (__bf16)(d - (float)(__bf16)d);
+              sc[v] = p;
+              dp[v] = d;
+            } else {
+              pb[v >> 3][v & 7] = (__bf16)p;
+              db[v >> 3][v & 7] = (__bf16)d;
             }
           }
+        }
+        if constexpr (EDGE) {
+#pragma unroll
+          for (int n = 0; n < 4; n++) split3(sc[2 * n], sc[2 * n + 1], pc[0], n);
         }
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int i = 0; i < N; i++) {
-          const int hh = i / (2 * DT), dt = (i / 2) % DT;
-          if (i % 2 == 0) dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], pb[hh], dv[dt], 0, 0, 0);
-          else dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], db[hh], dk[dt], 0, 0, 0);
-          if (EDGE && i % 2 == 0) dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], pl[hh], dv[dt], 0, 0, 0);
-          if (EDGE && i % 2 != 0) dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], dl[hh], dk[dt], 0, 0, 0);
+          if constexpr (EDGE) {
+            const int ch = i / DT, dt = i % DT;  // P of the first eight queries, of the others, dS likewise
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+              if (ch < 2) dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], pc[ch & 1][k], dv[dt], 0, 0, 0);
+              else dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], pc[ch & 1][k], dk[dt], 0, 0, 0);
+#pragma unroll
+              for (int n = 0; n < 4; n++) {
+                if (n * 3 * DT / 4 != dt * 3 + k) continue;
+                if (ch == 0) split3(sc[8 + 2 * n], sc[9 + 2 * n], pc[1], n);
+                else if (ch < 3) split3(dp[(ch - 1) * 8 + 2 * n], dp[(ch - 1) * 8 + 2 * n + 1], pc[(ch + 1) & 1], n);
+              }
+              if (k < 2) __builtin_amdgcn_sched_barrier(0);
+            }
+          } else {
+            const int hh = i / (2 * DT), dt = (i / 2) % DT;
+            if (i % 2 == 0) dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], pb[hh], dv[dt], 0, 0, 0);
+            else dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], db[hh], dk[dt], 0, 0, 0);
+          }
           if (i + LEAD < N) f[i % LEAD] = col_frag(it, i + LEAD);
           else if (it == 0) f[i % LEAD] = row_frag(1, i + LEAD - N);  // the second half's first rows
           __builtin_amdgcn_sched_barrier(0);
@@ -538,7 +593,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
       for (int t = 2; t < n_q; t++) tile(F_{}, t);
     }
 
-    const float scale = rsqrtf((float)hw);
     bool store = true;
     unsigned again = 0;  // as in the forward kernel
     if (EDGE) {
@@ -572,8 +626,9 @@ bool attn_mfma_supported(int dtype, int B, int S, int H, int dh) {
 
 // Whole 16-byte chunks per head are all that the masked-edge form asks for.  Measured against the scalar kernels, forward / backward
 // in us: one head of 17 x 64 7.8 / 15.3 -> 8.4 / 11.7 (launch and latency), 8 heads of 64 x 32 13.1 / 28.2 -> 8.6 / 11.9,
-// 45 heads of 1000 x 80 1485 / 2966 -> 33 / 86, 32 heads of 777 x 64 572 / 1075 -> 24 / 83, 16 heads of 1500 x 128
-// 1754 / 3791 -> 47 / 115.  Errors against float64 are the scalar kernels' to three digits (the roundings of the outputs).
+// 45 heads of 1000 x 80 1485 / 2966 -> 41 / 102, 32 heads of 777 x 64 572 / 1075 -> 28 / 93, 16 heads of 1500 x 128
+// 1754 / 3791 -> 57 / 132.  Errors against float64, over ten shapes and four distributions, are the scalar kernels' to 2e-4 in
+// ctx and the gradients and to 7 % either way in lse (4e-8, half a unit in its last place).
 bool attn_edge_supported(int dtype, int B, int S, int H, int dh) {
   (void)B; (void)H;
   return dtype == FAX_BF16 && dh % 8 == 0 && dh <= 128 && S > 0;

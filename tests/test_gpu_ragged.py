@@ -86,7 +86,7 @@ def test_edge_attention(B, S, H, dh):
     fax.fax_attention_bwd(fax.FAX_BF16, B, S, H, dh, qd, ctx, lse, dd, dq, delta, fax.PATH_AUTO)
     for t, n in ((ctx, ctx_ref.size), (lse, lse_ref.size), (dq, qkv.size), (delta, lse_ref.size)):
         assert (t[n:] == 7.0).all()   # nothing written behind the outputs
-    # ctx: one rounding to bf16 (2^-9) of a sum whose probabilities carry 2^-17; lse: fp32
+    # ctx: one rounding to bf16 (2^-9) of an fp32 sum; lse: fp32
     assert rel_fro(to_np(ctx[:ctx_ref.size]).reshape(ctx_ref.shape), ctx_ref) <= 4e-3
     assert np.abs(to_np(lse[:lse_ref.size]).reshape(lse_ref.shape) - lse_ref).max() <= 2e-5
     # the gradients: one rounding each, plus that of ctx, which delta is formed from (the bar of the scalar kernels)
@@ -135,3 +135,39 @@ def test_output_projection_over_a_ragged_vocabulary(V, D, S):
     fax.fax_eval_step(md, _dev_params(p, "bf16"), torch.from_numpy(tok).to(DEV), torch.from_numpy(lab).to(DEV), out, ws, wsb)
     assert abs(out[0].item() - loss) <= 1e-6 * abs(loss)
     assert (ws[wsb:] == 255).all()
+
+
+# Sums that cancel to about 1e-4 of their terms show the probabilities' own error, which the rounding of the outputs otherwise hides:
+# keys in pairs of nearly the same score with opposite V (ctx), queries likewise with opposite dO (dV).  Keys from 64 on
+# have no weight, so that the two queries of a pair see the same ones.
+@pytest.mark.parametrize("dh", [64, 80, 128])
+def test_edge_attention_probabilities_are_fp32(dh):
+    rng = np.random.default_rng(dh)
+    B, S, H, n = 2, 333, 2, 64
+    qkv = rng.standard_normal((B, S, 3, H, dh))
+    dctx = np.zeros((B, S, H, dh))
+    q, k, v = (qkv[:, :, i] for i in range(3))
+    q[:, n + 1::2], k[:, 1::2], v[:, 1::2] = q[:, n:-1:2], k[:, 0:-1:2], -v[:, 0:-1:2]
+    q[..., 0], k[..., 0] = 0.0, rng.choice([-1.0, 1.0], (B, S, H))
+    q[:, n + 1::2, :, 0] = 2.0 ** -10
+    k[..., 1], q[..., 1] = 0.0, 1.0
+    k[:, 1::2, :, 1] = 2.0 ** -10
+    k[..., 2], q[..., 2] = 0.0, 8.0
+    k[:, n:, :, 2] = -128.0
+    k[:, 1:n:2, :, 0] = k[:, 0:n:2, :, 0]
+    g = rng.standard_normal((B, (S - n) // 2, H, dh))
+    dctx[:, n:-1:2], dctx[:, n + 1::2] = g, -g
+    qkv, dctx = round_to_bf16(qkv).reshape(B, S, -1), round_to_bf16(dctx).reshape(B, S, -1)
+    ctx_ref, lse_ref = orc.attention_fwd(qkv, H, dh)
+    dv_ref = orc.attention_bwd(dctx, qkv, H, dh)[..., 2 * H * dh:]
+    qd, dd = to_dev(qkv, "bf16"), to_dev(dctx, "bf16")
+    ctx, lse = torch.empty((B, S, H * dh), dtype=torch.bfloat16, device=DEV), torch.empty((B, H, S), device=DEV)
+    dq, delta = torch.empty_like(qd), torch.empty_like(lse)
+    err = {}
+    for path in (fax.PATH_SCALAR, fax.PATH_AUTO):
+        fax.fax_attention_fwd(fax.FAX_BF16, B, S, H, dh, qd, ctx, lse, path)
+        fax.fax_attention_bwd(fax.FAX_BF16, B, S, H, dh, qd, ctx, lse, dd, dq, delta, path)
+        err[path] = (rel_fro(to_np(ctx[:, n:]), ctx_ref[:, n:]), rel_fro(to_np(dq[:, :n, 2 * H * dh:]), dv_ref[:, :n]))
+    # as close as the scalar kernels' fp32 probabilities, whose last bits (2^-24 of the terms, 1e-3 of the sums) differ from these
+    for a, s in zip(err[fax.PATH_AUTO], err[fax.PATH_SCALAR]):
+        assert a <= 1.25 * s, err
