@@ -148,3 +148,27 @@ def test_output_projection_f32_over_a_ragged_vocabulary(V, D, S):
     fax.fax_eval_step(md, _dev_params(p, "f32"), torch.from_numpy(tok).to(DEV), torch.from_numpy(lab).to(DEV), out, ws, wsb)
     assert abs(out[0].item() - loss) <= 1e-6 * abs(loss)
     assert (ws[wsb:] == 255).all()
+
+
+# b2's gradient is the sum of dy's rows.  Of N(0, 1) rows: the last rounding (2^-24 / 3^0.5 at most, rms) and those of sixteen terms a slab,
+# whose sums are carried exactly, come to 0.7e-7; a plain sum over the slabs gave 1.8e-7 (2048 rows) and 0.9e-7 (128).
+@pytest.mark.parametrize("shape,bar", [(dict(B=4, S=512, D=1024, H=16, dh=64, F=4096), 1.0e-7), (dict(B=1, S=1999, D=264, H=4, dh=64, F=500), 1.0e-7),
+                                       (dict(B=2, S=64, D=128, H=4, dh=32, F=512), 0.9e-7)])
+def test_bias_gradient_is_as_exact_as_a_pass_of_its_own(shape, bar):
+    sh = BlockShape(dtype="f32", sigma_w=0.02, **shape)
+    p, x, _ = make_block_inputs(sh, seed=0)
+    errs = []
+    for seed in range(4):
+        dy = _f32(np.random.default_rng(seed).standard_normal(x.shape))
+        ref = dy.reshape(-1, sh.D).sum(0)
+        errs.append(np.linalg.norm(helpers.run_block(sh, p, x, dy)["grads"]["b2"] - ref) / np.linalg.norm(ref))
+    assert np.mean(errs) <= bar, errs
+
+
+def test_bias_gradient_of_infinities():
+    sh = BlockShape(dtype="f32", sigma_w=0.02, B=1, S=200, D=64, H=1, dh=64, F=64)
+    p, x, dy = make_block_inputs(sh, seed=0)
+    dy = np.array(dy)
+    dy.reshape(-1, sh.D)[[3, 150], [1, 2]] = np.inf, np.nan
+    b2 = helpers.run_block(sh, p, x, dy)["grads"]["b2"]
+    assert np.isposinf(b2[1]) and np.isnan(b2[2]) and np.isfinite(np.delete(b2, [1, 2])).all()
