@@ -163,6 +163,9 @@ int fax_block_bwd_layout(const FaxBlockDims* dims, FaxBwdLayout* out);
 int fax_block_workspace_bytes(const FaxBlockDims* dims, size_t* out); /* covers fwd and bwd */
 int fax_train_workspace_bytes(const FaxModelDims* dims, size_t* out);
 
+/* Host-only: how many streams fax_block_bwd runs on, 1 (the caller's) or 2 (see FAX_FLAG_SINGLE_STREAM). */
+int fax_block_bwd_streams(const FaxBlockDims* dims, int* out);
+
 /* Host-only argument check used by every entry point; exposed for tests. */
 int fax_block_dims_check(const FaxBlockDims* dims);
 

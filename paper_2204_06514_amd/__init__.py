@@ -104,6 +104,7 @@ def _load():
         "fax_block_saved_layout": (i32, [P(FaxBlockDims), P(FaxSavedLayout)]),
         "fax_block_bwd_layout": (i32, [P(FaxBlockDims), P(FaxBwdLayout)]),
         "fax_block_workspace_bytes": (i32, [P(FaxBlockDims), P(sz)]),
+        "fax_block_bwd_streams": (i32, [P(FaxBlockDims), P(C.c_int)]),
         "fax_train_workspace_bytes": (i32, [P(FaxModelDims), P(sz)]),
         "fax_eval_workspace_bytes": (i32, [P(FaxModelDims), P(sz)]),
         "fax_eval_step": (i32, [P(FaxModelDims), P(FaxModelTensors), vp, vp, vp, vp, sz, vp]),
@@ -234,6 +235,12 @@ def fax_block_bwd_layout(dims):
 def fax_block_workspace_bytes(dims):
     out = C.c_size_t()
     _check(_lib.fax_block_workspace_bytes(C.byref(dims), C.byref(out)))
+    return out.value
+
+
+def fax_block_bwd_streams(dims):
+    out = C.c_int(0)
+    _check(_lib.fax_block_bwd_streams(C.byref(dims), C.byref(out)))
     return out.value
 
 

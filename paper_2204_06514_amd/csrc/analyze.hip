@@ -98,15 +98,16 @@ extern "C" int fax_analyze(const FaxModelDims* g, const FaxMesh* mesh, FaxAnalys
   double gemm_flop_fwd = 0, us_gemm = 0;
   for (const auto& s : fwd) {
     gemm_flop_fwd += 2.0 * s[0] * s[1] * s[2];
-    us_gemm += gemm_time_estimate_us(s[0], s[1], s[2], false);  // forward
-    us_gemm += gemm_time_estimate_us(s[0], s[2], s[1], false);  // input gradient: contraction over N
-    us_gemm += gemm_time_estimate_us(s[2], s[1], s[0], true);   // weight gradient: contraction over the tokens
+    us_gemm += gemm_time_estimate_us(dense_product(b.dtype, false, false, s[0], s[1], s[2], false));  // forward
+    us_gemm += gemm_time_estimate_us(dense_product(b.dtype, false, true, s[0], s[2], s[1], false));   // input gradient: contraction over N
+    us_gemm += gemm_time_estimate_us(dense_product(b.dtype, true, false, s[2], s[1], s[0], true));    // weight gradient: contraction over the tokens
   }
   gemm_flop_fwd *= L;
   us_gemm *= L;
   gemm_flop_fwd += 2.0 * T * (double)D * V;
-  us_gemm += gemm_time_estimate_us(T, V, D, false) + gemm_time_estimate_us(T, D, V, false) +
-             gemm_time_estimate_us(V, D, T, true);
+  us_gemm += gemm_time_estimate_us(logits_product(a.local, nullptr, nullptr, nullptr)) +
+             gemm_time_estimate_us(hidden_grad_product(a.local, nullptr, nullptr, nullptr)) +
+             gemm_time_estimate_us(embedding_grad_product(a.local, nullptr, nullptr, nullptr));
   const double pairs = (double)b.B * b.H * b.S * b.S / 2.0;  // (query, key) pairs under the mask, per layer
   const double attn_flop_fwd = L * 4.0 * pairs * b.dh;
   a.flop_step = 3.0 * (gemm_flop_fwd + attn_flop_fwd);

@@ -352,7 +352,8 @@ static bool use_side_stream(const FaxBlockDims& d) {
   constexpr long long kCUs = 256;
   double us = 0.0;
   for (const auto& g : shapes)
-    us += d.dtype == FAX_BF16 ? gemm_time_estimate_us(g[0], g[1], g[2], g[3] != 0) : 5.0 + 2.0 * g[0] * g[1] * g[2] / 90.0e6;
+    us += d.dtype == FAX_BF16 ? gemm_time_estimate_us(dense_product(FAX_BF16, g[3], !g[3], g[0], g[1], g[2], g[3]))
+                              : 5.0 + 2.0 * g[0] * g[1] * g[2] / 90.0e6;
   if (us < 110.0) return false;
   if (d.dtype != FAX_BF16) return true;
   for (const auto& g : shapes) {
@@ -473,14 +474,34 @@ static int logits_ld(const FaxModelDims& m) {
   const int unit = m.blk.D >= line ? line : chunk;
   return (m.V + unit - 1) / unit * unit;
 }
+// The output projection's three products, for the steps and for the analysis (without pointers).
 // logits = hf E^T, rows `ld` apart; in bf16 the columns up to the next multiple of 8 repeat the last one (the kernel
 // stores whole groups of four), and nothing is stored beyond
-static GemmArgs logits_product(const FaxModelDims& m, const void* hf, const void* tok_emb, void* logits, int ld) {
+GemmArgs logits_product(const FaxModelDims& m, const void* hf, const void* tok_emb, void* logits) {
+  const int ld = logits_ld(m);
   GemmArgs g;
   g.dtype = m.blk.dtype; g.ta = false; g.tb = true;
   g.M = m.blk.B * m.blk.S; g.N = g.dtype == FAX_BF16 && ld > m.V ? (m.V + 7) / 8 * 8 : m.V; g.K = m.blk.D;
   g.A = hf; g.lda = m.blk.D; g.B = tok_emb; g.ldb = m.blk.D; g.C = logits; g.ldc = ld;
   if (g.N > m.V) g.b_rows = m.V;
+  return g;
+}
+// dE = dlogits^T hf
+GemmArgs embedding_grad_product(const FaxModelDims& m, const void* dlogits, const void* hf, void* out) {
+  GemmArgs g;
+  g.dtype = m.blk.dtype; g.ta = true; g.tb = false;
+  g.M = m.V; g.N = m.blk.D; g.K = m.blk.B * m.blk.S;
+  g.a_padded = logits_ld(m) > m.V;
+  g.A = dlogits; g.lda = logits_ld(m); g.B = hf; g.ldb = m.blk.D; g.C = out; g.ldc = m.blk.D; g.c_f32 = true;
+  return g;
+}
+// dhf = dlogits E
+GemmArgs hidden_grad_product(const FaxModelDims& m, const void* dlogits, const void* tok_emb, void* out) {
+  GemmArgs g;
+  g.dtype = m.blk.dtype;
+  g.M = m.blk.B * m.blk.S; g.N = m.blk.D; g.K = m.V;
+  g.a_padded = logits_ld(m) > m.V;
+  g.A = dlogits; g.lda = logits_ld(m); g.B = tok_emb; g.ldb = m.blk.D; g.C = out; g.ldc = m.blk.D;
   return g;
 }
 
@@ -587,6 +608,13 @@ int fax_block_workspace_bytes(const FaxBlockDims* dims, size_t* out) {
   BwdWs W;
   bwd_layout(*dims, &W);
   *out = W.total;
+  return FAX_OK;
+}
+
+int fax_block_bwd_streams(const FaxBlockDims* dims, int* out) {
+  FAX_TRY(check_dims(dims));
+  if (!out) { set_error("out is NULL"); return FAX_ERR_INVALID_ARG; }
+  *out = use_side_stream(*dims) ? 2 : 1;
   return FAX_OK;
 }
 
@@ -740,7 +768,7 @@ int fax_eval_step(const FaxModelDims* dims, const FaxModelTensors* params, const
     FAX_TRY(block_fwd_impl(bd, params->blocks[l], w + W.x[l & 1], w + W.x[(l + 1) & 1], w + W.saved, nullptr, nullptr, s));
   FAX_TRY(ln_fwd(d.dtype, T, D, w + W.x[dims->L & 1], params->lnf_g, params->lnf_b, d.ln_eps, w + W.hf,
                  (float*)(w + W.muf), (float*)(w + W.rstdf), s));
-  FAX_TRY(gemm(logits_product(*dims, w + W.hf, params->tok_emb, w + W.logits, ldl), s));
+  FAX_TRY(gemm(logits_product(*dims, w + W.hf, params->tok_emb, w + W.logits), s));
   return cross_entropy(d.dtype, T, V, ldl, w + W.logits, labels, nullptr, (float*)(w + W.row_loss), loss_out, 1.0f, s);
 }
 
@@ -804,7 +832,7 @@ int fax_train_step(const FaxModelDims* dims, const FaxModelTensors* params, cons
                            w + W.saved + W.saved_stride * l, nullptr, nullptr, s));
   FAX_TRY(ln_fwd(d.dtype, T, D, xL, params->lnf_g, params->lnf_b, d.ln_eps, w + W.hf, (float*)(w + W.muf),
                  (float*)(w + W.rstdf), s));
-  FAX_TRY(gemm(logits_product(*dims, w + W.hf, params->tok_emb, w + W.logits, ldl), s));
+  FAX_TRY(gemm(logits_product(*dims, w + W.hf, params->tok_emb, w + W.logits), s));
   }
   // loss and its gradient, in place over the logits
   {
@@ -814,19 +842,12 @@ int fax_train_step(const FaxModelDims* dims, const FaxModelTensors* params, cons
   }
   {
   Timed phase_("phase_backward", WORK_FLOP, 2.0 * fwd_flop, s);
-  // output projection backward: dE = dlogits^T hf ; dhf = dlogits E
-  GemmArgs g; g.dtype = d.dtype; g.ta = true; g.tb = false;
-  g.M = V; g.N = D; g.K = T;
-  g.a_padded = ldl > V;
-  g.A = w + W.logits; g.lda = ldl; g.B = w + W.hf; g.ldb = D; g.C = grads->tok_emb; g.ldc = D; g.c_f32 = true;
+  // output projection backward
+  GemmArgs g = embedding_grad_product(*dims, w + W.logits, w + W.hf, grads->tok_emb);
   g.accumulate = acc;
   g.split_ws = W.headsplit < W.total ? w + W.headsplit : nullptr;
   FAX_TRY(gemm(g, s));
-  g = GemmArgs(); g.dtype = d.dtype;
-  g.M = T; g.N = D; g.K = V;
-  g.a_padded = ldl > V;
-  g.A = w + W.logits; g.lda = ldl; g.B = params->tok_emb; g.ldb = D; g.C = w + W.dhf; g.ldc = D;
-  FAX_TRY(gemm(g, s));
+  FAX_TRY(gemm(hidden_grad_product(*dims, w + W.logits, params->tok_emb, w + W.dhf), s));
   FAX_TRY(ln_bwd(d.dtype, T, D, w + W.dhf, xL, (const float*)(w + W.muf), (const float*)(w + W.rstdf), params->lnf_g,
                  nullptr, w + W.dcur, (float*)grads->lnf_g, (float*)grads->lnf_b, acc, w + W.blk, s));
   for (int l = L - 1; l >= 0; l--)

@@ -67,9 +67,27 @@ struct GemmArgs {
   int b_rows = 0;
 };
 int gemm(const GemmArgs& g, hipStream_t s);
+// What gemm() runs for a product: the scalar kernel, the fp32 matrix-core kernel, the bf16 one or its masked-edge form.
+// Host only; pointers that are NULL count as aligned.
+enum GemmForm { GEMM_SCALAR, GEMM_F32, GEMM_MFMA, GEMM_EDGE };
+GemmForm gemm_form(const GemmArgs& g);
+// Predicted duration of gemm() on this product, microseconds: by the form it takes, from that form's planner.  Host only.
+double gemm_time_estimate_us(const GemmArgs& g);
+// A product of densely stored operands, without pointers: for the two above.
+inline GemmArgs dense_product(int dtype, bool ta, bool tb, int M, int N, int K, bool c_f32) {
+  GemmArgs g;
+  g.dtype = dtype; g.ta = ta; g.tb = tb;
+  g.M = M; g.N = N; g.K = K; g.lda = ta ? M : K; g.ldb = tb ? K : N; g.ldc = N; g.c_f32 = c_f32;
+  return g;
+}
+// The output projection of a model: logits, gradient of the embedding, gradient of the hidden states.
+GemmArgs logits_product(const FaxModelDims& m, const void* hf, const void* tok_emb, void* logits);
+GemmArgs embedding_grad_product(const FaxModelDims& m, const void* dlogits, const void* hf, void* out);
+GemmArgs hidden_grad_product(const FaxModelDims& m, const void* dlogits, const void* tok_emb, void* out);
 int gemm_simt(const GemmArgs& g, hipStream_t s);
 bool gemm_f32_supported(const GemmArgs& g);
 int gemm_f32(const GemmArgs& g, hipStream_t s);
+double gemm_f32_time_us(int M, int N, int K);
 bool gemm_mfma_supported(const GemmArgs& g);
 bool gemm_edge_supported(const GemmArgs& g);
 // A weight-gradient product of a narrow model has few output tiles and a very long contraction
@@ -85,8 +103,7 @@ GemmSplitPlan gemm_split_plan(int M, int N, int K);
 size_t gemm_split_ws_bytes(int M, int N, int K);
 GemmSplitPlan gemm_plan_query(int M, int N, int K, bool f32_out, int* tail);
 int gemm_tile_walk_query(int M, int N, int K, bool f32_out, int* tm, int* tn, int capacity, int* count, int* group);
-// Predicted duration of gemm() on this shape from the same cost model (host only), microseconds.
-double gemm_time_estimate_us(int M, int N, int K, bool f32_out);
+double gemm_mfma_time_us(const GemmArgs& g);
 int gemm_mfma(const GemmArgs& g, hipStream_t s);
 struct EpiArgs;
 int gemm_mfma_edge(const GemmArgs& g, const EpiArgs& e, const GemmSplitPlan& plan, hipStream_t s);

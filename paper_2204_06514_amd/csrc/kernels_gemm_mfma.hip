@@ -154,22 +154,6 @@ size_t gemm_split_ws_bytes(int M, int N, int K) {
   return split_ws_bytes_1(M, N, K);  // a column strip keeps the leading dimension of C: no split there
 }
 
-static double time_estimate_1(int M, int N, int K, bool f32_out) {
-  const GemmSplitPlan plan = plan_tiles(M, N, K, f32_out, f32_out, !tiles_whole(M, N, K), true);
-  for (const TileClass& tc : kTiles)
-    if (tc.m == plan.tile_m && tc.n == plan.tile_n && tc.deep == plan.deep) return 3.0 + tile_time_us(tc, M, N, K, f32_out, plan.splits);
-  return 0.0;
-}
-
-double gemm_time_estimate_us(int M, int N, int K, bool f32_out) {
-  switch (tiles_whole(M, N, K) ? tail_dim(M, N) : 0) {
-    case 1: return time_estimate_1(M - 128, N, K, f32_out) + time_estimate_1(128, N, K, f32_out);
-    case 2: return time_estimate_1(M, N - 128, K, f32_out) + time_estimate_1(M, 128, K, f32_out);
-  }
-  return time_estimate_1(M, N, K, f32_out);
-}
-
-
 // What both forms of the kernel ask of a product, apart from its sizes.
 static bool mfma_layout_ok(const GemmArgs& g) {
   if (g.dtype != FAX_BF16) return false;
@@ -288,6 +272,22 @@ int gemm_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s) {
   }
   Timed t("gemm_mfma_pair", WORK_FLOP, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, s);
   return gemm_mfma_deep_pair(w, epi_args(w, wp), wp, d, epi_args(d, dp), dp, s);
+}
+
+// Launch included; with scratch for a split where the form may have one.
+double gemm_mfma_time_us(const GemmArgs& g) {
+  const bool edge = !tiles_whole(g.M, g.N, g.K) || b_short(g);
+  auto one = [&](int M, int N) {
+    const GemmSplitPlan plan = plan_tiles(M, N, g.K, g.c_f32, g.c_f32 && g.ldc == N, edge, gemm_edge_supported(g));
+    for (const TileClass& tc : kTiles)
+      if (tc.m == plan.tile_m && tc.n == plan.tile_n && tc.deep == plan.deep) return 3.0 + tile_time_us(tc, M, N, g.K, g.c_f32, plan.splits);
+    return 0.0;
+  };
+  switch (edge ? 0 : tail_dim(g.M, g.N)) {
+    case 1: return one(g.M - 128, g.N) + one(128, g.N);
+    case 2: return one(g.M, g.N - 128) + one(g.M, 128);
+  }
+  return one(g.M, g.N);
 }
 
 int gemm_mfma(const GemmArgs& g0, hipStream_t s) {

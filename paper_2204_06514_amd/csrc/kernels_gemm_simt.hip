@@ -1,6 +1,7 @@
 // Scalar-FMA GEMM: the fallback for what neither matrix-core form takes (bf16 operands that 16-byte loads do not fit, fp32
 // with both operands transposed), and the form a caller gets by asking for it.  Any M, N, K, any operand orientation.
 // 64x64x16 tile, 256 threads, 4x4 outputs per thread, operands staged through LDS as fp32.
+#include <algorithm>
 #include <cstdio>
 
 #include "fax_internal.h"
@@ -96,23 +97,47 @@ int gemm(const GemmArgs& g, hipStream_t s) {
   if (!timing_on()) return gemm_dispatch(g, s);
   // name the variant the way the kernel templates are instantiated: operand orientation
   // (k = contraction index contiguous, m = row/column index contiguous) and epilogue
-  const char* form = g.path == PATH_SIMT ? "scalar" : gemm_mfma_supported(g) ? "mfma" : g.path == PATH_AUTO && gemm_edge_supported(g) ? "edge" :
-                     g.path == PATH_AUTO && gemm_f32_supported(g) ? "mfma32" : "scalar";
+  static const char* const forms[] = {"scalar", "mfma32", "mfma", "edge"};  // by GemmForm
   char name[64];
-  snprintf(name, sizeof(name), "gemm_%s_A%c_B%c_%s", form, g.ta ? 'm' : 'k', g.tb ? 'k' : 'm',
+  snprintf(name, sizeof(name), "gemm_%s_A%c_B%c_%s", forms[gemm_form(g)], g.ta ? 'm' : 'k', g.tb ? 'k' : 'm',
            g.c_f32 ? "f32out" : g.epi == EPI_GELU ? "gelu" : g.epi == EPI_DGELU ? "dgelu" : "store");
   Timed t(name, WORK_FLOP, 2.0 * g.M * g.N * g.K, s);
   return gemm_dispatch(g, s);
 }
 
+GemmForm gemm_form(const GemmArgs& g) {
+  if (g.path != PATH_SIMT && gemm_mfma_supported(g)) return GEMM_MFMA;
+  if (g.path != PATH_AUTO) return GEMM_SCALAR;
+  return gemm_edge_supported(g) ? GEMM_EDGE : gemm_f32_supported(g) ? GEMM_F32 : GEMM_SCALAR;
+}
+
+// A workgroup takes its 64 x 64 tile through K in slabs of 16, each as long as its loads take to arrive (2.2 us, 2.7 with A stored
+// [K, M]) unless the CU's other workgroups fill that time: then 0.58 us a slab and tile (57 to 65 TFLOP/s).  Measured and
+// predicted, us: 4096 x 1500 x 500 115 / 114, 4096 x 500 x 2000 330 / 278, 8192 x 4004 x 1004 1194 / 1154, 3000 x 3600 x 1200 459 /
+// 458, 1024 x 500 x 500 57 / 73; weight gradients 500 x 2000 x 4096 716 / 694, 1200 x 3600 x 3000 540 / 511.
+static double gemm_simt_time_us(const GemmArgs& g) {
+  const double tiles = (double)((g.M + 63) / 64) * ((g.N + 63) / 64);
+  return 3.0 + (g.K + 15) / 16 * std::max(g.ta ? 2.7 : 2.2, 0.58 * tiles / 256.0);
+}
+
+double gemm_time_estimate_us(const GemmArgs& g) {
+  switch (gemm_form(g)) {
+    case GEMM_MFMA:
+    case GEMM_EDGE: return gemm_mfma_time_us(g);
+    case GEMM_F32: return 3.0 + gemm_f32_time_us(g.M, g.N, g.K);
+    case GEMM_SCALAR: break;
+  }
+  return gemm_simt_time_us(g);
+}
+
 static int gemm_dispatch(const GemmArgs& g, hipStream_t s) {
-  const bool mfma = g.path != PATH_SIMT && gemm_mfma_supported(g);
-  if (g.path == PATH_MFMA && !mfma) {
+  const GemmForm form = gemm_form(g);
+  if (g.path == PATH_MFMA && form != GEMM_MFMA) {
     set_error("fax_gemm: shape M=%d N=%d K=%d (dtype %d) does not tile for the MFMA kernel", g.M, g.N, g.K, g.dtype);
     return FAX_ERR_UNSUPPORTED;
   }
-  if (mfma || (g.path == PATH_AUTO && gemm_edge_supported(g))) return gemm_mfma(g, s);
-  if (g.path == PATH_AUTO && gemm_f32_supported(g)) return gemm_f32(g, s);
+  if (form == GEMM_MFMA || form == GEMM_EDGE) return gemm_mfma(g, s);
+  if (form == GEMM_F32) return gemm_f32(g, s);
   if (g.colsum) {
     // no fused form here: take the column sums of B [K, N] in a pass of their own
     if (g.tb || !g.colsum_ws) {

@@ -99,3 +99,45 @@ def test_mesh_must_divide_batch_heads_and_width():
     with pytest.raises(fax.FaxError) as e:
         fax.fax_analyze(odd, tensor=16)
     assert "feed-forward" in str(e.value)
+
+
+def _gemm_tflops(**kw):
+    """Rate at which the analyser prices the products of a model (its attention apart)."""
+    d = dict(B=8, S=512, D=512, H=8, dh=64, F=2048, dtype="bf16", L=6, V=32000)
+    d.update(kw)
+    V = d.pop("V")
+    ms = ModelShape(BlockShape(sigma_w=0.02, **d), V=V, S_max=d["S"])
+    a = fax.fax_analyze(mdims(ms))
+    attention = 3 * d["L"] * 2.0 * d["B"] * d["H"] * d["S"] ** 2 * d["dh"]
+    return (a.flop_step - attention) / (a.ms_gemm * 1e-3) / 1e12
+
+
+def test_products_are_priced_by_the_kernel_that_runs_them():
+    # rows of no whole 16-byte chunks: the scalar kernel, whose fp32 multiply-adds reach 79 TFLOP/s at the very most
+    scalar = _gemm_tflops(D=500, F=2000, H=10, dh=50, V=32003)
+    assert 4 < scalar < 40, scalar
+    # one such dimension puts the products it touches there; a vocabulary is none (its rows are padded)
+    whole = _gemm_tflops()
+    assert _gemm_tflops(F=2047) < 0.3 * whole and _gemm_tflops(V=32003) > 0.8 * whole
+    # whole chunks but no whole tiles: the masked-edge or small-tile form
+    assert _gemm_tflops(D=504, F=2016, H=9, dh=56, V=32003) > 5 * scalar
+    # fp32: the matrix cores give 155 TFLOP/s at most, whatever the sizes
+    for kw in (dict(D=1024, F=4096), dict(D=1000, F=4000, H=10, dh=100, V=32003), dict(D=501, F=2003, H=3, dh=167)):
+        assert 40 < _gemm_tflops(dtype="f32", **kw) < 155, kw
+
+
+def test_second_stream_of_the_backward_pass():
+    def streams(flags=0, **kw):
+        d = dict(B=1, S=512, D=512, H=8, dh=64, F=2048, dtype="bf16")
+        d.update(kw)
+        return fax.fax_block_bwd_streams(fax.block_dims(d["B"], d["S"], d["D"], d["H"], d["dh"], d["F"], CODE[d["dtype"]],
+                                                        fax.FAX_GELU_TANH, 1e-5, flags))
+    assert streams() == 1                                         # products shorter than the events that a second stream costs
+    assert streams(D=500, H=10, dh=50, F=2000) == 2               # the same sizes on the scalar kernel: milliseconds to overlap
+    assert streams(D=500, H=10, dh=50, F=2000, flags=fax.FAX_FLAG_SINGLE_STREAM) == 1
+    assert streams(B=4, S=2048, D=4096, H=32, dh=128, F=16384) == 1   # whole rounds of tiles: nothing to fill
+    assert streams(S=2048, D=5120, H=5, dh=128, F=2560) == 2
+    assert streams(B=2, S=64, D=128, H=4, dh=32, F=512, dtype="f32") == 1
+    assert streams(B=4, D=1024, H=16, F=4096, dtype="f32") == 2
+    with pytest.raises(fax.FaxError):
+        streams(dtype="bf16", dh=0)
