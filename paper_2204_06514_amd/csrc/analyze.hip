@@ -6,7 +6,9 @@
 // the mesh axis each tensor axis is split over (Sec. 2.2); its tensor parallelism splits heads and
 // every large weight over the model axis and requires the head count to divide (Sec. 3.2).
 // Nothing here touches a GPU; sizes come from the same layout functions the entry points use and
-// GEMM times from the launch planner's own cost model, so the analysis cannot drift from the code.
+// product times from the planners of the kernels that run them, and attention is priced by the form that takes it, so the
+// analysis cannot drift from the code.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -14,16 +16,39 @@
 
 namespace fax {
 
-// Measured cost of the attention kernels per 1000 (query, key) pairs under the causal mask, in
-// nanoseconds, by head width (forward, dQ, dK/dV kernels at S = 2048 on 128 (b, h) problems or more).
+// Microseconds of one layer's attention, forward and backward, by the form that attention_fwd and attention_bwd take: the
+// larger of what the chip needs for all (query, key) pairs under the causal mask (nanoseconds per 1000 pairs, measured at S =
+// 2000 to 2048 with 128 (b, h) problems) and what one workgroup needs for its chain of tiles, with its launches (from shapes of 1 to
+// 180 workgroups).  The bf16 kernels give two 128-row tiles of a head to a workgroup, one after the other, in steps of 64 of the
+// other index; the fp32 ones 32 rows, a quarter of whose 32-wide steps fall to each wave.  Measured and predicted, us: bf16, 4 x 777, 8
+// heads of 64 28 + 93 / 29 + 92, 45 heads of 1000 x 80 41 + 104 / 41 + 103, 5 of 2048 x 128 40 + 97 / 40 + 101; fp32, 64
+// heads of 512 x 64 39 + 111 / 23 + 80, 4 of 2000 x 128 89 + 180 / 88 + 185.  Scalar kernels: 64 heads of 1000 x 60 1559 + 3632 /
+// 1760 + 4288, of 1000 x 256 4875 + 13815 / 4896 + 13069.
 struct AttnCost {
-  double fwd, dq, dkv;
+  double fwd, bwd;
 };
-static AttnCost attn_cost(int dh, int S, int dtype) {
-  if (dtype == FAX_BF16 && S % 128 == 0 && dh == 128) return {0.59, 0.84, 1.48};
-  if (dtype == FAX_BF16 && S % 128 == 0 && dh == 64) return {0.32, 0.42, 0.63};
-  const double c = 0.25 * dh;  // the scalar kernels: a few TFLOP/s
-  return {c, 2 * c, 2 * c};
+static AttnCost attn_cost_us(const FaxBlockDims& b) {
+  const double pairs = (double)b.B * b.H * b.S * b.S / 2.0;
+  AttnCost rate, chain{0.0, 0.0};
+  if (attn_edge_supported(b.dtype, b.B, b.S, b.H, b.dh)) {
+    const double tiles = 2.0 * ((b.S + 127) / 128 + 1);
+    if (attn_mfma_supported(b.dtype, b.B, b.S, b.H, b.dh)) {
+      rate = b.dh == 64 ? AttnCost{0.32, 1.05} : AttnCost{0.59, 2.32};
+      chain = {3.0 + 1.1 * tiles, 9.0 + 2.7 * tiles};
+    } else {
+      rate = b.dh <= 64 ? AttnCost{0.70, 2.2} : b.dh <= 96 ? AttnCost{0.81, 2.6} : AttnCost{1.0, 3.2};
+      chain = {3.0 + (b.dh <= 64 ? 1.6 : 2.1) * tiles, 9.0 + 5.2 * tiles};
+    }
+  } else if (attn_f32_supported(b.dtype, b.dh, nullptr, nullptr, nullptr, nullptr)) {
+    const int width = (b.dh + 31) / 32 * 32;
+    const double tiles = ((b.S + 31) / 32 + 3) / 4, whole = b.dh == width ? 1.0 : 1.15;
+    rate = width == 32 ? AttnCost{1.6, 5.7} : width == 64 ? AttnCost{2.8, 9.6} : width == 96 ? AttnCost{4.5, 18.0} : AttnCost{5.7, 23.0};
+    rate = {rate.fwd * whole, rate.bwd * whole};
+    chain = {3.0 + (1.5 + 0.03 * width) * tiles, 9.0 + (2.0 + 0.07 * width) * tiles};
+  } else {
+    rate = b.dtype == FAX_BF16 ? AttnCost{25.0 + 0.5 * b.dh, 50.0 + 1.4 * b.dh} : AttnCost{30.0 + 0.6 * b.dh, 40.0 + 2.55 * b.dh};
+  }
+  return {std::max(pairs * rate.fwd * 1e-6, chain.fwd), std::max(pairs * rate.bwd * 1e-6, chain.bwd)};
 }
 
 static double block_params(double D, double Hd, double F) {
@@ -112,8 +137,8 @@ extern "C" int fax_analyze(const FaxModelDims* g, const FaxMesh* mesh, FaxAnalys
   const double attn_flop_fwd = L * 4.0 * pairs * b.dh;
   a.flop_step = 3.0 * (gemm_flop_fwd + attn_flop_fwd);
   a.flop_step_unhalved = 3.0 * (gemm_flop_fwd + 2.0 * attn_flop_fwd);
-  const AttnCost ac = attn_cost(b.dh, b.S, b.dtype);
-  a.ms_attention = L * pairs * (ac.fwd + ac.dq + ac.dkv) * 1e-9;
+  const AttnCost ac = attn_cost_us(b);
+  a.ms_attention = L * (ac.fwd + ac.bwd) * 1e-3;
   a.ms_gemm = us_gemm * 1e-3;
 
   // bandwidth-bound kernels: algorithmic bytes and launches

@@ -141,3 +141,15 @@ def test_second_stream_of_the_backward_pass():
     assert streams(B=4, D=1024, H=16, F=4096, dtype="f32") == 2
     with pytest.raises(fax.FaxError):
         streams(dtype="bf16", dh=0)
+
+
+# One layer's attention, forward and backward, as timed on the GPU (microseconds): every form, on full and nearly empty chips.
+@pytest.mark.parametrize("dtype,B,S,H,dh,us", [
+    ("bf16", 8, 2048, 16, 128, 705), ("bf16", 8, 2048, 12, 64, 288), ("bf16", 4, 768, 8, 64, 63), ("bf16", 2, 256, 4, 64, 39),       # plain
+    ("bf16", 8, 2000, 16, 96, 878), ("bf16", 8, 2000, 16, 64, 737), ("bf16", 4, 777, 8, 64, 121), ("bf16", 3, 1000, 15, 80, 145),   # masked edge
+    ("f32", 4, 512, 16, 64, 150), ("f32", 1, 2000, 4, 128, 269), ("f32", 8, 2000, 16, 40, 3675), ("f32", 2, 333, 4, 80, 60),        # fp32
+    ("bf16", 4, 1000, 16, 60, 5191), ("bf16", 4, 1000, 16, 256, 18690), ("f32", 4, 1000, 16, 30, 5331)])                            # scalar
+def test_attention_is_priced_by_the_kernel_that_runs_it(dtype, B, S, H, dh, us):
+    ms = ModelShape(BlockShape(B=B, S=S, D=256, H=H, dh=dh, F=256, dtype=dtype, sigma_w=0.02, L=3), V=1000, S_max=S)
+    predicted = fax.fax_analyze(mdims(ms)).ms_attention * 1e3 / 3
+    assert us / 1.6 < predicted < us * 1.6
