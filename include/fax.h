@@ -175,7 +175,7 @@ int fax_block_dims_check(const FaxBlockDims* dims);
  *   tail          0: one launch.  1 / 2: the last 128 rows / columns run as a launch of their own
  *                 (a dimension that is an odd multiple of 128); tile_* and splits then describe
  *                 the bulk.
- *   tile_m/tile_n the tile class; 0 when no class divides the shape (the scalar kernel runs).
+ *   tile_m/tile_n the tile class; 0 when no class divides the shape (fax_gemm_route says what runs then).
  *   splits        K ranges, each writing a partial product that a fold kernel sums (1: none).
  * Exposed so that a test can assert that a cut-down workload runs the plans of the full one. */
 typedef struct FaxGemmPlan {
@@ -192,6 +192,26 @@ int fax_gemm_plan(int M, int N, int K, int c_f32, FaxGemmPlan* out);
  * Exposed so that a test can check that every walk visits every tile exactly once. */
 int fax_gemm_tile_walk(int M, int N, int K, int c_f32, int32_t* tile_row, int32_t* tile_col, int capacity,
                        int* count, int* group);
+
+/* Host-only: what gemm entry points make of any product C[M,N] = op(A) op(B) of densely stored operands (ta, tb, c_f32
+ * as for fax_gemm, PATH_AUTO; scratch != 0: with scratch for a split, as in fax_block_bwd and fax_train_step, where
+ * fax_gemm has none).
+ *   form          FAX_GEMM_*: the scalar kernel; the fp32 matrix-core kernel; the bf16 one, whose tiles divide the shape; its
+ *                 masked-edge form; or the small-tile kernel for products that leave CUs idle (any shape).
+ *   tail, tile_*, splits   as in FaxGemmPlan, for the masked-edge and small-tile kernels too (0, 0, 1 for the scalar kernel).
+ *   tiles_m, tiles_n, group   the bf16 kernels' tile grid and the kind of its walk as in fax_gemm_tile_walk, group -1 for
+ *                 the others; tile_row[i], tile_col[i] receive the tile of work item i < capacity (may be NULL at 0).
+ * Exposed so that a test can assert that its sizes run the kernel it is about. */
+#define FAX_GEMM_SCALAR 0
+#define FAX_GEMM_F32 1
+#define FAX_GEMM_MFMA 2
+#define FAX_GEMM_EDGE 3
+#define FAX_GEMM_SMALL 4
+typedef struct FaxGemmRoute {
+  int32_t form, tail, tile_m, tile_n, splits, tiles_m, tiles_n, group;
+} FaxGemmRoute;
+int fax_gemm_route(int dtype, int ta, int tb, int M, int N, int K, int c_f32, int scratch, FaxGemmRoute* out, int32_t* tile_row,
+                   int32_t* tile_col, int capacity);
 
 /*
  * Forward pass of one pre-LayerNorm decoder block (Fig. 1; forward phase of Fig. 4):

@@ -24,6 +24,7 @@ FAX_FLAG_SKIP_UPDATE = 1
 FAX_FLAG_ACCUMULATE = 2
 FAX_FLAG_DETERMINISTIC = 4
 PATH_AUTO, PATH_SCALAR, PATH_MFMA = 0, 1, 2
+FAX_GEMM_SCALAR, FAX_GEMM_F32, FAX_GEMM_MFMA, FAX_GEMM_EDGE, FAX_GEMM_SMALL = 0, 1, 2, 3, 4
 
 TENSOR_NAMES = ("ln1_g", "ln1_b", "wqkv", "bqkv", "wo", "bo", "ln2_g", "ln2_b", "w1", "b1", "w2", "b2")
 
@@ -71,6 +72,10 @@ class FaxGemmPlan(C.Structure):
     _fields_ = [(n, C.c_int32) for n in ("tail", "tile_m", "tile_n", "splits")]
 
 
+class FaxGemmRoute(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("form", "tail", "tile_m", "tile_n", "splits", "tiles_m", "tiles_n", "group")]
+
+
 class FaxMesh(C.Structure):
     _fields_ = [("data", C.c_int32), ("tensor", C.c_int32)]
 
@@ -101,6 +106,7 @@ def _load():
         "fax_block_dims_check": (i32, [P(FaxBlockDims)]),
         "fax_gemm_plan": (i32, [i32, i32, i32, i32, P(FaxGemmPlan)]),
         "fax_gemm_tile_walk": (i32, [i32, i32, i32, i32, vp, vp, i32, P(C.c_int), P(C.c_int)]),
+        "fax_gemm_route": (i32, [i32] * 8 + [P(FaxGemmRoute), vp, vp, i32]),
         "fax_block_saved_layout": (i32, [P(FaxBlockDims), P(FaxSavedLayout)]),
         "fax_block_bwd_layout": (i32, [P(FaxBlockDims), P(FaxBwdLayout)]),
         "fax_block_workspace_bytes": (i32, [P(FaxBlockDims), P(sz)]),
@@ -218,6 +224,20 @@ def fax_gemm_tile_walk(M, N, K, c_f32=0):
     _check(_lib.fax_gemm_tile_walk(M, N, K, int(c_f32), C.cast(rows, C.c_void_p), C.cast(cols, C.c_void_p), n,
                                    C.byref(count), C.byref(group)))
     return group.value, [(rows[i], cols[i]) for i in range(n)]
+
+
+def fax_gemm_route(dtype, ta, tb, M, N, K, c_f32=0, scratch=0, walk=False):
+    """-> FaxGemmRoute: the kernel, tile and split that any product runs on (host only); walk: and [(tile_row, tile_col), ...]
+    in work-item order."""
+    out = FaxGemmRoute()
+    args = (dtype, ta, tb, M, N, K, int(c_f32), int(scratch), C.byref(out))
+    _check(_lib.fax_gemm_route(*args, None, None, 0))
+    if not walk:
+        return out
+    n = out.tiles_m * out.tiles_n
+    rows = (C.c_int32 * max(n, 1))(); cols = (C.c_int32 * max(n, 1))()
+    _check(_lib.fax_gemm_route(*args, C.cast(rows, C.c_void_p), C.cast(cols, C.c_void_p), n))
+    return out, [(rows[i], cols[i]) for i in range(n)]
 
 
 def fax_block_saved_layout(dims):

@@ -586,6 +586,21 @@ int fax_gemm_tile_walk(int M, int N, int K, int c_f32, int32_t* tile_row, int32_
   return FAX_OK;
 }
 
+int fax_gemm_route(int dtype, int ta, int tb, int M, int N, int K, int c_f32, int scratch, FaxGemmRoute* out, int32_t* tile_row,
+                   int32_t* tile_col, int capacity) {
+  if (!out) { set_error("out is NULL"); return FAX_ERR_INVALID_ARG; }
+  if (dtype != FAX_F32 && dtype != FAX_BF16) { set_error("bad dtype %d", dtype); return FAX_ERR_INVALID_ARG; }
+  if (capacity < 0 || (capacity > 0 && (!tile_row || !tile_col))) { set_error("tile_row / tile_col missing"); return FAX_ERR_INVALID_ARG; }
+  if (M <= 0 || N <= 0 || K <= 0) { set_error("non-positive GEMM size %d x %d x %d", M, N, K); return FAX_ERR_INVALID_ARG; }
+  const GemmRoute r = gemm_route(dense_product(dtype, ta != 0, tb != 0, M, N, K, c_f32 != 0), scratch != 0);
+  static const int32_t forms[] = {FAX_GEMM_SCALAR, FAX_GEMM_F32, FAX_GEMM_MFMA, FAX_GEMM_EDGE};  // by GemmForm
+  out->form = r.small ? FAX_GEMM_SMALL : forms[r.form];
+  out->tail = r.tail; out->tile_m = r.tile_m; out->tile_n = r.tile_n; out->splits = r.splits;
+  out->tiles_m = r.tiles_m; out->tiles_n = r.tiles_n; out->group = r.group;
+  for (int i = 0; i < r.tiles_m * r.tiles_n && i < capacity; i++) gemm_route_tile(r, i, tile_row + i, tile_col + i);
+  return FAX_OK;
+}
+
 int fax_block_saved_layout(const FaxBlockDims* dims, FaxSavedLayout* out) {
   FAX_TRY(check_dims(dims));
   if (!out) { set_error("out is NULL"); return FAX_ERR_INVALID_ARG; }

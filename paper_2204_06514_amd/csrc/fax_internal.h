@@ -88,6 +88,7 @@ int gemm_simt(const GemmArgs& g, hipStream_t s);
 bool gemm_f32_supported(const GemmArgs& g);
 int gemm_f32(const GemmArgs& g, hipStream_t s);
 double gemm_f32_time_us(int M, int N, int K);
+void gemm_f32_tile(int M, int N, int K, int* tile_m, int* tile_n);
 bool gemm_mfma_supported(const GemmArgs& g);
 bool gemm_edge_supported(const GemmArgs& g);
 // A weight-gradient product of a narrow model has few output tiles and a very long contraction
@@ -95,7 +96,7 @@ bool gemm_edge_supported(const GemmArgs& g);
 // partial product (and partial column sums), summed afterwards in a fixed order.  The plan (tile
 // class, number of ranges; 1 = no split) comes from a small cost model of the kernel.
 struct GemmSplitPlan {
-  int tile_m, tile_n;  // 256 x 256, 256 x 128, 128 x 128 or 64 x 64; 0: no tile class divides the shape
+  int tile_m, tile_n;  // 256 x 256, 256 x 128, 128 x 128, 128 x 64 or 64 x 64; 0: no tile class divides the shape
   int splits;
   bool deep;           // the form of kernels_gemm_deep.hip
 };
@@ -104,6 +105,16 @@ size_t gemm_split_ws_bytes(int M, int N, int K);
 GemmSplitPlan gemm_plan_query(int M, int N, int K, bool f32_out, int* tail);
 int gemm_tile_walk_query(int M, int N, int K, bool f32_out, int* tm, int* tn, int capacity, int* count, int* group);
 double gemm_mfma_time_us(const GemmArgs& g);
+// The launch gemm() makes of a product (of its bulk, where the last 128 rows (tail 1) or columns (2) are one of their own), with or
+// without scratch for a split: form, whether in its small-tile kernel, tile, K ranges, and the grid and grouping of the tile walk (bf16 forms; -1: none).
+struct GemmRoute {
+  GemmForm form;
+  bool small;
+  int tail, tile_m, tile_n, splits, tiles_m, tiles_n, group;
+};
+GemmRoute gemm_route(const GemmArgs& g, bool scratch);
+// Work item -> tile of that walk.
+void gemm_route_tile(const GemmRoute& r, int item, int* tile_row, int* tile_col);
 int gemm_mfma(const GemmArgs& g, hipStream_t s);
 struct EpiArgs;
 int gemm_mfma_edge(const GemmArgs& g, const EpiArgs& e, const GemmSplitPlan& plan, hipStream_t s);

@@ -324,13 +324,13 @@ static int dispatch_f32_class(int cls, const GemmArgs& g, const EpiArgs& e, hipS
 // quarters 0.88 to 1.07 for four times as many k's.  The small tiles fetch more operand bytes per product (64 x 64
 // reaches 90-100 TFLOP/s, 32 x 32 65-80) and win where larger ones leave CUs without work: 2048 x 1024 x 1024 95 us at
 // 128 x 128, 47 at 128 x 64, 49 at 64 x 64, 60 at 32 x 32; 128 x 128 x 512 42, 24, 16 and under 9.
+struct F32Class { int m, n, k; double slab_us, tile_us; };
+static constexpr F32Class kF32Classes[] = {{128, 128, 32, 2.40, 3.0}, {128, 64, 32, 1.43, 2.0}, {64, 64, 32, 0.75, 1.5}, {32, 32, 128, 0.95, 1.5}};
 static int gemm_f32_class(int M, int N, int K, double* time_us = nullptr) {
-  struct Class { int m, n, k; double slab_us, tile_us; };
-  static constexpr Class classes[] = {{128, 128, 32, 2.40, 3.0}, {128, 64, 32, 1.43, 2.0}, {64, 64, 32, 0.75, 1.5}, {32, 32, 128, 0.95, 1.5}};
   int best = 0;
   double best_t = 1e30;
   for (int c = 0; c < 4; c++) {
-    const Class& k = classes[c];
+    const F32Class& k = kF32Classes[c];
     const long long tiles = (long long)((M + k.m - 1) / k.m) * ((N + k.n - 1) / k.n);
     const double t = (double)((tiles + 255) / 256) * (((K + k.k - 1) / k.k) * k.slab_us + k.tile_us);
     if (t < best_t) { best_t = t; best = c; }
@@ -342,6 +342,11 @@ double gemm_f32_time_us(int M, int N, int K) {
   double t = 0.0;
   gemm_f32_class(M, N, K, &t);
   return t;
+}
+void gemm_f32_tile(int M, int N, int K, int* tile_m, int* tile_n) {
+  const F32Class& c = kF32Classes[gemm_f32_class(M, N, K)];
+  *tile_m = c.m;
+  *tile_n = c.n;
 }
 
 // What the kernel has no instance for: both operands transposed, GELU other than forward.

@@ -290,6 +290,27 @@ double gemm_mfma_time_us(const GemmArgs& g) {
   return one(g.M, g.N);
 }
 
+GemmRoute gemm_route(const GemmArgs& g, bool scratch) {
+  GemmRoute r{gemm_form(g), false, 0, 0, 0, 1, 0, 0, -1};
+  if (r.form == GEMM_F32) gemm_f32_tile(g.M, g.N, g.K, &r.tile_m, &r.tile_n);
+  if (r.form != GEMM_MFMA && r.form != GEMM_EDGE) return r;
+  const bool edge = r.form == GEMM_EDGE;
+  r.tail = edge ? 0 : tail_dim(g.M, g.N);
+  const int M = r.tail == 1 ? g.M - 128 : g.M, N = r.tail == 2 ? g.N - 128 : g.N;
+  const GemmSplitPlan p = plan_tiles(M, N, g.K, g.c_f32, g.c_f32 && scratch && g.ldc == N, edge, gemm_edge_supported(g));
+  r.small = p.deep; r.tile_m = p.tile_m; r.tile_n = p.tile_n; r.splits = p.splits;
+  r.tiles_m = (M + p.tile_m - 1) / p.tile_m;
+  r.tiles_n = (N + p.tile_n - 1) / p.tile_n;
+  r.group = walk_group(r.tiles_m, r.tiles_n, g.K, p.splits);
+  const int nt = r.tiles_m * r.tiles_n, slots = (p.tile_m == 128 && nt * p.splits <= 2 * kCUs) ? 2 * kCUs : kCUs;
+  if (r.group == 0 && (p.deep || std::min(nt * p.splits, slots) != 256)) r.group = 4;  // as launch_mfma and launch_deep decide
+  return r;
+}
+
+void gemm_route_tile(const GemmRoute& r, int item, int* tile_row, int* tile_col) {
+  tile_walk(item, r.tiles_m, r.tiles_n, r.group, *tile_row, *tile_col);
+}
+
 int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
   const bool edge = !tiles_whole(g0.M, g0.N, g0.K) || b_short(g0);
   if (const int td = edge ? 0 : tail_dim(g0.M, g0.N)) {

@@ -161,7 +161,7 @@ def test_gemm_plan_query():
     # a vocabulary that is an odd multiple of 128: bulk on 256-wide tiles, last 128 apart
     assert fax.fax_gemm_plan(65536, 50304, 768, 0)[0] == 2
     assert fax.fax_gemm_plan(50304, 768, 65536, 1)[0] == 1
-    # no tile class divides the shape: the scalar kernel's job
+    # no tile class divides the shape: this query describes launches of whole tiles only (fax_gemm_route has the others)
     assert fax.fax_gemm_plan(100, 72, 64, 0)[1] == 0
     with pytest.raises(fax.FaxError):
         fax.fax_gemm_plan(0, 128, 64)
@@ -210,6 +210,48 @@ def test_gemm_tile_walks_visit_every_tile_once():
     assert seen_groups >= {0, 4, 8}
     # no tile class: nothing to walk
     assert fax.fax_gemm_tile_walk(100, 72, 64, 0) == (-1, [])
+
+
+def test_gemm_routes():
+    def route(*a, **k):
+        r = fax.fax_gemm_route(*a, **k)
+        return r.form, r.tail, r.tile_m, r.tile_n, r.splits
+    bf16, f32 = fax.FAX_BF16, fax.FAX_F32
+    # where the plan query has an answer, the same one
+    for M, N, K, c in [(8192, 12288, 4096, 0), (768, 3072, 65536, 1), (65536, 50304, 768, 0), (50304, 768, 65536, 1)]:
+        assert route(bf16, c, 0, M, N, K, c, scratch=1) == (fax.FAX_GEMM_MFMA, *fax.fax_gemm_plan(M, N, K, c))
+    assert route(bf16, 1, 0, 768, 3072, 65536, 1)[4] == 1                                          # no scratch, no split
+    # sizes that no tile divides: the masked-edge form, or small tiles where those leave CUs idle; a split where there is scratch
+    assert route(bf16, 0, 0, 3000, 4800, 1200) == (fax.FAX_GEMM_EDGE, 0, 256, 256, 1)
+    assert route(bf16, 0, 1, 3000, 1200, 4800) == (fax.FAX_GEMM_EDGE, 0, 128, 128, 1)
+    assert route(bf16, 0, 0, 100, 72, 64)[0] in (fax.FAX_GEMM_EDGE, fax.FAX_GEMM_SMALL)
+    assert route(bf16, 0, 0, 512, 256, 1024) == (fax.FAX_GEMM_SMALL, 0, 64, 64, 1)
+    assert route(bf16, 1, 0, 392, 784, 6001, 1, scratch=1)[::4] == (fax.FAX_GEMM_EDGE, 8)
+    # rows of no whole 16-byte chunks, and orientations that only whole tiles have
+    for a in [(bf16, 0, 0, 100, 72, 62), (bf16, 0, 0, 100, 71, 64), (bf16, 1, 0, 100, 72, 64), (bf16, 1, 1, 104, 72, 64), (f32, 1, 1, 64, 64, 64)]:
+        assert route(*a) == (fax.FAX_GEMM_SCALAR, 0, 0, 0, 1), a
+    assert route(bf16, 1, 1, 128, 128, 64)[0] == fax.FAX_GEMM_MFMA
+    assert route(f32, 0, 0, 33, 35, 37) == (fax.FAX_GEMM_F32, 0, 32, 32, 1) and route(f32, 1, 0, 2048, 4096, 8192, 1)[2:4] == (128, 128)
+    with pytest.raises(fax.FaxError):
+        fax.fax_gemm_route(bf16, 0, 0, 0, 128, 64)
+    with pytest.raises(fax.FaxError):
+        fax.fax_gemm_route(7, 0, 0, 128, 128, 64)
+
+
+def test_tile_walks_of_every_route_visit_every_tile_once():
+    """As above, for the masked-edge and small-tile launches too: groups cut at the end, counts that are no multiple of eight."""
+    shapes = [(0, 0, 3000, 4800, 1200), (0, 1, 3000, 1200, 4800), (0, 0, 3108, 1536, 512), (0, 0, 1200, 4800, 3000), (0, 1, 20003, 1160, 72),
+              (0, 0, 4360, 4104, 200), (0, 0, 100, 72, 64), (0, 0, 512, 256, 1024), (0, 0, 1537, 512, 704), (0, 1, 2048, 640, 5120), (0, 0, 1, 8, 512),
+              (0, 0, 3100, 328, 520), (1, 0, 512, 512, 3108), (1, 0, 1200, 1200, 3000), (1, 0, 392, 784, 6001), (1, 0, 4360, 4104, 200),
+              (1, 0, 776, 2328, 8001), (1, 0, 136, 136, 4001), (0, 0, 8192, 4096, 4096), (1, 0, 768, 3072, 65536)]
+    forms = set()
+    for ta, tb, M, N, K in shapes:
+        r, walk = fax.fax_gemm_route(fax.FAX_BF16, ta, tb, M, N, K, ta, scratch=1, walk=True)
+        assert (r.tiles_m, r.tiles_n) == (-(-M // r.tile_m), -(-N // r.tile_n)) and r.tail == 0, (M, N, K)
+        assert sorted(walk) == [(i, j) for i in range(r.tiles_m) for j in range(r.tiles_n)], (M, N, K, r.group)
+        forms.add((r.form, r.tile_m, r.tile_n))
+    S, E = fax.FAX_GEMM_SMALL, fax.FAX_GEMM_EDGE
+    assert forms >= {(E, 256, 256), (E, 256, 128), (E, 128, 128), (S, 128, 64), (S, 64, 64), (fax.FAX_GEMM_MFMA, 256, 256)}
 
 
 def test_static_cross_entropy_checks_its_arguments_before_any_launch():
