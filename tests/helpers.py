@@ -58,9 +58,9 @@ def zeros_like_params(pd, dtype=torch.float32):
     return {k: torch.zeros(v.shape, dtype=dtype, device=DEV) for k, v in pd.items()}
 
 
-def run_block(sh, p, x, dy, gelu=None, partial=False, accumulate=False, grads_init=None):
+def run_block(sh, p, x, dy, gelu=None, partial=False, accumulate=False, grads_init=None, flags=0):
     """fax_block_fwd + fax_block_bwd through the C ABI.  Returns everything as float64 numpy."""
-    dims = dims_of(sh, fax.FAX_FLAG_TP_PARTIAL if partial else 0, gelu)
+    dims = dims_of(sh, flags | (fax.FAX_FLAG_TP_PARTIAL if partial else 0), gelu)
     pd = {k: to_dev(p[k], sh.dtype) for k in PARAM_NAMES}
     xd, dyd = to_dev(x, sh.dtype), to_dev(dy, sh.dtype)
     td = TDTYPE[sh.dtype]

@@ -119,7 +119,7 @@ BF16_SMALL = [
     BlockShape(B=1, S=384, D=512, H=2, dh=128, F=256, dtype="bf16", sigma_w=0.02),
     # ragged everything: the scalar fallback kernels
     BlockShape(B=2, S=100, D=136, H=3, dh=24, F=200, dtype="bf16", sigma_w=0.05),
-    # many tokens, narrow layers: the weight-gradient products split their contraction over several workgroups per tile
+    # many tokens, narrow layers: the weight-gradient products have few tiles and a long contraction
     BlockShape(B=2, S=1024, D=256, H=4, dh=64, F=512, dtype="bf16", sigma_w=0.02),
 ]
 
@@ -133,7 +133,7 @@ def test_bf16_small_blocks(sh, generic):
 
 
 def test_bf16_split_contraction_accumulates():
-    """Weight gradients whose contraction is split over workgroups, added onto existing values."""
+    """Weight gradients with few tiles and a long contraction, added onto existing values (test_gpu_routes.py has those in K ranges)."""
     sh = BF16_SMALL[3]
     p, x, dy = make_block_inputs(sh, seed=5, generic=True)
     rng = np.random.default_rng(1)

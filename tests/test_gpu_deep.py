@@ -71,7 +71,8 @@ def test_block_on_deep_tiles(shape, gelu):
 
 
 # A layer's weight and input gradient in one launch (small products, one stream): the bits that fax_gemm gives from the same tensors in
-# launches of their own.  Whole and cut slabs, 64- and 128-row tiles of either product, gradients stored and added to.
+# launches of their own.  Whole and cut slabs, gradients stored and added to, layers that pair next to layers that do not
+# (test_gpu_routes.py: which do, and 128-row tiles).
 @pytest.mark.parametrize("shape", [dict(B=2, S=256, D=256, H=4, dh=64, F=1024), dict(B=1, S=100, D=200, H=2, dh=72, F=520),
                                    dict(B=1, S=1, D=64, H=1, dh=64, F=72), dict(B=1, S=65, D=512, H=8, dh=64, F=2048)])
 @pytest.mark.parametrize("accumulate", [False, True])

@@ -11,7 +11,8 @@ from workloads import round_to_bf16
 
 pytestmark = pytest.mark.gpu
 
-# M, N, K.  The masked-edge GEMM keeps what is contiguous in memory a multiple of 8 elements; the rest is free.
+# M, N, K.  The masked-edge GEMM and the small-tile one that takes most of these keep what is contiguous in memory a multiple of 8 elements;
+# the rest is free.  (test_gpu_routes.py: every tile class of the masked-edge form.)
 FORWARD = [(1, 8, 8), (127, 136, 64), (129, 120, 72), (300, 264, 200), (1000, 1160, 136), (20003, 1160, 72)]
 WEIGHT_GRAD = [(8, 8, 1), (136, 120, 63), (128, 256, 65), (264, 200, 3001), (4360, 4104, 200)]
 
