@@ -96,11 +96,13 @@ static int gemm_dispatch(const GemmArgs& g, hipStream_t s);
 int gemm(const GemmArgs& g, hipStream_t s) {
   if (!timing_on()) return gemm_dispatch(g, s);
   // name the variant the way the kernel templates are instantiated: operand orientation
-  // (k = contraction index contiguous, m = row/column index contiguous) and epilogue
+  // (k = contraction index contiguous, m = row/column index contiguous) and epilogue; the small-tile kernel, which takes
+  // whole tiles and others alike, by a suffix
   static const char* const forms[] = {"scalar", "mfma32", "mfma", "edge"};  // by GemmForm
+  const GemmRoute r = gemm_route(g, g.split_ws != nullptr);
   char name[64];
-  snprintf(name, sizeof(name), "gemm_%s_A%c_B%c_%s", forms[gemm_form(g)], g.ta ? 'm' : 'k', g.tb ? 'k' : 'm',
-           g.c_f32 ? "f32out" : g.epi == EPI_GELU ? "gelu" : g.epi == EPI_DGELU ? "dgelu" : "store");
+  snprintf(name, sizeof(name), "gemm_%s_A%c_B%c_%s%s", r.small ? "mfma" : forms[r.form], g.ta ? 'm' : 'k', g.tb ? 'k' : 'm',
+           g.c_f32 ? "f32out" : g.epi == EPI_GELU ? "gelu" : g.epi == EPI_DGELU ? "dgelu" : "store", r.small ? "_small" : "");
   Timed t(name, WORK_FLOP, 2.0 * g.M * g.N * g.K, s);
   return gemm_dispatch(g, s);
 }

@@ -165,3 +165,24 @@ def test_pairs_of_every_tile(shape, w2, w1, pairs, gelu, accumulate):
     # through the stored derivative: one rounding to bf16
     du = (dy.reshape(T, sh.D) @ np.asarray(p["w2"]).T) * out["saved"]["dgelu"]
     assert rel_fro(bw["du"], du) <= 4e-3
+
+
+def test_timing_report_tells_the_kernels_apart():
+    def name(ta, tb, M, N, K, c_f32=0, dtype="bf16"):
+        A, B = torch.zeros((K, M) if ta else (M, K), dtype=helpers.TDTYPE[dtype], device=DEV), torch.zeros((N, K) if tb else (K, N), dtype=helpers.TDTYPE[dtype], device=DEV)
+        C = torch.empty((M, N), dtype=torch.float32 if c_f32 else helpers.TDTYPE[dtype], device=DEV)
+        fax.fax_timing_enable(1)
+        try:
+            fax.fax_gemm(helpers.CODE[dtype], ta, tb, M, N, K, A, A.shape[1], B, B.shape[1], C, N, c_f32=c_f32)
+            rows = fax.fax_timing_report(8)
+        finally:
+            fax.fax_timing_enable(0)
+        assert len(rows) == 1
+        return rows[0]["name"]
+
+    assert name(0, 0, 4096, 4096, 256) == "gemm_mfma_Ak_Bm_store"
+    assert name(0, 0, 3000, 4800, 1200) == "gemm_edge_Ak_Bm_store"
+    assert name(0, 1, 512, 256, 1024) == name(0, 1, 500, 264, 1000) == "gemm_mfma_Ak_Bk_store_small"
+    assert name(1, 0, 512, 512, 3108, 1) == "gemm_mfma_Am_Bm_f32out_small"
+    assert name(0, 0, 500, 500, 500) == "gemm_scalar_Ak_Bm_store"
+    assert name(0, 0, 500, 500, 500, dtype="f32") == "gemm_mfma32_Ak_Bm_store"
