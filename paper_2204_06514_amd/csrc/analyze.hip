@@ -92,7 +92,7 @@ extern "C" int fax_analyze(const FaxModelDims* g, const FaxMesh* mesh, FaxAnalys
   a.local.blk.B = g->blk.B / dp;
   a.local.blk.H = g->blk.H / tp;
   a.local.blk.F = g->blk.F / tp;
-  // rows of the token table: split only if every rank's slice stays on the MFMA path (a multiple of 128 rows)
+  // rows of the token table: split only into slices of whole 128-row tiles (other sizes run on the masked-edge form)
   a.local.V = g->V % (tp * 128) == 0 ? g->V / tp : g->V;
   if (tp > 1) a.local.blk.flags |= FAX_FLAG_TP_PARTIAL;
   const FaxBlockDims& b = a.local.blk;
