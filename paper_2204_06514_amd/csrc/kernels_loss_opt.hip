@@ -69,13 +69,15 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V,
         if (c * Vv::N + e >= V) zv[i].set(e, -INFINITY);
     }
   }
-  // this thread's maximum, then its sum of e^(z - maximum) (differences first, then the scale to base 2)
+  // this thread's maximum, then its sum of e^(z - maximum) (differences first, then the scale to base 2).  The maximum is the one
+  // that a NaN goes through: fmaxf would pass over it, and a thread with nothing but NaN (up to V = 2048 the last
+  // one may hold a single logit) would count as one without elements below.
   float mt = -INFINITY;
 #pragma unroll
   for (int i = 0; i < NV; i++) {
     if (threadIdx.x + i * nt < nvec) {
 #pragma unroll
-      for (int e = 0; e < Vv::N; e++) mt = fmaxf(mt, zv[i].get(e));
+      for (int e = 0; e < Vv::N; e++) mt = __builtin_elementwise_maximum(mt, zv[i].get(e));
     }
   }
   float se = 0.f;
@@ -87,32 +89,23 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V,
     }
   }
   // combine the (maximum, sum) pairs: within the wave, then across waves through LDS.  A thread
-  // without elements has maximum -inf and sum 0 and drops out; so does one whose elements are all -infinity, unless
-  // there is a NaN among them, which the maximum passes over: its sum is NaN and the row's with it.
-  if (mt == -INFINITY) {
-    se = 0.f;
-#pragma unroll
-    for (int i = 0; i < NV; i++) {
-      if (threadIdx.x + i * nt < nvec) {
-#pragma unroll
-        for (int e = 0; e < Vv::N; e++)
-          if (zv[i].get(e) != zv[i].get(e)) se = zv[i].get(e);
-      }
-    }
-  }
+  // without elements has maximum -inf and sum 0 and drops out.  The wave's maximum passes over NaN; its sum does not, and
+  // stands in for it then.
   const float mw = wave_max(mt);
-  const float sw = wave_sum(mt == -INFINITY ? se : se * ce_exp<PAD>(mt - mw));
+  const float sw = wave_sum(mt == -INFINITY ? 0.f : se * ce_exp<PAD>(mt - mw));
   const int wave = threadIdx.x >> 6, nw = nt >> 6;
   if ((threadIdx.x & 63) == 0) {
-    red_m[wave] = mw;
+    red_m[wave] = sw == sw ? mw : sw;
     red_s[wave] = sw;
   }
   __syncthreads();
   float M = red_m[0];
   for (int i = 1; i < nw; i++) M = fmaxf(M, red_m[i]);
   float S = 0.f;
-  for (int i = 0; i < nw; i++)  // fixed order
-    S += red_m[i] == -INFINITY ? red_s[i] : red_s[i] * ce_exp<PAD>(red_m[i] - M);
+  // fixed order.  (What drops out is a branch here; as one of two sums to select from it took the kernel from 51 registers to
+  // 88, one workgroup per CU instead of two, and 3108 x 32003 from 135 us to 167.)
+  for (int i = 0; i < nw; i++)
+    S += red_m[i] == -INFINITY ? 0.f : red_s[i] * ce_exp<PAD>(red_m[i] - M);
   if (threadIdx.x == 0) row_loss[row] = (M + (PAD ? logf(S) : __builtin_amdgcn_logf(S) * CE_LN2)) - z_label;  // v_log_f32 is log2
   if (!dlogits) return;
   const float invN = grad_scale / (float)N;
