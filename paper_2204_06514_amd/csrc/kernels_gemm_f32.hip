@@ -84,10 +84,11 @@ __device__ __forceinline__ void f32_tile(int id, int tiles_m, int tiles_n, int& 
   tn = rest / gsz;
 }
 
-// Bound by the matrix cores, which sustain 155 TFLOP/s in fp32 on register operands: 4001 x 31003 x 512 runs at 106, 2048 x 4096 x
-// 1024 at 105 (156 us; counters: matrix cores busy 83 % of the waves' time, the rest of the launch is its ramp and tail).  On the scalar
-// kernel the block of 2048 tokens x 1024 wide ran its products at 20 to 60 TFLOP/s.  Requesting slabs two ahead instead of one
-// changed nothing (187 us both ways at 2048 x 1024 x 4096) and cost weight gradients 10 %.
+// Bound by the matrix cores, which sustain 154 TFLOP/s in fp32 on register operands (132 to 136 in the first milliseconds of a run): 2048 x
+// 4096 x 1024 runs at 118 (146 us back to back, 173 to 181 inside a block's pass), 2048 x 1024 x 4096 at 99, 4001 x 31003 x 512 at 94.  In the
+// block of 2048 tokens x 1024 wide they are busy 64 to 76 % of the clocks of the CUs at work; the rest is waits for the next slab
+// and the launch's ramp and tail.  On the scalar kernel that block ran its products at 20 to 60 TFLOP/s.  Requesting slabs two
+// ahead instead of one changed nothing (187 us both ways at 2048 x 1024 x 4096) and cost weight gradients 10 %.
 // GELU: forward orientation with EPI_GELU, its transcendental code kept out of the other instances.
 template <int BM, int BN, int KS, bool TA, bool TB, bool VEC, bool GELU>
 __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A, int lda,
