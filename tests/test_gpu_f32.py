@@ -52,6 +52,47 @@ def test_gemm_f32_tiles_and_edges(M, N, K, ta, tb, pad):
     assert (C[M] == 7.0).all()  # nothing beyond the last row
 
 
+def _f32_product(ta, tb, A, B):
+    """A [M, K], B [K, N] on the device -> the kernel's product, operands stored as asked for."""
+    M, K, N = A.shape[0], A.shape[1], B.shape[1]
+    a, b = (A.T if ta else A).contiguous(), (B.T if tb else B).contiguous()
+    C = torch.empty(M, N, dtype=torch.float32, device=DEV)
+    fax.fax_gemm(fax.FAX_F32, ta, tb, M, N, K, a, a.shape[1], b, b.shape[1], C, N)
+    return C
+
+
+# M, N and the tile class that the planner gives them; every K ends inside a slab
+SPLIT = [(40, 70, 200, (32, 32)), (520, 2052, 72, (64, 64)), (2000, 1000, 1000, (128, 64)), (2047, 4100, 200, (128, 128))]
+
+
+@pytest.mark.parametrize("M,N,K,tile", SPLIT)
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+def test_gemm_f32_pieces(M, N, K, tile, ta, tb):
+    """The three bf16 pieces of a factor: products of single numbers, sums that are not finite, operands below the pieces' range."""
+    r = fax.fax_gemm_route(fax.FAX_F32, ta, tb, M, N, K)
+    assert (r.tile_m, r.tile_n) == tile
+    g = torch.Generator(device=DEV).manual_seed(M + ta + 2 * tb)
+    A, B = (torch.randn(s, generator=g, device=DEV) for s in ((M, K), (K, N)))
+    # one contraction index: the product of two numbers, of which the pieces leave out less than 2^-24 and two additions round
+    one = _f32_product(ta, tb, A[:, :1].contiguous(), B[:1].contiguous()).double()
+    ref = A[:, :1].double() @ B[:1].double()
+    assert ((one - ref).abs() <= 3 * EPS * ref.abs()).all()
+    # tiny factors: the same bound as for any (K sums and products)
+    bound = (K + 2) * EPS * (A.abs().double() @ B.abs().double())
+    for sa, sb in ((2.0 ** -120, 2.0 ** 100), (2.0 ** 100, 2.0 ** -120)):
+        assert ((_f32_product(ta, tb, A * sa, B * sb).double() / (sa * sb) - A.double() @ B.double()).abs() <= bound).all()
+    # infinities against ones (whose pieces are zero but for the first) and zeros, NaN, products that overflow, a number that no first piece holds
+    A[2] = 0.0
+    A[M // 2, 3], A[1, K - 1], A[M - 1, 0], A[2, 0], A[5, 7] = float("inf"), float("nan"), -float("inf"), 3e38, 3.4e38
+    B[3, ::3], B[3, 1::3], B[7, 4] = 1.0, 0.0, -1.0
+    B[0, N - 1] = 1.0
+    got, ref = _f32_product(ta, tb, A, B), A.double() @ B.double()
+    for f in (torch.isnan, torch.isposinf, torch.isneginf):
+        assert torch.equal(f(got), f(ref.float())), f
+    clean = torch.isfinite(ref.float())
+    assert ((got.double() - ref).abs() <= (K + 2) * EPS * (A.abs().double().nan_to_num() @ B.abs().double()))[clean].all()
+
+
 def test_gemm_f32_without_a_contraction():
     bias = torch.arange(40, dtype=torch.float32, device=DEV)
     C = torch.full((3, 40), 7.0, dtype=torch.float32, device=DEV)
