@@ -20,8 +20,9 @@ namespace fax {
 // larger of what the chip needs for all (query, key) pairs under the causal mask (nanoseconds per 1000 pairs, measured at S =
 // 2000 to 2048 with 128 (b, h) problems) and what one workgroup needs for its chain of tiles, with its launches (from shapes of 1 to
 // 180 workgroups).  The bf16 kernels give two 128-row tiles of a head to a workgroup, one after the other, in steps of 64 of the
-// other index; the fp32 ones 32 rows, a quarter of whose 32-wide steps fall to each wave.  Measured and predicted, us: bf16, 4 x 777, 8
-// heads of 64 28 + 93 / 29 + 92, 45 heads of 1000 x 80 41 + 104 / 41 + 103, 5 of 2048 x 128 40 + 97 / 40 + 101; fp32, 64
+// other index, or share a tile of few heads among two or four groups of waves; the fp32 ones 32 rows, a quarter of whose 32-wide steps
+// fall to each wave.  Measured and predicted, us: bf16, 4 x 777, 8 heads of 64 17 + 45 / 18 + 61, 45 heads of 1000 x 80 33 + 102 /
+// 31 + 86, 5 of 2048 x 128 23 + 48 / 24 + 59, 8 of 256 x 64 8 + 11 / 8 + 19; fp32, 64
 // heads of 512 x 64 39 + 111 / 23 + 80, 4 of 2000 x 128 89 + 180 / 88 + 185.  Scalar kernels: 64 heads of 1000 x 60 1559 + 3632 /
 // 1760 + 4288, of 1000 x 256 4875 + 13815 / 4896 + 13069.
 struct AttnCost {
@@ -32,12 +33,14 @@ static AttnCost attn_cost_us(const FaxBlockDims& b) {
   AttnCost rate, chain{0.0, 0.0};
   if (attn_edge_supported(b.dtype, b.B, b.S, b.H, b.dh)) {
     const double tiles = 2.0 * ((b.S + 127) / 128 + 1);
+    const bool split = attn_split_form(b.B, b.S, b.H, b.dh);
     if (attn_mfma_supported(b.dtype, b.B, b.S, b.H, b.dh)) {
       rate = b.dh == 64 ? AttnCost{0.32, 1.05} : AttnCost{0.59, 2.32};
-      chain = {3.0 + 1.1 * tiles, 9.0 + 2.7 * tiles};
+      chain = split ? AttnCost{4.0 + 0.6 * tiles, 10.0 + 1.45 * tiles} : AttnCost{3.0 + 1.1 * tiles, 9.0 + 2.7 * tiles};
     } else {
       rate = b.dh <= 64 ? AttnCost{0.70, 2.2} : b.dh <= 96 ? AttnCost{0.81, 2.6} : AttnCost{1.0, 3.2};
-      chain = {3.0 + (b.dh <= 64 ? 1.6 : 2.1) * tiles, 9.0 + 5.2 * tiles};
+      chain = split ? b.dh <= 64 ? AttnCost{4.0 + 0.9 * tiles, 10.0 + 3.2 * tiles} : AttnCost{4.0 + 1.5 * tiles, 10.0 + 4.2 * tiles}
+                    : AttnCost{3.0 + (b.dh <= 64 ? 1.6 : 2.1) * tiles, 9.0 + 5.2 * tiles};
     }
   } else if (attn_f32_supported(b.dtype, b.dh, nullptr, nullptr, nullptr, nullptr)) {
     const int width = (b.dh + 31) / 32 * 32;

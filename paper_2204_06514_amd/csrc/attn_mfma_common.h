@@ -187,7 +187,7 @@ __device__ __forceinline__ void split3(float x, float y, bf16x8 (&p)[3], int n) 
   }
 }
 __device__ __forceinline__ void clear_lds(char* smem, int bytes) {
-  for (int o = threadIdx.x * 16; o < bytes; o += 256 * 16) *reinterpret_cast<uint4*>(smem + o) = make_uint4(0u, 0u, 0u, 0u);
+  for (int o = threadIdx.x * 16; o < bytes; o += blockDim.x * 16) *reinterpret_cast<uint4*>(smem + o) = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
 }
 
@@ -222,13 +222,13 @@ __device__ __forceinline__ float not_finite(const V (&acc)[N], float sum) {
 // wave-uniform tile address in scalar registers plus a per-lane byte offset that depends only on
 // the lane, the segment and the row stride, so the compiler computes it once per kernel and a load
 // costs no vector arithmetic.  `wave` must be wave-uniform (readfirstlane).  EDGE: only the first
-// `rows` rows and `chunks` chunks exist.
-template <int DH, bool EDGE = false>
+// `rows` rows and `chunks` chunks exist.  WAVES: how many waves share the tile.
+template <int DH, bool EDGE = false, int WAVES = 4>
 __device__ __forceinline__ void tile_dma_seg(unsigned lds, const bf16_t* __restrict__ src, size_t ld, int wave, int i,
                                              int rows = TR, int chunks = DH / 8) {
   constexpr int NCH = DH / 8, RPI = 64 / NCH;
   const int lane = threadIdx.x & 63;
-  const int seg = wave * (DH / 32) + i;
+  const int seg = wave * (DH / 8 / WAVES) + i;
   const int row = seg * RPI + lane / NCH;
   const int chunk = (lane % NCH) ^ swz<DH>(row);
   if (!EDGE || (row < rows && chunk < chunks))
@@ -241,16 +241,52 @@ __device__ __forceinline__ void tile_dma_seg(unsigned lds, const bf16_t* __restr
 // the other: every workgroup then has the same amount of work and the grid drains without a
 // ragged tail.  Consecutive workgroup ids go to different XCDs; all workgroups of one
 // (batch, head) are dealt to the same XCD so that its K/V (Q/dO) stay in that XCD's L2.
-__device__ __forceinline__ void pair_of_tiles(int n_tiles, int BH, int& pair, int& bh) {
+__device__ __forceinline__ void pair_of_tiles(int block, int n_tiles, int BH, int& pair, int& bh) {
   const int n_pair = (n_tiles + 1) / 2;
   if (BH % 8 == 0) {
-    const int slot = blockIdx.x / 8;
-    bh = (slot / n_pair) * 8 + blockIdx.x % 8;
+    const int slot = block / 8;
+    bh = (slot / n_pair) * 8 + block % 8;
     pair = slot % n_pair;
   } else {
-    bh = blockIdx.x / n_pair;
-    pair = blockIdx.x % n_pair;
+    bh = block / n_pair;
+    pair = block % n_pair;
   }
+}
+
+// ---- the split forms (G = 2, 4 groups of WPG waves) ---------------------------------------------------
+// With few (batch, head)s the workgroups above (one group, G = 1) are too few to fill the chip, and each is as long as its two chains
+// of tiles.  In the split forms a workgroup is G groups of WPG waves and has 32 WPG rows (dK/dV above head width 64: 16 WPG), one
+// tile of them, the longest ones first (the shortest fill the gaps).  Its groups take every G-th tile of the
+// streamed index, each with LDS buffers of its own, and add up through LDS at the end: each workgroup is a G-th as long, and with WPG =
+// 4 / G there are G times as many.
+__device__ __forceinline__ void longest_first(int block, int BH, int& rank, int& bh) {
+  rank = block / BH;
+  bh = block % BH;  // (all of a head on one XCD where their number is a multiple of eight)
+}
+// Accumulators of group `grp` > 0 to the first group's wave with the same rows: float4 units at + 64 per unit, U units a lane.
+template <int U, typename V, int N>
+__device__ __forceinline__ void group_put(float* x, int slot, int at, const V (&acc)[N]) {
+  constexpr int E = sizeof(V) / sizeof(float);
+  float4* q = reinterpret_cast<float4*>(x) + (slot * U + at) * 64 + (threadIdx.x & 63);
+#pragma unroll
+  for (int t = 0; t < N; t++)
+#pragma unroll
+    for (int v = 0; v < E; v += 4) q[(t * E + v) / 4 * 64] = make_float4(acc[t][v], acc[t][v + 1], acc[t][v + 2], acc[t][v + 3]);
+}
+template <int U, typename V, int N>
+__device__ __forceinline__ void group_add(const float* x, int slot, int at, V (&acc)[N], float mine = 1.f, float theirs = 1.f) {
+  constexpr int E = sizeof(V) / sizeof(float);
+  const float4* q = reinterpret_cast<const float4*>(x) + (slot * U + at) * 64 + (threadIdx.x & 63);
+#pragma unroll
+  for (int t = 0; t < N; t++)
+#pragma unroll
+    for (int v = 0; v < E; v += 4) {
+      const float4 o = q[(t * E + v) / 4 * 64];
+      acc[t][v] = fmaf(acc[t][v], mine, o.x * theirs);
+      acc[t][v + 1] = fmaf(acc[t][v + 1], mine, o.y * theirs);
+      acc[t][v + 2] = fmaf(acc[t][v + 2], mine, o.z * theirs);
+      acc[t][v + 3] = fmaf(acc[t][v + 3], mine, o.w * theirs);
+    }
 }
 
 // The work on one block of keys (queries) is laid out by hand as three phases,

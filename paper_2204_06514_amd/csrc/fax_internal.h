@@ -158,16 +158,9 @@ int attn_bwd_f32(int B, int S, int H, int dh, const void* qkv, const void* ctx, 
 bool attn_mfma_supported(int dtype, int B, int S, int H, int dh);  // the plain form of the matrix-core kernels
 bool attn_edge_supported(int dtype, int B, int S, int H, int dh);  // plain or masked-edge form
 int attn_fwd_mfma(int B, int S, int H, int dh, const void* qkv, void* ctx, float* lse, hipStream_t s);
-// Optional: scratch for the dQ kernel's own copy of delta ([B,H,S] fp32) and a second stream with two
-// events; given them, and few enough workgroups (attn_bwd_side_by_side), dQ and dK/dV run side by side.
-struct AttnBwdSplit {
-  float* delta_scratch;
-  hipStream_t side;
-  hipEvent_t fork, join;
-};
-bool attn_bwd_side_by_side(int B, int S, int H);
+bool attn_split_form(int B, int S, int H, int dh);  // few enough workgroups for one of the split forms
 int attn_bwd_mfma(int B, int S, int H, int dh, const void* qkv, const void* ctx, const float* lse,
-                  const void* dctx, void* dqkv, float* delta, hipStream_t s, const AttnBwdSplit* split = nullptr);
+                  const void* dctx, void* dqkv, float* delta, hipStream_t s);
 
 // ---- loss, embedding, optimizer ---------------------------------------------------------------
 // dlogits = grad_scale (softmax - onehot) / N, may alias logits, NULL for the loss alone.  Rows are `ld` >= V elements apart in

@@ -27,12 +27,12 @@
 //
 // No atomics: dQ has one writer per query row, dK/dV one writer per key row; S and dP are
 // recomputed in both backward kernels (7 tile products instead of 5).
-#include "attn_mfma_common.h"
+#include "attn_dkv16.h"
 
 namespace fax {
 
 // dK, dV at head widths above 64: kernels_attn_dkv16.hip (16 keys per wave, its own LDS swizzle)
-int attn_bwd_dkv16_mfma(int B, int S, int H, int dh, bool edge, const bf16_t* qkv, const float* lse, const float* delta, const bf16_t* dctx,
+int attn_bwd_dkv16_mfma(int B, int S, int H, int dh, bool edge, int groups, int waves, const bf16_t* qkv, const float* lse, const float* delta, const bf16_t* dctx,
                         bf16_t* dqkv, hipStream_t s);
 
 // ---------------------------------------------------------------------------------------------
@@ -40,33 +40,38 @@ int attn_bwd_dkv16_mfma(int B, int S, int H, int dh, bool edge, const bf16_t* qk
 // K and V stream through two LDS buffers.  Per tile: P1 = S^T for both 32-key halves, V = online
 // softmax over the 64 keys, P3 = O^T += V^T P^T.
 // ---------------------------------------------------------------------------------------------
-template <int DW, bool EDGE>
-__global__ __launch_bounds__(256, DW == 64 && !EDGE ? 3 : 2) void attn_fwd_mfma_kernel(int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
+template <int DW, bool EDGE, int G, int WPG>
+__global__ __launch_bounds__(64 * G * WPG, DW == 64 && !EDGE && G == 1 ? 3 : 2) void attn_fwd_mfma_kernel(int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
                                                             bf16_t* __restrict__ ctx, float* __restrict__ lse) {
   constexpr int DH = row_width<DW>();  // row length in LDS
   constexpr int KS = DW / 16, DT = DW / 32, TB = TR * DH * 2;
   constexpr int N = 2 * KS;            // MFMAs per phase (P3: 2 halves x 2 k-steps x DT = 2 KS as well)
   constexpr int LEAD = N < 8 ? N : 8;  // fragments in flight
-  constexpr int NSEG = DH / 32;        // 1 KB load instructions per wave per tile
-  extern __shared__ __attribute__((aligned(16))) char smem[];  // 2 x [K tile | V tile]
-  const int n_qt = EDGE ? (S + 127) / 128 : S / 128;
+  constexpr int NSEG = DH / 8 / WPG;        // 1 KB load instructions per wave per tile
+  constexpr int LPS = (2 * NSEG + N - 1) / N;  // loads per slot of P1
+  extern __shared__ __attribute__((aligned(16))) char smem_all[];  // 2 x [K tile | V tile]
+  constexpr int RT = 32 * WPG, DIAG = WPG == 4 ? 2 : 1;  // rows of a workgroup, tiles that straddle its diagonal
+  const int n_qt = EDGE ? (S + RT - 1) / RT : S / RT;
   int pair, bh;
-  pair_of_tiles(n_qt, BH, pair, bh);
+  if (G == 1) pair_of_tiles(blockIdx.x, n_qt, BH, pair, bh);
+  else longest_first(blockIdx.x, BH, pair, bh);
   const int b = bh / H, h = bh % H;
   const int hw = EDGE ? dh : DW, nch = hw / 8;  // head width, in elements and in 16-byte chunks
   const int Hd = H * hw;
   const size_t ld = 3 * (size_t)Hd;
   const bf16_t* base = qkv + (size_t)b * S * ld + h * hw;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
+  const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
   const float scale = rsqrtf((float)hw);
   const float c = scale * LOG2E;
+  const int grp = G == 1 ? 0 : wave_all / WPG, wave = G == 1 ? wave_all : wave_all % WPG;
+  char* const smem = smem_all + grp * (4 * TB);
   const unsigned sm = lds_addr(smem);
-  if (EDGE) clear_lds(smem, 4 * TB);
+  if (EDGE) clear_lds(smem_all, G * 4 * TB);
 
-  for (int pass = 0; pass < 2; pass++) {
+  for (int pass = 0; pass < (G == 1 ? 2 : 1); pass++) {
     const int qt = pass == 0 ? n_qt - 1 - pair : pair;  // the long one first
     if (pass == 1 && qt == n_qt - 1 - pair) break;      // odd number of tiles: the middle one stands alone
-    const int q0w = qt * 128 + wave * 32, iq = q0w + (lane & 31);
+    const int q0w = qt * RT + wave * 32, iq = q0w + (lane & 31);
     bf16x8 qf[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ks++)
@@ -74,27 +79,28 @@ __global__ __launch_bounds__(256, DW == 64 && !EDGE ? 3 : 2) void attn_fwd_mfma_
                                                : *reinterpret_cast<const uint4*>(base + (size_t)iq * ld + ks * 16 + g * 8));
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) settle(qf[ks]);
-    float m = -INFINITY, l = 0.f;
+    // (G > 1: a group may not meet a key that some query sees for a while, or at all)
+    float m = G == 1 ? -INFINITY : -3.4028235e38f, l = 0.f;
     f32x16 oacc[DT];
 #pragma unroll
     for (int dt = 0; dt < DT; dt++)
 #pragma unroll
       for (int v = 0; v < 16; v++) oacc[dt][v] = 0.f;
 
-    const int n_kv = EDGE ? min(2 * (qt + 1), (S + TR - 1) / TR) : 2 * (qt + 1);
+    const int n_kv = G == 1 && !EDGE ? 2 * (qt + 1) : (min((qt + 1) * RT, S) + TR - 1) / TR;
     auto tile_load = [&](int j0, int buf, int i) {
       const unsigned st = sm + buf * 2 * TB;
-      if (i < NSEG) tile_dma_seg<DH, EDGE>(st, base + (size_t)j0 * ld + Hd, ld, wave, i, S - j0, nch);
-      else tile_dma_seg<DH, EDGE>(st + TB, base + (size_t)j0 * ld + 2 * Hd, ld, wave, i - NSEG, S - j0, nch);
+      if (i < NSEG) tile_dma_seg<DH, EDGE, WPG>(st, base + (size_t)j0 * ld + Hd, ld, wave, i, S - j0, nch);
+      else tile_dma_seg<DH, EDGE, WPG>(st + TB, base + (size_t)j0 * ld + 2 * Hd, ld, wave, i - NSEG, S - j0, nch);
     };
     bf16x8 fr[LEAD], fc[LEAD];
     // One 64-key tile.  MASK: the tile may reach past the wave's first query.
     auto tile = [&](auto mask_c, int t) {
       constexpr bool MASK = decltype(mask_c)::value;
-      const char* kt_ = smem + (t & 1) * 2 * TB;
+      const char* kt_ = smem + (t / G & 1) * 2 * TB;
       const char* vt_ = kt_ + TB;
       const int j0 = t * TR;
-      const int j0n = min(t + 1, n_kv - 1) * TR;  // past the end: the last tile again, into the buffer nobody reads
+      const int j0n = min(t + G, n_kv - 1) * TR;  // past the end: the last tile again, into the buffer nobody reads
       auto row_frag = [&](int i) { return frag_rows<DH>(kt_, (i % 2) * 32, i / 2, lane); };
       // P3 slot i: d-tile dt = i % DT (so that MFMAs on the same accumulator are DT slots apart),
       // then key half jt and k-step hh from i / DT
@@ -115,7 +121,9 @@ __global__ __launch_bounds__(256, DW == 64 && !EDGE ? 3 : 2) void attn_fwd_mfma_
         s[i % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % LEAD], qf[i / 2], s[i % 2], 0, 0, 0);
         if (i + LEAD < N) fr[i % LEAD] = row_frag(i + LEAD);
         else fc[i + LEAD - N] = col_frag(i + LEAD - N);
-        if (i < 2 * NSEG) tile_load(j0n, (t + 1) & 1, i);
+#pragma unroll
+        for (int n = i * LPS; n < (i + 1) * LPS; n++)
+          if (n < 2 * NSEG) tile_load(j0n, (t / G + 1) & 1, n);
         __builtin_amdgcn_sched_barrier(0);
       }
       __builtin_amdgcn_s_setprio(0);
@@ -141,7 +149,7 @@ __global__ __launch_bounds__(256, DW == 64 && !EDGE ? 3 : 2) void attn_fwd_mfma_
       // at most 2^MAX_LAG instead of 1; numerator, denominator and lse all use the same m, so
       // the result is the same softmax.
       // EDGE: m is in units of the scaled score.
-      const float mn = fmaxf(m, EDGE ? mx * scale : mx);  // finite: key 0 is visible to every query and comes in the first tile
+      const float mn = fmaxf(m, EDGE ? mx * scale : mx);  // finite (G = 1): key 0 is visible to every query and comes in the first tile
       const float octaves = EDGE ? LOG2E : c;
       if (__builtin_amdgcn_ballot_w64((mn - m) * octaves > MAX_LAG) != 0) {
         const float corr = __builtin_amdgcn_exp2f((m - mn) * octaves);
@@ -199,16 +207,45 @@ __global__ __launch_bounds__(256, DW == 64 && !EDGE ? 3 : 2) void attn_fwd_mfma_
     };
 
 #pragma unroll
-    for (int i = 0; i < 2 * NSEG; i++) tile_load(0, 0, i);
+    for (int i = 0; i < 2 * NSEG; i++) tile_load(min(grp, n_kv - 1) * TR, 0, i);
     lds_dma_wait();
     __syncthreads();
-    for (int t = 0; t < n_kv - 2; t++) tile(F_{}, t);
-    // the last two tiles (128 keys) straddle the diagonal of this workgroup's 128 queries
-    if (EDGE) {
-      for (int t = max(n_kv - 2, 0); t < n_kv; t++) tile(T_{}, t);
+    if (G == 1) {
+      for (int t = 0; t < n_kv - 2; t++) tile(F_{}, t);
+      // the last two tiles (128 keys) straddle the diagonal of this workgroup's 128 queries
+      if (EDGE) {
+        for (int t = max(n_kv - 2, 0); t < n_kv; t++) tile(T_{}, t);
+      } else {
+        tile(T_{}, n_kv - 2);
+        tile(T_{}, n_kv - 1);
+      }
     } else {
-      tile(T_{}, n_kv - 2);
-      tile(T_{}, n_kv - 1);
+      int t = grp;
+      for (; t < n_kv - DIAG; t += G) tile(F_{}, t);
+      for (; t < n_kv; t += G) tile(T_{}, t);
+      // every group meets as many barriers as the one with the most tiles
+      for (t = (n_kv + G - 1) / G - (n_kv - grp + G - 1) / G; t > 0; t--) __syncthreads();
+    }
+    if (G > 1) {
+      constexpr int U = DT * 4 + 1;
+      float* x = reinterpret_cast<float*>(smem_all);
+      if (grp) {
+        group_put<U>(x, wave_all - WPG, 0, oacc);
+        reinterpret_cast<float4*>(x)[((wave_all - WPG) * U + U - 1) * 64 + lane] = make_float4(m, l, 0.f, 0.f);
+      }
+      __syncthreads();
+      if (grp) return;
+      const float octaves = EDGE ? LOG2E : c;
+#pragma unroll
+      for (int o = 0; o < G - 1; o++) {
+        const int slot = o * WPG + wave;
+        const float4 ml = reinterpret_cast<const float4*>(x)[(slot * U + U - 1) * 64 + lane];
+        const float mn = fmaxf(m, ml.x);
+        const float a0 = __builtin_amdgcn_exp2f((m - mn) * octaves), a1 = __builtin_amdgcn_exp2f((ml.x - mn) * octaves);
+        l = fmaf(l, a0, ml.y * a1);
+        m = mn;
+        group_add<U>(x, slot, 0, oacc, a0, a1);
+      }
     }
 
     bool store = true;
@@ -245,39 +282,44 @@ __global__ __launch_bounds__(256, DW == 64 && !EDGE ? 3 : 2) void attn_fwd_mfma_
 // One barrier per 64-key tile.  Registers budgeted for two waves per SIMD, LDS for two workgroups
 // per CU (see above).
 // ---------------------------------------------------------------------------------------------
-template <int DW, bool EDGE>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
+template <int DW, bool EDGE, int G, int WPG>
+__device__ __forceinline__ void attn_bwd_dq_mfma_body(int block, int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
                                                                          const float* __restrict__ lse,
                                                                          const bf16_t* __restrict__ ctx,
                                                                          const bf16_t* __restrict__ dctx,
-                                                                         float* __restrict__ delta,
+                                                                         float* __restrict__ delta, bool have_delta,
                                                                          bf16_t* __restrict__ dqkv) {
   constexpr int DH = row_width<DW>();  // row length in LDS
   constexpr int KS = DW / 16, DT = DW / 32, TB = TR * DH * 2;
   constexpr int N1 = 2 * KS;   // score MFMAs per 32-key half: S and dP, KS each
   constexpr int N3 = 2 * DT;   // dQ MFMAs per half: two k-steps x DT
   constexpr int LEAD = N3;     // fragments in flight
-  constexpr int NSEG = DH / 32;
-  static_assert(2 * NSEG <= N1 && N1 % LEAD == 0, "slot plan");
-  extern __shared__ __attribute__((aligned(16))) char smem[];  // 2 x [K tile | V tile]
-  const int n_qt = EDGE ? (S + 127) / 128 : S / 128;
+  constexpr int NSEG = DH / 8 / WPG;
+  constexpr int LPS = (2 * NSEG + N1 - 1) / N1;  // loads per slot of P1
+  static_assert(N1 % LEAD == 0, "slot plan");
+  extern __shared__ __attribute__((aligned(16))) char smem_all[];  // 2 x [K tile | V tile]
+  constexpr int RT = 32 * WPG, DIAG = WPG == 4 ? 2 : 1;  // rows of a workgroup, tiles that straddle its diagonal
+  const int n_qt = EDGE ? (S + RT - 1) / RT : S / RT;
   int pair, bh;
-  pair_of_tiles(n_qt, BH, pair, bh);
+  if (G == 1) pair_of_tiles(block, n_qt, BH, pair, bh);
+  else longest_first(block, BH, pair, bh);
   const int b = bh / H, h = bh % H;
   const int hw = EDGE ? dh : DW, nch = hw / 8;  // head width, in elements and in 16-byte chunks
   const int Hd = H * hw;
   const size_t ld = 3 * (size_t)Hd;
   const bf16_t* base = qkv + (size_t)b * S * ld + h * hw;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
+  const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
   const float scale = rsqrtf((float)hw);
   const float c = scale * LOG2E;
+  const int grp = G == 1 ? 0 : wave_all / WPG, wave = G == 1 ? wave_all : wave_all % WPG;
+  char* const smem = smem_all + grp * (4 * TB);
   const unsigned sm = lds_addr(smem);
-  if (EDGE) clear_lds(smem, 4 * TB);
+  if (EDGE) clear_lds(smem_all, G * 4 * TB);
 
-  for (int pass = 0; pass < 2; pass++) {
+  for (int pass = 0; pass < (G == 1 ? 2 : 1); pass++) {
     const int qt = pass == 0 ? n_qt - 1 - pair : pair;
     if (pass == 1 && qt == n_qt - 1 - pair) break;
-    const int q0w = qt * 128 + wave * 32, iq = q0w + (lane & 31);
+    const int q0w = qt * RT + wave * 32, iq = q0w + (lane & 31);
     bf16x8 qf[KS], dof[KS];
     const bf16_t* dorow = dctx + ((size_t)b * S + iq) * Hd + h * hw;
 #pragma unroll
@@ -290,16 +332,20 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
     }
     float li = EDGE ? (iq >= S ? 0.f : lse[((size_t)b * H + h) * S + iq]) : lse[((size_t)b * H + h) * S + iq] * LOG2E;
     float di = 0.f;  // delta_i = sum_d dO[i, d] O[i, d], half of the row per lane
-    const bf16_t* orow = ctx + ((size_t)b * S + iq) * Hd + h * hw;
+    if (have_delta) {
+      if (!EDGE || iq < S) di = delta[((size_t)b * H + h) * S + iq];
+    } else {
+      const bf16_t* orow = ctx + ((size_t)b * S + iq) * Hd + h * hw;
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      const bf16x8 o = __builtin_bit_cast(bf16x8, EDGE ? edge_load16(orow + ks * 16 + g * 8, iq < S && ks * 2 + g < nch)
-                                                       : *reinterpret_cast<const uint4*>(orow + ks * 16 + g * 8));
+      for (int ks = 0; ks < KS; ks++) {
+        const bf16x8 o = __builtin_bit_cast(bf16x8, EDGE ? edge_load16(orow + ks * 16 + g * 8, iq < S && ks * 2 + g < nch)
+                                                         : *reinterpret_cast<const uint4*>(orow + ks * 16 + g * 8));
 #pragma unroll
-      for (int e = 0; e < 8; e++) di = fmaf((float)o[e], (float)dof[ks][e], di);
+        for (int e = 0; e < 8; e++) di = fmaf((float)o[e], (float)dof[ks][e], di);
+      }
+      di = sum32(di);
+      if (g == 0 && grp == 0 && (!EDGE || iq < S)) delta[((size_t)b * H + h) * S + iq] = di;
     }
-    di = sum32(di);
-    if (g == 0 && (!EDGE || iq < S)) delta[((size_t)b * H + h) * S + iq] = di;
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) { settle(qf[ks]); settle(dof[ks]); }
     settle(li); settle(di);
@@ -309,20 +355,20 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
 #pragma unroll
       for (int v = 0; v < 16; v++) dq[dt][v] = 0.f;
 
-    const int n_kv = EDGE ? min(2 * (qt + 1), (S + TR - 1) / TR) : 2 * (qt + 1);
+    const int n_kv = G == 1 && !EDGE ? 2 * (qt + 1) : (min((qt + 1) * RT, S) + TR - 1) / TR;
     auto tile_load = [&](int j0, int buf, int i) {
       const unsigned st = sm + buf * 2 * TB;
-      if (i < NSEG) tile_dma_seg<DH, EDGE>(st, base + (size_t)j0 * ld + Hd, ld, wave, i, S - j0, nch);
-      else tile_dma_seg<DH, EDGE>(st + TB, base + (size_t)j0 * ld + 2 * Hd, ld, wave, i - NSEG, S - j0, nch);
+      if (i < NSEG) tile_dma_seg<DH, EDGE, WPG>(st, base + (size_t)j0 * ld + Hd, ld, wave, i, S - j0, nch);
+      else tile_dma_seg<DH, EDGE, WPG>(st + TB, base + (size_t)j0 * ld + 2 * Hd, ld, wave, i - NSEG, S - j0, nch);
     };
     bf16x8 f[LEAD];  // one ring for both kinds of fragment: slot i reloads the register it has just used
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     // One 64-key tile, a 32-key half at a time.  MASK: the tile may reach past the wave's first query.
     auto tile = [&](auto mask_c, int t) {
       constexpr bool MASK = decltype(mask_c)::value;
-      const char* kt_ = smem + (t & 1) * 2 * TB;
+      const char* kt_ = smem + (t / G & 1) * 2 * TB;
       const char* vt_ = kt_ + TB;
-      const int j0n = min(t + 1, n_kv - 1) * TR;  // past the end: the last tile again, into the buffer nobody reads
+      const int j0n = min(t + G, n_kv - 1) * TR;  // past the end: the last tile again, into the buffer nobody reads
       // P1 slot i of half jt: S (K rows x Q) or dP (V rows x dO) by bit 0, k-step i / 2
       auto row_frag = [&](int jt, int i) { return frag_rows<DH>((i & 1) ? vt_ : kt_, jt * 32, i / 2, lane); };
       // P3 slot i of half jt: d-tile i % DT, k-step i / DT
@@ -341,7 +387,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
           else sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], qf[ks], i < 2 ? zero : sc, 0, 0, 0);
           if (i + LEAD < N1) f[i % LEAD] = row_frag(jt, i + LEAD);
           else f[i % LEAD] = col_frag(jt, i + LEAD - N1);  // (N1 is a multiple of LEAD)
-          if (jt == 0 && i < 2 * NSEG) tile_load(j0n, (t + 1) & 1, i);
+#pragma unroll
+          for (int n = i * LPS; n < (i + 1) * LPS; n++)
+            if (jt == 0 && n < 2 * NSEG) tile_load(j0n, (t / G + 1) & 1, n);
           __builtin_amdgcn_sched_barrier(0);
         }
         bf16x8 db[2], dc[2][3];  // dS; EDGE: in three terms, the second eight keys' formed between the first one's MFMAs
@@ -384,16 +432,33 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
     };
 
 #pragma unroll
-    for (int i = 0; i < 2 * NSEG; i++) tile_load(0, 0, i);
+    for (int i = 0; i < 2 * NSEG; i++) tile_load(min(grp, n_kv - 1) * TR, 0, i);
     lds_dma_wait();
     __syncthreads();
-    for (int t = 0; t < n_kv - 2; t++) tile(F_{}, t);
-    // the last two tiles (128 keys) straddle the diagonal of this workgroup's 128 queries
-    if (EDGE) {
-      for (int t = max(n_kv - 2, 0); t < n_kv; t++) tile(T_{}, t);
+    if (G == 1) {
+      for (int t = 0; t < n_kv - 2; t++) tile(F_{}, t);
+      // the last two tiles (128 keys) straddle the diagonal of this workgroup's 128 queries
+      if (EDGE) {
+        for (int t = max(n_kv - 2, 0); t < n_kv; t++) tile(T_{}, t);
+      } else {
+        tile(T_{}, n_kv - 2);
+        tile(T_{}, n_kv - 1);
+      }
     } else {
-      tile(T_{}, n_kv - 2);
-      tile(T_{}, n_kv - 1);
+      int t = grp;
+      for (; t < n_kv - DIAG; t += G) tile(F_{}, t);
+      for (; t < n_kv; t += G) tile(T_{}, t);
+      // every group meets as many barriers as the one with the most tiles
+      for (t = (n_kv + G - 1) / G - (n_kv - grp + G - 1) / G; t > 0; t--) __syncthreads();
+    }
+    if (G > 1) {
+      constexpr int U = DT * 4;
+      float* x = reinterpret_cast<float*>(smem_all);
+      if (grp) group_put<U>(x, wave_all - WPG, 0, dq);
+      __syncthreads();
+      if (grp) return;
+#pragma unroll
+      for (int o = 0; o < G - 1; o++) group_add<U>(x, o * WPG + wave, 0, dq);
     }
 
     bool store = true;
@@ -418,14 +483,22 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(int S, int H, 
   }  // pass
 }
 
+template <int DW, bool EDGE, int G, int WPG>
+__global__ __launch_bounds__(64 * G * WPG, 2) void attn_bwd_dq_mfma_kernel(int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
+                                                                         const float* __restrict__ lse, const bf16_t* __restrict__ ctx,
+                                                                         const bf16_t* __restrict__ dctx, float* __restrict__ delta,
+                                                                         bf16_t* __restrict__ dqkv) {
+  attn_bwd_dq_mfma_body<DW, EDGE, G, WPG>(blockIdx.x, S, H, BH, dh, qkv, lse, ctx, dctx, delta, false, dqkv);
+}
+
 // ---------------------------------------------------------------------------------------------
 // dK, dV without the skew (used for DH = 64, where the kernel then fits the register budget of
 // two waves per SIMD and several workgroups share a CU).  The same arithmetic as the kernel above,
 // a 32-query half at a time: P1 = S and dP (2 KS MFMAs), V = P and dS packed to bf16, P3 = dV^T and
 // dK^T (2 KS MFMAs); two LDS buffers, one barrier per 64-query tile.
 // ---------------------------------------------------------------------------------------------
-template <int DW, bool EDGE>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
+template <int DW, bool EDGE, int G, int WPG>
+__device__ __forceinline__ void attn_bwd_dkv_phased_mfma_body(int block, int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
                                                                           const float* __restrict__ lse,
                                                                           const float* __restrict__ delta,
                                                                           const bf16_t* __restrict__ dctx,
@@ -435,12 +508,15 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
   constexpr int LD_OFF = 2 * TB, STAGE = 2 * TB + 4 * 256;  // Q tile | dO tile | lse and delta as above
   constexpr int N = 2 * KS;                   // MFMAs per phase and half
   constexpr int LEAD = N < 8 ? N : 8;         // fragments in flight
-  constexpr int NSEG = DH / 32;
-  static_assert(N % LEAD == 0 && 2 * NSEG + 1 <= N, "slot plan");
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int n_kt = EDGE ? (S + 127) / 128 : S / 128;
+  constexpr int NSEG = DH / 8 / WPG;
+  static_assert(N % LEAD == 0 && N > 0, "slot plan");
+  constexpr int LOADS = 2 * NSEG + 4 / WPG, LPS = (LOADS + N - 1) / N;  // per wave and tile, per slot of P1
+  extern __shared__ __attribute__((aligned(16))) char smem_all[];
+  constexpr int RT = 32 * WPG;  // keys of a workgroup
+  const int n_kt = EDGE ? (S + RT - 1) / RT : S / RT;
   int pair, bh;
-  pair_of_tiles(n_kt, BH, pair, bh);
+  if (G == 1) pair_of_tiles(block, n_kt, BH, pair, bh);
+  else longest_first(block, BH, pair, bh);
   const int b = bh / H, h = bh % H;
   const int hw = EDGE ? dh : DW, nch = hw / 8;  // head width, in elements and in 16-byte chunks
   const int Hd = H * hw;
@@ -450,16 +526,18 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
   const float* lrow = lse + ((size_t)b * H + h) * S;
   const float* drow = delta + ((size_t)b * H + h) * S;
   const int lane = threadIdx.x & 63, g = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const float scale = rsqrtf((float)hw);
   const float c = scale * LOG2E;
+  const int grp = G == 1 ? 0 : wave_all / WPG, wave = G == 1 ? wave_all : wave_all % WPG;
+  char* const smem = smem_all + grp * (2 * STAGE);
   const unsigned sm = lds_addr(smem);
-  if (EDGE) clear_lds(smem, 2 * STAGE);
+  if (EDGE) clear_lds(smem_all, G * 2 * STAGE);
 
-  for (int pass = 0; pass < 2; pass++) {
+  for (int pass = 0; pass < (G == 1 ? 2 : 1); pass++) {
     const int kt = pass == 0 ? pair : n_kt - 1 - pair;
     if (pass == 1 && kt == pair) break;  // odd number of key tiles: the middle one stands alone
-    const int j0w = kt * 128 + wave * 32, jk = j0w + (lane & 31);
+    const int j0w = kt * RT + wave * 32, jk = j0w + (lane & 31);
     bf16x8 kf[KS], vf[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
@@ -476,21 +554,24 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
 #pragma unroll
       for (int v = 0; v < 16; v++) dk[dt][v] = dv[dt][v] = 0.f;
 
-    const int i_first = kt * 128;
+    const int i_first = kt * RT / TR * TR;
     const int n_q = EDGE ? (S - i_first + TR - 1) / TR : (S - i_first) / TR;
     auto tile_load = [&](int i0, int buf, int i) {
       const unsigned st = sm + buf * STAGE;
-      if (i < NSEG) tile_dma_seg<DH, EDGE>(st, base + (size_t)i0 * ld, ld, wave, i, S - i0, nch);
-      else if (i < 2 * NSEG) tile_dma_seg<DH, EDGE>(st + TB, dob + (size_t)i0 * Hd, (size_t)Hd, wave, i - NSEG, S - i0, nch);
-      else if (!EDGE || i0 + wave * 16 + (lane & 15) < S) lds_dma4(((lane & 16) ? drow : lrow) + i0 + wave * 16 + (lane & 15), st + LD_OFF + wave * 256);
+      if (i < NSEG) tile_dma_seg<DH, EDGE, WPG>(st, base + (size_t)i0 * ld, ld, wave, i, S - i0, nch);
+      else if (i < 2 * NSEG) tile_dma_seg<DH, EDGE, WPG>(st + TB, dob + (size_t)i0 * Hd, (size_t)Hd, wave, i - NSEG, S - i0, nch);
+      else {
+        const int rb = wave * (4 / WPG) + i - 2 * NSEG;  // sixteen rows
+        if (!EDGE || i0 + rb * 16 + (lane & 15) < S) lds_dma4(((lane & 16) ? drow : lrow) + i0 + rb * 16 + (lane & 15), st + LD_OFF + rb * 256);
+      }
     };
     bf16x8 f[LEAD];  // one ring for both kinds of fragment: slot i reloads the register it has just used
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     // One 64-query tile, a 32-query half at a time.  MASK: the tile may reach back before the wave's last key.
     auto tile = [&](auto mask_c, int t) {
       constexpr bool MASK = decltype(mask_c)::value;
-      const char* st = smem + (t & 1) * STAGE;
-      const int i0n = i_first + min(t + 1, n_q - 1) * TR;  // past the end: the last tile again, into the buffer nobody reads
+      const char* st = smem + (t / G & 1) * STAGE;
+      const int i0n = i_first + min(t + G, n_q - 1) * TR;  // past the end: the last tile again, into the buffer nobody reads
       // P1 slot i of half it: S (Q rows x K) or dP (dO rows x V) by bit 0, k-step i / 2
       auto row_frag = [&](int it, int i) { return frag_rows<DH>(i % 2 ? st + TB : st, it * 32, i / 2, lane); };
       // P3 slot i: dV (dO^T) or dK (Q^T) by bit 0, d-tile (i / 2) % DT, k-step i / (2 DT); EDGE: all of dV, then dK, whose factors are
@@ -518,7 +599,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
           else dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % LEAD], vf[i / 2], i < 2 ? zero : dp, 0, 0, 0);
           if (i + LEAD < N) f[i % LEAD] = row_frag(it, i + LEAD);
           else f[i % LEAD] = col_frag(it, i + LEAD - N);
-          if (it == 0 && i <= 2 * NSEG) tile_load(i0n, (t + 1) & 1, i);
+#pragma unroll
+          for (int n = i * LPS; n < (i + 1) * LPS; n++)
+            if (it == 0 && n < LOADS) tile_load(i0n, (t / G + 1) & 1, n);
           __builtin_amdgcn_sched_barrier(0);
         }
         bf16x8 pb[2], db[2], pc[2][3];  // P and dS; EDGE: eight queries' P or dS in three terms, and the next eight's
@@ -580,17 +663,38 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
     };
 
 #pragma unroll
-    for (int i = 0; i <= 2 * NSEG; i++) tile_load(i_first, 0, i);
+    for (int i = 0; i < LOADS; i++) tile_load(i_first + min(grp, n_q - 1) * TR, 0, i);
     lds_dma_wait();
     __syncthreads();
     // The first two tiles (128 queries) straddle the diagonal of this workgroup's 128 keys, and under EDGE the last may reach
     // past S; there every tile takes the masks (a second copy of the tile costs 63 spilled registers).
     if (EDGE) {
-      for (int t = 0; t < n_q; t++) tile(T_{}, t);
-    } else {
+      for (int t = grp; t < n_q; t += G) tile(T_{}, t);
+    } else if (G == 1) {
       tile(T_{}, 0);
       tile(T_{}, 1);
       for (int t = 2; t < n_q; t++) tile(F_{}, t);
+    } else {
+      static_assert(G == 1 || WPG < 4, "one tile on the diagonal");
+      if (grp == 0) tile(T_{}, 0);
+      for (int t = grp ? grp : G; t < n_q; t += G) tile(F_{}, t);
+    }
+    if (G > 1) {
+      // every group meets as many barriers as the one with the most tiles
+      for (int t = (n_q + G - 1) / G - (n_q - grp + G - 1) / G; t > 0; t--) __syncthreads();
+      constexpr int U = 2 * DT * 4;
+      float* x = reinterpret_cast<float*>(smem_all);
+      if (grp) {
+        group_put<U>(x, wave_all - WPG, 0, dk);
+        group_put<U>(x, wave_all - WPG, U / 2, dv);
+      }
+      __syncthreads();
+      if (grp) return;
+#pragma unroll
+      for (int o = 0; o < G - 1; o++) {
+        group_add<U>(x, o * WPG + wave, 0, dk);
+        group_add<U>(x, o * WPG + wave, U / 2, dv);
+      }
     }
 
     bool store = true;
@@ -619,6 +723,29 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_phased_mfma_kernel(int S,
   }  // pass
 }
 
+template <int DW, bool EDGE, int G, int WPG>
+__global__ __launch_bounds__(64 * G * WPG, 2) void attn_bwd_dkv_phased_mfma_kernel(int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
+                                                                          const float* __restrict__ lse, const float* __restrict__ delta,
+                                                                          const bf16_t* __restrict__ dctx, bf16_t* __restrict__ dqkv) {
+  attn_bwd_dkv_phased_mfma_body<DW, EDGE, G, WPG>(blockIdx.x, S, H, BH, dh, qkv, lse, delta, dctx, dqkv);
+}
+
+// dK, dV and dQ in one launch, delta given: the first `first` workgroups are the dK/dV kernel's, which are the longer ones.  Neither kernel
+// alone fills the chip where this form is used.
+template <int DW, bool EDGE, int G, int WPG>
+__global__ __launch_bounds__(64 * G * WPG, 2) void attn_bwd_both_mfma_kernel(int S, int H, int BH, int dh, const bf16_t* __restrict__ qkv,
+                                                                              const float* __restrict__ lse, float* __restrict__ delta,
+                                                                              const bf16_t* __restrict__ dctx, bf16_t* __restrict__ dqkv, int first) {
+  const int block = blockIdx.x;
+  if (block >= first) {
+    attn_bwd_dq_mfma_body<DW, EDGE, G, WPG>(block - first, S, H, BH, dh, qkv, lse, nullptr, dctx, delta, true, dqkv);
+  } else if constexpr (DW == 64) {
+    attn_bwd_dkv_phased_mfma_body<DW, EDGE, G, WPG>(block, S, H, BH, dh, qkv, lse, delta, dctx, dqkv);
+  } else {
+    attn_bwd_dkv16_mfma_body<DW, EDGE, G, WPG>(block, S, H, BH, dh, qkv, lse, delta, dctx, dqkv);
+  }
+}
+
 bool attn_mfma_supported(int dtype, int B, int S, int H, int dh) {
   (void)B; (void)H;
   return dtype == FAX_BF16 && (dh == 64 || dh == 128) && S > 0 && S % 128 == 0;
@@ -642,91 +769,107 @@ static int set_lds(K kern, size_t bytes) {
 
 static inline unsigned grid_of(int B, int S, int H) { return (unsigned)((((S + 127) / 128 + 1) / 2) * B * H); }
 
-template <int DW, bool EDGE>
+// Which form: groups and waves to a group.  The more groups, the shorter a workgroup's chain of tiles, until there are more
+// workgroups than CUs to take them: what a workgroup loads is then shared by fewer rows.  The lines lie where the forms cross, us, forward and
+// backward (heads x S x head width; 1x4 is the form of a full chip, a pair of 128-row tiles to a workgroup):
+//   up to 64 wide   2 x 2048 x 64    1x4 29 + 78, 2x2 15 + 39, 4x1 11 + 29      8 x 256 x 64     1x4 11 + 28, 2x2 9 + 13, 4x1 9 + 12
+//                   32 x 777 x 64    1x4 30 + 96, 2x2 17 + 56, 4x1 31 + 85      64 x 1024 x 64   1x4 21 + 57, 2x2 19 + 56
+//                   128 x 1024 x 64  1x4 31 + 97, 2x2 37 + 106
+//   wider           5 x 2048 x 128   1x4 40 + 95, 2x2 23 + 58, 2x4 30 + 75      12 x 2048 x 128  1x4 41 + 98, 2x2 24 + 80, 2x4 31 + 78
+//                   45 x 1000 x 80   1x4 39 + 105, 2x2 44 + 138, 2x4 32 + 98    32 x 2048 x 128  1x4 45 + 142, 2x4 44 + 150
+// (2x2 and 4x1 at 64 wide take 64 and 128 KB of LDS; 2x2 and 2x4 above it 128.)
+struct AttnForm { int groups, waves; };
+static AttnForm attn_form(int B, int S, int H, int dh) {
+  const long long heads = (long long)B * H, t32 = (S + 31) / 32 * heads, t64 = (S + 63) / 64 * heads, t128 = (S + 127) / 128 * heads;
+  if (dh <= 64) return t32 <= 256 ? AttnForm{4, 1} : t64 <= 1024 ? AttnForm{2, 2} : AttnForm{1, 4};
+  return t64 <= 384 ? AttnForm{2, 2} : t128 <= 400 ? AttnForm{2, 4} : AttnForm{1, 4};
+}
+bool attn_split_form(int B, int S, int H, int dh) { return attn_form(B, S, H, dh).groups > 1; }
+
+template <int DW, bool EDGE, int G, int WPG>
 static int fwd_t(int B, int S, int H, int dh, const bf16_t* qkv, bf16_t* ctx, float* lse, hipStream_t s) {
-  constexpr size_t lds = 2 * (2 * (size_t)TR * row_width<DW>() * 2);  // two stages of K tile | V tile
-  FAX_TRY(set_lds(attn_fwd_mfma_kernel<DW, EDGE>, lds));
-  hipLaunchKernelGGL((attn_fwd_mfma_kernel<DW, EDGE>), dim3(grid_of(B, S, H)), dim3(256), lds, s, S, H, B * H, dh, qkv, ctx, lse);
+  constexpr size_t lds = G * 2 * (2 * (size_t)TR * row_width<DW>() * 2);  // per group two stages of K tile | V tile
+  const dim3 grid(G == 1 ? grid_of(B, S, H) : (S + 32 * WPG - 1) / (32 * WPG) * B * H);
+  FAX_TRY(set_lds(attn_fwd_mfma_kernel<DW, EDGE, G, WPG>, lds));
+  hipLaunchKernelGGL((attn_fwd_mfma_kernel<DW, EDGE, G, WPG>), grid, dim3(64 * G * WPG), lds, s, S, H, B * H, dh, qkv, ctx, lse);
   FAX_LAUNCH_CHECK("attn_fwd_mfma");
   return FAX_OK;
+}
+
+// Whole tiles or masked edges, head width as computed, groups and their waves.
+template <typename F>
+static int by_form(int B, int S, int H, int dh, F f) {
+  const AttnForm form = attn_form(B, S, H, dh);
+  auto groups = [&](auto dw, auto edge) -> int {
+    if (form.groups == 1) return f(dw, edge, I<1>{}, I<4>{});
+    if constexpr (decltype(dw)::value == 64) {
+      if (form.groups == 4) return f(dw, edge, I<4>{}, I<1>{});
+    } else {
+      if (form.waves == 4) return f(dw, edge, I<2>{}, I<4>{});
+    }
+    return f(dw, edge, I<2>{}, I<2>{});
+  };
+  if (attn_mfma_supported(FAX_BF16, B, S, H, dh)) return dh == 64 ? groups(I<64>{}, F_{}) : groups(I<128>{}, F_{});
+  return dh <= 64 ? groups(I<64>{}, T_{}) : dh <= 96 ? groups(I<96>{}, T_{}) : groups(I<128>{}, T_{});
 }
 
 int attn_fwd_mfma(int B, int S, int H, int dh, const void* qkv, void* ctx, float* lse, hipStream_t s) {
   const bf16_t* q = (const bf16_t*)qkv;
   bf16_t* c = (bf16_t*)ctx;
-  if (!attn_mfma_supported(FAX_BF16, B, S, H, dh)) {
-    if (dh <= 64) return fwd_t<64, true>(B, S, H, dh, q, c, lse, s);
-    if (dh <= 96) return fwd_t<96, true>(B, S, H, dh, q, c, lse, s);
-    return fwd_t<128, true>(B, S, H, dh, q, c, lse, s);
-  }
-  if (dh == 64) return fwd_t<64, false>(B, S, H, dh, q, c, lse, s);
-  return fwd_t<128, false>(B, S, H, dh, q, c, lse, s);
+  return by_form(B, S, H, dh, [&](auto dw, auto edge, auto g, auto wpg) {
+    return fwd_t<decltype(dw)::value, decltype(edge)::value, decltype(g)::value, decltype(wpg)::value>(B, S, H, dh, q, c, lse, s);
+  });
 }
 
-template <int DW, bool EDGE>
+template <int DW, bool EDGE, int G, int WPG>
 static int bwd_t(int B, int S, int H, int dh, const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx,
-                 bf16_t* dqkv, float* delta, hipStream_t s, const AttnBwdSplit* split) {
+                 bf16_t* dqkv, float* delta, hipStream_t s) {
   constexpr int DH = row_width<DW>();
-  constexpr size_t lds_q = 2 * (2 * (size_t)TR * DH * 2);  // two stages of K tile | V tile
-  const dim3 grid(grid_of(B, S, H));
-  FAX_TRY(set_lds(attn_bwd_dq_mfma_kernel<DW, EDGE>, lds_q));
-  auto dkv = [&](hipStream_t st) -> int {
+  constexpr size_t lds_q = G * 2 * (2 * (size_t)TR * DH * 2);  // per group two stages of K tile | V tile
+  const dim3 grid(G == 1 ? grid_of(B, S, H) : (S + 32 * WPG - 1) / (32 * WPG) * B * H);
+  auto dkv = [&]() -> int {
     if constexpr (DW == 64) {
-      constexpr size_t lds_kv = 2 * (2 * (size_t)TR * DH * 2 + 4 * 256);  // two stages of Q tile | dO tile | lse, delta
-      FAX_TRY(set_lds(attn_bwd_dkv_phased_mfma_kernel<DW, EDGE>, lds_kv));
-      hipLaunchKernelGGL((attn_bwd_dkv_phased_mfma_kernel<DW, EDGE>), grid, dim3(256), lds_kv, st, S, H, B * H, dh, qkv, lse,
+      constexpr size_t lds_kv = G * 2 * (2 * (size_t)TR * DH * 2 + 4 * 256);  // per group two stages of Q tile | dO tile | lse, delta
+      FAX_TRY(set_lds(attn_bwd_dkv_phased_mfma_kernel<DW, EDGE, G, WPG>, lds_kv));
+      hipLaunchKernelGGL((attn_bwd_dkv_phased_mfma_kernel<DW, EDGE, G, WPG>), grid, dim3(64 * G * WPG), lds_kv, s, S, H, B * H, dh, qkv, lse,
                          delta, dctx, dqkv);
     } else {
-      FAX_TRY(attn_bwd_dkv16_mfma(B, S, H, dh, EDGE, qkv, lse, delta, dctx, dqkv, st));
+      FAX_TRY(attn_bwd_dkv16_mfma(B, S, H, dh, EDGE, G, WPG, qkv, lse, delta, dctx, dqkv, s));
     }
     return FAX_OK;
   };
-  // Few workgroups (a tensor-parallel share at batch 1: 40 to 128 of them on 256 CUs): the dQ and the
-  // dK/dV kernel fit on the chip side by side.  What ties them together is delta, which the dQ
-  // kernel produces as it goes; a small kernel of its own computes it first, the dQ kernel writes
-  // its copy to scratch, and with a second stream the two kernels run at the same time.  Whether
-  // this form is used depends on the shape only, so that one or two streams give the same bits.
-  if (split && split->delta_scratch && attn_bwd_side_by_side(B, S, H)) {
-    FAX_TRY(attn_delta(FAX_BF16, B, S, H, dh, ctx, dctx, delta, s));
-    const bool two = split->side && split->fork && split->join;
-    if (two) {
-      FAX_HIP(hipEventRecord(split->fork, s));
-      FAX_HIP(hipStreamWaitEvent(split->side, split->fork, 0));
-      FAX_TRY(dkv(split->side));
-      FAX_HIP(hipEventRecord(split->join, split->side));
+  // Up to two rounds of workgroups in all: the two kernels run side by side, as one launch.  What ties them together is delta, which
+  // the dQ kernel produces as it goes; a small kernel of its own computes it first, which costs 2.5 us: 32 heads of 777 x 64
+  // 57 -> 45 us, 5 of 2048 x 128 57 -> 48, 2 of 2048 x 64 29 -> 19.5; 64 of 512 x 64, just beyond the line, 24.5 and 25.8.
+  if constexpr (G > 1) {
+    constexpr size_t lds = G * 2 * (2 * (size_t)TR * DH * 2 + 4 * 256);
+    constexpr int KT = DW == 64 ? 32 * WPG : 16 * WPG;  // keys of a workgroup
+    const unsigned first = (S + KT - 1) / KT * B * H;
+    if (first + grid.x < 2 * 256 * (163840 / lds)) {
+      FAX_TRY(attn_delta(FAX_BF16, B, S, H, dh, ctx, dctx, delta, s));
+      FAX_TRY(set_lds(attn_bwd_both_mfma_kernel<DW, EDGE, G, WPG>, lds));
+      hipLaunchKernelGGL((attn_bwd_both_mfma_kernel<DW, EDGE, G, WPG>), dim3(first + grid.x), dim3(64 * G * WPG), lds, s, S, H, B * H, dh,
+                         qkv, lse, delta, dctx, dqkv, (int)first);
+      FAX_LAUNCH_CHECK("attn_bwd_mfma");
+      return FAX_OK;
     }
-    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<DW, EDGE>), grid, dim3(256), lds_q, s, S, H, B * H, dh, qkv, lse, ctx, dctx,
-                       split->delta_scratch, dqkv);
-    if (two) FAX_HIP(hipStreamWaitEvent(s, split->join, 0));
-    else FAX_TRY(dkv(s));
-    FAX_LAUNCH_CHECK("attn_bwd_mfma");
-    return FAX_OK;
   }
   // dQ first: it also produces delta, which the dK/dV kernel reads
-  hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<DW, EDGE>), grid, dim3(256), lds_q, s, S, H, B * H, dh, qkv, lse, ctx, dctx, delta,
+  FAX_TRY(set_lds(attn_bwd_dq_mfma_kernel<DW, EDGE, G, WPG>, lds_q));
+  hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<DW, EDGE, G, WPG>), grid, dim3(64 * G * WPG), lds_q, s, S, H, B * H, dh, qkv, lse, ctx, dctx, delta,
                      dqkv);
-  FAX_TRY(dkv(s));
+  FAX_TRY(dkv());
   FAX_LAUNCH_CHECK("attn_bwd_mfma");
   return FAX_OK;
 }
 
-// dK/dV runs one workgroup per CU, dQ two: side by side they need 1.5 CUs per pair of row tiles.
-bool attn_bwd_side_by_side(int B, int S, int H) {
-  const long long n = (long long)(((S + 127) / 128 + 1) / 2) * B * H;
-  return 3 * n <= 2 * 256;
-}
-
 int attn_bwd_mfma(int B, int S, int H, int dh, const void* qkv, const void* ctx, const float* lse, const void* dctx,
-                  void* dqkv, float* delta, hipStream_t s, const AttnBwdSplit* split) {
+                  void* dqkv, float* delta, hipStream_t s) {
   const bf16_t *q = (const bf16_t*)qkv, *c = (const bf16_t*)ctx, *dc = (const bf16_t*)dctx;
   bf16_t* dq = (bf16_t*)dqkv;
-  if (!attn_mfma_supported(FAX_BF16, B, S, H, dh)) {
-    if (dh <= 64) return bwd_t<64, true>(B, S, H, dh, q, c, lse, dc, dq, delta, s, split);
-    if (dh <= 96) return bwd_t<96, true>(B, S, H, dh, q, c, lse, dc, dq, delta, s, split);
-    return bwd_t<128, true>(B, S, H, dh, q, c, lse, dc, dq, delta, s, split);
-  }
-  if (dh == 64) return bwd_t<64, false>(B, S, H, dh, q, c, lse, dc, dq, delta, s, split);
-  return bwd_t<128, false>(B, S, H, dh, q, c, lse, dc, dq, delta, s, split);
+  return by_form(B, S, H, dh, [&](auto dw, auto edge, auto g, auto wpg) {
+    return bwd_t<decltype(dw)::value, decltype(edge)::value, decltype(g)::value, decltype(wpg)::value>(B, S, H, dh, q, c, lse, dc, dq, delta, s);
+  });
 }
 
 }  // namespace fax
