@@ -334,26 +334,36 @@ static int side_stream(SideStream** out) {
   return FAX_OK;
 }
 
-// When every product of the backward pass is a whole number of rounds of one workgroup per CU
-// (the 4096-wide block: 256 to 2048 tiles each), the second stream has nothing to fill and the
-// kernels would only take turns: everything then stays on the caller's stream.  Likewise when the products are so short
-// that the host cannot keep up: the ten events and waits of the second stream cost it some 85 us a call, on top of the 40 of
+// Products so short that the host cannot keep up with a second stream: its events and waits cost some 85 us a call, on top of the 40 of
 // the launches (fp32 block of 128 tokens x 128: 161 us with the second stream, 95 without; bf16, 512 tokens x 256: 192
 // and 165; where the products' estimate is 150 us, 3108 tokens x 512, it gains 5 %, at 420 us, 2048 x 5120 shares, 5 %).
-static bool use_side_stream(const FaxBlockDims& d) {
-  if (d.flags & FAX_FLAG_SINGLE_STREAM) return false;
-  Sizes z(d);
-  const int T = (int)z.T, D = d.D, Hd = (int)z.Hd, F = d.F;
-  const int shapes[8][4] = {{F, D, T, 1}, {D, F, T, 1}, {Hd, D, T, 1}, {D, 3 * Hd, T, 1},
-                            {T, F, D, 0}, {T, D, F, 0}, {T, Hd, D, 0}, {T, D, 3 * Hd, 0}};
-  constexpr long long kCUs = 256;
+struct BwdProducts {
+  int p[8][4];  // M, N, K, whether a weight gradient
+  explicit BwdProducts(const FaxBlockDims& d) {
+    const Sizes z(d);
+    const int T = (int)z.T, D = d.D, Hd = (int)z.Hd, F = d.F;
+    const int all[8][4] = {{F, D, T, 1}, {D, F, T, 1}, {Hd, D, T, 1}, {D, 3 * Hd, T, 1},
+                           {T, F, D, 0}, {T, D, F, 0}, {T, Hd, D, 0}, {T, D, 3 * Hd, 0}};
+    memcpy(p, all, sizeof(p));
+  }
+};
+static bool short_pass(const FaxBlockDims& d) {
+  const BwdProducts all(d);
   double us = 0.0;
-  for (const auto& g : shapes)
+  for (const auto& g : all.p)
     us += d.dtype == FAX_BF16 ? gemm_time_estimate_us(dense_product(FAX_BF16, g[3], !g[3], g[0], g[1], g[2], g[3]))
                               : 5.0 + 2.0 * g[0] * g[1] * g[2] / 90.0e6;
-  if (us < 110.0) return false;
+  return us < 110.0;
+}
+// When every product of the backward pass is a whole number of rounds of one workgroup per CU
+// (the 4096-wide block: 256 to 2048 tiles each), the second stream has nothing to fill and the
+// kernels would only take turns: everything then stays on the caller's stream.
+static bool use_side_stream(const FaxBlockDims& d) {
+  if ((d.flags & FAX_FLAG_SINGLE_STREAM) || short_pass(d)) return false;
   if (d.dtype != FAX_BF16) return true;
-  for (const auto& g : shapes) {
+  constexpr long long kCUs = 256;
+  const BwdProducts all(d);
+  for (const auto& g : all.p) {
     int tail = 0;
     const GemmSplitPlan p = gemm_plan_query(g[0], g[1], g[2], g[3] != 0, &tail);
     if (tail || p.tile_m == 0) return true;
@@ -417,32 +427,56 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
     return FAX_OK;
   };
 
+  const GemmArgs w2 = wgrad(saved + L.a, F, F, dy, D, D, gr.w2, gr.b2), w1 = wgrad(saved + L.h2, D, D, du, F, F, gr.w1, gr.b1),
+                 wo = wgrad(saved + L.ctx, Hd, Hd, dx1, D, D, gr.wo, gr.bo), wqkv = wgrad(saved + L.h1, D, D, dqkv, 3 * Hd, 3 * Hd, gr.wqkv, gr.bqkv);
+  GemmArgs d2 = dgrad(dy, D, D, p.w2, D, F, du);  // du = (dy W2^T) * gelu'(u)
+  d2.epi = EPI_DGELU; d2.U = saved + L.dgelu; d2.ldu = F;
+  const GemmArgs d1 = dgrad(du, F, F, p.w1, F, D, dh2), d_o = dgrad(dx1, D, D, p.wo, D, Hd, dctx), dqkv1 = dgrad(dqkv, 3 * Hd, 3 * Hd, p.wqkv, 3 * Hd, D, dh1);
+  // Weight gradients in one launch (gemm_group): all four behind the last input gradient, where every input gradient fills the chip by
+  // itself and a weight gradient run beside it only takes turns with it; otherwise the feed-forward's two as soon as the second's upstream
+  // gradient is there, and attention's two behind theirs.  By the sizes alone, so that one or two streams give the same bits.
+  const GemmArgs all[4] = {w2, w1, wqkv, wo}, in[4] = {d2, d1, d_o, dqkv1};
+  const bool apart = short_pass(d);
+  const bool group = !apart && gemm_group_pays(GROUP_ALL, all, in);
+  const bool ffn = !apart && !group && gemm_group_pays(GROUP_FFN, all, in), att = !apart && !group && gemm_group_pays(GROUP_ATTENTION, all, in);
+  auto layer = [&](const GemmArgs& w, const GemmArgs& g, bool in_group) -> int { return in_group ? gemm(g, s) : both(w, g, &w == &w2); };
+
   // feed-forward output projection
-  FAX_TRY(hand_over(&SideStream::fork));  // everything enqueued before this call (dy, saved, ...) is visible to the side stream
-  {
-    GemmArgs g = dgrad(dy, D, D, p.w2, D, F, du);  // du = (dy W2^T) * gelu'(u)
-    g.epi = EPI_DGELU; g.U = saved + L.dgelu; g.ldu = F;
-    FAX_TRY(both(wgrad(saved + L.a, F, F, dy, D, D, gr.w2, gr.b2), g, true));
-  }
+  if (!group && !ffn) FAX_TRY(hand_over(&SideStream::fork));  // everything enqueued before this call (dy, saved, ...) is visible to the side stream
+  FAX_TRY(layer(w2, d2, group || ffn));
   // feed-forward input projection
-  FAX_TRY(hand_over(&SideStream::du));
-  FAX_TRY(both(wgrad(saved + L.h2, D, D, du, F, F, gr.w1, gr.b1), dgrad(du, F, F, p.w1, F, D, dh2), false));
+  if (!group) FAX_TRY(hand_over(&SideStream::du));
+  if (ffn) {
+    FAX_TRY(gemm_group(all, 2, sw));
+    if (side) FAX_HIP(hipEventRecord(side->w2_done, side->s));
+  }
+  FAX_TRY(layer(w1, d1, group || ffn));
   // LN2 and the residual branch: dx1 = dy + LN2'(dh2)
   FAX_TRY(ln_bwd(d.dtype, T, D, dh2, saved + L.x1, (const float*)(saved + L.mu2), (const float*)(saved + L.rstd2),
                  p.ln2_g, dy, dx1, (float*)gr.ln2_g, (float*)gr.ln2_b, acc, red, s, side ? side->s : nullptr,
                  side ? side->ln2 : nullptr));
   // attention output projection
-  FAX_TRY(hand_over(&SideStream::dx1));
-  FAX_TRY(both(wgrad(saved + L.ctx, Hd, Hd, dx1, D, D, gr.wo, gr.bo), dgrad(dx1, D, D, p.wo, D, Hd, dctx), false));
+  if (!group && !att) FAX_TRY(hand_over(&SideStream::dx1));
+  FAX_TRY(layer(wo, d_o, group || att));
   // attention
   FAX_TRY(attention_bwd(d.dtype, d.B, d.S, d.H, d.dh, saved + L.qkv, saved + L.ctx, (const float*)(saved + L.lse), dctx,
                         dqkv, delta, PATH_AUTO, s));
   // QKV projection
   FAX_TRY(hand_over(&SideStream::dqkv));
-  FAX_TRY(both(wgrad(saved + L.h1, D, D, dqkv, 3 * Hd, 3 * Hd, gr.wqkv, gr.bqkv), dgrad(dqkv, 3 * Hd, 3 * Hd, p.wqkv, 3 * Hd, D, dh1), false));
-  // LN1 and the residual branch: dx = dx1 + LN1'(dh1).  dx may be the buffer dy came in: the first
-  // weight gradient, which reads dy, has to be through with it.
-  if (side) FAX_HIP(hipStreamWaitEvent(s, side->w2_done, 0));
+  if (group) {
+    FAX_TRY(gemm_group(all, 4, sw));
+    if (side) FAX_HIP(hipEventRecord(side->w2_done, side->s));
+  } else if (att) {
+    FAX_TRY(gemm_group(all + 2, 2, sw));
+  }
+  FAX_TRY(layer(wqkv, dqkv1, group || att));
+  // LN1 and the residual branch: dx = dx1 + LN1'(dh1).  dx may be the buffer dy came in: the weight gradient that reads dy
+  // (the first one, or all together) has to be through with it.
+  if (side) {
+    const size_t bytes = z.T * z.D * z.es;
+    const bool elsewhere = (const char*)dx + bytes <= (const char*)dy || (const char*)dy + bytes <= (const char*)dx;
+    if (!group || !elsewhere) FAX_HIP(hipStreamWaitEvent(s, side->w2_done, 0));
+  }
   FAX_TRY(ln_bwd(d.dtype, T, D, dh1, x, (const float*)(saved + L.mu1), (const float*)(saved + L.rstd1), p.ln1_g, dx1,
                  dx, (float*)gr.ln1_g, (float*)gr.ln1_b, acc, side ? (void*)(ws + W.red_ln1) : red, s, side ? side->s : nullptr,
                  side ? side->ln1 : nullptr));

@@ -125,6 +125,14 @@ int gemm_mfma_deep_pair(const GemmArgs& wg, const EpiArgs& we, const GemmSplitPl
 bool gemm_pair_supported(const GemmArgs& w, const GemmArgs& d);
 int gemm_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s);
 
+// Weight gradients of a layer (with column sums, over the same tokens) in one launch.
+int gemm_group(const GemmArgs* g, int n, hipStream_t s);
+// Whether that pays: for all four (w: FFN output, FFN input, QKV, attention output; in: the input gradients of the same layers' projections, in
+// order of execution), for the first two, for the last two.  Host only.
+enum GemmGroup { GROUP_ALL, GROUP_FFN, GROUP_ATTENTION };
+bool gemm_group_pays(GemmGroup which, const GemmArgs (&w)[4], const GemmArgs (&in)[4]);
+int gemm_mfma_group(const GemmArgs* g, int n, const EpiArgs* e, int tile, bool edge, hipStream_t s);
+
 // ---- LayerNorm, column sums ---------------------------------------------------------------
 int ln_fwd(int dtype, int rows, int D, const void* x, const void* gamma, const void* beta, float eps,
            void* h, float* mu, float* rstd, hipStream_t s);

@@ -330,6 +330,22 @@ __device__ __forceinline__ void tile_epilogue(const EpiArgs& e, const EpiArgs& e
   }
 }
 
+// Products of a grouped launch: weight gradients of one layer, which contract over the same tokens and do not depend on each other.
+struct GemmItem {
+  const bf16_t *A, *B;
+  float *C, *colsum;
+  int lda, ldb, ldc, M, N, tiles_m, tiles_n, group, a_lim, b_lim;
+  int first;  // number of this product's first tile
+};
+static constexpr int GEMM_GROUP = 4;
+template <bool GROUP>
+struct GemmList {};
+template <>
+struct GemmList<true> {
+  GemmItem p[GEMM_GROUP];
+  int count, items;
+};
+
 // EDGE = false: M, N are multiples of the tile, K of the slab.  EDGE = true: any M, N, K.  Rows and
 // columns beyond the operands' ends are fetched from their last row or column group (e.a_lim, e.b_lim:
 // how far the operands reach) and never stored; contraction indices beyond K are fetched as zeros
@@ -338,10 +354,12 @@ __device__ __forceinline__ void tile_epilogue(const EpiArgs& e, const EpiArgs& e
 // these shapes ran on before, a block at 3000 tokens x 1200 wide (F = 4800): forward products 1440 ->
 // 180 us, input gradients 1610 -> 152, weight gradients with their bias sums 2470 -> 200, FFN-in with
 // the GELU epilogue 680 -> 136, GELU' 528 -> 57.
-template <int BM, int BN, bool A_KC, bool B_KC, int EM, bool EDGE>
+// GROUP: the tiles of several products with the same K, one after the other (GemmList); the products' own sizes and operands
+// take the place of the arguments, which are those of the first.
+template <int BM, int BN, bool A_KC, bool B_KC, int EM, bool EDGE, bool GROUP>
 __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, const bf16_t* __restrict__ A, int lda,
                                                         const bf16_t* __restrict__ B, int ldb, EpiArgs e, int tiles_m,
-                                                        int tiles_n) {
+                                                        int tiles_n, GemmList<GROUP> list) {
   using LA = TileLds<BM, A_KC>;
   using LB = TileLds<BN, B_KC>;
   using EDGE_ = std::integral_constant<bool, EDGE>;
@@ -363,7 +381,19 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   // on the host) tile-rows to keep the working set of A and B panels small.  e.group = 0 selects the
   // walk in which the XCDs' blocks of a round lie side by side (below).
   const int nt = tiles_m * tiles_n;
-  auto tile_of = [&](int id, int& tm_i, int& tn_i) { tile_walk(id, tiles_m, tiles_n, e.group, tm_i, tn_i); };
+  int first = 0;  // GROUP: tile numbers before the current product's
+  auto tile_of = [&](int id, int& tm_i, int& tn_i) { tile_walk(GROUP ? id - first : id, tiles_m, tiles_n, e.group, tm_i, tn_i); };
+  auto product_of = [&](int id) {  // GROUP: the product that tile number `id` belongs to takes the arguments' place
+    if constexpr (GROUP) {
+      int n = 0;
+#pragma unroll
+      for (int q = 1; q < GEMM_GROUP; q++) n += q < list.count && id >= list.p[q].first;
+      const GemmItem& g = list.p[n];
+      A = g.A; B = g.B; lda = g.lda; ldb = g.ldb; M = g.M; N = g.N; tiles_m = g.tiles_m; tiles_n = g.tiles_n;
+      e.C = g.C; e.colsum = g.colsum; e.ldc = g.ldc; e.group = g.group; e.a_lim = g.a_lim; e.b_lim = g.b_lim;
+      first = g.first;
+    }
+  };
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // in a scalar register: LDS segment addresses stay scalar
@@ -374,11 +404,12 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   // +16 lane.  The global address of a segment is (uniform slab base) + (this lane's offset,
   // fixed for the whole kernel), so stepping along K is scalar arithmetic only.
   constexpr int NSA = LA::NSEG, NSB = LB::NSEG;
-  // (EDGE: where the tile lies against the operands' ends matters as well; recomputed per tile)
+  // (EDGE: where the tile lies against the operands' ends matters as well, GROUP: the product; recomputed per tile)
+  constexpr bool PER_TILE = EDGE || GROUP;
   unsigned a_lane_off[NSA], b_lane_off[NSB];
   auto set_lane_offsets = [&](int tm, int tn) {
     int lane_o = lane;
-    if (EDGE) asm volatile("" : "+v"(lane_o));  // opaque: the parts of the offsets that no tile changes are not worth a register each
+    if (PER_TILE) asm volatile("" : "+v"(lane_o));  // opaque: the parts of the offsets that no tile changes are not worth a register each
 #pragma unroll
     for (int q = 0; q < NSA; q++)
       a_lane_off[q] = slab_lane_offset<BM, A_KC, EDGE>(lda, (wave * NSA + q) * 1024 + lane_o * 16, e.a_lim - tm * BM);
@@ -386,8 +417,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
     for (int q = 0; q < NSB; q++)
       b_lane_off[q] = slab_lane_offset<BN, B_KC, EDGE>(ldb, (wave * NSB + q) * 1024 + lane_o * 16, e.b_lim - tn * BN);
   };
-  if (!EDGE) set_lane_offsets(0, 0);
-  const size_t a_kstride = A_KC ? 1 : (size_t)lda, b_kstride = B_KC ? 1 : (size_t)ldb;
+  if (!PER_TILE) set_lane_offsets(0, 0);
+  size_t a_kstride = A_KC ? 1 : (size_t)lda, b_kstride = B_KC ? 1 : (size_t)ldb;
   const unsigned smem_addr = lds_addr(smem);
   auto a_tile_of = [&](int tm_i) { return A + (A_KC ? (size_t)tm_i * BM * lda : (size_t)tm_i * BM); };
   auto b_tile_of = [&](int tn_i) { return B + (B_KC ? (size_t)tn_i * BN * ldb : (size_t)tn_i * BN); };
@@ -414,10 +445,15 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   // With the contraction split (fp32-output form) the work items are (K range, tile) pairs: item
   // v is tile v % nt over slabs [r nkt / splits, (r + 1) nkt / splits), r = v / nt, nkt = K / GK,
   // and writes the partial product r (and the partial column sums r).
-  const int splits = e.splits > 1 ? e.splits : 1;
+  const int splits = !GROUP && e.splits > 1 ? e.splits : 1;
+  const int n_items = nt * splits;
+  auto items = [&] {
+    if constexpr (GROUP) return list.items;
+    else return n_items;
+  };
   const int nk_total = EDGE ? (K + GK - 1) / GK : K / GK;
   auto k_range = [&](int item, int& first, int& count) {
-    const int r = item / nt;
+    const int r = GROUP ? 0 : item / nt;
     first = (int)((unsigned)r * (unsigned)nk_total / (unsigned)splits);  // r < 32, nk_total < 2^25
     count = (int)((unsigned)(r + 1) * (unsigned)nk_total / (unsigned)splits) - first;
   };
@@ -436,19 +472,26 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
 
   int tm_i, tn_i;
   int k_first, nk_item;
-  tile_of(blockIdx.x % nt, tm_i, tn_i);
-  k_range(blockIdx.x, k_first, nk_item);
+  // of tile number `id`: product, tile, K range
+  auto item_of = [&](int id) {
+    product_of(id);
+    if (GROUP) { a_kstride = A_KC ? 1 : (size_t)lda; b_kstride = B_KC ? 1 : (size_t)ldb; }
+    tile_of(GROUP ? id : id % nt, tm_i, tn_i);
+    k_range(id, k_first, nk_item);
+  };
+  item_of(blockIdx.x);
   size_t k_begin = (size_t)k_first * GK;
-  if (EDGE) set_lane_offsets(tm_i, tn_i);
+  if (PER_TILE) set_lane_offsets(tm_i, tn_i);
   request_first_slabs(a_tile_of(tm_i) + k_begin * a_kstride, b_tile_of(tn_i) + k_begin * b_kstride, nk_item, K - k_first * GK);
-  for (int tile = blockIdx.x; tile < nt * splits; tile += gridDim.x) {
+  for (int tile = blockIdx.x; tile < items(); tile += gridDim.x) {
   const int nk = nk_item;
   const int k_end = K - k_first * GK;  // contraction indices from this item's first to the end of the operands
   const int m0 = tm_i * BM, n0 = tn_i * BN;
   const bf16_t* const a_tile = a_tile_of(tm_i) + k_begin * a_kstride;
   const bf16_t* const b_tile = b_tile_of(tn_i) + k_begin * b_kstride;
   EpiArgs et = e;  // this item's view of the epilogue operands
-  if (em_kind(EM) == EK_F32) {
+  const int M_item = M, N_item = N;
+  if (!GROUP && em_kind(EM) == EK_F32) {
     et.C = (float*)e.C + (size_t)(tile / nt) * e.split_stride;
     if (EM & EM_COLSUM) et.colsum = e.colsum + (size_t)(tile / nt) * e.colsum_stride;
   }
@@ -628,18 +671,16 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
         for (int j = 0; j < TN; j++) {
           const float v = cs[j] + xch[j * 32 + lane];
           float* o = et.colsum + n0 + wn + j * 32 + lane;
-          if (!EDGE || n0 + wn + j * 32 + lane < N) *o = e.accumulate ? *o + v : v;
+          if (!EDGE || n0 + wn + j * 32 + lane < N_item) *o = e.accumulate ? *o + v : v;
         }
       }
     }
   }
   // the next tile's first slabs, before anything else of the epilogue
-  if (tile + (int)gridDim.x < nt * splits) {
-    const int next = tile + gridDim.x;
-    tile_of(next % nt, tm_i, tn_i);
-    k_range(next, k_first, nk_item);
+  if (tile + (int)gridDim.x < items()) {
+    item_of(tile + gridDim.x);
     k_begin = (size_t)k_first * GK;
-    if (EDGE) set_lane_offsets(tm_i, tn_i);
+    if (PER_TILE) set_lane_offsets(tm_i, tn_i);
     request_first_slabs(a_tile_of(tm_i) + k_begin * a_kstride, b_tile_of(tn_i) + k_begin * b_kstride, nk_item, K - k_first * GK);
   }
   // (lane index through an opaque copy: otherwise everything derived from it below is hoisted out of
@@ -647,10 +688,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));
   auto epilogue = [&](auto mask_c) {
-    tile_epilogue<EM, decltype(mask_c)::value, TM, TN>(e, et, acc, wbuf, m0 + wm, n0 + wn, M, N, lane_e);
+    tile_epilogue<EM, decltype(mask_c)::value, TM, TN>(GROUP ? et : e, et, acc, wbuf, m0 + wm, n0 + wn, M_item, N_item, lane_e);
   };  // epilogue
   if constexpr (EDGE) {
-    if (m0 + BM > M || n0 + BN > N) epilogue(T_{});
+    if (m0 + BM > M_item || n0 + BN > N_item) epilogue(T_{});
     else epilogue(F_{});
   } else {
     epilogue(F_{});
@@ -659,16 +700,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   lds_dma_wait();  // nothing is in flight here; stated for whoever reads the assembly in a straight line
 }
 
-template <int BM, int BN, bool A_KC, bool B_KC, int EM, bool EDGE = false>
-static int launch_mfma(const GemmArgs& g, const EpiArgs& e, hipStream_t s) {
-  constexpr size_t lds = 3 * (size_t)TileLds<BM, A_KC>::BYTES + 2 * (size_t)TileLds<BN, B_KC>::BYTES;  // 160 KB at 256^2; also covers the epilogue's staging
-  auto kern = gemm_mfma_kernel<BM, BN, A_KC, B_KC, EM, EDGE>;
-  static bool configured = false;  // benign race: the attribute is idempotent
-  if (!configured) {
-    FAX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    configured = true;
-  }
-  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+// Workgroups of a launch.  Persistent: one per CU.  A 128^2 workgroup needs 80 KB of LDS and under 256 registers,
+// so two fit on a CU; they share its LDS bandwidth, which bounds that kernel, and gain little
+// (measured: +-0.4 % with many tiles) except when that saves a second round for a few left-over
+// tiles (320 tiles: -4 % on the whole step).
+static inline int mfma_grid(int bm, int items, int* grid) {
   static int n_cu = 0;  // benign race: same value from every thread
   if (n_cu == 0) {
     int dev = 0, v = 0;
@@ -676,17 +712,28 @@ static int launch_mfma(const GemmArgs& g, const EpiArgs& e, hipStream_t s) {
     FAX_HIP(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
     n_cu = v > 0 ? v : 256;
   }
-  const int items = tiles_m * tiles_n * (e.splits > 1 ? e.splits : 1);
-  // Persistent: one workgroup per CU.  A 128^2 workgroup needs 80 KB of LDS and under 256 registers,
-  // so two fit on a CU; they share its LDS bandwidth, which bounds that kernel, and gain little
-  // (measured: +-0.4 % with many tiles) except when that saves a second round for a few left-over
-  // tiles (320 tiles: -4 % on the whole step).
-  const int slots = (BM == 128 && items <= 2 * n_cu) ? 2 * n_cu : n_cu;
-  const int grid = items < slots ? items : slots;
+  const int slots = (bm == 128 && items <= 2 * n_cu) ? 2 * n_cu : n_cu;
+  *grid = items < slots ? items : slots;
+  return FAX_OK;
+}
+
+template <int BM, int BN, bool A_KC, bool B_KC, int EM, bool EDGE = false, bool GROUP = false>
+static int launch_mfma(const GemmArgs& g, const EpiArgs& e, hipStream_t s, const GemmList<GROUP>& list = GemmList<GROUP>()) {
+  constexpr size_t lds = 3 * (size_t)TileLds<BM, A_KC>::BYTES + 2 * (size_t)TileLds<BN, B_KC>::BYTES;  // 160 KB at 256^2; also covers the epilogue's staging
+  auto kern = gemm_mfma_kernel<BM, BN, A_KC, B_KC, EM, EDGE, GROUP>;
+  static bool configured = false;  // benign race: the attribute is idempotent
+  if (!configured) {
+    FAX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    configured = true;
+  }
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  int items = tiles_m * tiles_n * (e.splits > 1 ? e.splits : 1), grid = 0;
+  if constexpr (GROUP) items = list.items;
+  FAX_TRY(mfma_grid(BM, items, &grid));
   EpiArgs ek = e;
   if (ek.group == 0 && grid != 256) ek.group = 4;  // the side-by-side walk is written for 8 XCDs x 32 workgroups
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, s, g.M, g.N, g.K, (const bf16_t*)g.A, g.lda,
-                     (const bf16_t*)g.B, g.ldb, ek, tiles_m, tiles_n);
+                     (const bf16_t*)g.B, g.ldb, ek, tiles_m, tiles_n, list);
   FAX_LAUNCH_CHECK("gemm_mfma");
   return FAX_OK;
 }

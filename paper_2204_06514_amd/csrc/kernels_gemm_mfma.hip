@@ -274,6 +274,79 @@ int gemm_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s) {
   return gemm_mfma_deep_pair(w, epi_args(w, wp), wp, d, epi_args(d, dp), dp, s);
 }
 
+// Weight gradients of one layer in one launch, whose tiles share the rounds: by themselves each ends in a partly filled one, takes tiles
+// too small for it, or cuts its contraction and folds.  The class with the smaller predicted time.
+struct GroupPlan { int tile; bool edge; double us; };
+static bool group_plan(const GemmArgs* g, int n, GroupPlan* plan) {
+  if (n < 1 || n > GEMM_GROUP) return false;
+  for (int i = 0; i < n; i++)
+    if (g[i].path != PATH_AUTO || !gemm_edge_supported(g[i]) || !g[i].c_f32 || !g[i].colsum || g[i].K != g[0].K || g[i].accumulate != g[0].accumulate)
+      return false;
+  plan->us = 1e30;
+  for (const TileClass& tc : kTiles) {
+    if (tc.m != tc.n || tc.deep) continue;
+    long long items = 0;
+    bool cut = g[0].K % GK != 0;
+    for (int i = 0; i < n; i++) {
+      items += (long long)((g[i].M + tc.m - 1) / tc.m) * ((g[i].N + tc.n - 1) / tc.n);
+      cut = cut || g[i].M % tc.m || g[i].N % tc.n;
+    }
+    const double round = (g[0].K + GK - 1) / GK * tc.full_us + tc.epi_f32_us;
+    const double t = 3.0 + (tc.m == 128 && items > kCUs && items <= 2 * kCUs ? 1.6 * round : (double)((items + kCUs - 1) / kCUs) * round);
+    if (t < plan->us) *plan = GroupPlan{tc.m, cut, t};
+  }
+  return true;
+}
+
+// The lines, with the block's forward and backward pass (us, tokens x width, F = 4 x width) before and after:
+// All four: 256^2 tiles, input gradients of at least a round of 256 x 128 tiles each, and 30 % less predicted time than apart.  8192 x 1024 980 -> 904
+//   (the feed-forward's two and attention's two by themselves 970); where the input gradients leave CUs idle the other way round, 3108 x 512
+//   271 -> 285, 16384 x 512 684 -> 766, 2048 x 5120 in an eighth's share 695 -> 728.
+// The feed-forward's two: any gain predicted for whole tiles, a quarter for masked edges (whose small tiles by themselves run 30 % over the
+//   model beside other kernels).  3108 x 512 271 -> 253, 4500 x 640 465 -> 438, 3000 x 1200 654 -> 626, 4096 x 1024 470 -> 460; 4200 x 968,
+//   beyond the line, 676 and 691.
+// Attention's two: at 128^2 tiles, and not much longer than the QKV one alone (the other one would start before the attention kernels and run
+//   beside them).  4096 x 1024 470 -> 449, 2222 x 1280 563 -> 552, 4096 x 768 380 -> 372; beyond the line 3108 x 512 271 and 277, 1999 x
+//   2000 843 and 854, 3600 x 1536 908 and 915.
+bool gemm_group_pays(GemmGroup which, const GemmArgs (&w)[4], const GemmArgs (&in)[4]) {
+  GemmSplitPlan p;
+  bool pairs = true, full = true;
+  for (int i = 0; i < 4; i++) {
+    const GemmArgs& g = in[i];
+    if (!gemm_edge_supported(g)) return false;
+    const GemmArgs& same = i < 2 ? w[i] : w[5 - i];  // the weight gradient of this layer
+    pairs = pairs && gemm_pair_supported(same, g);
+    p = plan_tiles(g.M, g.N, g.K, false, false, !tiles_whole(g.M, g.N, g.K), true);
+    full = full && p.tile_m == 256 && (long long)((g.M + 255) / 256) * ((g.N + p.tile_n - 1) / p.tile_n) >= kCUs;
+  }
+  if (pairs) return false;  // short products: one launch for a layer's weight and input gradient instead
+  const int first = which == GROUP_ATTENTION ? 2 : 0, n = which == GROUP_ALL ? 4 : 2;
+  GroupPlan plan;
+  if (!group_plan(w + first, n, &plan)) return false;
+  double apart = 0.0;
+  for (int i = first; i < first + n; i++)
+    apart += gemm_mfma_time_us(w[i]) * (gemm_route(w[i], true).small ? 1.3 : 1.0);
+  if (which == GROUP_ALL) return full && plan.tile == 256 && plan.us < 0.7 * apart;
+  if (which == GROUP_FFN) return plan.us < (plan.edge ? 0.76 : 0.97) * apart;
+  return plan.tile == 128 && plan.us < 0.97 * apart && plan.us < 1.45 * gemm_mfma_time_us(w[2]);
+}
+
+int gemm_group(const GemmArgs* g, int n, hipStream_t s) {
+  GroupPlan plan;
+  if (!group_plan(g, n, &plan)) {
+    set_error("gemm_group: not products for one launch");
+    return FAX_ERR_UNSUPPORTED;
+  }
+  EpiArgs e[GEMM_GROUP];
+  double work = 0.0;
+  for (int i = 0; i < n; i++) {
+    e[i] = epi_args(g[i], GemmSplitPlan{plan.tile, plan.tile, 1, false});
+    work += 2.0 * g[i].M * g[i].N * g[i].K;
+  }
+  Timed t("gemm_mfma_group", WORK_FLOP, work, s);
+  return gemm_mfma_group(g, n, e, plan.tile, plan.edge, s);
+}
+
 // Launch included; with scratch for a split where the form may have one.
 double gemm_mfma_time_us(const GemmArgs& g) {
   const bool edge = !tiles_whole(g.M, g.N, g.K) || b_short(g);

@@ -186,3 +186,37 @@ def test_timing_report_tells_the_kernels_apart():
     assert name(1, 0, 512, 512, 3108, 1) == "gemm_mfma_Am_Bm_f32out_small"
     assert name(0, 0, 500, 500, 500) == "gemm_scalar_Ak_Bm_store"
     assert name(0, 0, 500, 500, 500, dtype="f32") == "gemm_mfma32_Ak_Bm_store"
+
+
+# Weight gradients of a layer in one launch: how many such launches a backward pass makes.  All four on 256 x 256 tiles; the feed-forward's
+# and attention's two, whole tiles; the feed-forward's two on 256 x 256 and attention's on 128 x 128, masked edges; the former alone, 128 x 128.
+@pytest.mark.parametrize("shape,groups", [
+    (dict(B=8, S=1024, D=1024, H=16, dh=64, F=4096), 1),
+    (dict(B=8, S=512, D=1024, H=16, dh=64, F=4096), 2),
+    (dict(B=3, S=1000, D=1200, H=15, dh=80, F=4800), 2),
+    (dict(B=4, S=777, D=512, H=8, dh=64, F=2048), 1)])
+def test_grouped_weight_gradients(shape, groups):
+    sh = BlockShape(dtype="bf16", sigma_w=0.03, **shape)
+    p, x, dy = make_block_inputs(sh, seed=4, generic=True)
+
+    def run(**kw):
+        fax.fax_timing_enable(1)
+        try:
+            out = helpers.run_block(sh, p, x, dy, **kw)
+            rows = {r["name"]: r["launches"] for r in fax.fax_timing_report(64)}
+        finally:
+            fax.fax_timing_enable(0)
+        assert rows.get("gemm_mfma_group", 0) == groups, rows
+        return out
+
+    out = run()
+    for k, (act, grad) in _weight_grads(sh, out, dy).items():
+        # fp32 sums of exact products: 2^-24 a step, relative to the largest element of a long sum
+        assert rel_max(out["grads"][k].reshape(act.shape[1], -1), act.T @ grad) <= 1e-5, k
+        assert rel_max(out["grads"][BIAS[k]].reshape(-1), grad.sum(0)) <= 1e-5, k
+    one = run(flags=fax.FAX_FLAG_SINGLE_STREAM)
+    more = run(accumulate=True, grads_init={k: np.full(p[k].shape, 0.5) for k in PARAM_NAMES})
+    for k in PARAM_NAMES:
+        assert np.array_equal(one["grads"][k], out["grads"][k]), k
+        assert rel_max(more["grads"][k], 0.5 + out["grads"][k]) <= 1e-6, k
+    assert np.array_equal(one["dx"], out["dx"])
