@@ -39,10 +39,19 @@ __device__ __forceinline__ float block_reduce(float v, float* red, bool is_max) 
 
 // NV: 16-byte vectors per thread (V <= blockDim.x * NV * elements per vector).  PAD = false: V is a multiple of the vector.
 // PAD = true: V is not, but the row distance ld >= V is; the elements of the last vector beyond V count as -infinity, which gives
-// them the gradient zero.  Bound by HBM and the exponentials like the other; these are the library's there, as in the
-// generic kernel that served such V before, in three passes over the row with 2-byte accesses (3108 x 32003: 262 -> 140 us).
-template <bool PAD>
-__device__ __forceinline__ float ce_exp(float d) { return PAD ? expf(d) : __builtin_amdgcn_exp2f(d * CE_LOG2E); }
+// them the gradient zero.  Bound by HBM and the exponentials like the other, two of which there are to a logit.  Those of fp32 logits are
+// the library's; those of bf16 ones have its accuracy (1.2e-7 of themselves at most, 3.6e-8 rms, before the rounding to bf16) in six
+// instructions instead of thirteen: 3108 x 32003 135 -> 111 us, where HBM takes 91.
+template <typename T, bool PAD>
+__device__ __forceinline__ float ce_exp(float d) {
+  if (PAD && sizeof(T) == 4) return expf(d);
+  if (!PAD) return __builtin_amdgcn_exp2f(d * CE_LOG2E);
+  // d <= 0 or NaN.  t + r = d log2(e) to 48 bits, 2^r = 1 + r ln 2 to 2^-48; e^-200 is zero, and keeps infinities out of r.
+  d = __builtin_elementwise_maximum(d, -200.f);
+  const float t = d * CE_LOG2E, r = fmaf(d, 1.925963033e-8f, fmaf(d, CE_LOG2E, -t));
+  const float e = __builtin_amdgcn_exp2f(t);
+  return fmaf(e, r * CE_LN2, e);
+}
 
 template <typename T, int NV, bool PAD>
 __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V, int ld, const T* __restrict__ logits,
@@ -85,14 +94,14 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V,
   for (int i = 0; i < NV; i++) {
     if (threadIdx.x + i * nt < nvec) {
 #pragma unroll
-      for (int e = 0; e < Vv::N; e++) se += ce_exp<PAD>(zv[i].get(e) - mt);
+      for (int e = 0; e < Vv::N; e++) se += ce_exp<T, PAD>(zv[i].get(e) - mt);
     }
   }
   // combine the (maximum, sum) pairs: within the wave, then across waves through LDS.  A thread
   // without elements has maximum -inf and sum 0 and drops out.  The wave's maximum passes over NaN; its sum does not, and
   // stands in for it then.
   const float mw = wave_max(mt);
-  const float sw = wave_sum(mt == -INFINITY ? 0.f : se * ce_exp<PAD>(mt - mw));
+  const float sw = wave_sum(mt == -INFINITY ? 0.f : se * ce_exp<T, PAD>(mt - mw));
   const int wave = threadIdx.x >> 6, nw = nt >> 6;
   if ((threadIdx.x & 63) == 0) {
     red_m[wave] = sw == sw ? mw : sw;
@@ -105,7 +114,7 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V,
   // fixed order.  (What drops out is a branch here; as one of two sums to select from it took the kernel from 51 registers to
   // 88, one workgroup per CU instead of two, and 3108 x 32003 from 135 us to 167.)
   for (int i = 0; i < nw; i++)
-    S += red_m[i] == -INFINITY ? 0.f : red_s[i] * ce_exp<PAD>(red_m[i] - M);
+    S += red_m[i] == -INFINITY ? 0.f : red_s[i] * ce_exp<T, PAD>(red_m[i] - M);
   if (threadIdx.x == 0) row_loss[row] = (M + (PAD ? logf(S) : __builtin_amdgcn_logf(S) * CE_LN2)) - z_label;  // v_log_f32 is log2
   if (!dlogits) return;
   const float invN = grad_scale / (float)N;
@@ -117,7 +126,7 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V,
     if (c < nvec) {
       float g[Vv::N];
 #pragma unroll
-      for (int e = 0; e < Vv::N; e++) g[e] = ce_exp<PAD>(zv[i].get(e) - M) * inv;
+      for (int e = 0; e < Vv::N; e++) g[e] = ce_exp<T, PAD>(zv[i].get(e) - M) * inv;
       const int k = label - c * Vv::N;
       if (k >= 0 && k < Vv::N) {  // rare: the vector that holds the label's column
 #pragma unroll
@@ -172,15 +181,16 @@ __global__ __launch_bounds__(1024) void mean_kernel(int N, const float* __restri
 }
 
 // Threads per row and vectors per thread for a row of `nvec` 16-byte vectors: the pair with the
-// fewest idle vector slots among workgroups of 4 to 16 waves; of equals, the larger workgroup.
-static bool ce_shape(int nvec, int* threads, int* nv) {
+// fewest idle vector slots among workgroups of 4 to 16 waves; of equals, the larger workgroup.  The padded form, which unpacks its row
+// as it arrives, stays at 8 vectors where it can, and of equals takes the smaller workgroup (3108 x 32003: 1024 threads 111 us, 512 105, 256 188).
+static bool ce_shape(int nvec, bool pad, int* threads, int* nv) {
   long best = -1;
   for (int nt = CE_MAX_THREADS; nt >= 256; nt -= 64) {
     const int v = (nvec + nt - 1) / nt;
-    if (v > CE_MAX_NV) continue;
+    if (v > (pad && nvec <= 8 * CE_MAX_THREADS ? 8 : CE_MAX_NV)) continue;
     const int vt = v <= 2 ? 2 : v <= 4 ? 4 : v <= 6 ? 6 : v <= 8 ? 8 : v <= 10 ? 10 : v <= 12 ? 12 : 16;  // instantiated sizes
     const long waste = (long)nt * vt - nvec;
-    if (best < 0 || waste < best) {
+    if (best < 0 || waste < best || (pad && waste == best)) {
       best = waste;
       *threads = nt;
       *nv = vt;
@@ -209,7 +219,7 @@ static int ce_t(int N, int V, int ld, const T* logits, const int32_t* labels, T*
   constexpr int VN = Vec16<T>::N;
   int nt = 0, nv = 0;
   // rows that start on a vector and have room for whole ones; those that end inside one take the padded form
-  if (ld % VN == 0 && ce_shape((V + VN - 1) / VN, &nt, &nv)) {
+  if (ld % VN == 0 && ce_shape((V + VN - 1) / VN, V % VN != 0, &nt, &nv)) {
     if (V % VN) ce_cached<T, true>(nv, nt, N, V, ld, logits, labels, dlogits, row_loss, grad_scale, s);
     else ce_cached<T, false>(nv, nt, N, V, ld, logits, labels, dlogits, row_loss, grad_scale, s);
   } else {
