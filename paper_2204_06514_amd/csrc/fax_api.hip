@@ -260,7 +260,7 @@ static int attention_bwd(int dtype, int B, int S, int H, int dh, const void* qkv
 
 // ---- block forward --------------------------------------------------------------------------
 static int block_fwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const void* x, void* y, char* saved,
-                          void* p_attn, void* p_mlp, hipStream_t s) {
+                          void* p_attn, void* p_mlp, bool backward, hipStream_t s) {
   Sizes z(d);
   FaxSavedLayout L;
   saved_layout(d, &L);
@@ -289,7 +289,7 @@ static int block_fwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
   g = GemmArgs(); g.dtype = d.dtype; g.gelu_form = d.gelu;
   g.M = T; g.N = F; g.K = D;
   g.A = saved + L.h2; g.lda = D; g.B = p.w1; g.ldb = F; g.C = saved + L.dgelu; g.ldc = F; g.bias = p.b1;
-  g.epi = EPI_GELU; g.C2 = saved + L.a; g.ldc2 = F;
+  g.epi = EPI_GELU; g.C2 = saved + L.a; g.ldc2 = F; g.value_only = !backward;
   FAX_TRY(gemm(g, s));
   // y = x1 + a W2 + b2
   g = GemmArgs(); g.dtype = d.dtype; g.gelu_form = d.gelu;
@@ -689,7 +689,7 @@ int fax_block_fwd(const FaxBlockDims* dims, const FaxBlockTensors* params, const
     FAX_TRY(check_ptr(p_mlp, "p_mlp"));
   }
   (void)ws; (void)ws_bytes;  // the forward pass needs no scratch beyond `saved`
-  return block_fwd_impl(*dims, *params, x, y, (char*)saved, p_attn, p_mlp, (hipStream_t)stream);
+  return block_fwd_impl(*dims, *params, x, y, (char*)saved, p_attn, p_mlp, true, (hipStream_t)stream);
 }
 
 int fax_block_bwd(const FaxBlockDims* dims, const FaxBlockTensors* params, const void* x, const void* dy,
@@ -809,7 +809,7 @@ int fax_eval_step(const FaxModelDims* dims, const FaxModelTensors* params, const
   bd.flags &= ~FAX_FLAG_TP_PARTIAL;
   FAX_TRY(embed_fwd(d.dtype, d.B, d.S, D, tokens, params->tok_emb, params->pos_emb, w + W.x[0], s));
   for (int l = 0; l < dims->L; l++)
-    FAX_TRY(block_fwd_impl(bd, params->blocks[l], w + W.x[l & 1], w + W.x[(l + 1) & 1], w + W.saved, nullptr, nullptr, s));
+    FAX_TRY(block_fwd_impl(bd, params->blocks[l], w + W.x[l & 1], w + W.x[(l + 1) & 1], w + W.saved, nullptr, nullptr, false, s));
   FAX_TRY(ln_fwd(d.dtype, T, D, w + W.x[dims->L & 1], params->lnf_g, params->lnf_b, d.ln_eps, w + W.hf,
                  (float*)(w + W.muf), (float*)(w + W.rstdf), s));
   FAX_TRY(gemm(logits_product(*dims, w + W.hf, params->tok_emb, w + W.logits), s));
@@ -873,7 +873,7 @@ int fax_train_step(const FaxModelDims* dims, const FaxModelTensors* params, cons
   FAX_TRY(embed_fwd(d.dtype, d.B, d.S, D, tokens, params->tok_emb, params->pos_emb, w + W.xs, s));
   for (int l = 0; l < L; l++)
     FAX_TRY(block_fwd_impl(bd, params->blocks[l], w + W.xs + W.x_stride * l, w + W.xs + W.x_stride * (l + 1),
-                           w + W.saved + W.saved_stride * l, nullptr, nullptr, s));
+                           w + W.saved + W.saved_stride * l, nullptr, nullptr, true, s));
   FAX_TRY(ln_fwd(d.dtype, T, D, xL, params->lnf_g, params->lnf_b, d.ln_eps, w + W.hf, (float*)(w + W.muf),
                  (float*)(w + W.rstdf), s));
   FAX_TRY(gemm(logits_product(*dims, w + W.hf, params->tok_emb, w + W.logits), s));

@@ -51,6 +51,7 @@ struct GemmArgs {
   void* C2 = nullptr; int ldc2 = 0;
   const void* U = nullptr; int ldu = 0;
   int gelu_form = FAX_GELU_TANH;
+  bool value_only = false;  // EPI_GELU: nobody reads the derivative, C need not be written (not every kernel makes use of that)
   int path = PATH_AUTO;
   // Optional by-product, B stored [K, N] only: colsum[n] (+)= sum over k of B[k, n] (`accumulate`
   // applies to it as well).  colsum_ws: colsum_ws_bytes(N) of scratch for the paths that take the

@@ -116,7 +116,7 @@ __device__ __forceinline__ bf16x8 frag_load(const char* lds, int rb, int ks, int
 // in the store loop may hang on a run-time condition: stores count towards the same counter as
 // loads on this target, so the conservative wait the compiler places where branches that contain
 // loads rejoin would also wait for every earlier store to be acknowledged, once per row.
-enum { EK_STORE = 0, EK_GELU_TANH = 1, EK_GELU_ERF = 2, EK_DGELU = 3, EK_F32 = 5 };
+enum { EK_STORE = 0, EK_GELU_TANH = 1, EK_GELU_ERF = 2, EK_DGELU = 3, EK_F32 = 5, EK_VALUE_TANH = 6, EK_VALUE_ERF = 7 };  // VALUE: GELU without the derivative
 enum {
   EM_RES = 8,  // bf16 kinds: add the residual R;  EK_F32: add to what C already holds
   EM_C2 = 16,  // EK_STORE: also write the plain product (before bias and residual) to C2
@@ -124,7 +124,8 @@ enum {
 };
 constexpr int em_kind(int em) { return em & 7; }
 constexpr bool em_dgelu(int em) { return em_kind(em) == EK_DGELU; }
-constexpr bool em_gelu(int em) { return em_kind(em) == EK_GELU_TANH || em_kind(em) == EK_GELU_ERF; }
+constexpr bool em_value(int em) { return em_kind(em) == EK_VALUE_TANH || em_kind(em) == EK_VALUE_ERF; }
+constexpr bool em_gelu(int em) { return em_kind(em) == EK_GELU_TANH || em_kind(em) == EK_GELU_ERF || em_value(em); }
 
 // tanh-form GELU through the logistic function: (1 + tanh z) / 2 = 1 / (1 + exp(-2 z)), one
 // v_exp_f32 and one v_rcp_f32 per element.  In fp32, over N(0, 1) and against tanhf, which the scalar kernel has: the value
@@ -202,16 +203,16 @@ __device__ __forceinline__ void mfma_epilogue4(const EpiArgs& e, int m, int n, f
   if (!em_dgelu(EM) && (EM & EM_RES)) {
     a.x += side.x; a.y += side.y; a.z += side.z; a.w += side.w;
   }
-  if (em_gelu(EM)) {  // C = gelu'(acc), C2 = gelu(acc)
+  if (em_gelu(EM)) {  // C = gelu'(acc), C2 = gelu(acc); VALUE: C2 alone (16384 x 3072 x 768, whose stores are half of a round: 104 -> 90 us)
     float4 g, dg;
-    if (KIND == EK_GELU_TANH) {
+    if (KIND == EK_GELU_TANH || KIND == EK_VALUE_TANH) {
       gelu_tanh_both(a.x, g.x, dg.x); gelu_tanh_both(a.y, g.y, dg.y);
       gelu_tanh_both(a.z, g.z, dg.z); gelu_tanh_both(a.w, g.w, dg.w);
     } else {
       gelu_erf_both(a.x, g.x, dg.x); gelu_erf_both(a.y, g.y, dg.y);
       gelu_erf_both(a.z, g.z, dg.z); gelu_erf_both(a.w, g.w, dg.w);
     }
-    st_bf16x4(e.C, (size_t)m * e.ldc + n, dg);
+    if (!em_value(EM)) st_bf16x4(e.C, (size_t)m * e.ldc + n, dg);
     st_bf16x4(e.C2, (size_t)m * e.ldc2 + n, g);
     return;
   }

@@ -7,6 +7,8 @@ namespace fax {
 template <int BM, int BN>
 static int dispatch_edge(const GemmArgs& g, const EpiArgs& e, hipStream_t s) {
   const bool erf = g.gelu_form == FAX_GELU_ERF;
+  if (g.epi == EPI_GELU && g.value_only)
+    return erf ? launch_mfma<BM, BN, true, false, EK_VALUE_ERF, true>(g, e, s) : launch_mfma<BM, BN, true, false, EK_VALUE_TANH, true>(g, e, s);
   if (g.epi == EPI_GELU)
     return erf ? launch_mfma<BM, BN, true, false, EK_GELU_ERF, true>(g, e, s)
                : launch_mfma<BM, BN, true, false, EK_GELU_TANH, true>(g, e, s);

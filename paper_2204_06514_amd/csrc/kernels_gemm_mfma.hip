@@ -201,6 +201,8 @@ template <int BM, int BN>
 static int dispatch(const GemmArgs& g, const EpiArgs& e, hipStream_t s) {
   const bool a_kc = !g.ta, b_kc = g.tb;
   const bool erf = g.gelu_form == FAX_GELU_ERF;
+  if (g.epi == EPI_GELU && g.value_only)
+    return erf ? launch_mfma<BM, BN, true, false, EK_VALUE_ERF>(g, e, s) : launch_mfma<BM, BN, true, false, EK_VALUE_TANH>(g, e, s);
   if (g.epi == EPI_GELU)
     return erf ? launch_mfma<BM, BN, true, false, EK_GELU_ERF>(g, e, s) : launch_mfma<BM, BN, true, false, EK_GELU_TANH>(g, e, s);
   if (g.epi == EPI_DGELU)
