@@ -195,7 +195,8 @@ int fax_gemm_tile_walk(int M, int N, int K, int c_f32, int32_t* tile_row, int32_
 
 /* Host-only: what gemm entry points make of any product C[M,N] = op(A) op(B) of densely stored operands (ta, tb, c_f32
  * as for fax_gemm, PATH_AUTO; scratch != 0: with scratch for a split, as in fax_block_bwd and fax_train_step, where
- * fax_gemm has none).
+ * fax_gemm has none; the product for the hidden states' gradient in fax_train_step, the one bf16 output that may be split,
+ * is not told apart here: the answer is its undivided form).
  *   form          FAX_GEMM_*: the scalar kernel; the fp32 matrix-core kernel; the bf16 one, whose tiles divide the shape; its
  *                 masked-edge form; or the small-tile kernel for products that leave CUs idle (any shape).
  *   tail, tile_*, splits   as in FaxGemmPlan, for the masked-edge and small-tile kernels too (0, 0, 1 for the scalar kernel).

@@ -531,6 +531,7 @@ GemmArgs hidden_grad_product(const FaxModelDims& m, const void* dlogits, const v
   g.M = m.blk.B * m.blk.S; g.N = m.blk.D; g.K = m.V;
   g.a_padded = logits_ld(m) > m.V;
   g.A = dlogits; g.lda = logits_ld(m); g.B = tok_emb; g.ldb = m.blk.D; g.C = out; g.ldc = m.blk.D;
+  g.store_split = true;
   return g;
 }
 
@@ -560,7 +561,8 @@ static void train_layout(const FaxModelDims& m, TrainWs* W) {
   W->dcur = take(z.T * z.D * z.es);  // right behind the logits, whose padded rows may reach into it (logits_ld)
   W->dhf = take(z.T * z.D * z.es);
   W->blk = take(B.total);
-  W->headsplit = take(gemm_split_ws_bytes(m.V, (int)z.D, (int)z.T));  // the embedding gradient's product may split K
+  // the embedding gradient's product may split K, and after it the hidden states'
+  W->headsplit = take(std::max(gemm_split_ws_bytes(m.V, (int)z.D, (int)z.T), d.dtype == FAX_BF16 ? gemm_store_split_ws_bytes((int)z.T, d.D, m.V) : 0));
   W->embidx = take(embed_index_ws_bytes(m.V));  // first position and count per token id (FAX_FLAG_DETERMINISTIC)
   W->total = o;
 }
@@ -891,7 +893,9 @@ int fax_train_step(const FaxModelDims* dims, const FaxModelTensors* params, cons
   g.accumulate = acc;
   g.split_ws = W.headsplit < W.total ? w + W.headsplit : nullptr;
   FAX_TRY(gemm(g, s));
-  FAX_TRY(gemm(hidden_grad_product(*dims, w + W.logits, params->tok_emb, w + W.dhf), s));
+  g = hidden_grad_product(*dims, w + W.logits, params->tok_emb, w + W.dhf);
+  g.split_ws = W.headsplit < W.total ? w + W.headsplit : nullptr;
+  FAX_TRY(gemm(g, s));
   FAX_TRY(ln_bwd(d.dtype, T, D, w + W.dhf, xL, (const float*)(w + W.muf), (const float*)(w + W.rstdf), params->lnf_g,
                  nullptr, w + W.dcur, (float*)grads->lnf_g, (float*)grads->lnf_b, acc, w + W.blk, s));
   for (int l = L - 1; l >= 0; l--)

@@ -58,9 +58,11 @@ struct GemmArgs {
   // sums in a separate pass.
   float* colsum = nullptr;
   void* colsum_ws = nullptr;
-  // Scratch for splitting the contraction (fp32-output form only): gemm_split_ws_bytes(M, N, K)
+  // Scratch for splitting the contraction (fp32-output form): gemm_split_ws_bytes(M, N, K)
   // bytes, or NULL to forbid the split.
   void* split_ws = nullptr;
+  // The same for a plain bf16 output, A [M, K], B [K, N] (fp32 partial products, rounded once): gemm_store_split_ws_bytes(M, N, K) bytes.
+  bool store_split = false;
   // Internal buffers only: the rows of A, as stored, are readable up to the next multiple of 16 bytes
   // (zeros there if the contraction runs along them) / B stored [N, K] has only this many rows (0: N);
   // the columns of C beyond them hold nothing meaningful.
@@ -103,6 +105,7 @@ struct GemmSplitPlan {
 };
 GemmSplitPlan gemm_split_plan(int M, int N, int K);
 size_t gemm_split_ws_bytes(int M, int N, int K);
+size_t gemm_store_split_ws_bytes(int M, int N, int K);
 GemmSplitPlan gemm_plan_query(int M, int N, int K, bool f32_out, int* tail);
 int gemm_tile_walk_query(int M, int N, int K, bool f32_out, int* tm, int* tn, int capacity, int* count, int* group);
 double gemm_mfma_time_us(const GemmArgs& g);
@@ -150,6 +153,7 @@ size_t colsum_ws_bytes(int N);
 // out_b in the same launch.  Fixed summation order.
 int fold_partials(int parts, size_t n, const float* partial, float* out, bool accumulate, hipStream_t s, int nb = 0,
                   const float* partial_b = nullptr, float* out_b = nullptr);
+int fold_partials_bf16(int parts, size_t n, const float* partial, void* out, hipStream_t s);
 // out[n] (+)= sum over rows of a[r, n]; a in dtype with leading dimension lda.
 int colsum(int dtype, int rows, int N, const void* a, int lda, float* out, bool accumulate, void* ws,
            hipStream_t s);

@@ -16,6 +16,7 @@ static int dispatch_edge(const GemmArgs& g, const EpiArgs& e, hipStream_t s) {
   if (g.c_f32 && g.colsum)
     return g.accumulate ? launch_mfma<BM, BN, false, false, EK_F32 | EM_RES | EM_COLSUM, true>(g, e, s)
                         : launch_mfma<BM, BN, false, false, EK_F32 | EM_COLSUM, true>(g, e, s);
+  if (g.c_f32 && !g.ta) return launch_mfma<BM, BN, true, false, EK_F32, true>(g, e, s);  // partial products of a bf16 output
   if (g.c_f32)
     return g.accumulate ? launch_mfma<BM, BN, false, false, EK_F32 | EM_RES, true>(g, e, s)
                         : launch_mfma<BM, BN, false, false, EK_F32, true>(g, e, s);

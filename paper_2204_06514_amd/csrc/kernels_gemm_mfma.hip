@@ -154,6 +154,43 @@ size_t gemm_split_ws_bytes(int M, int N, int K) {
   return split_ws_bytes_1(M, N, K);  // a column strip keeps the leading dimension of C: no split there
 }
 
+// A plain bf16 output with few tiles and a very long contraction (the gradient of the hidden states: tokens x width, contracted over
+// the vocabulary) is likewise cut into K ranges: fp32 partial products in larger tiles, their sum rounded to bf16 once.  A workgroup
+// for every tile of the whole product spends K / 64 slabs one after another, at 25 to 200 workgroups on 256 CUs; the ranges fill them.
+// 3108 x 512 x 32003: 189 us as 128 x 64 tiles over all of K, 92 + 15 (fold) as 256 x 256 tiles in 9 ranges.  The line is where the
+// predicted times are equal (predicted split / unsplit time; what a whole one-layer training step changes, us): 0.18 128 x 256 x 32000
+// 316 -> 206, 0.40 600 x 256 x 16000 271 -> 225, 0.68 6000 x 256 x 32000 1033 -> 922, 0.95 600 x 768 x 6000 342 -> 335, 0.98
+// 6000 x 1600 x 32000 4043 -> 3979, 0.99 2048 x 256 x 6000 266 -> 257;  on the other side 1.16 600 x 1600 x 6000 722 -> 724 and
+// 6000 x 1600 x 16000 3023 -> 3006, 1.38 600 x 256 x 2500 175 -> 175, 1.45 2048 x 1600 x 6000 1098 -> 1116, 2.6 6000 x 1600 x 2500 2189 -> 2224.
+static GemmSplitPlan store_split_plan(int M, int N, int K) {
+  const bool edge = !tiles_whole(M, N, K);
+  GemmSplitPlan best{0, 0, 1, false};
+  double t1 = 1e30;
+  for (const TileClass& tc : kTiles)
+    if (edge || tc.deep || !(M % tc.m || N % tc.n)) t1 = std::min(t1, tile_time_us(tc, M, N, K, false, 1));
+  double best_t = t1;
+  const int nkt = (K + GK - 1) / GK;
+  for (const TileClass& tc : kTiles) {
+    if (tc.deep || tc.m != tc.n || ((M % tc.m || N % tc.n) && !edge)) continue;
+    for (int s = 2; s <= 32 && nkt / s >= 8; s++) {
+      const double t = tile_time_us(tc, M, N, K, true, s);
+      if (t < best_t) {
+        best_t = t;
+        best = GemmSplitPlan{tc.m, tc.n, s, false};
+      }
+    }
+  }
+  return best;
+}
+static bool store_split_ok(const GemmArgs& g) {
+  return g.store_split && !g.c_f32 && !g.ta && !g.tb && g.epi == EPI_NONE && !g.bias && !g.R && !g.C2 && !g.colsum && g.path == PATH_AUTO &&
+         g.ldc == g.N && g.N % 4 == 0 && !g.b_rows;
+}
+size_t gemm_store_split_ws_bytes(int M, int N, int K) {
+  const int s = store_split_plan(M, N, K).splits;
+  return s > 1 ? (size_t)s * M * N * sizeof(float) : 0;
+}
+
 // What both forms of the kernel ask of a product, apart from its sizes.
 static bool mfma_layout_ok(const GemmArgs& g) {
   if (g.dtype != FAX_BF16) return false;
@@ -352,6 +389,11 @@ int gemm_group(const GemmArgs* g, int n, hipStream_t s) {
 // Launch included; with scratch for a split where the form may have one.
 double gemm_mfma_time_us(const GemmArgs& g) {
   const bool edge = !tiles_whole(g.M, g.N, g.K) || b_short(g);
+  if (store_split_ok(g) && gemm_edge_supported(g)) {
+    const GemmSplitPlan plan = store_split_plan(g.M, g.N, g.K);
+    for (const TileClass& tc : kTiles)
+      if (plan.splits > 1 && tc.m == plan.tile_m && tc.n == plan.tile_n && !tc.deep) return 3.0 + tile_time_us(tc, g.M, g.N, g.K, true, plan.splits);
+  }
   auto one = [&](int M, int N) {
     const GemmSplitPlan plan = plan_tiles(M, N, g.K, g.c_f32, g.c_f32 && g.ldc == N, edge, gemm_edge_supported(g));
     for (const TileClass& tc : kTiles)
@@ -369,6 +411,11 @@ GemmRoute gemm_route(const GemmArgs& g, bool scratch) {
   GemmRoute r{gemm_form(g), false, 0, 0, 0, 1, 0, 0, -1};
   if (r.form == GEMM_F32) gemm_f32_tile(g.M, g.N, g.K, &r.tile_m, &r.tile_n);
   if (r.form != GEMM_MFMA && r.form != GEMM_EDGE) return r;
+  if (scratch && store_split_ok(g) && gemm_edge_supported(g)) {
+    const GemmSplitPlan p = store_split_plan(g.M, g.N, g.K);
+    if (p.splits > 1) return GemmRoute{r.form, false, 0, p.tile_m, p.tile_n, p.splits, (g.M + p.tile_m - 1) / p.tile_m, (g.N + p.tile_n - 1) / p.tile_n,
+                                       walk_group((g.M + p.tile_m - 1) / p.tile_m, (g.N + p.tile_n - 1) / p.tile_n, g.K, p.splits)};
+  }
   const bool edge = r.form == GEMM_EDGE;
   r.tail = edge ? 0 : tail_dim(g.M, g.N);
   const int M = r.tail == 1 ? g.M - 128 : g.M, N = r.tail == 2 ? g.N - 128 : g.N;
@@ -388,6 +435,19 @@ void gemm_route_tile(const GemmRoute& r, int item, int* tile_row, int* tile_col)
 
 int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
   const bool edge = !tiles_whole(g0.M, g0.N, g0.K) || b_short(g0);
+  if (store_split_ok(g0) && g0.split_ws && gemm_edge_supported(g0)) {
+    const GemmSplitPlan plan = store_split_plan(g0.M, g0.N, g0.K);
+    if (plan.splits > 1) {
+      GemmArgs g = g0;
+      g.c_f32 = true;
+      g.C = g0.split_ws;
+      const EpiArgs e = epi_args(g, plan);
+      if (edge) FAX_TRY(gemm_mfma_edge(g, e, plan, s));
+      else if (plan.tile_n == 256) FAX_TRY((dispatch<256, 256>(g, e, s)));
+      else FAX_TRY((dispatch<128, 128>(g, e, s)));
+      return fold_partials_bf16(plan.splits, (size_t)g.M * g.N, (const float*)g0.split_ws, g0.C, s);
+    }
+  }
   if (const int td = edge ? 0 : tail_dim(g0.M, g0.N)) {
     const size_t cb = g0.c_f32 ? 4 : 2;
     for (int part = 0; part < 2; part++) {

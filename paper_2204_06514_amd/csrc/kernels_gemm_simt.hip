@@ -102,7 +102,7 @@ int gemm(const GemmArgs& g, hipStream_t s) {
   const GemmRoute r = gemm_route(g, g.split_ws != nullptr);
   char name[64];
   snprintf(name, sizeof(name), "gemm_%s_A%c_B%c_%s%s", r.small ? "mfma" : forms[r.form], g.ta ? 'm' : 'k', g.tb ? 'k' : 'm',
-           g.c_f32 ? "f32out" : g.epi == EPI_GELU ? "gelu" : g.epi == EPI_DGELU ? "dgelu" : "store", r.small ? "_small" : "");
+           g.c_f32 ? "f32out" : g.epi == EPI_GELU ? "gelu" : g.epi == EPI_DGELU ? "dgelu" : "store", r.small ? "_small" : !g.c_f32 && r.splits > 1 ? "_ranges" : "");
   Timed t(name, WORK_FLOP, 2.0 * g.M * g.N * g.K, s);
   return gemm_dispatch(g, s);
 }

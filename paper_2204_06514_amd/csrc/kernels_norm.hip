@@ -484,6 +484,37 @@ int fold_partials(int parts, size_t n, const float* partial, float* out, bool ac
   return FAX_OK;
 }
 
+// The same into bf16, nothing added: one rounding of the whole sum, in the ranges' order.  n a multiple of 4.  Bound by reading the
+// parts (9 x 3108 x 512: 57 MB in 15 us, 3.9 TB/s, most of it from the caches the products wrote through).
+__global__ __launch_bounds__(256) void fold_partials_bf16_kernel(int parts, size_t n4, const float4* __restrict__ partial,
+                                                                 bf16_t* __restrict__ out) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n4) return;
+  float4 s = partial[i];
+#pragma unroll 4
+  for (int p = 1; p < parts; p++) {
+    const float4 v = partial[(size_t)p * n4 + i];
+    s.x += v.x;
+    s.y += v.y;
+    s.z += v.z;
+    s.w += v.w;
+  }
+  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+  *reinterpret_cast<bf16x4*>(out + i * 4) = bf16x4{(__bf16)s.x, (__bf16)s.y, (__bf16)s.z, (__bf16)s.w};
+}
+
+int fold_partials_bf16(int parts, size_t n, const float* partial, void* out, hipStream_t s) {
+  if (n % 4 || (reinterpret_cast<uintptr_t>(partial) & 15) || (reinterpret_cast<uintptr_t>(out) & 7) || n / 1024 > 0x7ff00000) {
+    set_error("fold_partials_bf16: %zu elements, or operands not aligned", n);
+    return FAX_ERR_UNSUPPORTED;
+  }
+  if (n == 0) return FAX_OK;
+  hipLaunchKernelGGL(fold_partials_bf16_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s, parts, n / 4, (const float4*)partial,
+                     (bf16_t*)out);
+  FAX_LAUNCH_CHECK("fold_partials_bf16");
+  return FAX_OK;
+}
+
 static int strips(int rows) { return max(1, min(CS_PARTS, (rows + 3) / 4)); }
 
 static constexpr int LN_BWD_PARTS = 1024;  // workgroups (= partial rows) of the fused LayerNorm backward
