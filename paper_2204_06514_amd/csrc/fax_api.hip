@@ -334,9 +334,7 @@ static int side_stream(SideStream** out) {
   return FAX_OK;
 }
 
-// Products so short that the host cannot keep up with a second stream: its events and waits cost some 85 us a call, on top of the 40 of
-// the launches (fp32 block of 128 tokens x 128: 161 us with the second stream, 95 without; bf16, 512 tokens x 256: 192
-// and 165; where the products' estimate is 150 us, 3108 tokens x 512, it gains 5 %, at 420 us, 2048 x 5120 shares, 5 %).
+// The backward pass's products, by size.
 struct BwdProducts {
   int p[8][4];  // M, N, K, whether a weight gradient
   explicit BwdProducts(const FaxBlockDims& d) {
@@ -347,30 +345,62 @@ struct BwdProducts {
     memcpy(p, all, sizeof(p));
   }
 };
-static bool short_pass(const FaxBlockDims& d) {
+static double products_us(const FaxBlockDims& d) {
   const BwdProducts all(d);
   double us = 0.0;
   for (const auto& g : all.p)
     us += d.dtype == FAX_BF16 ? gemm_time_estimate_us(dense_product(FAX_BF16, g[3], !g[3], g[0], g[1], g[2], g[3]))
                               : 5.0 + 2.0 * g[0] * g[1] * g[2] / 90.0e6;
-  return us < 110.0;
+  return us;
 }
-// When every product of the backward pass is a whole number of rounds of one workgroup per CU
-// (the 4096-wide block: 256 to 2048 tiles each), the second stream has nothing to fill and the
-// kernels would only take turns: everything then stays on the caller's stream.
-static bool use_side_stream(const FaxBlockDims& d) {
-  if ((d.flags & FAX_FLAG_SINGLE_STREAM) || short_pass(d)) return false;
-  if (d.dtype != FAX_BF16) return true;
-  constexpr long long kCUs = 256;
+
+// The second stream fills the places that the products' last rounds leave empty, at some 20 us a call for its events and waits.  Everything
+// stays on the caller's stream where there is nothing to fill and the kernels would only take turns (us, two streams and one; in bf16,
+// a forward and backward pass of tokens x width, F = 4 x width, unless stated):
+//   every product whole rounds of one workgroup per CU: the 4096-wide block (256 to 2048 tiles each) 8120 either way;
+//   all weight gradients in shared launches, and the input gradients whole rounds of tiles 256 rows high, 8192 x 1024 843 and 834, two layers
+//     of it with the update 1818 and 1772, 16384 x 1024 with heads of 128 1773 and 1727;  on the other side 8192 x 3200 (an eighth idle)
+//     3578 and 3596, 16384 x 2304 3442 and 3457;
+//   all weight gradients in shared launches, and products of less than 200 us that leave under a tenth idle, 2048 x 1024 346 and 325;  on the
+//     other side 4096 x 1024 (312 us) 452 and 466, 3108 x 512 (a fifth idle) 253 and 268, 4096 x 512 (separate launches), two layers, 570 and 588.
+// groups: the weight gradients that share a launch.  By the sizes alone, so that one or two streams give the same bits.
+struct BwdPlan { bool side; int groups; };
+static BwdPlan bwd_plan(const FaxBlockDims& d) {
+  const bool may = !(d.flags & FAX_FLAG_SINGLE_STREAM);
+  const double us = products_us(d);
+  // Products so short that the host cannot keep up with a second stream: its events and waits cost some 85 us a call, on top of the 40 of
+  // the launches (fp32 block of 128 tokens x 128: 161 us with the second stream, 95 without; bf16, 512 tokens x 256: 192
+  // and 165; where the products' estimate is 150 us, 3108 tokens x 512, it gains 5 %, at 420 us, 2048 x 5120 shares, 5 %).
+  if (us < 110.0) return BwdPlan{false, 0};
+  if (d.dtype != FAX_BF16) return BwdPlan{may, 0};
   const BwdProducts all(d);
-  for (const auto& g : all.p) {
-    int tail = 0;
-    const GemmSplitPlan p = gemm_plan_query(g[0], g[1], g[2], g[3] != 0, &tail);
-    if (tail || p.tile_m == 0) return true;
-    const long long items = (long long)(g[0] / p.tile_m) * (g[1] / p.tile_n) * p.splits;
-    if (items % kCUs) return true;
+  GemmArgs w[4], in[4];
+  static const int order[8] = {0, 1, 3, 2, 4, 5, 6, 7};  // FFN out and in, QKV, attention out
+  for (int i = 0; i < 8; i++) {
+    const int* g = all.p[order[i]];
+    GemmArgs& a = i < 4 ? w[i] : in[i - 4];
+    a = dense_product(FAX_BF16, g[3], !g[3], g[0], g[1], g[2], g[3]);
+    if (g[3]) {  // marks what the pass will ask for; nothing is read
+      a.colsum = reinterpret_cast<float*>(16);
+      a.split_ws = reinterpret_cast<void*>(16);
+    }
   }
-  return false;
+  const int groups = gemm_groups(w, in);
+  if (!may) return BwdPlan{false, groups};
+  bool rounds = true;
+  if (groups == GROUP_ALL || groups == (GROUP_FFN | GROUP_ATTENTION)) {
+    for (const GemmArgs& g : in) rounds = rounds && gemm_fill(g).rounds;
+    if (!rounds && us < 200.0) {
+      double idle = 0.0;
+      for (const GemmArgs& g : w) idle += gemm_fill(g).idle * gemm_time_estimate_us(g);
+      for (const GemmArgs& g : in) idle += gemm_fill(g).idle * gemm_time_estimate_us(g);
+      rounds = idle < 0.1 * us;
+    }
+  } else {
+    for (const GemmArgs& g : in) rounds = rounds && gemm_fill(g).idle == 0.0;
+    for (const GemmArgs& g : w) rounds = rounds && gemm_fill(g).idle == 0.0;
+  }
+  return BwdPlan{!rounds, groups};
 }
 
 // ---- block backward -------------------------------------------------------------------------
@@ -391,7 +421,8 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
   void* red = ws + W.red;
 
   SideStream* side = nullptr;
-  if (use_side_stream(d)) FAX_TRY(side_stream(&side));
+  const BwdPlan plan = bwd_plan(d);
+  if (plan.side) FAX_TRY(side_stream(&side));
   std::unique_lock<std::mutex> side_lock;
   if (side) side_lock = std::unique_lock<std::mutex>(side->mu);
   hipStream_t sw = side ? side->s : s;  // where the weight gradients go
@@ -434,11 +465,9 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
   const GemmArgs d1 = dgrad(du, F, F, p.w1, F, D, dh2), d_o = dgrad(dx1, D, D, p.wo, D, Hd, dctx), dqkv1 = dgrad(dqkv, 3 * Hd, 3 * Hd, p.wqkv, 3 * Hd, D, dh1);
   // Weight gradients in one launch (gemm_group): all four behind the last input gradient, where every input gradient fills the chip by
   // itself and a weight gradient run beside it only takes turns with it; otherwise the feed-forward's two as soon as the second's upstream
-  // gradient is there, and attention's two behind theirs.  By the sizes alone, so that one or two streams give the same bits.
-  const GemmArgs all[4] = {w2, w1, wqkv, wo}, in[4] = {d2, d1, d_o, dqkv1};
-  const bool apart = short_pass(d);
-  const bool group = !apart && gemm_group_pays(GROUP_ALL, all, in);
-  const bool ffn = !apart && !group && gemm_group_pays(GROUP_FFN, all, in), att = !apart && !group && gemm_group_pays(GROUP_ATTENTION, all, in);
+  // gradient is there, and attention's two behind theirs.
+  const GemmArgs all[4] = {w2, w1, wqkv, wo};
+  const bool group = plan.groups == GROUP_ALL, ffn = plan.groups & GROUP_FFN, att = plan.groups & GROUP_ATTENTION;
   auto layer = [&](const GemmArgs& w, const GemmArgs& g, bool in_group) -> int { return in_group ? gemm(g, s) : both(w, g, &w == &w2); };
 
   // feed-forward output projection
@@ -660,7 +689,7 @@ int fax_block_workspace_bytes(const FaxBlockDims* dims, size_t* out) {
 int fax_block_bwd_streams(const FaxBlockDims* dims, int* out) {
   FAX_TRY(check_dims(dims));
   if (!out) { set_error("out is NULL"); return FAX_ERR_INVALID_ARG; }
-  *out = use_side_stream(*dims) ? 2 : 1;
+  *out = bwd_plan(*dims).side ? 2 : 1;
   return FAX_OK;
 }
 

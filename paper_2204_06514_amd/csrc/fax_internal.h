@@ -117,6 +117,12 @@ struct GemmRoute {
   int tail, tile_m, tile_n, splits, tiles_m, tiles_n, group;
 };
 GemmRoute gemm_route(const GemmArgs& g, bool scratch);
+// How a product fills the chip: the share of its rounds' places that no tile takes; whether it is whole rounds of tiles 256 rows high.
+struct GemmFill {
+  double idle;
+  bool rounds;
+};
+GemmFill gemm_fill(const GemmArgs& g);
 // Work item -> tile of that walk.
 void gemm_route_tile(const GemmRoute& r, int item, int* tile_row, int* tile_col);
 int gemm_mfma(const GemmArgs& g, hipStream_t s);
@@ -131,10 +137,10 @@ int gemm_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s);
 
 // Weight gradients of a layer (with column sums, over the same tokens) in one launch.
 int gemm_group(const GemmArgs* g, int n, hipStream_t s);
-// Whether that pays: for all four (w: FFN output, FFN input, QKV, attention output; in: the input gradients of the same layers' projections, in
-// order of execution), for the first two, for the last two.  Host only.
-enum GemmGroup { GROUP_ALL, GROUP_FFN, GROUP_ATTENTION };
-bool gemm_group_pays(GemmGroup which, const GemmArgs (&w)[4], const GemmArgs (&in)[4]);
+// For which that pays, GROUP_* added up: all four (w: FFN output, FFN input, QKV, attention output; in: the input gradients of the same layers' projections, in
+// order of execution), the first two, the last two.  Host only.
+enum GemmGroup { GROUP_FFN = 1, GROUP_ATTENTION = 2, GROUP_ALL = 4 };
+int gemm_groups(const GemmArgs (&w)[4], const GemmArgs (&in)[4]);
 int gemm_mfma_group(const GemmArgs* g, int n, const EpiArgs* e, int tile, bool edge, hipStream_t s);
 
 // ---- LayerNorm, column sums ---------------------------------------------------------------

@@ -313,6 +313,34 @@ int gemm_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s) {
   return gemm_mfma_deep_pair(w, epi_args(w, wp), wp, d, epi_args(d, dp), dp, s);
 }
 
+// Launch included; with scratch for a split where the form may have one.
+// small: whether (the bulk of) it takes the small-tile form.
+static double mfma_time_us(const GemmArgs& g, bool* small) {
+  *small = false;
+  const bool edge = !tiles_whole(g.M, g.N, g.K) || b_short(g);
+  if (store_split_ok(g) && gemm_edge_supported(g)) {
+    const GemmSplitPlan plan = store_split_plan(g.M, g.N, g.K);
+    for (const TileClass& tc : kTiles)
+      if (plan.splits > 1 && tc.m == plan.tile_m && tc.n == plan.tile_n && !tc.deep) return 3.0 + tile_time_us(tc, g.M, g.N, g.K, true, plan.splits);
+  }
+  auto one = [&](int M, int N, bool bulk) {
+    const GemmSplitPlan plan = plan_tiles(M, N, g.K, g.c_f32, g.c_f32 && g.ldc == N, edge, gemm_edge_supported(g));
+    if (bulk) *small = plan.deep;
+    for (const TileClass& tc : kTiles)
+      if (tc.m == plan.tile_m && tc.n == plan.tile_n && tc.deep == plan.deep) return 3.0 + tile_time_us(tc, M, N, g.K, g.c_f32, plan.splits);
+    return 0.0;
+  };
+  switch (edge ? 0 : tail_dim(g.M, g.N)) {
+    case 1: return one(g.M - 128, g.N, true) + one(128, g.N, false);
+    case 2: return one(g.M, g.N - 128, true) + one(g.M, 128, false);
+  }
+  return one(g.M, g.N, true);
+}
+double gemm_mfma_time_us(const GemmArgs& g) {
+  bool small;
+  return mfma_time_us(g, &small);
+}
+
 // Weight gradients of one layer in one launch, whose tiles share the rounds: by themselves each ends in a partly filled one, takes tiles
 // too small for it, or cuts its contraction and folds.  The class with the smaller predicted time.
 struct GroupPlan { int tile; bool edge; double us; };
@@ -347,27 +375,31 @@ static bool group_plan(const GemmArgs* g, int n, GroupPlan* plan) {
 // Attention's two: at 128^2 tiles, and not much longer than the QKV one alone (the other one would start before the attention kernels and run
 //   beside them).  4096 x 1024 470 -> 449, 2222 x 1280 563 -> 552, 4096 x 768 380 -> 372; beyond the line 3108 x 512 271 and 277, 1999 x
 //   2000 843 and 854, 3600 x 1536 908 and 915.
-bool gemm_group_pays(GemmGroup which, const GemmArgs (&w)[4], const GemmArgs (&in)[4]) {
-  GemmSplitPlan p;
+int gemm_groups(const GemmArgs (&w)[4], const GemmArgs (&in)[4]) {
   bool pairs = true, full = true;
   for (int i = 0; i < 4; i++) {
     const GemmArgs& g = in[i];
-    if (!gemm_edge_supported(g)) return false;
-    const GemmArgs& same = i < 2 ? w[i] : w[5 - i];  // the weight gradient of this layer
-    pairs = pairs && gemm_pair_supported(same, g);
-    p = plan_tiles(g.M, g.N, g.K, false, false, !tiles_whole(g.M, g.N, g.K), true);
-    full = full && p.tile_m == 256 && (long long)((g.M + 255) / 256) * ((g.N + p.tile_n - 1) / p.tile_n) >= kCUs;
+    if (!gemm_edge_supported(g)) return 0;
+    pairs = pairs && gemm_pair_supported(i < 2 ? w[i] : w[5 - i], g);  // with the weight gradient of this layer
+    if (!full) continue;
+    const GemmSplitPlan p = plan_tiles(g.M, g.N, g.K, false, false, !tiles_whole(g.M, g.N, g.K), true);
+    full = p.tile_m == 256 && (long long)((g.M + 255) / 256) * ((g.N + p.tile_n - 1) / p.tile_n) >= kCUs;
   }
-  if (pairs) return false;  // short products: one launch for a layer's weight and input gradient instead
-  const int first = which == GROUP_ATTENTION ? 2 : 0, n = which == GROUP_ALL ? 4 : 2;
-  GroupPlan plan;
-  if (!group_plan(w + first, n, &plan)) return false;
-  double apart = 0.0;
-  for (int i = first; i < first + n; i++)
-    apart += gemm_mfma_time_us(w[i]) * (gemm_route(w[i], true).small ? 1.3 : 1.0);
-  if (which == GROUP_ALL) return full && plan.tile == 256 && plan.us < 0.7 * apart;
-  if (which == GROUP_FFN) return plan.us < (plan.edge ? 0.76 : 0.97) * apart;
-  return plan.tile == 128 && plan.us < 0.97 * apart && plan.us < 1.45 * gemm_mfma_time_us(w[2]);
+  if (pairs) return 0;  // short products: one launch for a layer's weight and input gradient instead
+  GroupPlan all, ffn, att;
+  if (!group_plan(w, 4, &all)) return 0;
+  group_plan(w, 2, &ffn);
+  group_plan(w + 2, 2, &att);
+  double apart[4];
+  for (int i = 0; i < 4; i++) {
+    bool small;
+    apart[i] = mfma_time_us(w[i], &small);
+    if (i == 2 && !(att.us < 1.45 * apart[2])) att.tile = 0;
+    if (small) apart[i] *= 1.3;
+  }
+  if (full && all.tile == 256 && all.us < 0.7 * (apart[0] + apart[1] + apart[2] + apart[3])) return GROUP_ALL;
+  return (ffn.us < (ffn.edge ? 0.76 : 0.97) * (apart[0] + apart[1]) ? GROUP_FFN : 0) |
+         (att.tile == 128 && att.us < 0.97 * (apart[2] + apart[3]) ? GROUP_ATTENTION : 0);
 }
 
 int gemm_group(const GemmArgs* g, int n, hipStream_t s) {
@@ -384,27 +416,6 @@ int gemm_group(const GemmArgs* g, int n, hipStream_t s) {
   }
   Timed t("gemm_mfma_group", WORK_FLOP, work, s);
   return gemm_mfma_group(g, n, e, plan.tile, plan.edge, s);
-}
-
-// Launch included; with scratch for a split where the form may have one.
-double gemm_mfma_time_us(const GemmArgs& g) {
-  const bool edge = !tiles_whole(g.M, g.N, g.K) || b_short(g);
-  if (store_split_ok(g) && gemm_edge_supported(g)) {
-    const GemmSplitPlan plan = store_split_plan(g.M, g.N, g.K);
-    for (const TileClass& tc : kTiles)
-      if (plan.splits > 1 && tc.m == plan.tile_m && tc.n == plan.tile_n && !tc.deep) return 3.0 + tile_time_us(tc, g.M, g.N, g.K, true, plan.splits);
-  }
-  auto one = [&](int M, int N) {
-    const GemmSplitPlan plan = plan_tiles(M, N, g.K, g.c_f32, g.c_f32 && g.ldc == N, edge, gemm_edge_supported(g));
-    for (const TileClass& tc : kTiles)
-      if (tc.m == plan.tile_m && tc.n == plan.tile_n && tc.deep == plan.deep) return 3.0 + tile_time_us(tc, M, N, g.K, g.c_f32, plan.splits);
-    return 0.0;
-  };
-  switch (edge ? 0 : tail_dim(g.M, g.N)) {
-    case 1: return one(g.M - 128, g.N) + one(128, g.N);
-    case 2: return one(g.M, g.N - 128) + one(g.M, 128);
-  }
-  return one(g.M, g.N);
 }
 
 GemmRoute gemm_route(const GemmArgs& g, bool scratch) {
@@ -427,6 +438,15 @@ GemmRoute gemm_route(const GemmArgs& g, bool scratch) {
   const int nt = r.tiles_m * r.tiles_n, slots = (p.tile_m == 128 && nt * p.splits <= 2 * kCUs) ? 2 * kCUs : kCUs;
   if (r.group == 0 && (p.deep || std::min(nt * p.splits, slots) != 256)) r.group = 4;  // as launch_mfma and launch_deep decide
   return r;
+}
+
+GemmFill gemm_fill(const GemmArgs& g) {
+  const GemmRoute r = gemm_route(g, true);
+  if (r.form != GEMM_MFMA && r.form != GEMM_EDGE) return GemmFill{1.0, false};
+  const long long items = (long long)r.tiles_m * r.tiles_n * r.splits;
+  const long long slots = r.tile_m == 128 && !r.small && items > kCUs && items <= 2 * kCUs ? 2 * kCUs : kCUs;
+  const long long rounds = (items + slots - 1) / slots;
+  return GemmFill{std::max(1.0 - (double)items / (double)(rounds * slots), r.tail ? 0.05 : 0.0), !r.tail && r.tile_m == 256 && items % kCUs == 0};
 }
 
 void gemm_route_tile(const GemmRoute& r, int item, int* tile_row, int* tile_col) {
