@@ -1,7 +1,7 @@
 // LayerNorm forward/backward and column sums: HBM-bound kernels.
 //
 // Forward reads each row once (16-byte loads, row cached in registers), writes it once.
-// Backward is one pass as well: a workgroup walks over row blocks, reads dh and x once, writes dx
+// Backward is one pass as well: a workgroup walks over row blocks with the next block's row in flight, reads dh and x once, writes dx
 // once and keeps running per-column sums of dh * xhat and dh in registers; each workgroup leaves
 // one partial row of dgamma and of dbeta, and a second small kernel folds the partial rows in a
 // fixed order, so no result depends on scheduling order.  (Row lengths the vector kernels do not
@@ -10,7 +10,7 @@
 
 namespace fax {
 
-static constexpr int LN_MAXV = 8;      // 16-byte vectors cached per thread
+static constexpr int LN_MAXV = 8;      // 16-byte vectors of a row per 256 threads
 static constexpr int LN_THREADS = 256;
 static constexpr int CS_PARTS = 128;   // row strips of the column-sum kernels
 
@@ -31,7 +31,10 @@ __device__ __forceinline__ float row_sum(float v, float* red /* [LN_THREADS/64] 
   return s;
 }
 
-template <typename T, int TPR>
+// NV: 16-byte vectors per thread (D <= TPR * NV * V::N).  x, gamma and beta are requested together: fetched after the two sums, the
+// parameters' trip to the caches stood between them and the stores.  Bound by memory: bf16, 65536 x 768 36 -> 31 us (6.4 TB/s), 16384 x 768
+// 12.2 -> 10.4, 8192 x 2048 14.1 -> 11.8.
+template <typename T, int TPR, int NV>
 __global__ __launch_bounds__(LN_THREADS) void ln_fwd_kernel(int rows, int D, const T* __restrict__ x,
                                                             const T* __restrict__ gamma,
                                                             const T* __restrict__ beta, float eps,
@@ -44,14 +47,20 @@ __global__ __launch_bounds__(LN_THREADS) void ln_fwd_kernel(int rows, int D, con
   const int row = blockIdx.x * RPB + threadIdx.x / TPR;
   const bool live = row < rows;
   const int nvec = D / V::N;
-  V xv[LN_MAXV];
+  V xv[NV], gv[NV], bv[NV];
   float s = 0.f;
   const T* xr = x + (size_t)(live ? row : 0) * D;
 #pragma unroll
-  for (int i = 0; i < LN_MAXV; i++) {
-    int c = tr + i * TPR;
-    if (c < nvec) {
-      xv[i].load(xr + c * V::N);
+  for (int i = 0; i < NV; i++) xv[i].load(xr + min(tr + i * TPR, nvec - 1) * V::N);
+#pragma unroll
+  for (int i = 0; i < NV; i++) {
+    const int c = min(tr + i * TPR, nvec - 1) * V::N;
+    gv[i].load(gamma + c);
+    bv[i].load(beta + c);
+  }
+#pragma unroll
+  for (int i = 0; i < NV; i++) {
+    if (tr + i * TPR < nvec) {
 #pragma unroll
       for (int e = 0; e < V::N; e++) s += xv[i].get(e);
     }
@@ -59,9 +68,8 @@ __global__ __launch_bounds__(LN_THREADS) void ln_fwd_kernel(int rows, int D, con
   const float mean = row_sum<TPR>(s, red) / D;
   float q = 0.f;
 #pragma unroll
-  for (int i = 0; i < LN_MAXV; i++) {
-    int c = tr + i * TPR;
-    if (c < nvec) {
+  for (int i = 0; i < NV; i++) {
+    if (tr + i * TPR < nvec) {
 #pragma unroll
       for (int e = 0; e < V::N; e++) {
         float d = xv[i].get(e) - mean;
@@ -78,14 +86,12 @@ __global__ __launch_bounds__(LN_THREADS) void ln_fwd_kernel(int rows, int D, con
   }
   T* hr = h + (size_t)row * D;
 #pragma unroll
-  for (int i = 0; i < LN_MAXV; i++) {
-    int c = tr + i * TPR;
+  for (int i = 0; i < NV; i++) {
+    const int c = tr + i * TPR;
     if (c < nvec) {
-      V g, b, o;
-      g.load(gamma + c * V::N);
-      b.load(beta + c * V::N);
+      V o;
 #pragma unroll
-      for (int e = 0; e < V::N; e++) o.set(e, (xv[i].get(e) - mean) * r * g.get(e) + b.get(e));
+      for (int e = 0; e < V::N; e++) o.set(e, (xv[i].get(e) - mean) * r * gv[i].get(e) + bv[i].get(e));
       o.store(hr + c * V::N);
     }
   }
@@ -125,16 +131,17 @@ static int ln_fwd_t(int rows, int D, const T* x, const T* gamma, const T* beta, 
   constexpr int VN = Vec16<T>::N;
   const int nvec = D / VN;
   if (D % VN == 0 && nvec <= 256 * LN_MAXV) {
-    if (nvec <= 64 * LN_MAXV / 2) {
-      hipLaunchKernelGGL((ln_fwd_kernel<T, 64>), dim3((rows + 3) / 4), dim3(LN_THREADS), 0, s, rows, D, x, gamma, beta,
-                         eps, h, mu, rstd);
-    } else if (nvec <= 128 * LN_MAXV / 2) {
-      hipLaunchKernelGGL((ln_fwd_kernel<T, 128>), dim3((rows + 1) / 2), dim3(LN_THREADS), 0, s, rows, D, x, gamma, beta,
-                         eps, h, mu, rstd);
-    } else {
-      hipLaunchKernelGGL((ln_fwd_kernel<T, 256>), dim3(rows), dim3(LN_THREADS), 0, s, rows, D, x, gamma, beta, eps, h, mu,
-                         rstd);
-    }
+#define FAX_LN_FWD(TPR, NV)                                                                                              \
+  hipLaunchKernelGGL((ln_fwd_kernel<T, TPR, NV>), dim3((rows + LN_THREADS / TPR - 1) / (LN_THREADS / TPR)), dim3(LN_THREADS), \
+                     0, s, rows, D, x, gamma, beta, eps, h, mu, rstd)
+    if (nvec <= 64) FAX_LN_FWD(64, 1);
+    else if (nvec <= 64 * 2) FAX_LN_FWD(64, 2);
+    else if (nvec <= 64 * 4) FAX_LN_FWD(64, 4);
+    else if (nvec <= 128 * 4) FAX_LN_FWD(128, 4);
+    else if (nvec <= 256 * 4) FAX_LN_FWD(256, 4);
+    else if (nvec <= 256 * 6) FAX_LN_FWD(256, 6);
+    else FAX_LN_FWD(256, LN_MAXV);
+#undef FAX_LN_FWD
   } else {
     hipLaunchKernelGGL((ln_fwd_generic_kernel<T>), dim3((rows + 3) / 4), dim3(LN_THREADS), 0, s, rows, D, x, gamma, beta,
                        eps, h, mu, rstd);
@@ -160,17 +167,23 @@ int ln_fwd(int dtype, int rows, int D, const void* x, const void* gamma, const v
 // (-> dbeta) for the columns it owns; dh and x are read once for all three results.  At the end
 // the row groups of the workgroup are combined through LDS and one partial row per workgroup is
 // written: partial[0][blockIdx.x][D] (dgamma), partial[1][blockIdx.x][D] (dbeta).
-// NV: 16-byte vectors per thread and row (D <= TPR * NV * V::N).
-template <typename T, int TPR, int NV>
-__global__ __launch_bounds__(LN_THREADS) void ln_bwd_fused_kernel(int rows, int D, const T* __restrict__ dh,
-                                                                  const T* __restrict__ x, const float* __restrict__ mu,
-                                                                  const float* __restrict__ rstd,
-                                                                  const T* __restrict__ gamma, const T* __restrict__ dres,
-                                                                  T* __restrict__ dx, float* __restrict__ partial) {
+constexpr int ln_bwd_threads(int tpr) { return tpr > LN_THREADS ? tpr : LN_THREADS; }
+// NV: 16-byte vectors per thread and row (D <= TPR * NV * V::N).  RES: dx = ... + dres.
+// Bound by memory once enough of it is in flight: a row's loads stood behind the previous row's two sums and its residual behind its own, at
+// two to four workgroups a CU.  So the next row (residual included) is requested before the current one is worked on.  Threads per row are
+// chosen for at most four vectors each, which is what the registers of two waves per SIMD hold twice beside the running sums.  With the
+// fold, us: bf16, 16384 x 768 30 -> 24, 16384 x 2560 91 -> 73, 8192 x 4096 63 -> 53, 8192 x 8192 154 -> 117, 16384 x 12288 408 -> 313
+// (5.2 TB/s), 65536 x 768 90 -> 83; fp32, 8192 x 768 29 -> 22, 2048 x 5120 37 -> 32.
+template <typename T, int TPR, int NV, bool RES>
+__global__ __launch_bounds__(ln_bwd_threads(TPR)) void ln_bwd_fused_kernel(int rows, int D, const T* __restrict__ dh,
+                                                                           const T* __restrict__ x, const float* __restrict__ mu,
+                                                                           const float* __restrict__ rstd,
+                                                                           const T* __restrict__ gamma, const T* __restrict__ dres,
+                                                                           T* __restrict__ dx, float* __restrict__ partial) {
   using V = Vec16<T>;
-  constexpr int RPB = LN_THREADS / TPR;
+  constexpr int THREADS = ln_bwd_threads(TPR), RPB = THREADS / TPR;
   constexpr int NACC = NV * V::N * 2;  // running sums per thread
-  __shared__ float red[LN_THREADS / 64];
+  __shared__ float2 red[2][THREADS / 64];
   __shared__ float comb[RPB > 1 ? (RPB - 1) * NACC * TPR : 1];
   const int tr = threadIdx.x % TPR, rg = threadIdx.x / TPR;
   const int nvec = D / V::N;
@@ -179,46 +192,87 @@ __global__ __launch_bounds__(LN_THREADS) void ln_bwd_fused_kernel(int rows, int 
   for (int i = 0; i < NV; i++)
 #pragma unroll
     for (int e = 0; e < V::N; e++) ag[i][e] = ab[i][e] = 0.f;
+  V gv[NV];
+#pragma unroll
+  for (int i = 0; i < NV; i++) gv[i].load(gamma + min(tr + i * TPR, nvec - 1) * V::N);
+  struct Row {
+    V d[NV], x[NV], r[RES ? NV : 1];
+    float m, rstd;
+  };
+  auto request = [&](int rb, Row& w) {  // without a branch around a load: places beyond the rows or the row's end read the last one
+    const int row = (int)min((unsigned)rb * RPB + rg, (unsigned)rows - 1);
+    const size_t off = (size_t)row * D;
+    w.m = mu[row];
+    w.rstd = rstd[row];
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+      const size_t c = off + min(tr + i * TPR, nvec - 1) * V::N;
+      w.d[i].load(dh + c);
+      w.x[i].load(x + c);
+      if (RES) w.r[i].load(dres + c);
+    }
+  };
+  auto opaque = [](V& v) {  // what was unpacked from it is unpacked again, not kept
+    unsigned* w = reinterpret_cast<unsigned*>(&v.raw);
+    asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]));
+  };
+  int turn = 0;
+  // sums over the TPR threads of a row, both in one exchange
+  auto row_sums = [&](float& a, float& b) {
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if constexpr (TPR > 64) {
+      const int wave = threadIdx.x >> 6;
+      if ((threadIdx.x & 63) == 0) red[turn][wave] = make_float2(a, b);
+      __syncthreads();
+      constexpr int WPR = TPR / 64;
+      const int w0 = (wave / WPR) * WPR;
+      a = b = 0.f;
+#pragma unroll
+      for (int i = 0; i < WPR; i++) {
+        a += red[turn][w0 + i].x;
+        b += red[turn][w0 + i].y;
+      }
+      turn ^= 1;  // the next exchange's barrier lies between these reads and the next writes here
+    }
+  };
+  Row cur;
+  request(blockIdx.x, cur);
   for (int rb = blockIdx.x; rb * RPB < rows; rb += gridDim.x) {  // trip count uniform over the workgroup
+    Row next;
+    request(rb + gridDim.x, next);
     const int row = rb * RPB + rg;
-    const bool live = row < rows;
-    const size_t off = (size_t)(live ? row : 0) * D;
-    const float m = live ? mu[row] : 0.f, r = live ? rstd[row] : 0.f;
-    V dv[NV], xv[NV];
+    const float m = cur.m, r = cur.rstd;
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; i++) {
-      const int c = tr + i * TPR;
-      if (c < nvec) {
-        V gv;
-        gv.load(gamma + c * V::N);
-        dv[i].load(dh + off + c * V::N);
-        xv[i].load(x + off + c * V::N);
+      if (tr + i * TPR < nvec) {
 #pragma unroll
         for (int e = 0; e < V::N; e++) {
-          const float xh = (xv[i].get(e) - m) * r;
-          const float g = dv[i].get(e) * gv.get(e);
+          const float xh = (cur.x[i].get(e) - m) * r;
+          const float g = cur.d[i].get(e) * gv[i].get(e);
           s1 += g;
           s2 += g * xh;
         }
       }
     }
-    const float m1 = row_sum<TPR>(s1, red) / D;
-    const float m2 = row_sum<TPR>(s2, red) / D;
-    if (live) {
+    row_sums(s1, s2);
+    const float m1 = s1 / D, m2 = s2 / D;
+    if (row < rows) {
+      const size_t off = (size_t)row * D;
 #pragma unroll
       for (int i = 0; i < NV; i++) {
         const int c = tr + i * TPR;
         if (c < nvec) {
-          V gv, o, rv;
-          gv.load(gamma + c * V::N);
-          if (dres) rv.load(dres + off + c * V::N);
+          opaque(cur.d[i]);
+          opaque(cur.x[i]);
+          V o;
 #pragma unroll
           for (int e = 0; e < V::N; e++) {
-            const float xh = (xv[i].get(e) - m) * r;
-            const float dhe = dv[i].get(e);
-            float d = r * (dhe * gv.get(e) - m1 - xh * m2);
-            if (dres) d += rv.get(e);
+            const float xh = (cur.x[i].get(e) - m) * r;
+            const float dhe = cur.d[i].get(e);
+            float d = r * (dhe * gv[i].get(e) - m1 - xh * m2);
+            if (RES) d += cur.r[RES ? i : 0].get(e);
             o.set(e, d);
             ag[i][e] += dhe * xh;
             ab[i][e] += dhe;
@@ -227,6 +281,7 @@ __global__ __launch_bounds__(LN_THREADS) void ln_bwd_fused_kernel(int rows, int 
         }
       }
     }
+    cur = next;
   }
   if (RPB > 1) {
     __syncthreads();
@@ -535,25 +590,31 @@ static int ln_bwd_t(int rows, int D, const T* dh, const T* x, const float* mu, c
     // workgroup that is 2 / R on top of the rows' own traffic.  Eight row blocks per workgroup, fewer
     // (down to two) while that leaves less than two workgroups per CU: with few tokens the
     // parallelism is worth more than the partial rows cost (2048 x 5120: 43 -> 31 us).
-    auto grid = [&](int rpb) {
+    // And no more workgroups than the chip holds at once (by their registers): 1024 of the three a CU were a round and a third, 16384 x 1536
+    // 43 us instead of 40.
+    auto grid = [&](int rpb, int tpr, int nv) {
+      const int most = tpr == 512 ? 256 : nv <= 2 ? (VN == 8 ? 768 : 1024) : VN == 4 && nv == 3 ? 768 : 512;
       int per_wg = 8;
       while (per_wg > 2 && rows / (per_wg * rpb) < 512) per_wg /= 2;
-      return parts = max(1, min(LN_BWD_PARTS, (rows + per_wg * rpb - 1) / (per_wg * rpb)));
+      return parts = max(1, min(most, (rows + per_wg * rpb - 1) / (per_wg * rpb)));
     };
     // threads per row and vectors per thread: as few registers as the row length allows, so that
     // several workgroups fit on a CU
-#define FAX_LN_BWD_FUSED(TPR, NV)                                                                                   \
-  hipLaunchKernelGGL((ln_bwd_fused_kernel<T, TPR, NV>), dim3(grid(LN_THREADS / TPR)), dim3(LN_THREADS), 0, s, rows, D, \
-                     dh, x, mu, rstd, gamma, dres, dx, partial)
-    if (nvec <= 64 * 2) FAX_LN_BWD_FUSED(64, 2);
-    else if (nvec <= 128 * 2) FAX_LN_BWD_FUSED(128, 2);  // D = 2048: twice the workgroups of (64, 4) at two thirds of its registers
-    else if (nvec <= 256 * 2) FAX_LN_BWD_FUSED(256, 2);
-    else if (nvec <= 256 * 3) FAX_LN_BWD_FUSED(256, 3);
-    else if (nvec <= 256 * 4) FAX_LN_BWD_FUSED(256, 4);
-    else if (nvec <= 256 * 5) FAX_LN_BWD_FUSED(256, 5);
-    else if (nvec <= 256 * 6) FAX_LN_BWD_FUSED(256, 6);
-    else FAX_LN_BWD_FUSED(256, LN_MAXV);
+#define FAX_LN_BWD_LAUNCH(TPR, NV, RES)                                                                            \
+  hipLaunchKernelGGL((ln_bwd_fused_kernel<T, TPR, NV, RES>), dim3(grid(ln_bwd_threads(TPR) / TPR, TPR, NV)),       \
+                     dim3(ln_bwd_threads(TPR)), 0, s, rows, D, dh, x, mu, rstd, gamma, dres, dx, partial)
+#define FAX_LN_BWD_FUSED(TPR, NV)                        \
+  if (dres) FAX_LN_BWD_LAUNCH(TPR, NV, true);            \
+  else FAX_LN_BWD_LAUNCH(TPR, NV, false)
+    if (nvec <= 64 * 2) { FAX_LN_BWD_FUSED(64, 2); }
+    else if (nvec <= 128 * 2) { FAX_LN_BWD_FUSED(128, 2); }  // D = 2048: twice the workgroups of (64, 4) at two thirds of its registers
+    else if (nvec <= 256 * 2) { FAX_LN_BWD_FUSED(256, 2); }
+    else if (nvec <= 256 * 3) { FAX_LN_BWD_FUSED(256, 3); }
+    else if (nvec <= 256 * 4) { FAX_LN_BWD_FUSED(256, 4); }
+    else if (nvec <= 512 * 3) { FAX_LN_BWD_FUSED(512, 3); }
+    else { FAX_LN_BWD_FUSED(512, 4); }
 #undef FAX_LN_BWD_FUSED
+#undef FAX_LN_BWD_LAUNCH
     FAX_LAUNCH_CHECK("ln_bwd_fused");
     // The fold only feeds the parameter gradients, nothing further down the backward pass: given a
     // second stream it goes there, behind an event that marks the partial rows complete.
