@@ -441,6 +441,7 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
     g.dtype = d.dtype; g.ta = false; g.tb = true;
     g.M = T; g.N = Kdim; g.K = Ndim;
     g.A = grad; g.lda = lda; g.B = w; g.ldb = ldw; g.C = out; g.ldc = Kdim;
+    g.beside = side != nullptr;
     return g;
   };
   // a layer's two products: on one stream each, or, on the caller's stream, in one launch where that is offered

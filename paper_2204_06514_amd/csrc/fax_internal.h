@@ -51,6 +51,7 @@ struct GemmArgs {
   void* C2 = nullptr; int ldc2 = 0;
   const void* U = nullptr; int ldu = 0;
   int gelu_form = FAX_GELU_TANH;
+  bool beside = false;  // another stream's kernels run beside it
   bool value_only = false;  // EPI_GELU: nobody reads the derivative, C need not be written (not every kernel makes use of that)
   int path = PATH_AUTO;
   // Optional by-product, B stored [K, N] only: colsum[n] (+)= sum over k of B[k, n] (`accumulate`

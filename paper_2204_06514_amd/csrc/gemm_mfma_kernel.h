@@ -60,10 +60,10 @@ struct TileLds {
 // eight different groups of the 256-byte bank window: bits 0-1 of kr go to bits 1-2 of the XOR
 // (four rows, two apart), bit 3 of kr to bit 0.
 // A 64-wide operand has four groups per k-row and two k-rows per bank window: bit 0 of kr picks the half of the window
-// already, bit 1 goes to bit 1 of the XOR.
+// already, bit 1 goes to bit 1 of the XOR.  The same for a 192-wide one, whose k-rows are a window and a half long.
 template <int ROWS>
 __device__ __forceinline__ int mc_swizzle(int kr) {
-  return ROWS == 64 ? (kr & 2) | ((kr >> 3) & 1) : ((kr & 3) << 1) | ((kr >> 3) & 1);
+  return ROWS % 128 ? (kr & 2) | ((kr >> 3) & 1) : ((kr & 3) << 1) | ((kr >> 3) & 1);
 }
 
 // EDGE: the operand ends `lim` rows (KC) or columns (MC, at least 8 of them) after the slab's first; a
@@ -331,6 +331,78 @@ __device__ __forceinline__ void tile_epilogue(const EpiArgs& e, const EpiArgs& e
   }
 }
 
+// The same for a wave tile 96 columns wide, whole and with a bf16 output: 24 lanes to a row, so that a store instruction takes two
+// rows and two thirds and a lane's place repeats after three of them, eight rows on.  (A function of its own: with both walks
+// in one the compiler needed a hundred more address instructions for the other widths, 1.4 % of a step of 1024-wide layers.)
+template <int EM, int TM>
+__device__ __forceinline__ void tile_epilogue96(const EpiArgs& e, const f32x16 (&acc)[TM][3], float* wbuf, int mw, int nw, int lane_e) {
+  constexpr int WC = 96, LPR = WC / 4, PER = 3, NIT = 12, BATCH = 6;
+  constexpr bool DG = em_dgelu(EM), SIDE = DG || (EM & EM_RES);
+  int c[PER], rsub[PER], ncol[PER];
+  float4 bias[PER];
+#pragma unroll
+  for (int j = 0; j < PER; j++) {
+    c[j] = (j * 64 + lane_e) % LPR;
+    rsub[j] = (j * 64 + lane_e) / LPR;
+    ncol[j] = nw + c[j] * 4;
+    bias[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  if (e.bias) {
+#pragma unroll
+    for (int j = 0; j < PER; j++) bias[j] = ld_bf16x4(e.bias, ncol[j]);
+  }
+  const bf16_t* sp = (const bf16_t*)(DG ? e.U : e.R);
+  const int lds_ = DG ? e.ldu : e.ldr;
+  bf16x4 side[2][SIDE ? NIT : 1];
+  auto side_request = [&](int i, bf16x4 (&dst)[SIDE ? NIT : 1]) {
+    if (SIDE) {
+#pragma unroll
+      for (int k = 0; k < NIT; k++)
+        dst[k] = *reinterpret_cast<const bf16x4*>(sp + (size_t)(mw + i * 32 + rsub[k % PER] + k / PER * 8) * lds_ + ncol[k % PER]);
+    }
+  };
+  side_request(0, side[0]);
+#pragma unroll
+  for (int i = 0; i < TM; i++) {
+    if (i + 1 < TM) side_request(i + 1, side[(i + 1) & 1]);
+#pragma unroll
+    for (int j = 0; j < 3; j++)
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        const int row = lane_e & 31;
+        const int chunk = j * 8 + g * 2 + (lane_e >> 5);
+        const f32x16& t = acc[i][j];
+        *reinterpret_cast<float4*>(wbuf + row * WC + ((chunk ^ (row & 7)) << 2)) =
+            make_float4(t[g * 4], t[g * 4 + 1], t[g * 4 + 2], t[g * 4 + 3]);
+      }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int k0 = 0; k0 < NIT; k0 += BATCH) {
+      float4 a[BATCH];
+#pragma unroll
+      for (int u = 0; u < BATCH; u++) {
+        const int k = k0 + u, row = rsub[k % PER] + k / PER * 8;  // rsub < 8
+        a[u] = *reinterpret_cast<const float4*>(wbuf + row * WC + ((c[k % PER] ^ rsub[k % PER]) << 2));
+      }
+#pragma unroll
+      for (int u = 0; u < BATCH; u++) {
+        const int k = k0 + u;
+        float4 sd = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (SIDE) {
+          const bf16x4 v = side[i & 1][k];
+          sd = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+        }
+        mfma_epilogue4<EM>(e, mw + i * 32 + rsub[k % PER] + k / PER * 8, ncol[k % PER], a[u], bias[k % PER], sd);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+
 // Products of a grouped launch: weight gradients of one layer, which contract over the same tokens and do not depend on each other.
 struct GemmItem {
   const bf16_t *A, *B;
@@ -536,6 +608,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   static_assert(GK / 16 == 4, "pipeline below is written for four k-steps per slab");
   constexpr int NSLOT = TM * TN;
   static_assert(TM + TN <= NSLOT, "slots per phase");
+  static_assert(TN != 3 || (!EDGE && !GROUP && em_kind(EM) != EK_F32), "tile_epilogue96");
   constexpr int PB = (TM + TN + 4 < NSLOT) ? TM + TN + 4 : NSLOT;  // barrier position within phase 2
   constexpr int SLOTS_A = 2 * NSLOT;             // slots open to the A loads
   constexpr int SLOTS_B = NSLOT - PB + NSLOT;    // ... and to the B loads
@@ -689,7 +762,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));
   auto epilogue = [&](auto mask_c) {
-    tile_epilogue<EM, decltype(mask_c)::value, TM, TN>(GROUP ? et : e, et, acc, wbuf, m0 + wm, n0 + wn, M_item, N_item, lane_e);
+    if constexpr (TN == 3) tile_epilogue96<EM, TM>(e, acc, wbuf, m0 + wm, n0 + wn, lane_e);
+    else tile_epilogue<EM, decltype(mask_c)::value, TM, TN>(GROUP ? et : e, et, acc, wbuf, m0 + wm, n0 + wn, M_item, N_item, lane_e);
   };  // epilogue
   if constexpr (EDGE) {
     if (m0 + BM > M_item || n0 + BN > N_item) epilogue(T_{});

@@ -45,6 +45,7 @@ struct TileClass {
   double epi_bf16_us, epi_f32_us;
 };
 static constexpr TileClass kTiles[] = {{256, 256, false, 1.55, 0.48, 1.10, 7.0, 8.0},
+                                       {256, 192, false, 1.20, 0.40, 0.85, 6.0, 6.0},
                                        {256, 128, false, 0.90, 0.25, 0.78, 4.0, 4.5},
                                        {128, 128, false, 0.66, 1.00, 0.66, 3.0, 3.0},
                                        {128, 64, true, 0.42, 0.85, 0.37, 3.5, 3.5},
@@ -85,7 +86,17 @@ static bool tiles_whole(int M, int N, int K) { return M % 128 == 0 && N % 128 ==
 // no class divides the shape.  The 256 x 128 class is used for bf16 outputs only: on weight-gradient
 // products (both operands through the LDS transpose read, with or without K ranges) it measured
 // 10-50 % above this model.
-static GemmSplitPlan plan_tiles(int M, int N, int K, bool f32_out, bool may_split, bool edge, bool deep) {
+// The 256 x 192 class: whole tiles with bf16 outputs, where 256^2 tiles leave CUs idle.  It moves a seventh more bytes per flop than
+// 256^2 and a seventh fewer than 256 x 128.  One product, us, against the class it takes over from: 16384 x 768 x 3072 64 (73 at 256^2), 16384 x
+// 2304 x 768 60 (70), 8192 x 3072 x 3072 124 (135), 4096 x 9216 x 3072 175 (200), 8192 x 2304 x 2304 83 (93 at 256 x 128), 8192 x 1152 x 3456
+// 61 (83); nothing or a little the other way 16384 x 1920 x 1920 112 (109), 8192 x 3072 x 768 41.5 (40.6).
+// `beside`: another stream's kernels have the CUs that this product leaves idle, so 256^2 stays where it is the best of the others.
+// Forward and backward pass with that line and without, us: 16384 tokens x 768 1165 and 1173, 1024 x 3072 951 and 967, 32768 x 768 2138 and 2163.
+static GemmSplitPlan plan_tiles(int M, int N, int K, bool f32_out, bool may_split, bool edge, bool deep, bool beside, bool with_192 = true) {
+  if (beside && with_192) {
+    const GemmSplitPlan p = plan_tiles(M, N, K, f32_out, may_split, edge, deep, beside, false);
+    if (p.tile_m == 256 && p.tile_n == 256) return p;
+  }
   GemmSplitPlan best{0, 0, 1, false};
   if (M <= 0 || N <= 0 || K <= 0 || (K % GK && !edge)) return best;
   const int nkt = (K + GK - 1) / GK;
@@ -93,6 +104,7 @@ static GemmSplitPlan plan_tiles(int M, int N, int K, bool f32_out, bool may_spli
   for (const TileClass& tc : kTiles) {
     if (tc.deep ? !deep : (M % tc.m || N % tc.n) && !edge) continue;
     if (f32_out && tc.m != tc.n && !tc.deep) continue;
+    if (tc.n == 192 && (edge || !with_192)) continue;
     for (int s = 1; s <= (may_split ? 32 : 1) && (s == 1 || nkt / s >= 8); s++) {
       const double t = tile_time_us(tc, M, N, K, f32_out, s);
       if (t < best_t * 0.97) {
@@ -104,7 +116,7 @@ static GemmSplitPlan plan_tiles(int M, int N, int K, bool f32_out, bool may_spli
   return best;
 }
 
-GemmSplitPlan gemm_split_plan(int M, int N, int K) { return plan_tiles(M, N, K, true, true, !tiles_whole(M, N, K), true); }
+GemmSplitPlan gemm_split_plan(int M, int N, int K) { return plan_tiles(M, N, K, true, true, !tiles_whole(M, N, K), true, false); }
 
 // One dimension an odd multiple of 128 and the rest big enough to fill the chip with 256^2 tiles:
 // the product is computed as two, the bulk on 256^2 tiles and the last 128 rows (1) or columns (2)
@@ -122,9 +134,9 @@ GemmSplitPlan gemm_plan_query(int M, int N, int K, bool f32_out, int* tail) {
   const int td = tail_dim(M, N);
   *tail = td;
   const bool deep = tiles_whole(M, N, K);
-  if (td == 1) return plan_tiles(M - 128, N, K, f32_out, f32_out, false, deep);
-  if (td == 2) return plan_tiles(M, N - 128, K, f32_out, false, false, deep);  // the strip keeps C's leading dimension: no split
-  return plan_tiles(M, N, K, f32_out, f32_out, false, deep);
+  if (td == 1) return plan_tiles(M - 128, N, K, f32_out, f32_out, false, deep, false);
+  if (td == 2) return plan_tiles(M, N - 128, K, f32_out, false, false, deep, false);  // the strip keeps C's leading dimension: no split
+  return plan_tiles(M, N, K, f32_out, f32_out, false, deep, false);
 }
 
 // The tile walk of the main launch of a product (not of the 128-wide strip an odd multiple of 128
@@ -167,7 +179,7 @@ static GemmSplitPlan store_split_plan(int M, int N, int K) {
   GemmSplitPlan best{0, 0, 1, false};
   double t1 = 1e30;
   for (const TileClass& tc : kTiles)
-    if (edge || tc.deep || !(M % tc.m || N % tc.n)) t1 = std::min(t1, tile_time_us(tc, M, N, K, false, 1));
+    if (edge ? tc.n != 192 : tc.deep || !(M % tc.m || N % tc.n)) t1 = std::min(t1, tile_time_us(tc, M, N, K, false, 1));
   double best_t = t1;
   const int nkt = (K + GK - 1) / GK;
   for (const TileClass& tc : kTiles) {
@@ -244,10 +256,15 @@ static int dispatch(const GemmArgs& g, const EpiArgs& e, hipStream_t s) {
     return erf ? launch_mfma<BM, BN, true, false, EK_GELU_ERF>(g, e, s) : launch_mfma<BM, BN, true, false, EK_GELU_TANH>(g, e, s);
   if (g.epi == EPI_DGELU)
     return launch_mfma<BM, BN, true, true, EK_DGELU>(g, e, s);
-  if (g.c_f32 && g.colsum)
+  if constexpr (BN == 192) {  // bf16 outputs only (plan_tiles)
+    if (g.c_f32) {
+      set_error("gemm_mfma: no fp32 output on 256 x 192 tiles");
+      return FAX_ERR_UNSUPPORTED;
+    }
+  } else if (g.c_f32 && g.colsum) {
     return g.accumulate ? launch_mfma<BM, BN, false, false, EK_F32 | EM_RES | EM_COLSUM>(g, e, s)
                         : launch_mfma<BM, BN, false, false, EK_F32 | EM_COLSUM>(g, e, s);
-  if (g.c_f32) {
+  } else if (g.c_f32) {
     if (g.accumulate) {
       if (a_kc && b_kc) return launch_mfma<BM, BN, true, true, EK_F32 | EM_RES>(g, e, s);
       if (a_kc && !b_kc) return launch_mfma<BM, BN, true, false, EK_F32 | EM_RES>(g, e, s);
@@ -291,7 +308,7 @@ static bool deep_alone(const GemmArgs& g, GemmSplitPlan* plan) {
   if (g.path != PATH_AUTO || !gemm_edge_supported(g)) return false;
   const bool edge = !tiles_whole(g.M, g.N, g.K) || b_short(g);
   if (!edge && tail_dim(g.M, g.N)) return false;
-  *plan = plan_tiles(g.M, g.N, g.K, g.c_f32, g.c_f32 && g.split_ws && g.ldc == g.N, edge, true);
+  *plan = plan_tiles(g.M, g.N, g.K, g.c_f32, g.c_f32 && g.split_ws && g.ldc == g.N, edge, true, g.beside);
   return plan->deep && plan->splits == 1;
 }
 
@@ -324,7 +341,7 @@ static double mfma_time_us(const GemmArgs& g, bool* small) {
       if (plan.splits > 1 && tc.m == plan.tile_m && tc.n == plan.tile_n && !tc.deep) return 3.0 + tile_time_us(tc, g.M, g.N, g.K, true, plan.splits);
   }
   auto one = [&](int M, int N, bool bulk) {
-    const GemmSplitPlan plan = plan_tiles(M, N, g.K, g.c_f32, g.c_f32 && g.ldc == N, edge, gemm_edge_supported(g));
+    const GemmSplitPlan plan = plan_tiles(M, N, g.K, g.c_f32, g.c_f32 && g.ldc == N, edge, gemm_edge_supported(g), g.beside);
     if (bulk) *small = plan.deep;
     for (const TileClass& tc : kTiles)
       if (tc.m == plan.tile_m && tc.n == plan.tile_n && tc.deep == plan.deep) return 3.0 + tile_time_us(tc, M, N, g.K, g.c_f32, plan.splits);
@@ -382,7 +399,7 @@ int gemm_groups(const GemmArgs (&w)[4], const GemmArgs (&in)[4]) {
     if (!gemm_edge_supported(g)) return 0;
     pairs = pairs && gemm_pair_supported(i < 2 ? w[i] : w[5 - i], g);  // with the weight gradient of this layer
     if (!full) continue;
-    const GemmSplitPlan p = plan_tiles(g.M, g.N, g.K, false, false, !tiles_whole(g.M, g.N, g.K), true);
+    const GemmSplitPlan p = plan_tiles(g.M, g.N, g.K, false, false, !tiles_whole(g.M, g.N, g.K), true, g.beside);
     full = p.tile_m == 256 && (long long)((g.M + 255) / 256) * ((g.N + p.tile_n - 1) / p.tile_n) >= kCUs;
   }
   if (pairs) return 0;  // short products: one launch for a layer's weight and input gradient instead
@@ -430,7 +447,7 @@ GemmRoute gemm_route(const GemmArgs& g, bool scratch) {
   const bool edge = r.form == GEMM_EDGE;
   r.tail = edge ? 0 : tail_dim(g.M, g.N);
   const int M = r.tail == 1 ? g.M - 128 : g.M, N = r.tail == 2 ? g.N - 128 : g.N;
-  const GemmSplitPlan p = plan_tiles(M, N, g.K, g.c_f32, g.c_f32 && scratch && g.ldc == N, edge, gemm_edge_supported(g));
+  const GemmSplitPlan p = plan_tiles(M, N, g.K, g.c_f32, g.c_f32 && scratch && g.ldc == N, edge, gemm_edge_supported(g), g.beside);
   r.small = p.deep; r.tile_m = p.tile_m; r.tile_n = p.tile_n; r.splits = p.splits;
   r.tiles_m = (M + p.tile_m - 1) / p.tile_m;
   r.tiles_n = (N + p.tile_n - 1) / p.tile_n;
@@ -500,7 +517,7 @@ int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
   // Split the contraction?  Only the fp32-output form, with scratch from the caller and C stored
   // densely; the partial products (and partial column sums) are then folded in a fixed order.
   const GemmSplitPlan plan = plan_tiles(g.M, g.N, g.K, g.c_f32, g.c_f32 && g.split_ws && g.ldc == g.N, edge,
-                                        gemm_edge_supported(g));
+                                        gemm_edge_supported(g), g.beside);
   if (plan.tile_m == 0) {
     set_error("gemm_mfma: %d x %d x %d fits no tile class", g.M, g.N, g.K);
     return FAX_ERR_UNSUPPORTED;
@@ -518,6 +535,7 @@ int gemm_mfma(const GemmArgs& g0, hipStream_t s) {
   if (plan.deep) FAX_TRY(gemm_mfma_deep(g, e, plan, s));
   else if (edge) FAX_TRY(gemm_mfma_edge(g, e, plan, s));
   else if (plan.tile_n == 256) FAX_TRY((dispatch<256, 256>(g, e, s)));
+  else if (plan.tile_n == 192) FAX_TRY((dispatch<256, 192>(g, e, s)));
   else if (plan.tile_m == 256) FAX_TRY((dispatch<256, 128>(g, e, s)));
   else FAX_TRY((dispatch<128, 128>(g, e, s)));
   if (splits > 1) {
