@@ -91,7 +91,8 @@ static bool tiles_whole(int M, int N, int K) { return M % 128 == 0 && N % 128 ==
 // 2304 x 768 60 (70), 8192 x 3072 x 3072 124 (135), 4096 x 9216 x 3072 175 (200), 8192 x 2304 x 2304 83 (93 at 256 x 128), 8192 x 1152 x 3456
 // 61 (83); nothing or a little the other way 16384 x 1920 x 1920 112 (109), 8192 x 3072 x 768 41.5 (40.6).
 // `beside`: another stream's kernels have the CUs that this product leaves idle, so 256^2 stays where it is the best of the others.
-// Forward and backward pass with that line and without, us: 16384 tokens x 768 1165 and 1173, 1024 x 3072 951 and 967, 32768 x 768 2138 and 2163.
+// Forward and backward pass against a planner without the class, with that line and with 256 x 192 there as well: 16384 tokens x 768 -1.2 % and
+// +0.7 %, 32768 x 768 -1.0 % and +1.2 %, 2048 x 768 -0.7 % and +1.3 %; the other way 4096 x 3072 -1.7 % and -2.4 %.
 static GemmSplitPlan plan_tiles(int M, int N, int K, bool f32_out, bool may_split, bool edge, bool deep, bool beside, bool with_192 = true) {
   if (beside && with_192) {
     const GemmSplitPlan p = plan_tiles(M, N, K, f32_out, may_split, edge, deep, beside, false);
