@@ -1,8 +1,9 @@
 // fp32 GEMM on the CDNA4 matrix cores through their bf16 instruction: every fp32 factor is cut into three bf16 numbers, and
 // v_mfma_f32_32x32x16_bf16 multiplies the pieces and adds the products in fp32.
 //
-// x = hi + mid + lo, each the bf16 nearest to what the ones before leave: 8 + 8 + 8 significant bits, so the sum is x itself, down to
-// 2^-110, where lo's last bit is the smallest number there is.  Of the nine products of two such sums the kernel
+// 2^24 x = hi + mid + lo, each the bf16 nearest to what the ones before leave: 8 + 8 + 8 significant bits, so the sum is 2^24 x itself.  The
+// factor 2^24, taken out of the sums again, is what makes that so for every x: without it lo's last bits fall off the end of bf16 below
+// 2^-110; with it every piece, of subnormal x too, is a multiple of 2^-125.  Of the nine products of two such sums the kernel
 // forms the six that matter: hi hi, hi mid, mid hi, mid mid, hi lo, lo hi.  The three others are below 2^-24 of |x y| together
 // (|mid| <= 2^-8 |x|, |lo| <= 2^-17 |x|), 2^-27 in the mean.  hi hi has accumulators of its own, the five small ones share
 // others: of the additions that round at the size of the result there is one for sixteen contraction indices, where
@@ -22,10 +23,11 @@
 // place so that sixteen consecutive rows meet sixteen different places of the 256-byte bank window; the other kind as [k][row], as
 // in the bf16 kernel, and read with the LDS transpose read (frag_load, mc_swizzle).  No bank conflicts either way (SQ_LDS_BANK_CONFLICT).
 //
-// What the pieces cannot carry is computed again, by the workgroup that finds it, with v_mfma_f32_32x32x2_f32 on the factors as they are,
-// straight from memory (slow, and only then): a sum that is not finite (an infinite factor's remainder is NaN, and an infinity times a
-// piece that is zero is NaN where the product is an infinity; a factor that is not finite always leaves such a sum), and an
-// operand of which nothing the tile has seen reaches 2^-100, so that what lo loses below 2^-134 would show.
+// What the pieces cannot carry is computed again, by the wave that finds it in its own partial sums, with v_mfma_f32_32x32x2_f32 on the
+// factors as they are, straight from memory: sums that are not finite (an infinite factor's remainder is NaN, and an infinity times a
+// piece that is zero is NaN where the product is an infinity; a factor that is not finite, or not below 2^103, always leaves such a sum, and
+// so does a partial sum that is not below 2^80).  A sum that is finite stays as it is, whatever its neighbours are: which of the two an
+// element gets hangs on its own row and column alone.
 //
 // Lane layout (lane l): operands = row / column l & 31, k = 8 (l >> 5) + 0..7; accumulator v holds element
 // [8 (v >> 2) + 4 (l >> 5) + (v & 3)][l & 31]: 32 lanes store 32 consecutive columns.
@@ -59,9 +61,11 @@ __device__ __forceinline__ float4 chunk_mask(float4 v, int K, int k0, int c) {
   return k0 + c / (ROWS / 4) < K ? v : make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// Four numbers as 3 x 4 bf16.
+static constexpr float SPLIT_UP = 16777216.f, SPLIT_DOWN = 1.f / SPLIT_UP / SPLIT_UP;  // 2^24 of each factor, 2^-48 of a product
+
+// Four numbers, times SPLIT_UP, as 3 x 4 bf16.
 __device__ __forceinline__ void split4(float4 v, uint2 (&p)[3]) {
-  float r[4] = {v.x, v.y, v.z, v.w};
+  float r[4] = {v.x * SPLIT_UP, v.y * SPLIT_UP, v.z * SPLIT_UP, v.w * SPLIT_UP};
 #pragma unroll
   for (int q = 0; q < 3; q++) {
     unsigned w[2];
@@ -86,7 +90,6 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&f)[3]) {
 #pragma unroll
   for (int q = 0; q < 3; q++) f[q] = __builtin_bit_cast(bf16x8, make_uint4(lo[q].x, lo[q].y, hi[q].x, hi[q].y));
 }
-static constexpr float SPLIT_MIN = 7.888609e-31f;  // 2^-100
 
 // One operand's slab in LDS: three planes.
 template <int ROWS, int BK, bool KC>
@@ -187,7 +190,6 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, c
     }
   }
 
-  float a_most = 0.f, b_most = 0.f;
   // hi hi goes to `acc`, the other products to `small`, which is 2^-8 of it and rounds off that much less.
   f32x16 acc[TM][TN], small[TM][TN];
   auto clear = [&](f32x16 (&t)[TM][TN]) {
@@ -235,11 +237,6 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, c
       bf16x8 ga[3], gb[3];
       split8(xa[SET], ga);
       split8(xb[SET], gb);
-#pragma unroll
-      for (int t = 0; t < 8; t++) {
-        a_most = fmaxf(a_most, fabsf(xa[SET][t]));
-        b_most = fmaxf(b_most, fabsf(xb[SET][t]));
-      }
       if (CS && cs_on) {
         const float* x = xb[SET];
         const float c = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
@@ -289,18 +286,16 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, c
 #pragma unroll
         for (int i = 0; i < SB::CHUNKS; i++) rb[SET][i] = chunk_mask<BN, BK, TB, VEC>(rb[SET][i], K, k0, tid + i * 512);
       }
-      auto put = [&](char* p, int plane, float4 v, float& most) {
-        most = fmaxf(fmaxf(most, fabsf(v.x)), fabsf(v.y));
-        most = fmaxf(fmaxf(most, fabsf(v.z)), fabsf(v.w));
+      auto put = [&](char* p, int plane, float4 v) {
         uint2 w[3];
         split4(v, w);
 #pragma unroll
         for (int q = 0; q < 3; q++) *reinterpret_cast<uint2*>(p + q * plane) = w[q];
       };
 #pragma unroll
-      for (int i = 0; i < SA::CHUNKS; i++) put(buf + SA::place(tid + i * 512), SA::PLANE, ra[SET][i], a_most);
+      for (int i = 0; i < SA::CHUNKS; i++) put(buf + SA::place(tid + i * 512), SA::PLANE, ra[SET][i]);
 #pragma unroll
-      for (int i = 0; i < SB::CHUNKS; i++) put(buf + SA::BYTES + SB::place(tid + i * 512), SB::PLANE, rb[SET][i], b_most);
+      for (int i = 0; i < SB::CHUNKS; i++) put(buf + SA::BYTES + SB::place(tid + i * 512), SB::PLANE, rb[SET][i]);
       if (CS && cs_on) {
         float t4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -381,21 +376,57 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, c
     }
   }
 
-  // The end: accumulators that other groups store, column sums and what the waves have seen go through LDS together.
+  // The sums of this wave's contraction indices; again, of the same indices, on the fp32 instruction where they are not finite.  The wave loads
+  // its fragments from memory as it multiplies.  2048 x 4096 x 1024, 98 to 126 us by orientation, takes 224 to 266 with one
+  // infinite factor, 306 to 540 with one in every row; the kernel on that instruction alone 143 to 161.
+  bool finite = true;
 #pragma unroll
   for (int i = 0; i < TM; i++)
 #pragma unroll
     for (int j = 0; j < TN; j++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) acc[i][j][v] += small[i][j][v];
-  bool finite = true;
+      for (int v = 0; v < 16; v++) {
+        acc[i][j][v] = (acc[i][j][v] + small[i][j][v]) * SPLIT_DOWN;
+        finite = finite && fabsf(acc[i][j][v]) <= 3.4028235e38f;
+      }
+  if (__ballot(!finite)) {
+    clear(small);
+    for (int k0 = kg * 16; k0 < K; k0 += k0 % 16 ? BK - 8 : 8) {  // a slab's sixteen in two eights
+      float xa[TM][4], xb[TN][4];
 #pragma unroll
-  for (int t = 0; t < NV; t++) finite = finite && fabsf(acc[t / 16 / TN][t / 16 % TN][t % 16]) <= 3.4028235e38f;
-  auto any = [](bool c) { return __ballot(c) != 0; };
-  unsigned seen = (any(!finite) ? 1 : 0) | (any(a_most >= SPLIT_MIN) ? 2 : 0) | (any(a_most > 0.f) ? 4 : 0) |
-                  (any(b_most >= SPLIT_MIN) ? 8 : 0) | (any(b_most > 0.f) ? 16 : 0);
+      for (int t = 0; t < 4; t++) {
+        const int k = k0 + 4 * h + t, kr = min(k, K - 1);
+#pragma unroll
+        for (int i = 0; i < TM; i++) {
+          const int row = min(m0 + wm + i * 32 + l31, M - 1);
+          const float x = A[TA ? (size_t)kr * lda + row : (size_t)row * lda + kr];
+          xa[i][t] = k < K ? x : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < TN; j++) {
+          const int row = min(n0 + wn + j * 32 + l31, N - 1);
+          const float x = B[TB ? (size_t)row * ldb + kr : (size_t)kr * ldb + row];
+          xb[j][t] = k < K ? x : 0.f;
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < 4; t++)
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+          for (int j = 0; j < TN; j++) small[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i][t], xb[j][t], small[i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++)
+          if (!(fabsf(acc[i][j][v]) <= 3.4028235e38f)) acc[i][j][v] = small[i][j][v];
+  }
+
+  // The end: accumulators that other groups store and column sums go through LDS together.
   float* const cs_x = smem_f + S::XCH;
-  unsigned* const seen_x = reinterpret_cast<unsigned*>(cs_x + 8 * BN);
   constexpr int NH = NV / KS;  // accumulators of a lane that its group stores: tiles of 16, or a part of one
   constexpr int GW = WM * WN;  // waves of a group
   auto mine = [&](int t) { return acc[t / 16 / TN][t / 16 % TN][t % 16]; };
@@ -444,7 +475,6 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, c
   };
   if (KS < 8) __syncthreads();  // every wave is done with the slabs
   exchange();
-  if (lane == 0) seen_x[wave] = seen;
   if (CS && cs_on) {  // lanes CL apart have the same columns, and so have the waves
     constexpr int CC = KS == 8 ? 1 : 4, CL = BN / CC;
 #pragma unroll
@@ -456,38 +486,6 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, c
     }
   }
   __syncthreads();
-#pragma unroll
-  for (int w = 0; w < 8; w++) seen |= seen_x[w];
-  if ((seen & 1) || (seen & 6) == 4 || (seen & 24) == 16) {  // uniform over the workgroup
-    clear(acc);
-    for (int k0 = kg * 8; k0 < K; k0 += 8 * KS) {
-      float xa[TM][4], xb[TN][4];
-#pragma unroll
-      for (int t = 0; t < 4; t++) {
-        const int k = k0 + 4 * h + t, kr = min(k, K - 1);
-#pragma unroll
-        for (int i = 0; i < TM; i++) {
-          const int row = min(m0 + wm + i * 32 + l31, M - 1);
-          const float x = A[TA ? (size_t)kr * lda + row : (size_t)row * lda + kr];
-          xa[i][t] = k < K ? x : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < TN; j++) {
-          const int row = min(n0 + wn + j * 32 + l31, N - 1);
-          const float x = B[TB ? (size_t)row * ldb + kr : (size_t)kr * ldb + row];
-          xb[j][t] = k < K ? x : 0.f;
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < 4; t++)
-#pragma unroll
-        for (int i = 0; i < TM; i++)
-#pragma unroll
-          for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i][t], xb[j][t], acc[i][j], 0, 0, 0);
-    }
-    exchange();  // (nobody has read the first one)
-    __syncthreads();
-  }
   if (CS && cs_on && tid < BN && n0 + tid < N) {
     const float* q = cs_x + tid;
     const float c = ((q[0] + q[BN]) + (q[2 * BN] + q[3 * BN])) + ((q[4 * BN] + q[5 * BN]) + (q[6 * BN] + q[7 * BN]));
@@ -512,7 +510,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, c
     const float bias = KS == 8 ? pre_bias : e.bias ? ((const float*)e.bias)[nr] : 0.f;
     if (GELU) {
       // one element at a time out of the lane's own LDS slots: sixteen copies of tanh and erf would not fit the instruction cache
-      float* slot = smem_f + S::XCH + 8 * BN + 16 + wave * 64 * NE + lane;
+      float* slot = smem_f + S::XCH + 8 * BN + wave * 64 * NE + lane;
 #pragma unroll
       for (int t = 0; t < NE; t++) slot[t * 64] = v[t];
 #pragma unroll 1
@@ -572,7 +570,7 @@ template <int WM, int WN, int KS, int TM, int TN, bool TA, bool TB, bool VEC, bo
 static int launch_f32(const GemmArgs& g, const EpiArgs& e, hipStream_t s) {
   using S = SplitShape<WM, WN, KS, TM, TN>;
   constexpr size_t slabs = 2 * (SplitSlab<S::BM, S::BK, !TA>::BYTES + SplitSlab<S::BN, S::BK, TB>::BYTES);
-  constexpr size_t tail = (S::XCH + 8 * S::BN + 16 + (GELU ? 8 * 64 * (S::NV / KS < 16 ? S::NV / KS : 16) : 0)) * sizeof(float);
+  constexpr size_t tail = (S::XCH + 8 * S::BN + (GELU ? 8 * 64 * (S::NV / KS < 16 ? S::NV / KS : 16) : 0)) * sizeof(float);
   constexpr size_t lds = slabs > tail && KS < 8 ? slabs : tail;
   auto kern = gemm_f32_kernel<WM, WN, KS, TM, TN, TA, TB, VEC, GELU>;
   static bool configured = false;  // benign race: the attribute is idempotent

@@ -93,6 +93,32 @@ def test_gemm_f32_pieces(M, N, K, tile, ta, tb):
     assert ((got.double() - ref).abs() <= (K + 2) * EPS * (A.abs().double().nan_to_num() @ B.abs().double()))[clean].all()
 
 
+@pytest.mark.parametrize("M,N,K,tile", SPLIT)
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+def test_gemm_f32_small_numbers_beside_ordinary_ones(M, N, K, tile, ta, tb):
+    """Rows, columns and single factors down to the smallest fp32 numbers in tiles that hold ordinary ones: every sum within K roundings of
+    its own terms.  And what a row that is not finite has computed again leaves the other rows' bits alone."""
+    r = fax.fax_gemm_route(fax.FAX_F32, ta, tb, M, N, K)
+    assert (r.tile_m, r.tile_n) == tile
+    g = torch.Generator(device=DEV).manual_seed(M + ta + 2 * tb)
+    A, B = (torch.randn(s, generator=g, device=DEV) for s in ((M, K), (K, N)))
+    even = torch.arange(K, device=DEV) % 2 == 0
+    A[1] *= torch.where(even, 2.0 ** -120, 1.0)   # one row of both kinds, whose terms are of a size
+    B *= torch.where(even, 2.0 ** 60, 2.0 ** -60)[:, None]
+    A[3], A[M - 2] = A[3] * 2.0 ** -120, A[M - 2] * 2.0 ** -140
+    B[:, 5], B[:, N - 3] = B[:, 5] * 2.0 ** -100, B[:, N - 3] * 2.0 ** -190
+    got, ref = _f32_product(ta, tb, A, B), A.double() @ B.double()
+    # (2^-150: half of the smallest number there is, for terms and sums that are smaller)
+    bound = (K + 2) * (EPS * (A.abs().double() @ B.abs().double()) + 2.0 ** -150)
+    assert ((got.double() - ref).abs() <= bound).all()
+    A[7, K // 2], A[M - 5, 0] = float("inf"), float("nan")
+    again = _f32_product(ta, tb, A, B)
+    rest = torch.ones(M, dtype=torch.bool, device=DEV)
+    rest[7], rest[M - 5] = False, False
+    assert not torch.isfinite(again[~rest]).any()
+    assert torch.equal(again[rest], got[rest])
+
+
 def test_gemm_f32_without_a_contraction():
     bias = torch.arange(40, dtype=torch.float32, device=DEV)
     C = torch.full((3, 40), 7.0, dtype=torch.float32, device=DEV)
