@@ -27,7 +27,9 @@
 // factors as they are, straight from memory: sums that are not finite (an infinite factor's remainder is NaN, and an infinity times a
 // piece that is zero is NaN where the product is an infinity; a factor that is not finite, or not below 2^103, always leaves such a sum, and
 // so does a partial sum that is not below 2^80).  A sum that is finite stays as it is, whatever its neighbours are: which of the two an
-// element gets hangs on its own row and column alone.
+// element gets hangs on its own row and column alone.  So are contractions over fewer than four indices, whose sums are so short that the
+// instruction rounds less: over 1 index 2.5e-8 and 2.6e-8 in the pieces, at most 1.0 and 1.8 x 2^-24 of |x y|, over 2 at most 1.9 and 2.4 of
+// the sum of |x y|, over 4 3.3 and 2.4.
 //
 // Lane layout (lane l): operands = row / column l & 31, k = 8 (l >> 5) + 0..7; accumulator v holds element
 // [8 (v >> 2) + 4 (l >> 5) + (v & 3)][l & 31]: 32 lanes store 32 consecutive columns.
@@ -62,6 +64,7 @@ __device__ __forceinline__ float4 chunk_mask(float4 v, int K, int k0, int c) {
 }
 
 static constexpr float SPLIT_UP = 16777216.f, SPLIT_DOWN = 1.f / SPLIT_UP / SPLIT_UP;  // 2^24 of each factor, 2^-48 of a product
+static constexpr int SPLIT_MIN_K = 4;
 
 // Four numbers, times SPLIT_UP, as 3 x 4 bf16.
 __device__ __forceinline__ void split4(float4 v, uint2 (&p)[3]) {
@@ -379,7 +382,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, c
   // The sums of this wave's contraction indices; again, of the same indices, on the fp32 instruction where they are not finite.  The wave loads
   // its fragments from memory as it multiplies.  2048 x 4096 x 1024, 98 to 126 us by orientation, takes 224 to 266 with one
   // infinite factor, 306 to 540 with one in every row; the kernel on that instruction alone 143 to 161.
-  bool finite = true;
+  bool finite = K >= SPLIT_MIN_K;
 #pragma unroll
   for (int i = 0; i < TM; i++)
 #pragma unroll
@@ -422,7 +425,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, c
       for (int j = 0; j < TN; j++)
 #pragma unroll
         for (int v = 0; v < 16; v++)
-          if (!(fabsf(acc[i][j][v]) <= 3.4028235e38f)) acc[i][j][v] = small[i][j][v];
+          if (K < SPLIT_MIN_K || !(fabsf(acc[i][j][v]) <= 3.4028235e38f)) acc[i][j][v] = small[i][j][v];
   }
 
   // The end: accumulators that other groups store and column sums go through LDS together.

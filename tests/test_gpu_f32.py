@@ -119,6 +119,17 @@ def test_gemm_f32_small_numbers_beside_ordinary_ones(M, N, K, tile, ta, tb):
     assert torch.equal(again[rest], got[rest])
 
 
+@pytest.mark.parametrize("M,N", [(40, 70), (520, 2052), (2047, 4100)])
+@pytest.mark.parametrize("K", [1, 2, 3])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+def test_gemm_f32_short_contractions(M, N, K, ta, tb):
+    g = torch.Generator(device=DEV).manual_seed(M + K)
+    A, B = (torch.randn(s, generator=g, device=DEV) for s in ((M, K), (K, N)))
+    size = A.abs().double() @ B.abs().double()
+    # a multiply-add rounds once, by 2^-24 of its result at most
+    assert ((_f32_product(ta, tb, A, B).double() - A.double() @ B.double()).abs() <= K * EPS * size).all()
+
+
 def test_gemm_f32_without_a_contraction():
     bias = torch.arange(40, dtype=torch.float32, device=DEV)
     C = torch.full((3, 40), 7.0, dtype=torch.float32, device=DEV)
