@@ -25,6 +25,7 @@ static constexpr int CE_MAX_THREADS = 1024;
 static constexpr int CE_MAX_NV = 16;
 static constexpr float CE_LOG2E = 1.4426950408889634f;
 static constexpr float CE_LN2 = 0.6931471805599453f;
+static constexpr float CE_LOW = -87.f;  // e^-87 = 2^-125.5
 
 __device__ __forceinline__ float block_reduce(float v, float* red, bool is_max) {
   v = is_max ? wave_max(v) : wave_sum(v);
@@ -40,18 +41,22 @@ __device__ __forceinline__ float block_reduce(float v, float* red, bool is_max) 
 // NV: 16-byte vectors per thread (V <= blockDim.x * NV * elements per vector).  PAD = false: V is a multiple of the vector.
 // PAD = true: V is not, but the row distance ld >= V is; the elements of the last vector beyond V count as -infinity, which gives
 // them the gradient zero.  Bound by HBM and the exponentials like the other, two of which there are to a logit.  Those of fp32 logits are
-// the library's; those of bf16 ones have its accuracy (1.2e-7 of themselves at most, 3.6e-8 rms, before the rounding to bf16) in six
+// the library's; those of bf16 ones have its accuracy (1.2e-7 of themselves at most, 3.6e-8 rms, where they are normal numbers, before the rounding to bf16) in six
 // instructions instead of thirteen: 3108 x 32003 135 -> 111 us, where HBM takes 91.
-template <typename T, bool PAD>
+// LOW: times 2^64 where e^d is below 2^-126 (ce_up).  v_exp_f32 has no subnormal results: alone it gives zero there, which the sums, at least 1,
+// do not notice, but a gradient of few positions or a large grad_scale does.
+template <typename T, bool PAD, bool LOW = false>
 __device__ __forceinline__ float ce_exp(float d) {
   if (PAD && sizeof(T) == 4) return expf(d);
   if (!PAD) return __builtin_amdgcn_exp2f(d * CE_LOG2E);
   // d <= 0 or NaN.  t + r = d log2(e) to 48 bits, 2^r = 1 + r ln 2 to 2^-48; e^-200 is zero, and keeps infinities out of r.
   d = __builtin_elementwise_maximum(d, -200.f);
   const float t = d * CE_LOG2E, r = fmaf(d, 1.925963033e-8f, fmaf(d, CE_LOG2E, -t));
-  const float e = __builtin_amdgcn_exp2f(t);
+  const float e = __builtin_amdgcn_exp2f(LOW && d < CE_LOW ? t + 64.f : t);
   return fmaf(e, r * CE_LN2, e);
 }
+template <bool LOW>
+__device__ __forceinline__ float ce_up(float d, float inv) { return LOW && d < CE_LOW ? inv * 5.421010862e-20f : inv; }  // 2^-64
 
 template <typename T, int NV, bool PAD>
 __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V, int ld, const T* __restrict__ logits,
@@ -81,12 +86,16 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V,
   // this thread's maximum, then its sum of e^(z - maximum) (differences first, then the scale to base 2).  The maximum is the one
   // that a NaN goes through: fmaxf would pass over it, and a thread with nothing but NaN (up to V = 2048 the last
   // one may hold a single logit) would count as one without elements below.
-  float mt = -INFINITY;
+  constexpr bool RANGE = PAD && sizeof(T) == 2;  // the exponentials of ce_exp that have no subnormal results
+  float mt = -INFINITY, least = INFINITY;
 #pragma unroll
   for (int i = 0; i < NV; i++) {
     if (threadIdx.x + i * nt < nvec) {
 #pragma unroll
-      for (int e = 0; e < Vv::N; e++) mt = __builtin_elementwise_maximum(mt, zv[i].get(e));
+      for (int e = 0; e < Vv::N; e++) {
+        mt = __builtin_elementwise_maximum(mt, zv[i].get(e));
+        if (RANGE) least = __builtin_elementwise_minimum(least, zv[i].get(e));
+      }
     }
   }
   float se = 0.f;
@@ -120,25 +129,31 @@ __global__ __launch_bounds__(CE_MAX_THREADS) void ce_cached_kernel(int N, int V,
   const float invN = grad_scale / (float)N;
   const float inv = invN / S;
   T* dz = dlogits + (size_t)row * ld;
+  auto gradient = [&](auto low_c) __attribute__((always_inline)) {
+    constexpr bool LOW = decltype(low_c)::value;
 #pragma unroll
-  for (int i = 0; i < NV; i++) {
-    const int c = threadIdx.x + i * nt;
-    if (c < nvec) {
-      float g[Vv::N];
+    for (int i = 0; i < NV; i++) {
+      const int c = threadIdx.x + i * nt;
+      if (c < nvec) {
+        float g[Vv::N];
 #pragma unroll
-      for (int e = 0; e < Vv::N; e++) g[e] = ce_exp<T, PAD>(zv[i].get(e) - M) * inv;
-      const int k = label - c * Vv::N;
-      if (k >= 0 && k < Vv::N) {  // rare: the vector that holds the label's column
+        for (int e = 0; e < Vv::N; e++) g[e] = ce_exp<T, PAD, LOW>(zv[i].get(e) - M) * ce_up<LOW>(zv[i].get(e) - M, inv);
+        const int k = label - c * Vv::N;
+        if (k >= 0 && k < Vv::N) {  // rare: the vector that holds the label's column
 #pragma unroll
-        for (int e = 0; e < Vv::N; e++)
-          if (e == k) g[e] -= invN;
+          for (int e = 0; e < Vv::N; e++)
+            if (e == k) g[e] -= invN;
+        }
+        Vv o;
+#pragma unroll
+        for (int e = 0; e < Vv::N; e++) o.set(e, g[e]);
+        o.store_nt(dz + (size_t)c * Vv::N);  // gigabytes of gradient: streaming (-3 % on this kernel; the same store for LayerNorm's output cost the next GEMM more than it saved)
       }
-      Vv o;
-#pragma unroll
-      for (int e = 0; e < Vv::N; e++) o.set(e, g[e]);
-      o.store_nt(dz + (size_t)c * Vv::N);  // gigabytes of gradient: streaming (-3 % on this kernel; the same store for LayerNorm's output cost the next GEMM more than it saved)
     }
-  }
+  };
+  // (asked once a wave: 3108 x 32003 101 -> 104 us; a choice for every logit made it 113)
+  if (RANGE && __ballot(least - M < CE_LOW)) gradient(std::true_type{});
+  else gradient(std::false_type{});
 }
 
 // Any V: three passes over the row in memory (the re-reads hit cache).

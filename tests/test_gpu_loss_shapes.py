@@ -1,5 +1,6 @@
 """Cross-entropy over rows that end inside a 16-byte vector, at the workgroup shapes they take: one vector, a few, most threads idle, up to and
 beyond eight vectors a thread, the most that registers hold."""
+import numpy as np
 import pytest
 
 from helpers import to_np, rel_fro
@@ -21,3 +22,21 @@ def test_padded_rows(dtype, V):
     # a loss of bf16 logits: 2^-9 of a logit each, averaged; gradients: the bars of the two types
     assert abs(loss - loss_ref) <= (1e-5 if dtype == "f32" else 1e-3) * abs(loss_ref)
     assert rel_fro(to_np(grads["tok_emb"]), g_ref["tok_emb"]) <= (1e-5 if dtype == "f32" else 2e-2)
+
+
+@pytest.mark.parametrize("V", [1001, 32003])
+def test_gradients_of_far_off_logits(V):
+    """One position, every logit chosen: what an exponential below 2^-126 leaves in the gradient, down to the smallest bf16 number."""
+    ms = ModelShape(BlockShape(B=1, S=1, D=64, H=1, dh=64, F=128, dtype="bf16", sigma_w=0.05, L=1), V=V, S_max=1)
+    p, tok, lab = make_model_inputs(ms, seed=9, generic=True)
+    up = 2.0 ** 20  # the last LayerNorm gives (2^20, 0, ...) whatever comes in
+    p["lnf_g"], p["lnf_b"] = np.zeros(64), np.where(np.arange(64) == 0, up, 0.0)
+    z = -((np.arange(V) * 7 % 241) / 2.0)   # 0, -0.5, ... -120
+    p["tok_emb"] = np.zeros((V, 64))
+    p["tok_emb"][:, 0] = z / up
+    tok[:], lab[:] = 0, 1
+    _, _, _, _, _, grads = run_train_step(ms, p, tok, lab, update=False)
+    got = to_np(grads["tok_emb"])[2:, 0] / up
+    want = (np.exp(z) / np.exp(z).sum())[2:]
+    # one rounding to 8 bits (2^-8 of the power of two below, among subnormals half of 2^-133) of a value that an exponential, a sum and a division have rounded
+    assert (np.abs(got - want) <= (2.0 ** -8 + 1e-6) * want + 2.0 ** -134).all()
