@@ -349,8 +349,7 @@ static double products_us(const FaxBlockDims& d) {
   const BwdProducts all(d);
   double us = 0.0;
   for (const auto& g : all.p)
-    us += d.dtype == FAX_BF16 ? gemm_time_estimate_us(dense_product(FAX_BF16, g[3], !g[3], g[0], g[1], g[2], g[3]))
-                              : 5.0 + 2.0 * g[0] * g[1] * g[2] / 90.0e6;
+    us += gemm_time_estimate_us(dense_product(d.dtype, g[3], !g[3], g[0], g[1], g[2], g[3]));
   return us;
 }
 
@@ -370,8 +369,10 @@ static BwdPlan bwd_plan(const FaxBlockDims& d) {
   const double us = products_us(d);
   // Products so short that the host cannot keep up with a second stream: its events and waits cost some 85 us a call, on top of the 40 of
   // the launches (fp32 block of 128 tokens x 128: 161 us with the second stream, 95 without; bf16, 512 tokens x 256: 192
-  // and 165; where the products' estimate is 150 us, 3108 tokens x 512, it gains 5 %, at 420 us, 2048 x 5120 shares, 5 %).
-  if (us < 110.0) return BwdPlan{false, 0};
+  // and 165; where the products' estimate is 150 us, 3108 tokens x 512, it gains 5 %, at 420 us, 2048 x 5120 shares, 5 %).  In fp32, two streams
+  // and one, forward and backward: estimate 120, 512 x 512, 202 and 194; 185, 700 x 512, 308 and 313; 188, 256 x 1024, 316 and 287; beyond the line 200,
+  // 900 x 512, 314 and 312; 252, 1500 x 512, 393 and 415; 347, 777 x 768, 476 and 523; 840, 2048 x 1024, 1202 and 1214.
+  if (us < (d.dtype == FAX_BF16 ? 110.0 : 195.0)) return BwdPlan{false, 0};
   if (d.dtype != FAX_BF16) return BwdPlan{may, 0};
   const BwdProducts all(d);
   GemmArgs w[4], in[4];

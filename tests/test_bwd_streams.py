@@ -18,3 +18,9 @@ import paper_2204_06514_amd as fax
 def test_second_stream_where_rounds_leave_places(B, S, D, H, F, streams):
     for flags, want in ((0, streams), (fax.FAX_FLAG_SINGLE_STREAM, 1), (fax.FAX_FLAG_TP_PARTIAL, streams)):
         assert fax.fax_block_bwd_streams(fax.block_dims(B, S, D, H, D // H, F, fax.FAX_BF16, fax.FAX_GELU_TANH, 1e-5, flags)) == want
+
+
+@pytest.mark.parametrize("B,S,D,H,streams", [(2, 64, 128, 4, 1), (2, 256, 512, 8, 1), (1, 256, 1024, 16, 1), (3, 300, 512, 8, 2), (1, 777, 768, 12, 2), (4, 512, 1024, 16, 2)])
+def test_second_stream_of_fp32_blocks_by_the_estimate_of_their_kernel(B, S, D, H, streams):
+    d = lambda flags: fax.block_dims(B, S, D, H, D // H, 4 * D, fax.FAX_F32, fax.FAX_GELU_TANH, 1e-5, flags)  # noqa: E731
+    assert fax.fax_block_bwd_streams(d(0)) == streams and fax.fax_block_bwd_streams(d(fax.FAX_FLAG_SINGLE_STREAM)) == 1
