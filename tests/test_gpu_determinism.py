@@ -53,9 +53,9 @@ def test_block_forward_and_backward_are_bit_reproducible(sh):
                                 BlockShape(B=2, S=1024, D=256, H=2, dh=128, F=512, dtype="bf16", sigma_w=0.02)],
                          ids=lambda s: "%s_D%d_S%d" % (s.dtype, s.D, s.S))
 def test_the_second_stream_changes_no_bit(sh):
-    """Weight gradients on the library's own stream (the default) against FAX_FLAG_SINGLE_STREAM:
-    the same kernels in a different enqueue order, so every output must agree bit for bit; and
-    dx written over dy, which the first weight gradient reads on the other stream."""
+    """FAX_FLAG_SINGLE_STREAM at sizes that keep to the caller's stream by themselves: every output must agree
+    bit for bit; and dx written over dy, which the first weight gradient reads.  (Sizes that take the
+    second stream: below.)"""
     a, b = _block_twice(sh, seed=8, flags=(0, fax.FAX_FLAG_SINGLE_STREAM))
     for k in a:
         assert torch.equal(a[k], b[k]), k
@@ -74,6 +74,64 @@ def test_the_second_stream_changes_no_bit(sh):
     assert torch.equal(dyd, a["dx"])
     for k in PARAM_NAMES:
         assert torch.equal(gd[k], a["d" + k]), k
+
+
+def _blk(B, S, D, H, dh, dtype="bf16", F=None):
+    return BlockShape(B=B, S=S, D=D, H=H, dh=dh, F=F or 4 * D, dtype=dtype, sigma_w=0.02)
+
+
+# Sizes that take the second stream, with the launches of grouped weight gradients there and what those compute of all weight-gradient
+# work: none, in fp32 and in bf16; the feed-forward's two of three; attention's two; both pairs; all four in one launch
+TWO_STREAMS = [(_blk(3, 500, 512, 8, 64, "f32"), 0, 0), (_blk(4, 900, 1536, 12, 128), 0, 0), (_blk(4, 777, 512, 8, 64), 1, 2 / 3), (_blk(2, 1000, 800, 10, 80), 1, 1 / 3),
+               (_blk(8, 512, 1024, 16, 64), 2, 1), (_blk(4, 1024, 2176, 17, 128), 1, 1),
+               # input gradients of 768 columns: 256 x 192 tiles on one stream, 256 x 256 beside another
+               (_blk(8, 2048, 768, 12, 64), 0, 0)]
+
+
+@pytest.mark.parametrize("sh,launches,share", TWO_STREAMS, ids=lambda s: "%s_T%d_D%d" % (s.dtype, s.T, s.D) if isinstance(s, BlockShape) else "")
+def test_two_streams_change_no_bit(sh, launches, share):
+    """The backward pass on two streams against the caller's alone: dx in a buffer of its own, and over dy, which a weight gradient reads on
+    the other stream until late in the pass."""
+    assert fax.fax_block_bwd_streams(dims_of(sh)) == 2
+    if (sh.T, sh.D) == (16384, 768):
+        assert all(fax.fax_gemm_route(fax.FAX_BF16, 0, 1, sh.T, 768, k).tile_n == 192 for k in (768, 2304, 3072))
+    g = torch.Generator(device=DEV).manual_seed(sh.T)
+    td = torch.float32 if sh.dtype == "f32" else torch.bfloat16
+    rnd = lambda shape, sigma: (sigma * torch.randn(shape, generator=g, device=DEV)).to(td)  # noqa: E731
+    Hd = sh.H * sh.dh
+    shapes = dict(ln1_g=(sh.D,), ln1_b=(sh.D,), wqkv=(sh.D, 3 * Hd), bqkv=(3 * Hd,), wo=(Hd, sh.D), bo=(sh.D,), ln2_g=(sh.D,), ln2_b=(sh.D,),
+                  w1=(sh.D, sh.F), b1=(sh.F,), w2=(sh.F, sh.D), b2=(sh.D,))
+    pd = {k: rnd(v, 1.0 if k.endswith("_g") else 0.02) for k, v in shapes.items()}
+    x, dy = rnd((sh.T, sh.D), 1.0), rnd((sh.T, sh.D), 1.0)
+    saved = torch.empty(fax.fax_block_saved_layout(dims_of(sh)).total, dtype=torch.uint8, device=DEV)
+    wsb = fax.fax_block_workspace_bytes(dims_of(sh))
+    y, ws = torch.empty_like(x), torch.empty(wsb, dtype=torch.uint8, device=DEV)
+    fax.fax_block_fwd(dims_of(sh), pd, x, y, saved, None, None, ws, wsb)
+
+    def run(flags, over):
+        up = dy.clone()
+        out = {"dx": up if over else torch.empty_like(x)}
+        out.update({k: torch.full(v, 7.0, dtype=torch.float32, device=DEV) for k, v in shapes.items()})
+        ws.fill_(255)  # NaN wherever a kernel reads what none has written
+        fax.fax_block_bwd(dims_of(sh, flags), pd, x, up, saved, out["dx"], out, 0, None, None, ws, wsb)
+        torch.cuda.synchronize()
+        return out
+
+    want = run(fax.FAX_FLAG_SINGLE_STREAM, False)
+    assert all(torch.isfinite(t).all() for t in want.values())
+    for over in (False, True):
+        for _ in range(2):
+            got = run(0, over)
+            for k in want:
+                assert torch.equal(got[k], want[k]), (k, over)
+    fax.fax_timing_enable(1)
+    try:
+        run(0, False)
+        rows = {r["name"]: (r["launches"], r["work"]) for r in fax.fax_timing_report(64)}
+    finally:
+        fax.fax_timing_enable(0)
+    n, work = rows.get("gemm_mfma_group", (0, 0.0))
+    assert n == launches and abs(work - share * 2.0 * sh.T * sh.D * (4 * Hd + 2 * sh.F)) <= 1e-6 * work
 
 
 CASES = [
