@@ -214,6 +214,22 @@ typedef struct FaxGemmRoute {
 int fax_gemm_route(int dtype, int ta, int tb, int M, int N, int K, int c_f32, int scratch, FaxGemmRoute* out, int32_t* tile_row,
                    int32_t* tile_col, int capacity);
 
+/* Host-only: what fax_attention_fwd and fax_attention_bwd make of a size (PATH_AUTO).
+ *   form           FAX_ATTENTION_*: the scalar kernels; the fp32 matrix-core ones; the bf16 ones, whose tiles divide the shape; their
+ *                  masked-edge form.
+ *   groups, waves  of the bf16 kernels' workgroups: a 32-row strip of queries (or keys) a wave, the groups sharing the other index
+ *                  (1 x 4: the form of a full chip; 0, 0 for the other kernels).
+ *   joint          1: the backward pass runs dQ and dK/dV as one launch.
+ * Exposed so that a test can assert that its sizes run the form they are about. */
+#define FAX_ATTENTION_SCALAR 0
+#define FAX_ATTENTION_F32 1
+#define FAX_ATTENTION_MFMA 2
+#define FAX_ATTENTION_EDGE 3
+typedef struct FaxAttentionRoute {
+  int32_t form, groups, waves, joint;
+} FaxAttentionRoute;
+int fax_attention_route(int dtype, int B, int S, int H, int dh, FaxAttentionRoute* out);
+
 /*
  * Forward pass of one pre-LayerNorm decoder block (Fig. 1; forward phase of Fig. 4):
  *   h1 = LN(x; ln1);  qkv = h1 Wqkv + bqkv;  ctx = causal softmax(Q K^T / sqrt(dh)) V per head;

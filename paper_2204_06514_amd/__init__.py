@@ -25,6 +25,7 @@ FAX_FLAG_ACCUMULATE = 2
 FAX_FLAG_DETERMINISTIC = 4
 PATH_AUTO, PATH_SCALAR, PATH_MFMA = 0, 1, 2
 FAX_GEMM_SCALAR, FAX_GEMM_F32, FAX_GEMM_MFMA, FAX_GEMM_EDGE, FAX_GEMM_SMALL = 0, 1, 2, 3, 4
+FAX_ATTENTION_SCALAR, FAX_ATTENTION_F32, FAX_ATTENTION_MFMA, FAX_ATTENTION_EDGE = 0, 1, 2, 3
 
 TENSOR_NAMES = ("ln1_g", "ln1_b", "wqkv", "bqkv", "wo", "bo", "ln2_g", "ln2_b", "w1", "b1", "w2", "b2")
 
@@ -76,6 +77,10 @@ class FaxGemmRoute(C.Structure):
     _fields_ = [(n, C.c_int32) for n in ("form", "tail", "tile_m", "tile_n", "splits", "tiles_m", "tiles_n", "group")]
 
 
+class FaxAttentionRoute(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("form", "groups", "waves", "joint")]
+
+
 class FaxMesh(C.Structure):
     _fields_ = [("data", C.c_int32), ("tensor", C.c_int32)]
 
@@ -107,6 +112,7 @@ def _load():
         "fax_gemm_plan": (i32, [i32, i32, i32, i32, P(FaxGemmPlan)]),
         "fax_gemm_tile_walk": (i32, [i32, i32, i32, i32, vp, vp, i32, P(C.c_int), P(C.c_int)]),
         "fax_gemm_route": (i32, [i32] * 8 + [P(FaxGemmRoute), vp, vp, i32]),
+        "fax_attention_route": (i32, [i32] * 5 + [P(FaxAttentionRoute)]),
         "fax_block_saved_layout": (i32, [P(FaxBlockDims), P(FaxSavedLayout)]),
         "fax_block_bwd_layout": (i32, [P(FaxBlockDims), P(FaxBwdLayout)]),
         "fax_block_workspace_bytes": (i32, [P(FaxBlockDims), P(sz)]),
@@ -348,6 +354,12 @@ def fax_attention_fwd(dtype, B, S, H, dh, qkv, ctx, lse, path=PATH_AUTO, stream=
 def fax_attention_bwd(dtype, B, S, H, dh, qkv, ctx, lse, dctx, dqkv, delta, path=PATH_AUTO, stream=None):
     _check(_lib.fax_attention_bwd(dtype, B, S, H, dh, _ptr(qkv), _ptr(ctx), _ptr(lse), _ptr(dctx), _ptr(dqkv),
                                   _ptr(delta), path, _stream(stream)))
+
+
+def fax_attention_route(dtype, B, S, H, dh):
+    out = FaxAttentionRoute()
+    _check(_lib.fax_attention_route(dtype, B, S, H, dh, C.byref(out)))
+    return out
 
 
 def fax_timing_enable(on):

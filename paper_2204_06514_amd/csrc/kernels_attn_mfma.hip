@@ -753,8 +753,8 @@ bool attn_mfma_supported(int dtype, int B, int S, int H, int dh) {
 
 // Whole 16-byte chunks per head are all that the masked-edge form asks for.  Measured against the scalar kernels, forward / backward
 // in us: one head of 17 x 64 7.8 / 15.3 -> 8.4 / 11.7 (launch and latency), 8 heads of 64 x 32 13.1 / 28.2 -> 8.6 / 11.9,
-// 45 heads of 1000 x 80 1485 / 2966 -> 41 / 102, 32 heads of 777 x 64 572 / 1075 -> 28 / 93, 16 heads of 1500 x 128
-// 1754 / 3791 -> 57 / 132.  Errors against float64, over ten shapes and four distributions, are the scalar kernels' to 2e-4 in
+// 45 heads of 1000 x 80 1485 / 2966 -> 37 / 104, 32 heads of 777 x 64 572 / 1075 -> 16 / 43, 16 heads of 1500 x 128
+// 1754 / 3791 -> 32 / 106.  Errors against float64, over ten shapes and four distributions, are the scalar kernels' to 2e-4 in
 // ctx and the gradients and to 7 % either way in lse (4e-8, half a unit in its last place).
 bool attn_edge_supported(int dtype, int B, int S, int H, int dh) {
   (void)B; (void)H;
@@ -778,11 +778,20 @@ static inline unsigned grid_of(int B, int S, int H) { return (unsigned)((((S + 1
 //   wider           5 x 2048 x 128   1x4 40 + 95, 2x2 23 + 58, 2x4 30 + 75      12 x 2048 x 128  1x4 41 + 98, 2x2 24 + 80, 2x4 31 + 78
 //                   45 x 1000 x 80   1x4 39 + 105, 2x2 44 + 138, 2x4 32 + 98    32 x 2048 x 128  1x4 45 + 142, 2x4 44 + 150
 // (2x2 and 4x1 at 64 wide take 64 and 128 KB of LDS; 2x2 and 2x4 above it 128.)
-struct AttnForm { int groups, waves; };
-static AttnForm attn_form(int B, int S, int H, int dh) {
+// Joint: up to two rounds of workgroups in all, dQ and dK/dV run side by side, as one launch.  What ties them together is delta, which
+// the dQ kernel produces as it goes; a small kernel of its own computes it first, which costs 2.5 us: 32 heads of 777 x 64
+// 57 -> 45 us, 5 of 2048 x 128 57 -> 48, 2 of 2048 x 64 29 -> 19.5; 64 of 512 x 64, just beyond the line, 24.5 and 25.8.
+static constexpr size_t bwd_lds(int groups, int row) { return groups * 2 * (2 * (size_t)TR * row * 2 + 4 * 256); }  // two stages of Q tile | dO tile | lse, delta each
+AttnForm attn_form(int B, int S, int H, int dh) {
   const long long heads = (long long)B * H, t32 = (S + 31) / 32 * heads, t64 = (S + 63) / 64 * heads, t128 = (S + 127) / 128 * heads;
-  if (dh <= 64) return t32 <= 256 ? AttnForm{4, 1} : t64 <= 1024 ? AttnForm{2, 2} : AttnForm{1, 4};
-  return t64 <= 384 ? AttnForm{2, 2} : t128 <= 400 ? AttnForm{2, 4} : AttnForm{1, 4};
+  AttnForm f;
+  if (dh <= 64) f = t32 <= 256 ? AttnForm{4, 1, false} : t64 <= 1024 ? AttnForm{2, 2, false} : AttnForm{1, 4, false};
+  else f = t64 <= 384 ? AttnForm{2, 2, false} : t128 <= 400 ? AttnForm{2, 4, false} : AttnForm{1, 4, false};
+  if (f.groups > 1) {
+    const int keys = (dh <= 64 ? 32 : 16) * f.waves, queries = 32 * f.waves;  // of a workgroup
+    f.joint = ((S + keys - 1) / keys + (S + queries - 1) / queries) * heads < 2 * 256 * (long long)(163840 / bwd_lds(f.groups, dh <= 64 ? 64 : 128));
+  }
+  return f;
 }
 bool attn_split_form(int B, int S, int H, int dh) { return attn_form(B, S, H, dh).groups > 1; }
 
@@ -829,7 +838,7 @@ static int bwd_t(int B, int S, int H, int dh, const bf16_t* qkv, const bf16_t* c
   const dim3 grid(G == 1 ? grid_of(B, S, H) : (S + 32 * WPG - 1) / (32 * WPG) * B * H);
   auto dkv = [&]() -> int {
     if constexpr (DW == 64) {
-      constexpr size_t lds_kv = G * 2 * (2 * (size_t)TR * DH * 2 + 4 * 256);  // per group two stages of Q tile | dO tile | lse, delta
+      constexpr size_t lds_kv = bwd_lds(G, DH);
       FAX_TRY(set_lds(attn_bwd_dkv_phased_mfma_kernel<DW, EDGE, G, WPG>, lds_kv));
       hipLaunchKernelGGL((attn_bwd_dkv_phased_mfma_kernel<DW, EDGE, G, WPG>), grid, dim3(64 * G * WPG), lds_kv, s, S, H, B * H, dh, qkv, lse,
                          delta, dctx, dqkv);
@@ -838,14 +847,11 @@ static int bwd_t(int B, int S, int H, int dh, const bf16_t* qkv, const bf16_t* c
     }
     return FAX_OK;
   };
-  // Up to two rounds of workgroups in all: the two kernels run side by side, as one launch.  What ties them together is delta, which
-  // the dQ kernel produces as it goes; a small kernel of its own computes it first, which costs 2.5 us: 32 heads of 777 x 64
-  // 57 -> 45 us, 5 of 2048 x 128 57 -> 48, 2 of 2048 x 64 29 -> 19.5; 64 of 512 x 64, just beyond the line, 24.5 and 25.8.
-  if constexpr (G > 1) {
-    constexpr size_t lds = G * 2 * (2 * (size_t)TR * DH * 2 + 4 * 256);
+  if constexpr (G > 1 && WPG < 4) {  // (2x4 begins beyond two rounds)
+    constexpr size_t lds = bwd_lds(G, DH);
     constexpr int KT = DW == 64 ? 32 * WPG : 16 * WPG;  // keys of a workgroup
     const unsigned first = (S + KT - 1) / KT * B * H;
-    if (first + grid.x < 2 * 256 * (163840 / lds)) {
+    if (attn_form(B, S, H, dh).joint) {
       FAX_TRY(attn_delta(FAX_BF16, B, S, H, dh, ctx, dctx, delta, s));
       FAX_TRY(set_lds(attn_bwd_both_mfma_kernel<DW, EDGE, G, WPG>, lds));
       hipLaunchKernelGGL((attn_bwd_both_mfma_kernel<DW, EDGE, G, WPG>), dim3(first + grid.x), dim3(64 * G * WPG), lds, s, S, H, B * H, dh,
