@@ -25,7 +25,11 @@
  *     projection has 3*H*dh columns ordered [Q | K | V], head-major within each.
  *   - dtype FAX_BF16: activations, parameters and activation gradients are
  *     bfloat16, every accumulation, statistic and softmax is fp32.
- *     dtype FAX_F32: everything is fp32 with true fp32 multiply-add.
+ *     dtype FAX_F32: tensors, statistics, sums and results are fp32.  In the matrix products every factor, whatever its size,
+ *     enters as three bf16 numbers that add up to it exactly, and six of their nine products are added in fp32: an element is
+ *     within (K + 2) 2^-24 of its K terms' magnitudes added up, as with fp32 multiply-add in any order (2-norm error at K = 1024
+ *     1.3e-7, where that instruction gives 5.7e-7).  Fewer than four terms, and elements whose sum in pieces is not finite or
+ *     beyond 2^80, are fp32 multiply-add; so are attention and the sizes that the scalar kernels take.
  *     Parameter GRADIENTS are fp32 for both dtypes.
  *   - Pointers must be 16-byte aligned.
  */
@@ -53,18 +57,18 @@ enum { FAX_GELU_TANH = 0, FAX_GELU_ERF = 1 };
 /* FaxBlockDims.flags */
 #define FAX_FLAG_TP_PARTIAL 1u /* also emit the pre-reduction partial sums (Sec. 3.2) */
 /* fax_block_bwd (and the backward pass inside fax_train_step) by default enqueues the four
- * weight-gradient products and the folds of the LayerNorm parameter gradients on a stream of the
- * library's own, forked from the caller's stream when the call begins and joined back into it
- * before the call returns: they depend on nothing later in the chain of input gradients and run
- * beside it.  To the caller the call behaves as if everything were on its stream (ordered after
+ * weight-gradient products, some of them together in one launch, and the folds of the LayerNorm
+ * parameter gradients on a stream of the library's own, forked from the caller's stream at the
+ * point where the first of them can start and joined back into it before the call returns: they
+ * depend on nothing later in the chain of input gradients and run beside it.  To the caller the call behaves as if everything were on its stream (ordered after
  * what was enqueued before, before what is enqueued after).  The stream and its events are
  * created once per device, on first use (not under stream capture: make one call before
  * capturing), and live until the process ends; no device memory is involved.  Host threads that
  * call into the library on the same device share that stream: their calls are enqueued one after
- * the other on it.  (When every product of
- * the backward pass fills the chip a whole number of times there is nothing to run beside, and
- * the library keeps to the caller's stream by itself.)  With this flag everything is enqueued on
- * the caller's stream only. */
+ * the other on it.  The library keeps to the caller's stream by
+ * itself where the products are too short for the host to keep up with two, and where they leave
+ * next to nothing idle to run beside (fax_block_bwd_streams tells).  With this flag everything is
+ * enqueued on the caller's stream only; the results are the same bits. */
 #define FAX_FLAG_SINGLE_STREAM 2u
 
 /* FaxModelDims.flags */

@@ -362,6 +362,8 @@ static double products_us(const FaxBlockDims& d) {
 //     3578 and 3596, 16384 x 2304 3442 and 3457;
 //   all weight gradients in shared launches, and products of less than 200 us that leave under a tenth idle, 2048 x 1024 346 and 325;  on the
 //     other side 4096 x 1024 (312 us) 452 and 466, 3108 x 512 (a fifth idle) 253 and 268, 4096 x 512 (separate launches), two layers, 570 and 588.
+// What a product leaves idle is asked of the tiles it takes on one stream: on two, input gradients may stay on 256 x 256 tiles where one takes
+// 256 x 192 (GemmArgs::beside), which add up the same terms in the same order.
 // groups: the weight gradients that share a launch.  By the sizes alone, so that one or two streams give the same bits.
 struct BwdPlan { bool side; int groups; };
 static BwdPlan bwd_plan(const FaxBlockDims& d) {

@@ -1,32 +1,5 @@
-// Causal flash attention on the CDNA4 matrix cores: bf16 operands, fp32 scores and statistics.
-//
-// All three kernels work on "transposed" MFMA products so that the softmax row of one query
-// (forward, dQ) or the column of one key (dK/dV) sits inside one lane plus its partner lane
-// (lane ^ 32), and the probabilities come out of the score accumulators already in the
-// register layout the next MFMA wants as its B operand: no cross-lane shuffles of P.
-//
-//   forward   S^T = K Q^T (A = K tile from LDS, B = Q rows held in registers)
-//             O^T += V^T P^T (A = V tile through the LDS transpose read, B = P registers)
-//   dQ        S^T, dP^T = V dO^T as above, dS^T = P^T (dP^T - delta);  dQ^T += K^T dS^T
-//   dK, dV    S = Q K^T, dP = dO V^T (A = Q / dO tile from LDS, B = K / V rows in registers),
-//             dV^T += dO^T P,  dK^T += Q^T dS   (A through the transpose read)
-//
-// 32x32x16 MFMA lane layout (lane l, g = l >> 5): operand element e of row/col (l & 31) is
-// k = 8 g + e; accumulator v holds row 8 (v >> 2) + 4 g + (v & 3), column (l & 31).  Taking
-// accumulator elements 8 h .. 8 h + 7 as the B operand of step h therefore assigns k-slot
-// (g, e) to row 16 h + 8 (e >> 2) + 4 g + (e & 3): two runs of four consecutive rows, which is
-// exactly what two ds_read_b64_tr_b16 deliver for the matching A operand.
-//
-// LDS tiles are [64 rows][DH] bf16 with the 16-byte chunk index XOR-ed by
-// f(row) = ((row & 3) << 1) | ((row >> 2) & 1), plus (row & 8) when a row has 16 chunks:
-// consecutive rows land in distinct chunks (128-bit row-fragment reads) and 4 consecutive rows in
-// 4 distinct 32-byte pairs (transpose reads), so one copy of a tile serves both access patterns.
-// Measured on gfx950 with 256-byte rows: row-fragment reads 122 B/clk/CU with the (row & 8) term,
-// 102 without; transpose reads 77 B/clk/CU either way (55 unswizzled) -- ds_read_b64_tr_b16 tops
-// out at about 60 % of the plain read rate.
-//
-// No atomics: dQ has one writer per query row, dK/dV one writer per key row; S and dP are
-// recomputed in both backward kernels (7 tile products instead of 5).
+// Causal flash attention on the CDNA4 matrix cores: bf16 operands, fp32 scores and statistics.  How the three kernels lay out their
+// products, registers and LDS tiles: attn_mfma_common.h.
 #include "attn_dkv16.h"
 
 namespace fax {

@@ -14,7 +14,7 @@
 //
 // A 512-thread workgroup (8 wavefronts, two per SIMD) computes a BM x BN tile: WM x WN waves share the tile, KS such groups of
 // waves share the contraction indices of a slab (16 each) and add their accumulators up through LDS at the end.
-// Slabs come as fp32 through registers, one or two ahead, are cut there (11 vector instructions for a pair of numbers, once per
+// Slabs come as fp32 through registers, one or two ahead, are cut there (13 vector instructions for a pair of numbers, once per
 // workgroup) and stored as three bf16 planes to the other LDS buffer while the current slab is multiplied; one barrier per slab.
 // Any M, N, K and orientation: rows and columns beyond the operands are fetched from their last
 // row or column and never stored, contraction indices beyond K become zeros on the way into LDS.
@@ -25,8 +25,8 @@
 //
 // What the pieces cannot carry is computed again, by the wave that finds it in its own partial sums, with v_mfma_f32_32x32x2_f32 on the
 // factors as they are, straight from memory: sums that are not finite (an infinite factor's remainder is NaN, and an infinity times a
-// piece that is zero is NaN where the product is an infinity; a factor that is not finite, or not below 2^103, always leaves such a sum, and
-// so does a partial sum that is not below 2^80).  A sum that is finite stays as it is, whatever its neighbours are: which of the two an
+// piece that is zero is NaN where the product is an infinity; a factor that is not finite, or 2^104 and more, always leaves such a sum, and
+// so does a partial sum of 2^80 and more).  A sum that is finite stays as it is, whatever its neighbours are: which of the two an
 // element gets hangs on its own row and column alone.  So are contractions over fewer than four indices, whose sums are so short that the
 // instruction rounds less: over 1 index 2.5e-8 and 2.6e-8 in the pieces, at most 1.0 and 1.8 x 2^-24 of |x y|, over 2 at most 1.9 and 2.4 of
 // the sum of |x y|, over 4 3.3 and 2.4.
@@ -132,11 +132,12 @@ __device__ __forceinline__ void f32_tile(int id, int tiles_m, int tiles_n, int& 
   tn = rest / gsz;
 }
 
-// Bound, with a full chip, by the matrix cores at the clock that their power leaves (4096 x 4096 x 4096: 196 TFLOP/s counted once, 1.18 of
-// bf16 PFLOP/s, busy 55 to 60 % of 2.0 GHz), with one workgroup on a CU by the chain from barrier to barrier: loads, cutting, LDS and back, 24
-// MFMAs.  v_mfma_f32_32x32x2_f32 sustains 154 from registers alone; the kernel on it that this one replaces, us: 2048 x 3072 x 1024 145, here
-// 95; 2048 x 1024 x 1024 52, 32; 2048 x 4096 x 1024 160, 100; 2048 x 1024 x 4096 172, 103; its block of 2048 tokens x 1024 wide,
-// forward and backward, 1625, 1200.
+// Bound, with a full chip, by the matrix cores at the clock that their power leaves (4096 x 4096 x 4096: 185 to 202 TFLOP/s counted once, 1.1 to
+// 1.2 bf16 PFLOP/s), with one workgroup on a CU by the chain from barrier to barrier: loads, cutting, LDS and back, 24
+// MFMAs.  In the block below the matrix cores are busy 37 to 59 % of the busy CUs' clocks, the vector unit, mostly with the cutting, 41 to 56 %, and
+// waits are 19 to 24 % of the waves' time.  v_mfma_f32_32x32x2_f32 sustains 154 from registers alone; the kernel on it that this one replaces, us: 2048 x 3072 x 1024 145, here
+// 95; 2048 x 1024 x 1024 52, 30; 2048 x 4096 x 1024 160, 98; 2048 x 1024 x 4096 172, 104; its block of 2048 tokens x 1024 wide,
+// forward and backward, 1625, 1165.
 // Phases the other way round in one or both waves of a SIMD, s_setprio around the cutting, requests further ahead: within 2 %.
 // Fragments requested before the slab is cut instead of where they are used: 3 %, 128 x 64 8 %.  128 x 64 as 64 x 32 per wave and slabs of 32: 6 % slower.
 template <int WM, int WN, int KS, int TM, int TN>

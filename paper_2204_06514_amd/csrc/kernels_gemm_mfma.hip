@@ -392,7 +392,10 @@ static bool group_plan(const GemmArgs* g, int n, GroupPlan* plan) {
 //   beyond the line, 676 and 691.
 // Attention's two: at 128^2 tiles, and not much longer than the QKV one alone (the other one would start before the attention kernels and run
 //   beside them).  4096 x 1024 470 -> 449, 2222 x 1280 563 -> 552, 4096 x 768 380 -> 372; beyond the line 3108 x 512 271 and 277, 1999 x
-//   2000 843 and 854, 3600 x 1536 908 and 915.
+//   2000 843 and 854, 3600 x 1536 908 and 915.  With the feed-forward's two apart, apart and together: 2500 x 968 472 and 458, 3500 x 768 406 and
+//   392, 3000 x 1024 491 and 485, 4000 x 968 699 and 691, 5000 x 800 652 and 639; the other way 2500 x 768 318 and 325, and around 4200 to 4560 rows
+//   960 to 1024 wide up to 1 % where attention is a split form, whose workgroups leave no room beside them, and 2 to 3.5 % against apart beside
+//   the unsplit one (66 heads of 700 x 88 688 and 700, of 760 x 88 730 and 757): each choice alone is within 1 % there, and no size tells them from 4000 x 968.
 int gemm_groups(const GemmArgs (&w)[4], const GemmArgs (&in)[4]) {
   bool pairs = true, full = true;
   for (int i = 0; i < 4; i++) {

@@ -121,7 +121,7 @@ def test_products_are_priced_by_the_kernel_that_runs_them():
     assert _gemm_tflops(F=2047) < 0.3 * whole and _gemm_tflops(V=32003) > 0.8 * whole
     # whole chunks but no whole tiles: the masked-edge or small-tile form
     assert _gemm_tflops(D=504, F=2016, H=9, dh=56, V=32003) > 5 * scalar
-    # fp32: the matrix cores give 155 TFLOP/s at most, whatever the sizes
+    # fp32: six bf16 products to one, 155 TFLOP/s at most inside a pass
     for kw in (dict(D=1024, F=4096), dict(D=1000, F=4000, H=10, dh=100, V=32003), dict(D=501, F=2003, H=3, dh=167)):
         assert 40 < _gemm_tflops(dtype="f32", **kw) < 155, kw
 
