@@ -221,8 +221,8 @@ int fax_gemm_route(int dtype, int ta, int tb, int M, int N, int K, int c_f32, in
 /* Host-only: what fax_attention_fwd and fax_attention_bwd make of a size (PATH_AUTO).
  *   form           FAX_ATTENTION_*: the scalar kernels; the fp32 matrix-core ones; the bf16 ones, whose tiles divide the shape; their
  *                  masked-edge form.
- *   groups, waves  of the bf16 kernels' workgroups: a 32-row strip of queries (or keys) a wave, the groups sharing the other index
- *                  (1 x 4: the form of a full chip; 0, 0 for the other kernels).
+ *   groups, waves  of the bf16 kernels' workgroups in the forward pass, bwd_groups, bwd_waves in the backward pass: a strip of rows to a
+ *                  wave, the groups sharing the other index (1 x 4: the form of a full chip; 0, 0 for the other kernels).
  *   joint          1: the backward pass runs dQ and dK/dV as one launch.
  * Exposed so that a test can assert that its sizes run the form they are about. */
 #define FAX_ATTENTION_SCALAR 0
@@ -230,7 +230,7 @@ int fax_gemm_route(int dtype, int ta, int tb, int M, int N, int K, int c_f32, in
 #define FAX_ATTENTION_MFMA 2
 #define FAX_ATTENTION_EDGE 3
 typedef struct FaxAttentionRoute {
-  int32_t form, groups, waves, joint;
+  int32_t form, groups, waves, bwd_groups, bwd_waves, joint;
 } FaxAttentionRoute;
 int fax_attention_route(int dtype, int B, int S, int H, int dh, FaxAttentionRoute* out);
 

@@ -78,7 +78,7 @@ class FaxGemmRoute(C.Structure):
 
 
 class FaxAttentionRoute(C.Structure):
-    _fields_ = [(n, C.c_int32) for n in ("form", "groups", "waves", "joint")]
+    _fields_ = [(n, C.c_int32) for n in ("form", "groups", "waves", "bwd_groups", "bwd_waves", "joint")]
 
 
 class FaxMesh(C.Structure):

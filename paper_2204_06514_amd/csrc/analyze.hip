@@ -33,14 +33,14 @@ static AttnCost attn_cost_us(const FaxBlockDims& b) {
   AttnCost rate, chain{0.0, 0.0};
   if (attn_edge_supported(b.dtype, b.B, b.S, b.H, b.dh)) {
     const double tiles = 2.0 * ((b.S + 127) / 128 + 1);
-    const bool split = attn_split_form(b.B, b.S, b.H, b.dh);
+    const bool fwd_split = attn_fwd_form(b.B, b.S, b.H, b.dh).groups > 1, bwd_split = attn_bwd_form(b.B, b.S, b.H, b.dh).groups > 1;
     if (attn_mfma_supported(b.dtype, b.B, b.S, b.H, b.dh)) {
       rate = b.dh == 64 ? AttnCost{0.32, 1.05} : AttnCost{0.59, 2.32};
-      chain = split ? AttnCost{4.0 + 0.6 * tiles, 10.0 + 1.45 * tiles} : AttnCost{3.0 + 1.1 * tiles, 9.0 + 2.7 * tiles};
+      chain = {fwd_split ? 4.0 + 0.6 * tiles : 3.0 + 1.1 * tiles, bwd_split ? 10.0 + 1.45 * tiles : 9.0 + 2.7 * tiles};
     } else {
       rate = b.dh <= 64 ? AttnCost{0.70, 2.2} : b.dh <= 96 ? AttnCost{0.81, 2.6} : AttnCost{1.0, 3.2};
-      chain = split ? b.dh <= 64 ? AttnCost{4.0 + 0.9 * tiles, 10.0 + 3.2 * tiles} : AttnCost{4.0 + 1.5 * tiles, 10.0 + 4.2 * tiles}
-                    : AttnCost{3.0 + (b.dh <= 64 ? 1.6 : 2.1) * tiles, 9.0 + 5.2 * tiles};
+      chain = {fwd_split ? 4.0 + (b.dh <= 64 ? 0.9 : 1.5) * tiles : 3.0 + (b.dh <= 64 ? 1.6 : 2.1) * tiles,
+               bwd_split ? 10.0 + (b.dh <= 64 ? 3.2 : 4.2) * tiles : 9.0 + 5.2 * tiles};
     }
   } else if (attn_f32_supported(b.dtype, b.dh, nullptr, nullptr, nullptr, nullptr)) {
     const int width = (b.dh + 31) / 32 * 32;

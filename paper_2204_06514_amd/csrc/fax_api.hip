@@ -669,11 +669,11 @@ int fax_attention_route(int dtype, int B, int S, int H, int dh, FaxAttentionRout
   if (!out) { set_error("out is NULL"); return FAX_ERR_INVALID_ARG; }
   if (dtype != FAX_F32 && dtype != FAX_BF16) { set_error("bad dtype %d", dtype); return FAX_ERR_INVALID_ARG; }
   if (B <= 0 || S <= 0 || H <= 0 || dh <= 0) { set_error("non-positive attention size B=%d S=%d H=%d dh=%d", B, S, H, dh); return FAX_ERR_INVALID_ARG; }
-  *out = FaxAttentionRoute{FAX_ATTENTION_SCALAR, 0, 0, 0};
+  *out = FaxAttentionRoute{FAX_ATTENTION_SCALAR, 0, 0, 0, 0, 0};
   if (attn_f32_supported(dtype, dh, nullptr, nullptr, nullptr, nullptr)) out->form = FAX_ATTENTION_F32;
   if (!attn_edge_supported(dtype, B, S, H, dh)) return FAX_OK;
-  const AttnForm f = attn_form(B, S, H, dh);
-  *out = FaxAttentionRoute{attn_mfma_supported(dtype, B, S, H, dh) ? FAX_ATTENTION_MFMA : FAX_ATTENTION_EDGE, f.groups, f.waves, f.joint};
+  const AttnForm f = attn_fwd_form(B, S, H, dh), b = attn_bwd_form(B, S, H, dh);
+  *out = FaxAttentionRoute{attn_mfma_supported(dtype, B, S, H, dh) ? FAX_ATTENTION_MFMA : FAX_ATTENTION_EDGE, f.groups, f.waves, b.groups, b.waves, b.joint};
   return FAX_OK;
 }
 

@@ -178,9 +178,9 @@ int attn_bwd_f32(int B, int S, int H, int dh, const void* qkv, const void* ctx, 
 bool attn_mfma_supported(int dtype, int B, int S, int H, int dh);  // the plain form of the matrix-core kernels
 bool attn_edge_supported(int dtype, int B, int S, int H, int dh);  // plain or masked-edge form
 int attn_fwd_mfma(int B, int S, int H, int dh, const void* qkv, void* ctx, float* lse, hipStream_t s);
-bool attn_split_form(int B, int S, int H, int dh);  // few enough workgroups for one of the split forms
 struct AttnForm { int groups, waves; bool joint; };  // waves of a group; joint: dQ and dK/dV in one launch
-AttnForm attn_form(int B, int S, int H, int dh);
+AttnForm attn_fwd_form(int B, int S, int H, int dh);
+AttnForm attn_bwd_form(int B, int S, int H, int dh);
 int attn_bwd_mfma(int B, int S, int H, int dh, const void* qkv, const void* ctx, const float* lse,
                   const void* dctx, void* dqkv, float* delta, hipStream_t s);
 

@@ -740,33 +740,53 @@ static int set_lds(K kern, size_t bytes) {
   return FAX_OK;
 }
 
+static constexpr size_t bwd_lds(int groups, int row) { return groups * 2 * (2 * (size_t)TR * row * 2 + 4 * 256); }  // two stages of Q tile | dO tile | lse, delta each
 static inline unsigned grid_of(int B, int S, int H) { return (unsigned)((((S + 127) / 128 + 1) / 2) * B * H); }
 
-// Which form: groups and waves to a group.  The more groups, the shorter a workgroup's chain of tiles, until there are more
-// workgroups than CUs to take them: what a workgroup loads is then shared by fewer rows.  The lines lie where the forms cross, us, forward and
-// backward (heads x S x head width; 1x4 is the form of a full chip, a pair of 128-row tiles to a workgroup):
-//   up to 64 wide   2 x 2048 x 64    1x4 29 + 78, 2x2 15 + 39, 4x1 11 + 29      8 x 256 x 64     1x4 11 + 28, 2x2 9 + 13, 4x1 9 + 12
-//                   32 x 777 x 64    1x4 30 + 96, 2x2 17 + 56, 4x1 31 + 85      64 x 1024 x 64   1x4 21 + 57, 2x2 19 + 56
-//                   128 x 1024 x 64  1x4 31 + 97, 2x2 37 + 106
-//   wider           5 x 2048 x 128   1x4 40 + 95, 2x2 23 + 58, 2x4 30 + 75      12 x 2048 x 128  1x4 41 + 98, 2x2 24 + 80, 2x4 31 + 78
-//                   45 x 1000 x 80   1x4 39 + 105, 2x2 44 + 138, 2x4 32 + 98    32 x 2048 x 128  1x4 45 + 142, 2x4 44 + 150
-// (2x2 and 4x1 at 64 wide take 64 and 128 KB of LDS; 2x2 and 2x4 above it 128.)
-// Joint: up to two rounds of workgroups in all, dQ and dK/dV run side by side, as one launch.  What ties them together is delta, which
-// the dQ kernel produces as it goes; a small kernel of its own computes it first, which costs 2.5 us: 32 heads of 777 x 64
-// 57 -> 45 us, 5 of 2048 x 128 57 -> 48, 2 of 2048 x 64 29 -> 19.5; 64 of 512 x 64, just beyond the line, 24.5 and 25.8.
-static constexpr size_t bwd_lds(int groups, int row) { return groups * 2 * (2 * (size_t)TR * row * 2 + 4 * 256); }  // two stages of Q tile | dO tile | lse, delta each
-AttnForm attn_form(int B, int S, int H, int dh) {
-  const long long heads = (long long)B * H, t32 = (S + 31) / 32 * heads, t64 = (S + 63) / 64 * heads, t128 = (S + 127) / 128 * heads;
-  AttnForm f;
-  if (dh <= 64) f = t32 <= 256 ? AttnForm{4, 1, false} : t64 <= 1024 ? AttnForm{2, 2, false} : AttnForm{1, 4, false};
-  else f = t64 <= 384 ? AttnForm{2, 2, false} : t128 <= 400 ? AttnForm{2, 4, false} : AttnForm{1, 4, false};
-  if (f.groups > 1) {
-    const int keys = (dh <= 64 ? 32 : 16) * f.waves, queries = 32 * f.waves;  // of a workgroup
-    f.joint = ((S + keys - 1) / keys + (S + queries - 1) / queries) * heads < 2 * 256 * (long long)(163840 / bwd_lds(f.groups, dh <= 64 ? 64 : 128));
+// Which form: groups and waves to a group.  1x4 (a pair of 128-row tiles to a workgroup, two of them on a CU) is the form of a full chip.
+// The more groups, the shorter a workgroup's chain of 64-wide tiles, but the more of the streamed index is loaded again, and the split forms'
+// workgroups, which all groups' tiles make large, are alone on a CU (2x2 up to 64 wide: two).  So a split pays while its workgroups are
+// about a round of the 256 CUs, and for more of them the longer the sequence is: its workgroups' chains differ, short ones fill up
+// behind long ones.  With one 64-wide tile to a sequence
+// there is nothing to split (2x2 takes part in the backward pass for the joint launch).
+// The lines lie where the forms cross in 968 shapes of 2 to 1000 heads, 17 to 4096 long, 40 to 128 wide, each kernel timed back to back
+// in a graph.  Over those the choice is 1.1 % above the fastest form of each, at most 1.5 % above 1x4, on average 25 % below it; over 330 others, drawn
+// at random, 1.8 %, 1.6 % and 31 %.  us, 1x4 and the others:
+//   forward, up to 64 wide   100 heads of 34 5.3, 2x2 5.8, 4x1 7.5;  128 of 100 7.7, 2x2 6.4;  400 of 100 10.9, 2x2 14.2;  6 of 256 10.4, 2x2 5.2, 4x1 5.1;  200 of 256 14.3, 2x2 14.1, 300 18.8 and 19.7;
+//                            2 of 2048 32, 2x2 17.5, 4x1 14.0;  32 of 777 32, 2x2 19, 4x1 34;  66 of 1024 31, 2x2 28, 128 34 and 38
+//   forward, wider           300 of 64 x 80 8.6, 2x2 14.9;  128 of 256 x 80 23, 2x2 21, 2x4 17;  200 of 256 x 128 21, 2x4 23;  6 of 2048 x 128 43, 2x2 25, 2x4 33;
+//                            45 of 1024 x 80 42, 2x2 47, 2x4 36;  32 of 2048 x 128 47, 2x4 47
+//   backward, up to 64 wide  100 of 34 14.3, 2x2 11.7, 4x1 18.7;  400 of 64 19.7, 2x2 22.4;  400 of 100 32, 2x2 40;  200 of 256 35.6, 2x2 36.4;  2 of 2048 80, 2x2 29, 4x1 22.5;  32 of 777 97, 2x2 46, 4x1 85
+//   backward, wider          300 of 34 x 80 18, 2x2 32;  66 of 64 x 80 14.5, 2x2 11.1;  128 of 256 x 80 50, 2x2 61, 2x4 45;  200 of 256 x 128 51, 2x4 67;  6 of 2048 x 128 100, 2x2 56, 2x4 78;
+//                            12 of 2048 x 128 103, 2x2 83, 2x4 82;  45 of 1024 x 80 107, 2x4 103;  32 of 2048 x 128 139, 2x4 154
+AttnForm attn_fwd_form(int B, int S, int H, int dh) {
+  const long long heads = (long long)B * H;
+  const int n32 = (S + 31) / 32, n64 = (S + 63) / 64, n128 = (S + 127) / 128;
+  if (n64 == 1) return AttnForm{1, 4, false};
+  if (dh <= 64) {
+    if (n128 > 1 && n32 * heads <= 256) return AttnForm{4, 1, false};
+    return n64 * heads <= (n128 == 1 ? 400 : n128 == 2 ? 800 : 1024) ? AttnForm{2, 2, false} : AttnForm{1, 4, false};
   }
-  return f;
+  if (n64 * heads <= (n64 < 12 ? 256 : 416)) return AttnForm{2, 2, false};
+  return n128 > 1 && n128 * heads <= (n128 < 4 ? 256 : n128 < 6 ? 300 : 528) ? AttnForm{2, 4, false} : AttnForm{1, 4, false};
 }
-bool attn_split_form(int B, int S, int H, int dh) { return attn_form(B, S, H, dh).groups > 1; }
+// Joint: dQ and dK/dV side by side, as one launch, while their workgroups are up to two rounds or so.  What ties them together is delta, which
+// the dQ kernel produces as it goes; a small kernel of its own computes it first, which costs 2.5 us: 32 heads of 777 x 64
+// 57 -> 46 us, 6 of 2048 x 128 60 -> 56, 2 of 2048 x 64 31.5 -> 22.5; 66 of 1024 x 64 and 200 of 256 x 64, beyond the line, 72 and 76, 36 and 39.
+AttnForm attn_bwd_form(int B, int S, int H, int dh) {
+  const long long heads = (long long)B * H;
+  const int n32 = (S + 31) / 32, n64 = (S + 63) / 64, n128 = (S + 127) / 128;
+  if (dh <= 64) {
+    if (n128 > 1 && n32 * heads <= (n128 < 4 ? 144 : 256)) return AttnForm{4, 1, true};
+    const long long t64 = n64 * heads;
+    return t64 <= (n64 == 1 ? 256 : n128 == 1 ? 400 : n128 == 2 ? 800 : 1024) ? AttnForm{2, 2, 2 * t64 < (n64 <= 2 ? 640 : n64 <= 4 ? 780 : 1024)} : AttnForm{1, 4, false};
+  }
+  const bool whole = attn_mfma_supported(FAX_BF16, B, S, H, dh);
+  const long long both = (n32 + n64) * heads;  // workgroups of 2x2: 32 keys, 64 queries
+  if (both <= (n64 == 1 ? 256 : n64 == 2 ? (whole ? 768 : 500) : n64 < 8 ? min(700, 256 + 144 * (n64 - 1)) : 900)) return AttnForm{2, 2, both <= 600};
+  const int most = n128 == 1 ? 128 : n128 < 4 ? 256 : n128 < 6 ? (whole ? 256 : 300) : whole && n128 <= 16 ? 320 : 400;
+  return n64 > 1 && n128 * heads <= most ? AttnForm{2, 4, false} : AttnForm{1, 4, false};
+}
 
 template <int DW, bool EDGE, int G, int WPG>
 static int fwd_t(int B, int S, int H, int dh, const bf16_t* qkv, bf16_t* ctx, float* lse, hipStream_t s) {
@@ -780,8 +800,7 @@ static int fwd_t(int B, int S, int H, int dh, const bf16_t* qkv, bf16_t* ctx, fl
 
 // Whole tiles or masked edges, head width as computed, groups and their waves.
 template <typename F>
-static int by_form(int B, int S, int H, int dh, F f) {
-  const AttnForm form = attn_form(B, S, H, dh);
+static int by_form(const AttnForm& form, int B, int S, int H, int dh, F f) {
   auto groups = [&](auto dw, auto edge) -> int {
     if (form.groups == 1) return f(dw, edge, I<1>{}, I<4>{});
     if constexpr (decltype(dw)::value == 64) {
@@ -798,13 +817,13 @@ static int by_form(int B, int S, int H, int dh, F f) {
 int attn_fwd_mfma(int B, int S, int H, int dh, const void* qkv, void* ctx, float* lse, hipStream_t s) {
   const bf16_t* q = (const bf16_t*)qkv;
   bf16_t* c = (bf16_t*)ctx;
-  return by_form(B, S, H, dh, [&](auto dw, auto edge, auto g, auto wpg) {
+  return by_form(attn_fwd_form(B, S, H, dh), B, S, H, dh, [&](auto dw, auto edge, auto g, auto wpg) {
     return fwd_t<decltype(dw)::value, decltype(edge)::value, decltype(g)::value, decltype(wpg)::value>(B, S, H, dh, q, c, lse, s);
   });
 }
 
 template <int DW, bool EDGE, int G, int WPG>
-static int bwd_t(int B, int S, int H, int dh, const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx,
+static int bwd_t(bool joint, int B, int S, int H, int dh, const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx,
                  bf16_t* dqkv, float* delta, hipStream_t s) {
   constexpr int DH = row_width<DW>();
   constexpr size_t lds_q = G * 2 * (2 * (size_t)TR * DH * 2);  // per group two stages of K tile | V tile
@@ -824,7 +843,7 @@ static int bwd_t(int B, int S, int H, int dh, const bf16_t* qkv, const bf16_t* c
     constexpr size_t lds = bwd_lds(G, DH);
     constexpr int KT = DW == 64 ? 32 * WPG : 16 * WPG;  // keys of a workgroup
     const unsigned first = (S + KT - 1) / KT * B * H;
-    if (attn_form(B, S, H, dh).joint) {
+    if (joint || G == 4) {
       FAX_TRY(attn_delta(FAX_BF16, B, S, H, dh, ctx, dctx, delta, s));
       FAX_TRY(set_lds(attn_bwd_both_mfma_kernel<DW, EDGE, G, WPG>, lds));
       hipLaunchKernelGGL((attn_bwd_both_mfma_kernel<DW, EDGE, G, WPG>), dim3(first + grid.x), dim3(64 * G * WPG), lds, s, S, H, B * H, dh,
@@ -833,12 +852,14 @@ static int bwd_t(int B, int S, int H, int dh, const bf16_t* qkv, const bf16_t* c
       return FAX_OK;
     }
   }
-  // dQ first: it also produces delta, which the dK/dV kernel reads
-  FAX_TRY(set_lds(attn_bwd_dq_mfma_kernel<DW, EDGE, G, WPG>, lds_q));
-  hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<DW, EDGE, G, WPG>), grid, dim3(64 * G * WPG), lds_q, s, S, H, B * H, dh, qkv, lse, ctx, dctx, delta,
-                     dqkv);
-  FAX_TRY(dkv());
-  FAX_LAUNCH_CHECK("attn_bwd_mfma");
+  if constexpr (G < 4) {
+    // dQ first: it also produces delta, which the dK/dV kernel reads
+    FAX_TRY(set_lds(attn_bwd_dq_mfma_kernel<DW, EDGE, G, WPG>, lds_q));
+    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<DW, EDGE, G, WPG>), grid, dim3(64 * G * WPG), lds_q, s, S, H, B * H, dh, qkv, lse, ctx, dctx, delta,
+                       dqkv);
+    FAX_TRY(dkv());
+    FAX_LAUNCH_CHECK("attn_bwd_mfma");
+  }
   return FAX_OK;
 }
 
@@ -846,8 +867,9 @@ int attn_bwd_mfma(int B, int S, int H, int dh, const void* qkv, const void* ctx,
                   void* dqkv, float* delta, hipStream_t s) {
   const bf16_t *q = (const bf16_t*)qkv, *c = (const bf16_t*)ctx, *dc = (const bf16_t*)dctx;
   bf16_t* dq = (bf16_t*)dqkv;
-  return by_form(B, S, H, dh, [&](auto dw, auto edge, auto g, auto wpg) {
-    return bwd_t<decltype(dw)::value, decltype(edge)::value, decltype(g)::value, decltype(wpg)::value>(B, S, H, dh, q, c, lse, dc, dq, delta, s);
+  const AttnForm form = attn_bwd_form(B, S, H, dh);
+  return by_form(form, B, S, H, dh, [&](auto dw, auto edge, auto g, auto wpg) {
+    return bwd_t<decltype(dw)::value, decltype(edge)::value, decltype(g)::value, decltype(wpg)::value>(form.joint, B, S, H, dh, q, c, lse, dc, dq, delta, s);
   });
 }
 

@@ -1,6 +1,6 @@
 """bf16 attention in each of its forms (groups x waves of a workgroup: 1x4, 2x2, 2x4, 4x1; dQ and dK/dV apart and in one launch), at
-sequence lengths around a workgroup's rows and the groups' tiles.  The form follows from B H and S alone: by 32-row tiles up to 256
-4x1, by 64-row tiles up to 1024 2x2 (head widths up to 64); by 64-row tiles up to 384 2x2, by 128-row tiles up to 400 2x4 (wider)."""
+sequence lengths around a workgroup's rows and the groups' tiles.  The form follows from B H, S and the head width alone; test_attn_routes.py asserts which
+one each size takes."""
 import numpy as np
 import pytest
 import torch
@@ -11,20 +11,19 @@ from helpers import DEV
 pytestmark = pytest.mark.gpu
 
 CASES = [  # B, S, H, dh
-    # 4x1, one launch: fewer tiles than groups, as many, one more; whole and ragged
+    # up to 64 wide, few heads: one tile to three and more than there are groups, whole and ragged
     (1, 1, 1, 64), (2, 31, 3, 32), (1, 33, 2, 64), (1, 65, 3, 40), (1, 128, 2, 64), (1, 193, 2, 64), (1, 256, 4, 64), (1, 321, 3, 56), (1, 2048, 2, 64),
-    # 2x2 in one launch, whole and ragged, an odd number of tiles and an even one
+    # more of them: an odd number of tiles and an even one, one launch and two
     (3, 63, 86, 64), (4, 65, 65, 64), (10, 128, 8, 64), (4, 777, 8, 64), (4, 129, 16, 8),
-    # 2x2, two launches
     (4, 512, 16, 64), (5, 517, 15, 64),
-    # 1x4: beyond 1024 tiles
+    # a full chip
     (33, 128, 16, 64), (15, 523, 8, 64), (35, 100, 30, 24),
-    # wider: 2x2 in one launch and in two
+    # wider
     (1, 1, 1, 128), (1, 31, 2, 72), (1, 65, 2, 96), (1, 128, 3, 128), (1, 384, 2, 128), (2, 333, 3, 80), (1, 1111, 2, 104), (6, 300, 10, 128), (5, 640, 6, 128),
-    # 2x4: one group alone, both, an odd number of tiles
     (25, 63, 16, 96), (20, 128, 20, 128), (9, 257, 12, 80), (10, 384, 11, 128),
-    # 1x4
-    (41, 128, 10, 128), (45, 70, 10, 88)]
+    (41, 128, 10, 128), (45, 70, 10, 88),
+    # 4x1 with a group that has no tile; 2x4 whole and ragged, one group alone and an odd number of tiles; 2x2 in two launches and 1x4 at masked widths
+    (1, 129, 3, 64), (1, 150, 2, 40), (10, 256, 10, 128), (8, 257, 10, 80), (5, 129, 25, 96), (3, 250, 18, 80), (3, 250, 18, 104), (40, 70, 10, 104)]
 
 
 def _reference(qkv, dctx):
