@@ -197,15 +197,18 @@ __global__ __launch_bounds__(1024) void mean_kernel(int N, const float* __restri
 
 // Threads per row and vectors per thread for a row of `nvec` 16-byte vectors: the pair with the
 // fewest idle vector slots among workgroups of 4 to 16 waves; of equals, the larger workgroup.  The padded form, which unpacks its row
-// as it arrives, stays at 8 vectors where it can, and of equals takes the smaller workgroup (3108 x 32003: 1024 threads 111 us, 512 105, 256 188).
-static bool ce_shape(int nvec, bool pad, int* threads, int* nv) {
+// as it arrives, stays at 8 vectors where it can (3108 x 32003: 512 threads 104 us, 256 188), and with more than two rows to a CU takes the smaller of
+// equals in place of one with two vectors a thread, or where it still has eight waves (bf16, larger and smaller, us: 3108 x 14890, 960 x 2 and 320 x 6, 73 and 58,
+// 800 rows of it 29 and 27; 3108 x 32003, 1024 x 4 and 512 x 8, 110 and 106; the other way 3108 x 20001, 640 x 4 and 320 x 8, 80 and 84, and few rows, 95 x 14890 13.5
+// and 15.6, 384 18.9 and 19.8).
+static bool ce_shape(int rows, int nvec, bool pad, int* threads, int* nv) {
   long best = -1;
   for (int nt = CE_MAX_THREADS; nt >= 256; nt -= 64) {
     const int v = (nvec + nt - 1) / nt;
     if (v > (pad && nvec <= 8 * CE_MAX_THREADS ? 8 : CE_MAX_NV)) continue;
     const int vt = v <= 2 ? 2 : v <= 4 ? 4 : v <= 6 ? 6 : v <= 8 ? 8 : v <= 10 ? 10 : v <= 12 ? 12 : 16;  // instantiated sizes
     const long waste = (long)nt * vt - nvec;
-    if (best < 0 || waste < best || (pad && waste == best)) {
+    if (best < 0 || waste < best || (pad && rows > 512 && waste == best && (*nv == 2 || nt >= 512))) {
       best = waste;
       *threads = nt;
       *nv = vt;
@@ -234,7 +237,7 @@ static int ce_t(int N, int V, int ld, const T* logits, const int32_t* labels, T*
   constexpr int VN = Vec16<T>::N;
   int nt = 0, nv = 0;
   // rows that start on a vector and have room for whole ones; those that end inside one take the padded form
-  if (ld % VN == 0 && ce_shape((V + VN - 1) / VN, V % VN != 0, &nt, &nv)) {
+  if (ld % VN == 0 && ce_shape(N, (V + VN - 1) / VN, V % VN != 0, &nt, &nv)) {
     if (V % VN) ce_cached<T, true>(nv, nt, N, V, ld, logits, labels, dlogits, row_loss, grad_scale, s);
     else ce_cached<T, false>(nv, nt, N, V, ld, logits, labels, dlogits, row_loss, grad_scale, s);
   } else {

@@ -24,6 +24,20 @@ def test_padded_rows(dtype, V):
     assert rel_fro(to_np(grads["tok_emb"]), g_ref["tok_emb"]) <= (1e-5 if dtype == "f32" else 2e-2)
 
 
+@pytest.mark.parametrize("dtype,V", [("bf16", 14890), ("bf16", 20001), ("bf16", 32003), ("f32", 5003)])
+def test_padded_rows_on_a_full_chip(dtype, V):
+    """Beyond two rows to a CU some lengths take a smaller workgroup: 320 threads instead of 960, 640 as with few rows, 512 instead of 1024, 320 instead of
+    640."""
+    ms = ModelShape(BlockShape(B=1, S=520, D=64, H=1, dh=64, F=128, dtype=dtype, sigma_w=0.05, L=1), V=V, S_max=520)
+    sh = ms.blk
+    p, tok, lab = make_model_inputs(ms, seed=9, generic=True)
+    lab[0, 0], lab[0, -1] = V - 1, 0
+    loss_ref, g_ref, _ = orc.model_loss_and_grads(p, tok, lab, sh.H, sh.dh, sh.gelu, sh.ln_eps)
+    loss, _, _, _, _, grads = run_train_step(ms, p, tok, lab, update=False)
+    assert abs(loss - loss_ref) <= (1e-5 if dtype == "f32" else 1e-3) * abs(loss_ref)
+    assert rel_fro(to_np(grads["tok_emb"]), g_ref["tok_emb"]) <= (1e-5 if dtype == "f32" else 2e-2)
+
+
 @pytest.mark.parametrize("V", [1001, 32003])
 def test_gradients_of_far_off_logits(V):
     """One position, every logit chosen: what an exponential below 2^-126 leaves in the gradient, down to the smallest bf16 number."""
