@@ -396,11 +396,16 @@ static bool group_plan(const GemmArgs* g, int n, GroupPlan* plan) {
 //   392, 3000 x 1024 491 and 485, 4000 x 968 699 and 691, 5000 x 800 652 and 639; the other way 2500 x 768 318 and 325, and around 4200 to 4560 rows
 //   960 to 1024 wide up to 1 % where attention is a split form, whose workgroups leave no room beside them, and 2 to 3.5 % against apart beside
 //   the unsplit one (66 heads of 700 x 88 688 and 700, of 760 x 88 730 and 757): each choice alone is within 1 % there, and no size tells them from 4000 x 968.
+//   Nor longer than 92 us by itself, unless input gradients of whole rounds keep the pass on one stream: the output projection's share of it, the
+//   longer the more, would have run beside the attention kernels.  Apart and together, 1024 wide: 6144 708 and 696, 7168 780 and 782, 8000 921 and
+//   924, 8448 920 and 956, 9000 1129 and 1165, 10240 1060 and 1079, 12288 1192 and 1243, 14336 1409 and 1513, 20480 1998 and 2108; 9000 x 968 1136 and
+//   1179, 9216 x 1280 1283 and 1301, 6144 x 1280 942 and 940; with whole rounds 16384 x 1024 1564 and 1558.
 int gemm_groups(const GemmArgs (&w)[4], const GemmArgs (&in)[4]) {
-  bool pairs = true, full = true;
+  bool pairs = true, full = true, rounds = true;
   for (int i = 0; i < 4; i++) {
     const GemmArgs& g = in[i];
     if (!gemm_edge_supported(g)) return 0;
+    rounds = rounds && gemm_fill(g).rounds;
     pairs = pairs && gemm_pair_supported(i < 2 ? w[i] : w[5 - i], g);  // with the weight gradient of this layer
     if (!full) continue;
     const GemmSplitPlan p = plan_tiles(g.M, g.N, g.K, false, false, !tiles_whole(g.M, g.N, g.K), true, g.beside);
@@ -420,7 +425,7 @@ int gemm_groups(const GemmArgs (&w)[4], const GemmArgs (&in)[4]) {
   }
   if (full && all.tile == 256 && all.us < 0.7 * (apart[0] + apart[1] + apart[2] + apart[3])) return GROUP_ALL;
   return (ffn.us < (ffn.edge ? 0.76 : 0.97) * (apart[0] + apart[1]) ? GROUP_FFN : 0) |
-         (att.tile == 128 && att.us < 0.97 * (apart[2] + apart[3]) ? GROUP_ATTENTION : 0);
+         (att.tile == 128 && (att.us < 92.0 || rounds) && att.us < 0.97 * (apart[2] + apart[3]) ? GROUP_ATTENTION : 0);
 }
 
 int gemm_group(const GemmArgs* g, int n, hipStream_t s) {
