@@ -358,7 +358,7 @@ static double products_us(const FaxBlockDims& d) {
 // a forward and backward pass of tokens x width, F = 4 x width, unless stated):
 //   every product whole rounds of one workgroup per CU: the 4096-wide block (256 to 2048 tiles each) 8120 either way;
 //   all weight gradients in shared launches, and the input gradients whole rounds of tiles 256 rows high, 8192 x 1024 843 and 834, two layers
-//     of it with the update 1818 and 1772, 16384 x 1024 with heads of 128 1773 and 1727;  on the other side 8192 x 3200 (an eighth idle)
+//     of it with the update 1818 and 1772;  on the other side 8192 x 3200 (an eighth idle)
 //     3578 and 3596, 16384 x 2304 3442 and 3457;
 //   all weight gradients in shared launches, and products of less than 200 us that leave under a tenth idle, 2048 x 1024 346 and 325;  on the
 //     other side 4096 x 1024 (312 us) 452 and 466, 3108 x 512 (a fifth idle) 253 and 268, 4096 x 512 (separate launches), two layers, 570 and 588.

@@ -389,23 +389,23 @@ static bool group_plan(const GemmArgs* g, int n, GroupPlan* plan) {
 //   271 -> 285, 16384 x 512 684 -> 766, 2048 x 5120 in an eighth's share 695 -> 728.
 // The feed-forward's two: any gain predicted for whole tiles, a quarter for masked edges (whose small tiles by themselves run 30 % over the
 //   model beside other kernels).  3108 x 512 271 -> 253, 4500 x 640 465 -> 438, 3000 x 1200 654 -> 626, 4096 x 1024 470 -> 460; 4200 x 968,
-//   beyond the line, 676 and 691.
+//   beyond the line, 676 and 691.  Not in 128^2 tiles where each alone fills whole rounds of 256^2 ones, which load half as much: apart and
+//   together, with attention's two apart, 14336 x 1024 1387 and 1444, 16384 x 1024 1527 and 1593, 24576 x 1024 2216 and 2369, 32768 x 1024
+//   2861 and 2867; where they leave CUs idle 12288 x 768 925 and 910, 16384 x 768 1040 and 1037.
 // Attention's two: at 128^2 tiles, and not much longer than the QKV one alone (the other one would start before the attention kernels and run
 //   beside them).  4096 x 1024 470 -> 449, 2222 x 1280 563 -> 552, 4096 x 768 380 -> 372; beyond the line 3108 x 512 271 and 277, 1999 x
 //   2000 843 and 854, 3600 x 1536 908 and 915.  With the feed-forward's two apart, apart and together: 2500 x 968 472 and 458, 3500 x 768 406 and
 //   392, 3000 x 1024 491 and 485, 4000 x 968 699 and 691, 5000 x 800 652 and 639; the other way 2500 x 768 318 and 325, and around 4200 to 4560 rows
 //   960 to 1024 wide up to 1 % where attention is a split form, whose workgroups leave no room beside them, and 2 to 3.5 % against apart beside
 //   the unsplit one (66 heads of 700 x 88 688 and 700, of 760 x 88 730 and 757): each choice alone is within 1 % there, and no size tells them from 4000 x 968.
-//   Nor longer than 92 us by itself, unless input gradients of whole rounds keep the pass on one stream: the output projection's share of it, the
-//   longer the more, would have run beside the attention kernels.  Apart and together, 1024 wide: 6144 708 and 696, 7168 780 and 782, 8000 921 and
-//   924, 8448 920 and 956, 9000 1129 and 1165, 10240 1060 and 1079, 12288 1192 and 1243, 14336 1409 and 1513, 20480 1998 and 2108; 9000 x 968 1136 and
-//   1179, 9216 x 1280 1283 and 1301, 6144 x 1280 942 and 940; with whole rounds 16384 x 1024 1564 and 1558.
+//   Nor longer than 92 us by itself: the output projection's share of it, the longer the more, would have run beside the attention kernels.
+//   Apart and together, 1024 wide: 6144 708 and 696, 7168 780 and 782, 8000 921 and 924, 8448 920 and 956, 9000 1129 and 1165, 10240 1060 and
+//   1079, 12288 1192 and 1243, 14336 1409 and 1513, 20480 1998 and 2108; 9000 x 968 1136 and 1179, 9216 x 1280 1283 and 1301, 6144 x 1280 942 and 940.
 int gemm_groups(const GemmArgs (&w)[4], const GemmArgs (&in)[4]) {
-  bool pairs = true, full = true, rounds = true;
+  bool pairs = true, full = true;
   for (int i = 0; i < 4; i++) {
     const GemmArgs& g = in[i];
     if (!gemm_edge_supported(g)) return 0;
-    rounds = rounds && gemm_fill(g).rounds;
     pairs = pairs && gemm_pair_supported(i < 2 ? w[i] : w[5 - i], g);  // with the weight gradient of this layer
     if (!full) continue;
     const GemmSplitPlan p = plan_tiles(g.M, g.N, g.K, false, false, !tiles_whole(g.M, g.N, g.K), true, g.beside);
@@ -424,8 +424,9 @@ int gemm_groups(const GemmArgs (&w)[4], const GemmArgs (&in)[4]) {
     if (small) apart[i] *= 1.3;
   }
   if (full && all.tile == 256 && all.us < 0.7 * (apart[0] + apart[1] + apart[2] + apart[3])) return GROUP_ALL;
-  return (ffn.us < (ffn.edge ? 0.76 : 0.97) * (apart[0] + apart[1]) ? GROUP_FFN : 0) |
-         (att.tile == 128 && (att.us < 92.0 || rounds) && att.us < 0.97 * (apart[2] + apart[3]) ? GROUP_ATTENTION : 0);
+  const bool filled = ffn.tile == 128 && gemm_fill(w[0]).rounds && gemm_fill(w[1]).rounds;
+  return (!filled && ffn.us < (ffn.edge ? 0.76 : 0.97) * (apart[0] + apart[1]) ? GROUP_FFN : 0) |
+         (att.tile == 128 && att.us < 92.0 && att.us < 0.97 * (apart[2] + apart[3]) ? GROUP_ATTENTION : 0);
 }
 
 int gemm_group(const GemmArgs* g, int n, hipStream_t s) {
