@@ -392,6 +392,7 @@ static bool group_plan(const GemmArgs* g, int n, GroupPlan* plan) {
 //   beyond the line, 676 and 691.  Not in 128^2 tiles where each alone fills whole rounds of 256^2 ones, which load half as much: apart and
 //   together, with attention's two apart, 14336 x 1024 1387 and 1444, 16384 x 1024 1527 and 1593, 24576 x 1024 2216 and 2369, 32768 x 1024
 //   2861 and 2867; where they leave CUs idle 12288 x 768 925 and 910, 16384 x 768 1040 and 1037.
+//   Within the line and slower 6000 x 3072 with F 6144, 2017 and 2069, where 5000, 8000 and 10000 rows of it are within 0.3 %.
 // Attention's two: at 128^2 tiles, and not much longer than the QKV one alone (the other one would start before the attention kernels and run
 //   beside them).  4096 x 1024 470 -> 449, 2222 x 1280 563 -> 552, 4096 x 768 380 -> 372; beyond the line 3108 x 512 271 and 277, 1999 x
 //   2000 843 and 854, 3600 x 1536 908 and 915.  With the feed-forward's two apart, apart and together: 2500 x 968 472 and 458, 3500 x 768 406 and
