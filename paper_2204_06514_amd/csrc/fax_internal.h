@@ -93,6 +93,8 @@ bool gemm_f32_supported(const GemmArgs& g);
 int gemm_f32(const GemmArgs& g, hipStream_t s);
 double gemm_f32_time_us(int M, int N, int K);
 void gemm_f32_tile(int M, int N, int K, int* tile_m, int* tile_n);
+bool gemm_f32_pair_supported(const GemmArgs& w, const GemmArgs& d);
+int gemm_f32_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s);
 bool gemm_mfma_supported(const GemmArgs& g);
 bool gemm_edge_supported(const GemmArgs& g);
 // A weight-gradient product of a narrow model has few output tiles and a very long contraction

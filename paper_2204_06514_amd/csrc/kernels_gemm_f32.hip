@@ -150,9 +150,8 @@ struct SplitShape {
 
 // GELU: forward orientation with EPI_GELU, its transcendental code kept out of the other instances.
 template <int WM, int WN, int KS, int TM, int TN, bool TA, bool TB, bool VEC, bool GELU>
-__global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A, int lda,
-                                                       const float* __restrict__ B, int ldb, EpiArgs e, int tiles_m,
-                                                       int tiles_n) {
+__device__ __forceinline__ void f32_product_tile(int block, int M, int N, int K, const float* __restrict__ A, int lda,
+                                                 const float* __restrict__ B, int ldb, const EpiArgs& e, int tiles_m, int tiles_n) {
   using S = SplitShape<WM, WN, KS, TM, TN>;
   static_assert(WM * WN * KS == 8, "eight waves");
   constexpr int BM = S::BM, BN = S::BN, BK = S::BK, NV = S::NV, AHEAD = S::AHEAD;
@@ -163,7 +162,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, c
   float* const smem_f = reinterpret_cast<float*>(smem);
 
   int tm_i, tn_i;
-  f32_tile(blockIdx.x, tiles_m, tiles_n, tm_i, tn_i);
+  f32_tile(block, tiles_m, tiles_n, tm_i, tn_i);
   const int m0 = tm_i * BM, n0 = tn_i * BN;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l31 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -571,11 +570,24 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, c
 }
 
 template <int WM, int WN, int KS, int TM, int TN, bool TA, bool TB, bool VEC, bool GELU>
-static int launch_f32(const GemmArgs& g, const EpiArgs& e, hipStream_t s) {
+__global__ __launch_bounds__(512, 2) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A, int lda,
+                                                       const float* __restrict__ B, int ldb, EpiArgs e, int tiles_m,
+                                                       int tiles_n) {
+  f32_product_tile<WM, WN, KS, TM, TN, TA, TB, VEC, GELU>(blockIdx.x, M, N, K, A, lda, B, ldb, e, tiles_m, tiles_n);
+}
+
+template <int WM, int WN, int KS, int TM, int TN, bool TA, bool TB, bool GELU>
+static constexpr size_t f32_lds() {
   using S = SplitShape<WM, WN, KS, TM, TN>;
   constexpr size_t slabs = 2 * (SplitSlab<S::BM, S::BK, !TA>::BYTES + SplitSlab<S::BN, S::BK, TB>::BYTES);
   constexpr size_t tail = (S::XCH + 8 * S::BN + (GELU ? 8 * 64 * (S::NV / KS < 16 ? S::NV / KS : 16) : 0)) * sizeof(float);
-  constexpr size_t lds = slabs > tail && KS < 8 ? slabs : tail;
+  return slabs > tail && KS < 8 ? slabs : tail;
+}
+
+template <int WM, int WN, int KS, int TM, int TN, bool TA, bool TB, bool VEC, bool GELU>
+static int launch_f32(const GemmArgs& g, const EpiArgs& e, hipStream_t s) {
+  using S = SplitShape<WM, WN, KS, TM, TN>;
+  constexpr size_t lds = f32_lds<WM, WN, KS, TM, TN, TA, TB, GELU>();
   auto kern = gemm_f32_kernel<WM, WN, KS, TM, TN, TA, TB, VEC, GELU>;
   static bool configured = false;  // benign race: the attribute is idempotent
   if (!configured) {
@@ -643,14 +655,75 @@ bool gemm_f32_supported(const GemmArgs& g) {
   return g.dtype == FAX_F32 && !(g.ta && g.tb) && !(g.epi == EPI_GELU && (g.ta || g.tb)) && !(g.colsum && !g.ta);
 }
 
-int gemm_f32(const GemmArgs& g, hipStream_t s) {
+struct F32Operands {
+  EpiArgs e;
+  bool vec;
+};
+static F32Operands f32_operands(const GemmArgs& g) {
   auto vec_ok = [](const void* p, int ld, int extent) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && ld % 4 == 0 && extent % 4 == 0; };
   const int a_row = g.ta ? g.M : g.K, a_lim = g.a_padded ? (a_row + 3) / 4 * 4 : a_row;  // how far A's rows may be read
-  const bool vec = vec_ok(g.A, g.lda, a_lim) && vec_ok(g.B, g.ldb, g.tb ? g.K : g.N);
-  EpiArgs e{g.bias, g.R, g.ldr, g.C, g.ldc, g.C2, g.ldc2, g.U, g.ldu, g.epi, g.gelu_form, 1, g.accumulate ? 1 : 0, g.colsum};
-  e.a_lim = a_lim;
+  F32Operands o{{g.bias, g.R, g.ldr, g.C, g.ldc, g.C2, g.ldc2, g.U, g.ldu, g.epi, g.gelu_form, 1, g.accumulate ? 1 : 0, g.colsum},
+                vec_ok(g.A, g.lda, a_lim) && vec_ok(g.B, g.ldb, g.tb ? g.K : g.N)};
+  o.e.a_lim = a_lim;
+  return o;
+}
+
+int gemm_f32(const GemmArgs& g, hipStream_t s) {
+  const F32Operands o = f32_operands(g);
   const int cls = gemm_f32_class(g.M, g.N, g.K);
-  return vec ? dispatch_f32_class<true>(cls, g, e, s) : dispatch_f32_class<false>(cls, g, e, s);
+  return o.vec ? dispatch_f32_class<true>(cls, g, o.e, s) : dispatch_f32_class<false>(cls, g, o.e, s);
+}
+
+// A layer's weight gradient and input gradient in one launch: the first workgroups take the tiles of the first, the others those of the
+// second, each as it would in a launch of its own (the same bits).
+struct F32Product {
+  int M, N, K;
+  const float* A;
+  int lda;
+  const float* B;
+  int ldb;
+  EpiArgs e;
+  int tiles_m, tiles_n;
+};
+
+// Bound like gemm_f32_kernel; what it saves is a launch's ramp and tail, which are most of a product of one short round.
+template <int WKS, int WT, int DKS, int DT>
+__global__ __launch_bounds__(512, 2) void gemm_f32_pair_kernel(F32Product w, F32Product d, int first) {
+  const int block = blockIdx.x;
+  if (block < first)
+    f32_product_tile<WT, WT, WKS, 1, 1, true, false, true, false>(block, w.M, w.N, w.K, w.A, w.lda, w.B, w.ldb, w.e, w.tiles_m, w.tiles_n);
+  else
+    f32_product_tile<DT, DT, DKS, 1, 1, false, true, true, false>(block - first, d.M, d.N, d.K, d.A, d.lda, d.B, d.ldb, d.e, d.tiles_m, d.tiles_n);
+}
+
+template <int WKS, int WT, int DKS, int DT>
+static int launch_f32_pair(const GemmArgs& wg, const GemmArgs& dg, hipStream_t s) {
+  constexpr size_t lw = f32_lds<WT, WT, WKS, 1, 1, true, false, false>(), ld = f32_lds<DT, DT, DKS, 1, 1, false, true, false>(), lds = lw > ld ? lw : ld;
+  auto product = [](const GemmArgs& g, int tile) {
+    return F32Product{g.M, g.N, g.K, (const float*)g.A, g.lda, (const float*)g.B, g.ldb, f32_operands(g).e, (g.M + tile - 1) / tile, (g.N + tile - 1) / tile};
+  };
+  const F32Product w = product(wg, 32 * WT), d = product(dg, 32 * DT);
+  auto kern = gemm_f32_pair_kernel<WKS, WT, DKS, DT>;
+  static bool configured = false;  // benign race: the attribute is idempotent
+  if (!configured) {
+    FAX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    configured = true;
+  }
+  const int first = w.tiles_m * w.tiles_n;
+  hipLaunchKernelGGL(kern, dim3(first + d.tiles_m * d.tiles_n), dim3(512), lds, s, w, d, first);
+  FAX_LAUNCH_CHECK("gemm_f32_pair");
+  return FAX_OK;
+}
+
+// For products that take 64 x 64 or 32 x 32 tiles by themselves (larger ones fill the chip alone), operands in whole vectors.
+bool gemm_f32_pair_supported(const GemmArgs& w, const GemmArgs& d) {
+  auto small = [](const GemmArgs& g) { return gemm_f32_supported(g) && gemm_f32_class(g.M, g.N, g.K) >= 2 && f32_operands(g).vec; };
+  return w.ta && !w.tb && w.epi == EPI_NONE && !d.ta && d.tb && (d.epi == EPI_NONE || d.epi == EPI_DGELU) && !d.colsum && small(w) && small(d);
+}
+int gemm_f32_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s) {
+  const bool w32 = gemm_f32_class(w.M, w.N, w.K) == 3, d32 = gemm_f32_class(d.M, d.N, d.K) == 3;
+  if (w32) return d32 ? launch_f32_pair<8, 1, 8, 1>(w, d, s) : launch_f32_pair<8, 1, 2, 2>(w, d, s);
+  return d32 ? launch_f32_pair<2, 2, 8, 1>(w, d, s) : launch_f32_pair<2, 2, 2, 2>(w, d, s);
 }
 
 }  // namespace fax

@@ -313,15 +313,24 @@ static bool deep_alone(const GemmArgs& g, GemmSplitPlan* plan) {
   return plan->deep && plan->splits == 1;
 }
 
-// The pair takes one launch where both products take the small-tile form by themselves, undivided: those leave CUs idle or last
-// little longer than a launch.  The results are the same bits.  (Larger tiles fill the chip alone.)
+// The pair takes one launch where both products take the small-tile form by themselves, undivided (in fp32: 64 x 64 or 32 x 32 tiles): those
+// leave CUs idle or last little longer than a launch.  The results are the same bits.  (Larger tiles fill the chip alone.)
 bool gemm_pair_supported(const GemmArgs& w, const GemmArgs& d) {
+  if (w.dtype == FAX_F32) return d.dtype == FAX_F32 && gemm_f32_pair_supported(w, d);
   GemmSplitPlan wp, dp;
   return w.c_f32 && w.ta && !w.tb && w.colsum && !d.c_f32 && !d.ta && d.tb && !d.C2 && !d.R && !d.bias &&
          (d.epi == EPI_NONE || d.epi == EPI_DGELU) && deep_alone(w, &wp) && deep_alone(d, &dp);
 }
 
 int gemm_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s) {
+  if (w.dtype == FAX_F32) {
+    if (!gemm_pair_supported(w, d)) {
+      set_error("gemm_pair: not two fp32 products of small tiles");
+      return FAX_ERR_UNSUPPORTED;
+    }
+    Timed t("gemm_f32_pair", WORK_FLOP, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, s);
+    return gemm_f32_pair(w, d, s);
+  }
   GemmSplitPlan wp, dp;
   if (!deep_alone(w, &wp) || !deep_alone(d, &dp)) {
     set_error("gemm_pair: not two products of the small-tile form");
