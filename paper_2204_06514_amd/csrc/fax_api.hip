@@ -132,7 +132,7 @@ static void saved_layout(const FaxBlockDims& d, FaxSavedLayout* L) {
 
 struct BwdWs {
   FaxBwdLayout pub;
-  size_t delta, red, red_ln1, red_side, splitk, total;
+  size_t delta, red_ln2, red_ln1, red_colsum, splitk, total;
 };
 
 static void bwd_layout(const FaxBlockDims& d, BwdWs* W) {
@@ -149,11 +149,9 @@ static void bwd_layout(const FaxBlockDims& d, BwdWs* W) {
   size_t widest = z.D;
   if (z.F > widest) widest = z.F;
   if (3 * z.Hd > widest) widest = 3 * z.Hd;
-  size_t red = ln_bwd_ws_bytes(d.D);
-  if (colsum_ws_bytes((int)widest) > red) red = colsum_ws_bytes((int)widest);
-  W->red = take(red);
-  W->red_ln1 = take(ln_bwd_ws_bytes(d.D));  // LN1's partial rows: LN2's may still await their fold on the second stream
-  W->red_side = take(colsum_ws_bytes((int)widest));  // column-sum scratch of the weight-gradient stream
+  W->red_ln2 = take(ln_bwd_ws_bytes(d.D));  // partial rows of both LayerNorms, which one launch folds
+  W->red_ln1 = take(ln_bwd_ws_bytes(d.D));
+  W->red_colsum = take(colsum_ws_bytes((int)widest));  // column sums, where they are a pass of their own
   // scratch for the weight-gradient products whose contraction gets split (narrow models)
   const int T = (int)z.T, D = (int)z.D, Hd = (int)z.Hd, F = (int)z.F;
   size_t sk = gemm_split_ws_bytes(F, D, T);
@@ -313,7 +311,7 @@ static int block_fwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
 struct SideStream {
   std::mutex mu;  // held while one call enqueues: the events are shared, so record/wait pairs of two host threads must not interleave
   hipStream_t s = nullptr;
-  hipEvent_t fork = nullptr, du = nullptr, dx1 = nullptr, dqkv = nullptr, ln2 = nullptr, ln1 = nullptr, w2_done = nullptr, join = nullptr;
+  hipEvent_t fork = nullptr, du = nullptr, dx1 = nullptr, dqkv = nullptr, w2_done = nullptr, join = nullptr;
 };
 static std::mutex g_side_mu;
 static SideStream* g_side[64];
@@ -326,7 +324,7 @@ static int side_stream(SideStream** out) {
   if (!g_side[dev]) {
     SideStream* n = new SideStream;
     FAX_HIP(hipStreamCreateWithFlags(&n->s, hipStreamNonBlocking));  // default priority
-    for (hipEvent_t* e : {&n->fork, &n->du, &n->dx1, &n->dqkv, &n->ln2, &n->ln1, &n->w2_done, &n->join})
+    for (hipEvent_t* e : {&n->fork, &n->du, &n->dx1, &n->dqkv, &n->w2_done, &n->join})
       FAX_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
     g_side[dev] = n;
   }
@@ -421,7 +419,6 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
   char* du = ws + W.pub.du; char* dh2 = dh2_out ? (char*)dh2_out : ws + W.pub.dh2; char* dx1 = ws + W.pub.dx1;
   char* dctx = ws + W.pub.dctx; char* dqkv = ws + W.pub.dqkv; char* dh1 = dh1_out ? (char*)dh1_out : ws + W.pub.dh1;
   float* delta = (float*)(ws + W.delta);
-  void* red = ws + W.red;
 
   SideStream* side = nullptr;
   const BwdPlan plan = bwd_plan(d);
@@ -429,13 +426,12 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
   std::unique_lock<std::mutex> side_lock;
   if (side) side_lock = std::unique_lock<std::mutex>(side->mu);
   hipStream_t sw = side ? side->s : s;  // where the weight gradients go
-  void* red_w = side ? (void*)(ws + W.red_side) : red;
   auto wgrad = [&](const void* act, int lda, int Kdim, const void* grad, int ldb, int Ndim, void* out, void* bias_grad) {
     GemmArgs g;  // out[Kdim, Ndim] (+)= act^T grad, contraction over the T rows; bias_grad[Ndim] (+)= column sums of grad
     g.dtype = d.dtype; g.ta = true; g.tb = false;
     g.M = Kdim; g.N = Ndim; g.K = T;
     g.A = act; g.lda = lda; g.B = grad; g.ldb = ldb; g.C = out; g.ldc = Ndim; g.c_f32 = true; g.accumulate = acc;
-    g.colsum = (float*)bias_grad; g.colsum_ws = red_w;
+    g.colsum = (float*)bias_grad; g.colsum_ws = ws + W.red_colsum;
     g.split_ws = W.splitk < W.total ? ws + W.splitk : nullptr;
     return g;
   };
@@ -485,9 +481,9 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
   }
   FAX_TRY(layer(w1, d1, group || ffn));
   // LN2 and the residual branch: dx1 = dy + LN2'(dh2)
-  FAX_TRY(ln_bwd(d.dtype, T, D, dh2, saved + L.x1, (const float*)(saved + L.mu2), (const float*)(saved + L.rstd2),
-                 p.ln2_g, dy, dx1, (float*)gr.ln2_g, (float*)gr.ln2_b, acc, red, s, side ? side->s : nullptr,
-                 side ? side->ln2 : nullptr));
+  LnFold ln2, ln1;
+  FAX_TRY(ln_bwd_rows(d.dtype, T, D, dh2, saved + L.x1, (const float*)(saved + L.mu2), (const float*)(saved + L.rstd2),
+                      p.ln2_g, dy, dx1, (float*)gr.ln2_g, (float*)gr.ln2_b, ws + W.red_ln2, &ln2, s));
   // attention output projection
   if (!group && !att) FAX_TRY(hand_over(&SideStream::dx1));
   FAX_TRY(layer(wo, d_o, group || att));
@@ -510,9 +506,10 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
     const bool elsewhere = (const char*)dx + bytes <= (const char*)dy || (const char*)dy + bytes <= (const char*)dx;
     if (!group || !elsewhere) FAX_HIP(hipStreamWaitEvent(s, side->w2_done, 0));
   }
-  FAX_TRY(ln_bwd(d.dtype, T, D, dh1, x, (const float*)(saved + L.mu1), (const float*)(saved + L.rstd1), p.ln1_g, dx1,
-                 dx, (float*)gr.ln1_g, (float*)gr.ln1_b, acc, side ? (void*)(ws + W.red_ln1) : red, s, side ? side->s : nullptr,
-                 side ? side->ln1 : nullptr));
+  FAX_TRY(ln_bwd_rows(d.dtype, T, D, dh1, x, (const float*)(saved + L.mu1), (const float*)(saved + L.rstd1), p.ln1_g, dx1,
+                      dx, (float*)gr.ln1_g, (float*)gr.ln1_b, ws + W.red_ln1, &ln1, s));
+  // the folds of both, which feed only the gain and shift gradients, in one launch; on the caller's stream, while the other one finishes
+  FAX_TRY(ln_bwd_fold(ln2, &ln1, acc, s));
   // join: later work on the caller's stream (the next block, the update) sees every gradient, and the
   // workspace is free again
   if (side) {
