@@ -387,7 +387,6 @@ static BwdPlan bwd_plan(const FaxBlockDims& d) {
     }
   }
   const int groups = gemm_groups(w, in);
-  if (!may) return BwdPlan{false, groups};
   bool rounds = true;
   if (groups == GROUP_ALL || groups == (GROUP_FFN | GROUP_ATTENTION)) {
     for (const GemmArgs& g : in) rounds = rounds && gemm_fill(g).rounds;
@@ -401,7 +400,17 @@ static BwdPlan bwd_plan(const FaxBlockDims& d) {
     for (const GemmArgs& g : in) rounds = rounds && gemm_fill(g).idle == 0.0;
     for (const GemmArgs& g : w) rounds = rounds && gemm_fill(g).idle == 0.0;
   }
-  return BwdPlan{!rounds, groups};
+  // One round of weight gradients and QKV's input gradient on the CUs that it leaves, in one launch or, where the pass has a second stream, on
+  // both (gemm_group_input), in place of all other orders (us, forward and backward, the other order and this one; 64-wide heads):
+  //   on one stream: 2048 tokens x 1024 293 and 272, with F 3072 279 and 248, an eighth's share of 2048 tokens x 2048 302 and 281, 8192 x 1024 820 and 787;
+  //   on two, weight gradients of 140 us or more: 6144 x 1024 797 and 762, 7500 x 1024 1242 and 1167, 12288 x 1024 1183 and 1110, 16384 x 1024 1651 and
+  //     1588, 5555 x 1000 868 and 828, 8192 x 1024 with half the heads 713 and 666;  or the feed-forward's input gradients whole rounds: 4096 x 2048 with a
+  //     quarter of the heads, F 2048, 471 and 429;  beyond the line within 2 %: 4096 x 1024 465 and 455, 3000 x 1000 495 and 492, 4096 x 768 with
+  //     F 6144 484 and 492.
+  double group_us;
+  const bool one_launch =
+      gemm_group_input_pays(w, 4, in[3], &group_us) && (rounds || group_us >= 140.0 || (gemm_fill(in[0]).rounds && gemm_fill(in[1]).rounds));
+  return BwdPlan{may && !rounds, one_launch ? GROUP_ALL : groups};
 }
 
 // ---- block backward -------------------------------------------------------------------------
@@ -450,6 +459,10 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
     if (side && mark_w2) FAX_HIP(hipEventRecord(side->w2_done, side->s));
     return gemm(g, s);
   };
+  auto apart = [&](const void* a, const void* b) {  // two [T, D] tensors
+    const size_t bytes = z.T * z.D * z.es;
+    return (const char*)a + bytes <= (const char*)b || (const char*)b + bytes <= (const char*)a;
+  };
   // main stream records `e` once the tensor the next weight gradient reads is complete; the side stream waits for it
   auto hand_over = [&](hipEvent_t SideStream::*e) -> int {
     if (!side) return FAX_OK;
@@ -492,19 +505,21 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
                         dqkv, delta, PATH_AUTO, s));
   // QKV projection
   FAX_TRY(hand_over(&SideStream::dqkv));
-  if (group) {
+  const bool with_input = group && (!dh1_out || apart(dh1, dy)) && gemm_group_input_supported(all, 4, dqkv1);
+  if (with_input && !side) {
+    FAX_TRY(gemm_group_input(all, 4, dqkv1, false, s));
+  } else if (group) {
     FAX_TRY(gemm_group(all, 4, sw));
     if (side) FAX_HIP(hipEventRecord(side->w2_done, side->s));
   } else if (att) {
     FAX_TRY(gemm_group(all + 2, 2, sw));
   }
-  FAX_TRY(layer(wqkv, dqkv1, group || att));
+  if (!with_input) FAX_TRY(layer(wqkv, dqkv1, group || att));
+  else if (side) FAX_TRY(gemm_group_input(all, 4, dqkv1, true, s));
   // LN1 and the residual branch: dx = dx1 + LN1'(dh1).  dx may be the buffer dy came in: the weight gradient that reads dy
   // (the first one, or all together) has to be through with it.
   if (side) {
-    const size_t bytes = z.T * z.D * z.es;
-    const bool elsewhere = (const char*)dx + bytes <= (const char*)dy || (const char*)dy + bytes <= (const char*)dx;
-    if (!group || !elsewhere) FAX_HIP(hipStreamWaitEvent(s, side->w2_done, 0));
+    if (!group || !apart(dx, dy)) FAX_HIP(hipStreamWaitEvent(s, side->w2_done, 0));
   }
   FAX_TRY(ln_bwd_rows(d.dtype, T, D, dh1, x, (const float*)(saved + L.mu1), (const float*)(saved + L.rstd1), p.ln1_g, dx1,
                       dx, (float*)gr.ln1_g, (float*)gr.ln1_b, ws + W.red_ln1, &ln1, s));

@@ -429,10 +429,11 @@ struct GemmList<true> {
 // the GELU epilogue 680 -> 136, GELU' 528 -> 57.
 // GROUP: the tiles of several products with the same K, one after the other (GemmList); the products' own sizes and operands
 // take the place of the arguments, which are those of the first.
+// `block` of `blocks` workgroups that share the tiles.
 template <int BM, int BN, bool A_KC, bool B_KC, int EM, bool EDGE, bool GROUP>
-__global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, const bf16_t* __restrict__ A, int lda,
-                                                        const bf16_t* __restrict__ B, int ldb, EpiArgs e, int tiles_m,
-                                                        int tiles_n, GemmList<GROUP> list) {
+__device__ __forceinline__ void mfma_tiles(int block, int blocks, int M, int N, int K, const bf16_t* __restrict__ A, int lda,
+                                           const bf16_t* __restrict__ B, int ldb, EpiArgs e, int tiles_m, int tiles_n,
+                                           const GemmList<GROUP>& list) {
   using LA = TileLds<BM, A_KC>;
   using LB = TileLds<BN, B_KC>;
   using EDGE_ = std::integral_constant<bool, EDGE>;
@@ -442,13 +443,13 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   constexpr int A_BUFS = 3;  // and two for B
   constexpr int B_BASE = A_BUFS * LA::BYTES;
 
-  // Persistent workgroups: workgroup b works through tiles b, b + gridDim.x, ...  (the host
+  // Persistent workgroups: workgroup b works through tiles b, b + blocks, ...  (the host
   // launches one workgroup per CU, or fewer when there are fewer tiles).  The point is the seam
   // between two tiles: the first slabs of the next tile are requested before the epilogue of the
   // finished one, so their latency (about 3 us from a cold start) runs behind the epilogue.
   //
   // Tile number -> tile.  Consecutive workgroup ids land on different XCDs (8 of them, each with
-  // its own L2) and gridDim.x is a multiple of 8 whenever that matters, so a workgroup's tile
+  // its own L2) and `blocks` is a multiple of 8 whenever that matters, so a workgroup's tile
   // numbers all have its own residue mod 8; the number is first re-dealt so that each XCD owns a
   // contiguous run of tiles, then tiles are walked in column-major groups of e.group (4 or 8, chosen
   // on the host) tile-rows to keep the working set of A and B panels small.  e.group = 0 selects the
@@ -552,11 +553,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
     tile_of(GROUP ? id : id % nt, tm_i, tn_i);
     k_range(id, k_first, nk_item);
   };
-  item_of(blockIdx.x);
+  item_of(block);
   size_t k_begin = (size_t)k_first * GK;
   if (PER_TILE) set_lane_offsets(tm_i, tn_i);
   request_first_slabs(a_tile_of(tm_i) + k_begin * a_kstride, b_tile_of(tn_i) + k_begin * b_kstride, nk_item, K - k_first * GK);
-  for (int tile = blockIdx.x; tile < items(); tile += gridDim.x) {
+  for (int tile = block; tile < items(); tile += blocks) {
   const int nk = nk_item;
   const int k_end = K - k_first * GK;  // contraction indices from this item's first to the end of the operands
   const int m0 = tm_i * BM, n0 = tn_i * BN;
@@ -751,8 +752,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
     }
   }
   // the next tile's first slabs, before anything else of the epilogue
-  if (tile + (int)gridDim.x < items()) {
-    item_of(tile + gridDim.x);
+  if (tile + blocks < items()) {
+    item_of(tile + blocks);
     k_begin = (size_t)k_first * GK;
     if (PER_TILE) set_lane_offsets(tm_i, tn_i);
     request_first_slabs(a_tile_of(tm_i) + k_begin * a_kstride, b_tile_of(tn_i) + k_begin * b_kstride, nk_item, K - k_first * GK);
@@ -775,6 +776,18 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   lds_dma_wait();  // nothing is in flight here; stated for whoever reads the assembly in a straight line
 }
 
+template <int BM, int BN, bool A_KC, bool B_KC, int EM, bool EDGE, bool GROUP>
+__global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, const bf16_t* __restrict__ A, int lda,
+                                                        const bf16_t* __restrict__ B, int ldb, EpiArgs e, int tiles_m,
+                                                        int tiles_n, GemmList<GROUP> list) {
+  mfma_tiles<BM, BN, A_KC, B_KC, EM, EDGE, GROUP>(blockIdx.x, gridDim.x, M, N, K, A, lda, B, ldb, e, tiles_m, tiles_n, list);
+}
+
+template <int BM, int BN>
+constexpr size_t mfma_lds() {  // 160 KB at 256^2; also covers the epilogue's staging
+  return 3 * (size_t)TileLds<BM, true>::BYTES + 2 * (size_t)TileLds<BN, true>::BYTES;
+}
+
 // Workgroups of a launch.  Persistent: one per CU.  A 128^2 workgroup needs 80 KB of LDS and under 256 registers,
 // so two fit on a CU; they share its LDS bandwidth, which bounds that kernel, and gain little
 // (measured: +-0.4 % with many tiles) except when that saves a second round for a few left-over
@@ -794,7 +807,7 @@ static inline int mfma_grid(int bm, int items, int* grid) {
 
 template <int BM, int BN, bool A_KC, bool B_KC, int EM, bool EDGE = false, bool GROUP = false>
 static int launch_mfma(const GemmArgs& g, const EpiArgs& e, hipStream_t s, const GemmList<GROUP>& list = GemmList<GROUP>()) {
-  constexpr size_t lds = 3 * (size_t)TileLds<BM, A_KC>::BYTES + 2 * (size_t)TileLds<BN, B_KC>::BYTES;  // 160 KB at 256^2; also covers the epilogue's staging
+  constexpr size_t lds = mfma_lds<BM, BN>();
   auto kern = gemm_mfma_kernel<BM, BN, A_KC, B_KC, EM, EDGE, GROUP>;
   static bool configured = false;  // benign race: the attribute is idempotent
   if (!configured) {

@@ -392,6 +392,63 @@ static bool group_plan(const GemmArgs* g, int n, GroupPlan* plan) {
   return true;
 }
 
+// Weight gradients and an input gradient in one launch: as many workgroups for the former as share their tiles in no more rounds than the whole
+// chip would; the latter has the others, in tiles 256 or 128 columns wide, if it is through by then.
+struct GroupInputPlan { int rounds, first, blocks, tile_n; bool edge; };
+static bool group_input_plan(const GemmArgs* g, int n, const GemmArgs& d, GroupInputPlan* plan) {
+  GroupPlan gp;
+  if (!group_plan(g, n, &gp) || gp.tile != 256) return false;
+  if (d.path != PATH_AUTO || !gemm_edge_supported(d) || d.ta || !d.tb || d.c_f32 || d.epi != EPI_NONE || d.bias || d.R || d.C2 || d.colsum || b_short(d))
+    return false;
+  int items = 0;
+  for (int i = 0; i < n; i++) items += ((g[i].M + 255) / 256) * ((g[i].N + 255) / 256);
+  plan->rounds = (items + kCUs - 1) / kCUs;
+  plan->first = ((items + plan->rounds - 1) / plan->rounds + 7) / 8 * 8;  // a multiple of the XCDs, which the tile walk deals in
+  const int left = kCUs - plan->first;
+  if (left <= 0) return false;
+  double best = 1e30;
+  for (const TileClass& tc : kTiles) {
+    if (tc.m != 256 || tc.n == 192) continue;
+    const long long tiles = (long long)((d.M + 255) / 256) * ((d.N + tc.n - 1) / tc.n);
+    const double t = (double)((tiles + left - 1) / left) * ((d.K + GK - 1) / GK * tc.full_us + tc.epi_bf16_us);
+    if (t < best) {
+      best = t;
+      plan->tile_n = tc.n;
+      plan->blocks = (int)std::min<long long>(tiles, left);
+    }
+  }
+  plan->edge = gp.edge || !tiles_whole(d.M, d.N, d.K) || d.M % 256 || d.N % plan->tile_n;
+  if (items < plan->first) plan->first = items;  // (one round)
+  return best < gp.us;
+}
+bool gemm_group_input_supported(const GemmArgs* w, int n, const GemmArgs& d) {
+  GroupInputPlan plan;
+  return group_input_plan(w, n, d, &plan);
+}
+bool gemm_group_input_pays(const GemmArgs* w, int n, const GemmArgs& d, double* group_us) {
+  GroupInputPlan plan;
+  GroupPlan gp;
+  if (!group_input_plan(w, n, d, &plan) || plan.rounds != 1 || !group_plan(w, n, &gp)) return false;
+  *group_us = gp.us;
+  return true;
+}
+int gemm_group_input(const GemmArgs* w, int n, const GemmArgs& d, bool alone, hipStream_t s) {
+  GroupInputPlan plan;
+  if (!group_input_plan(w, n, d, &plan)) {
+    set_error("gemm_group_input: not products for one launch");
+    return FAX_ERR_UNSUPPORTED;
+  }
+  EpiArgs e[GEMM_GROUP];
+  double work = 2.0 * d.M * d.N * d.K;
+  for (int i = 0; i < n; i++) {
+    e[i] = epi_args(w[i], GemmSplitPlan{256, 256, 1, false});
+    if (!alone) work += 2.0 * w[i].M * w[i].N * w[i].K;
+  }
+  if (alone) plan.first = 0;
+  Timed t(alone ? "gemm_mfma_Ak_Bk_store" : "gemm_mfma_group_input", WORK_FLOP, work, s);
+  return gemm_mfma_group_input(w, n, e, plan.first, plan.blocks, d, epi_args(d, GemmSplitPlan{256, plan.tile_n, 1, false}), plan.tile_n, plan.edge, s);
+}
+
 // The lines, with the block's forward and backward pass (us, tokens x width, F = 4 x width) before and after:
 // All four: 256^2 tiles, input gradients of at least a round of 256 x 128 tiles each, and 30 % less predicted time than apart.  8192 x 1024 980 -> 904
 //   (the feed-forward's two and attention's two by themselves 970); where the input gradients leave CUs idle the other way round, 3108 x 512
