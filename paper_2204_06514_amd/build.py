@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfax.so")
 
-SOURCES = ["fax_api.hip", "kernels_norm.hip", "kernels_gemm_simt.hip", "kernels_gemm_f32.hip", "kernels_gemm_mfma.hip", "kernels_gemm_edge.hip", "kernels_gemm_deep.hip", "kernels_gemm_group.hip",
+SOURCES = ["fax_api.hip", "kernels_norm.hip", "kernels_gemm_simt.hip", "kernels_gemm_f32.hip", "kernels_gemm_mfma.hip", "kernels_gemm_edge.hip", "kernels_gemm_deep.hip", "kernels_gemm_group.hip", "kernels_gemm_lse.hip",
            "kernels_attn_simt.hip", "kernels_attn_f32.hip", "kernels_attn_mfma.hip", "kernels_attn_dkv16.hip", "kernels_loss_opt.hip",
            "analyze.hip", "probes.hip"]
 

@@ -871,6 +871,10 @@ int fax_eval_step(const FaxModelDims* dims, const FaxModelTensors* params, const
     FAX_TRY(block_fwd_impl(bd, params->blocks[l], w + W.x[l & 1], w + W.x[(l + 1) & 1], w + W.saved, nullptr, nullptr, false, s));
   FAX_TRY(ln_fwd(d.dtype, T, D, w + W.x[dims->L & 1], params->lnf_g, params->lnf_b, d.ln_eps, w + W.hf,
                  (float*)(w + W.muf), (float*)(w + W.rstdf), s));
+  if (lse_loss_supported(d.dtype, T, V, D, w + W.hf, params->tok_emb)) {  // the parts take a sixteenth of a row of logits, or little more
+    FAX_TRY(lse_loss(T, V, D, w + W.hf, params->tok_emb, labels, w + W.logits, (float*)(w + W.row_loss), s));
+    return mean_loss(T, (const float*)(w + W.row_loss), loss_out, s);
+  }
   FAX_TRY(gemm(logits_product(*dims, w + W.hf, params->tok_emb, w + W.logits), s));
   return cross_entropy(d.dtype, T, V, ldl, w + W.logits, labels, nullptr, (float*)(w + W.row_loss), loss_out, 1.0f, s);
 }

@@ -126,7 +126,8 @@ struct GemmFill {
   bool rounds;
 };
 GemmFill gemm_fill(const GemmArgs& g);
-// Work item -> tile of that walk.
+// Grouping of a product's tile walk (tile_walk); work item -> tile of it.
+int gemm_walk_group(int tiles_m, int tiles_n, int K, int splits);
 void gemm_route_tile(const GemmRoute& r, int item, int* tile_row, int* tile_col);
 int gemm_mfma(const GemmArgs& g, hipStream_t s);
 struct EpiArgs;
@@ -152,6 +153,11 @@ int gemm_group_input(const GemmArgs* w, int n, const GemmArgs& d, bool alone, hi
 int gemm_mfma_group_input(const GemmArgs* g, int n, const EpiArgs* e, int first, int blocks, const GemmArgs& d, const EpiArgs& de, int tile_n, bool edge, hipStream_t s);
 // Whether the weight gradients are one round of tiles with that place left in it, and how long they take.
 bool gemm_group_input_pays(const GemmArgs* w, int n, const GemmArgs& d, double* group_us);
+
+// Loss of every row of hf emb^T (bf16, [M, K] and [N, K], densely stored) without storing the product.
+bool lse_loss_supported(int dtype, int M, int N, int K, const void* hf, const void* emb);
+size_t lse_loss_ws_bytes(int M, int N, int K);
+int lse_loss(int M, int N, int K, const void* hf, const void* emb, const int32_t* labels, void* ws, float* row_loss, hipStream_t s);
 
 // ---- LayerNorm, column sums ---------------------------------------------------------------
 int ln_fwd(int dtype, int rows, int D, const void* x, const void* gamma, const void* beta, float eps,
@@ -206,6 +212,8 @@ int attn_bwd_mfma(int B, int S, int H, int dh, const void* qkv, const void* ctx,
 // bytes at least, where ld is one.
 int cross_entropy(int dtype, int N, int V, int ld, const void* logits, const int32_t* labels, void* dlogits,
                   float* row_loss, float* loss_out, float grad_scale, hipStream_t s);
+// loss_out = mean of row_loss
+int mean_loss(int N, const float* row_loss, float* loss_out, hipStream_t s);
 // Per-row losses in a file-scope device array of the library (CE_STATIC_MAX_ROWS floats, 1 MiB per GPU).
 constexpr int CE_STATIC_MAX_ROWS = 1 << 18;
 int cross_entropy_static(int dtype, int N, int V, const void* logits, const int32_t* labels, void* dlogits,

@@ -116,7 +116,8 @@ __device__ __forceinline__ bf16x8 frag_load(const char* lds, int rb, int ks, int
 // in the store loop may hang on a run-time condition: stores count towards the same counter as
 // loads on this target, so the conservative wait the compiler places where branches that contain
 // loads rejoin would also wait for every earlier store to be acknowledged, once per row.
-enum { EK_STORE = 0, EK_GELU_TANH = 1, EK_GELU_ERF = 2, EK_DGELU = 3, EK_F32 = 5, EK_VALUE_TANH = 6, EK_VALUE_ERF = 7 };  // VALUE: GELU without the derivative
+// VALUE: GELU without the derivative.  LSE: no output at all but what a softmax over the columns needs (lse_epilogue).
+enum { EK_STORE = 0, EK_GELU_TANH = 1, EK_GELU_ERF = 2, EK_DGELU = 3, EK_LSE = 4, EK_F32 = 5, EK_VALUE_TANH = 6, EK_VALUE_ERF = 7 };
 enum {
   EM_RES = 8,  // bf16 kinds: add the residual R;  EK_F32: add to what C already holds
   EM_C2 = 16,  // EK_STORE: also write the plain product (before bias and residual) to C2
@@ -400,6 +401,39 @@ __device__ __forceinline__ void tile_epilogue96(const EpiArgs& e, const f32x16 (
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+
+// EK_LSE: of every row of the wave tile its largest element, in units of log2, and the sum of 2^(element - largest), the element in those
+// units too; to C as float2, one run of M rows for every 32 TN columns (ldc = M).  In place of the stores of 128 KB a tile, which a kernel of its own would
+// read again.  A lane has half of a row in its accumulators and lane l ^ 32 the other: nothing goes through LDS.  A NaN gets through the
+// maximum and the sum; a part without elements has -infinity and 0.
+static constexpr float LSE_LOG2E = 1.4426950408889634f;
+template <bool MASK, int TM, int TN>
+__device__ __forceinline__ void lse_epilogue(const EpiArgs& e, const f32x16 (&acc)[TM][TN], int mw, int nw, int M, int N, int lane) {
+  const int h4 = lane >> 5 << 2;
+#pragma unroll
+  for (int i = 0; i < TM; i++) {
+    float z[TN * 16];
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) {
+        z[j * 16 + v] = acc[i][j][v];
+        if (MASK) z[j * 16 + v] = nw + j * 32 + 8 * (v >> 2) + h4 + (v & 3) < N ? z[j * 16 + v] : -INFINITY;
+      }
+    float top = z[0];
+#pragma unroll
+    for (int t = 1; t < TN * 16; t++) top = __builtin_elementwise_maximum(top, z[t]);
+    top = __builtin_elementwise_maximum(top, __shfl_xor(top, 32, 64));
+    const float ref = top * LSE_LOG2E, from = top == -INFINITY ? 0.f : ref;
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < TN * 16; t++) sum[t & 3] += __builtin_amdgcn_exp2f(fmaf(z[t], LSE_LOG2E, -from));
+    float s = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    s += __shfl_xor(s, 32, 64);
+    const int m = mw + i * 32 + (lane & 31);
+    if (lane < 32 && (!MASK || m < M)) reinterpret_cast<float2*>(e.C)[(size_t)(nw / (TN * 32)) * e.ldc + m] = make_float2(ref, s);
   }
 }
 
@@ -763,7 +797,8 @@ __device__ __forceinline__ void mfma_tiles(int block, int blocks, int M, int N, 
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));
   auto epilogue = [&](auto mask_c) {
-    if constexpr (TN == 3) tile_epilogue96<EM, TM>(e, acc, wbuf, m0 + wm, n0 + wn, lane_e);
+    if constexpr (em_kind(EM) == EK_LSE) lse_epilogue<decltype(mask_c)::value, TM, TN>(e, acc, m0 + wm, n0 + wn, M_item, N_item, lane_e);
+    else if constexpr (TN == 3) tile_epilogue96<EM, TM>(e, acc, wbuf, m0 + wm, n0 + wn, lane_e);
     else tile_epilogue<EM, decltype(mask_c)::value, TM, TN>(GROUP ? et : e, et, acc, wbuf, m0 + wm, n0 + wn, M_item, N_item, lane_e);
   };  // epilogue
   if constexpr (EDGE) {

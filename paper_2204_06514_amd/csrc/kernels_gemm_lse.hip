@@ -1,0 +1,90 @@
+// The loss of a validation step without its logits: the output projection's tiles leave, of every row, a maximum and a sum of exponentials for
+// each 128 (64) columns (gemm_mfma_kernel.h, EK_LSE), and one kernel makes the row's loss of them.
+#include "gemm_mfma_kernel.h"
+
+namespace fax {
+
+static constexpr int LSE_ROWS = 64, LSE_WAVES = 16;
+
+// A workgroup takes 64 rows: its waves share the parts, a row to a lane, and then the rows' label logits, which are 64-wide dot products of the hidden
+// state with the label's row of the embedding.  Bound by reading both and the parts: 16384 rows, 394 parts, D 768: 100 MB in
+// 17 us.
+__global__ __launch_bounds__(64 * LSE_WAVES) void lse_row_loss_kernel(int M, int N, int D, int parts, const float2* __restrict__ part, const bf16_t* __restrict__ hf,
+                                                                      const bf16_t* __restrict__ emb, const int32_t* __restrict__ labels,
+                                                                      float* __restrict__ row_loss) {
+  __shared__ float tops[LSE_WAVES][LSE_ROWS], sums[LSE_WAVES][LSE_ROWS], label_logit[LSE_ROWS];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = blockIdx.x * LSE_ROWS, m = min(m0 + lane, M - 1);
+  auto join = [](float& top, float& sum, float2 p) {  // a part with -infinity has no elements, or none that count
+    const float t = __builtin_elementwise_maximum(top, p.x);
+    sum = (top == -INFINITY ? 0.f : sum * __builtin_amdgcn_exp2f(top - t)) + (p.x == -INFINITY ? 0.f : p.y * __builtin_amdgcn_exp2f(p.x - t));
+    top = t;
+  };
+  float top = -INFINITY, sum = 0.f;
+#pragma unroll 4
+  for (int p = wave; p < parts; p += LSE_WAVES) join(top, sum, part[(size_t)p * M + m]);
+  tops[wave][lane] = top;
+  sums[wave][lane] = sum;
+  for (int r = wave; r < LSE_ROWS && m0 + r < M; r += LSE_WAVES) {
+    const bf16_t *x = hf + (size_t)(m0 + r) * D, *w = emb + (size_t)min(max(labels[m0 + r], 0), N - 1) * D;
+    float z = 0.f;
+    for (int d = lane * 8; d < D; d += 512) {
+      const bf16x8 a = *reinterpret_cast<const bf16x8*>(x + d), b = *reinterpret_cast<const bf16x8*>(w + d);
+#pragma unroll
+      for (int k = 0; k < 8; k++) z = fmaf((float)a[k], (float)b[k], z);
+    }
+    z = wave_sum(z);
+    if (lane == 0) label_logit[r] = z;
+  }
+  __syncthreads();
+  if (wave == 0 && m0 + lane < M) {
+    for (int w = 1; w < LSE_WAVES; w++) join(top, sum, make_float2(tops[w][lane], sums[w][lane]));
+    row_loss[m0 + lane] = (top + __builtin_amdgcn_logf(sum)) * 0.6931471805599453f - label_logit[lane];  // v_log_f32 is log2
+  }
+}
+
+// Bulk and strip of the output projection: whole 256 x 256 tiles with the last 128 columns on 256 x 128 ones, or masked tiles.
+struct LsePlan { bool edge; int bulk, parts; };
+static LsePlan lse_plan(int M, int N, int K) {
+  const bool edge = M % 256 || N % 128 || K % GK;
+  const int bulk = edge ? N : N / 256 * 256;
+  return LsePlan{edge, bulk, 2 * ((bulk + 255) / 256) + (bulk < N ? 2 : 0)};
+}
+
+// hf [M, K], emb [N, K], both densely stored.  What it saves is the logits' way to memory and back: 16384 x 50304 x 768 1450 -> 1210 us.  From 192
+// tiles on, below which 256 x 256 ones leave too many CUs idle.  Validation steps, stored logits and this, us (tokens x vocabulary, width): 128 tiles
+// 1024 x 8192, 64 57 and 57;  200 2048 x 6400, 1024 155 and 150;  256 4096 x 4096, 1024 217 and 215;  400 2048 x 12800, 1024 191 and 179;  2000
+// 4096 x 32000, 1024 500 and 436, 4000 x 32003, 512 345 and 285, 3998 x 50257, 768 730 and 555.
+bool lse_loss_supported(int dtype, int M, int N, int K, const void* hf, const void* emb) {
+  const uintptr_t at = reinterpret_cast<uintptr_t>(hf) | reinterpret_cast<uintptr_t>(emb);
+  return dtype == FAX_BF16 && K % 8 == 0 && (at & 15) == 0 && (long long)((M + 255) / 256) * ((N + 255) / 256) >= 192;
+}
+size_t lse_loss_ws_bytes(int M, int N, int K) { return (size_t)lse_plan(M, N, K).parts * M * sizeof(float2); }
+
+int lse_loss(int M, int N, int K, const void* hf, const void* emb, const int32_t* labels, void* ws, float* row_loss, hipStream_t s) {
+  const LsePlan plan = lse_plan(M, N, K);
+  {
+    Timed t("gemm_mfma_Ak_Bk_lse", WORK_FLOP, 2.0 * M * N * K, s);
+    GemmArgs g = dense_product(FAX_BF16, false, true, M, plan.bulk, K, false);
+    g.A = hf; g.B = emb; g.C = ws; g.ldc = M;
+    EpiArgs e{};
+    e.C = g.C; e.ldc = M; e.splits = 1; e.group = gemm_walk_group((M + 255) / 256, (plan.bulk + 255) / 256, K, 1); e.a_lim = M; e.b_lim = N;
+    if (plan.edge) {
+      FAX_TRY((launch_mfma<256, 256, true, true, EK_LSE, true>(g, e, s)));
+    } else {
+      FAX_TRY((launch_mfma<256, 256, true, true, EK_LSE>(g, e, s)));
+      if (plan.bulk < N) {
+        g.N = N - plan.bulk;
+        g.B = (const bf16_t*)emb + (size_t)plan.bulk * K;
+        e.C = (float2*)ws + (size_t)(plan.parts - 2) * M;
+        FAX_TRY((launch_mfma<256, 128, true, true, EK_LSE>(g, e, s)));
+      }
+    }
+  }
+  hipLaunchKernelGGL(lse_row_loss_kernel, dim3((M + LSE_ROWS - 1) / LSE_ROWS), dim3(64 * LSE_WAVES), 0, s, M, N, K, plan.parts, (const float2*)ws,
+                     (const bf16_t*)hf, (const bf16_t*)emb, labels, row_loss);
+  FAX_LAUNCH_CHECK("lse_row_loss");
+  return FAX_OK;
+}
+
+}  // namespace fax

@@ -19,7 +19,7 @@ static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // XCDs are laid side by side as well, 4 x 2 of them to a 16 x 16 block of tiles per round (group 0;
 // the launch falls back to 4 when it does not run 256 workgroups): the d_model 4096 block another
 // -0.4 % (8.065 -> 8.03 ms, A-B on one box), the others unchanged.
-static int walk_group(int tiles_m, int tiles_n, int K, int splits) {
+int gemm_walk_group(int tiles_m, int tiles_n, int K, int splits) {
   if (K < 1024 || !(tiles_n >= 16 || tiles_n % 8 == 0)) return 8;
   return (splits == 1 && tiles_m % 16 == 0 && tiles_n % 16 == 0) ? 0 : 4;
 }
@@ -147,7 +147,7 @@ int gemm_tile_walk_query(int M, int N, int K, bool f32_out, int* tm, int* tn, in
   const GemmSplitPlan plan = gemm_plan_query(M, N, K, f32_out, &tail);
   if (plan.tile_m == 0) { *count = 0; *group = -1; return 0; }
   const int tiles_m = (tail == 1 ? M - 128 : M) / plan.tile_m, tiles_n = (tail == 2 ? N - 128 : N) / plan.tile_n;
-  int grp = walk_group(tiles_m, tiles_n, K, plan.splits);
+  int grp = gemm_walk_group(tiles_m, tiles_n, K, plan.splits);
   const int nt = tiles_m * tiles_n;
   const int slots = (plan.tile_m == 128 && nt * plan.splits <= 2 * kCUs) ? 2 * kCUs : kCUs;
   if (grp == 0 && (plan.deep || (nt < slots ? nt : slots) != 256)) grp = 4;  // as launch_mfma and launch_deep decide
@@ -300,7 +300,7 @@ static void* offset(void* p, size_t elements, size_t elem_bytes) { return p ? (c
 static EpiArgs epi_args(const GemmArgs& g, const GemmSplitPlan& plan) {
   return EpiArgs{g.bias, g.R, g.ldr, g.C, g.ldc, g.C2, g.ldc2, g.U, g.ldu, g.epi, g.gelu_form, g.c_f32 ? 1 : 0,
                  g.accumulate ? 1 : 0, g.colsum, plan.splits, (size_t)g.M * g.N, (size_t)g.N,
-                 walk_group((g.M + plan.tile_m - 1) / plan.tile_m, (g.N + plan.tile_n - 1) / plan.tile_n, g.K, plan.splits),
+                 gemm_walk_group((g.M + plan.tile_m - 1) / plan.tile_m, (g.N + plan.tile_n - 1) / plan.tile_n, g.K, plan.splits),
                  g.ta ? (g.M + 7) / 8 * 8 : g.M, g.b_rows ? g.b_rows : g.N};
 }
 
@@ -519,7 +519,7 @@ GemmRoute gemm_route(const GemmArgs& g, bool scratch) {
   if (scratch && store_split_ok(g) && gemm_edge_supported(g)) {
     const GemmSplitPlan p = store_split_plan(g.M, g.N, g.K);
     if (p.splits > 1) return GemmRoute{r.form, false, 0, p.tile_m, p.tile_n, p.splits, (g.M + p.tile_m - 1) / p.tile_m, (g.N + p.tile_n - 1) / p.tile_n,
-                                       walk_group((g.M + p.tile_m - 1) / p.tile_m, (g.N + p.tile_n - 1) / p.tile_n, g.K, p.splits)};
+                                       gemm_walk_group((g.M + p.tile_m - 1) / p.tile_m, (g.N + p.tile_n - 1) / p.tile_n, g.K, p.splits)};
   }
   const bool edge = r.form == GEMM_EDGE;
   r.tail = edge ? 0 : tail_dim(g.M, g.N);
@@ -528,7 +528,7 @@ GemmRoute gemm_route(const GemmArgs& g, bool scratch) {
   r.small = p.deep; r.tile_m = p.tile_m; r.tile_n = p.tile_n; r.splits = p.splits;
   r.tiles_m = (M + p.tile_m - 1) / p.tile_m;
   r.tiles_n = (N + p.tile_n - 1) / p.tile_n;
-  r.group = walk_group(r.tiles_m, r.tiles_n, g.K, p.splits);
+  r.group = gemm_walk_group(r.tiles_m, r.tiles_n, g.K, p.splits);
   const int nt = r.tiles_m * r.tiles_n, slots = (p.tile_m == 128 && nt * p.splits <= 2 * kCUs) ? 2 * kCUs : kCUs;
   if (r.group == 0 && (p.deep || std::min(nt * p.splits, slots) != 256)) r.group = 4;  // as launch_mfma and launch_deep decide
   return r;

@@ -245,6 +245,10 @@ static int ce_t(int N, int V, int ld, const T* logits, const int32_t* labels, T*
                        grad_scale);
   }
   FAX_LAUNCH_CHECK("cross_entropy");
+  return mean_loss(N, row_loss, loss_out, s);
+}
+
+int mean_loss(int N, const float* row_loss, float* loss_out, hipStream_t s) {
   hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(1024), 0, s, N, row_loss, loss_out);
   FAX_LAUNCH_CHECK("cross_entropy_mean");
   return FAX_OK;
