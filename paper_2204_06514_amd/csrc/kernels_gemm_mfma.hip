@@ -445,7 +445,7 @@ int gemm_group_input(const GemmArgs* w, int n, const GemmArgs& d, bool alone, hi
     if (!alone) work += 2.0 * w[i].M * w[i].N * w[i].K;
   }
   if (alone) plan.first = 0;
-  Timed t(alone ? "gemm_mfma_Ak_Bk_store" : "gemm_mfma_group_input", WORK_FLOP, work, s);
+  Timed t(alone ? "gemm_mfma_Ak_Bk_store" : "gemm_mfma_group", WORK_FLOP, work, s);
   return gemm_mfma_group_input(w, n, e, plan.first, plan.blocks, d, epi_args(d, GemmSplitPlan{256, plan.tile_n, 1, false}), plan.tile_n, plan.edge, s);
 }
 

@@ -85,13 +85,18 @@ def test_same_bits_on_one_and_two_streams_and_over_dy(i):
             assert torch.equal(got[k], want[k]), (k, flags, over, dh1)
 
 
-def test_launches():
-    for i, name in ((0, "gemm_mfma_group_input"), (1, "gemm_mfma_group"), (2, "gemm_mfma_group"), (3, "gemm_mfma_group")):
-        s = _Pass(SHAPES[i][0], 20 + i)
-        fax.fax_timing_enable(1)
-        try:
-            s.backward()
-            rows = {r["name"]: r["launches"] for r in fax.fax_timing_report(64)}
-        finally:
-            fax.fax_timing_enable(0)
-        assert rows.get(name) == 1 and not any("f32out" in r for r in rows), rows
+@pytest.mark.parametrize("i", range(len(SHAPES)))
+def test_launches(i):
+    """One launch of all weight gradients; on one stream it does the input gradient's work too."""
+    sh, streams = SHAPES[i]
+    s = _Pass(sh, 20 + i)
+    fax.fax_timing_enable(1)
+    try:
+        s.backward()
+        rows = {r["name"]: (r["launches"], r["work"]) for r in fax.fax_timing_report(64)}
+    finally:
+        fax.fax_timing_enable(0)
+    assert not any("f32out" in r for r in rows), rows
+    n, work = rows["gemm_mfma_group"]
+    want = 2.0 * sh.T * sh.D * (4 * sh.Hd + 2 * sh.F + (3 * sh.Hd if streams == 1 else 0))
+    assert n == 1 and abs(work - want) <= 1e-6 * want
