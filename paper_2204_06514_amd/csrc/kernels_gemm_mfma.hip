@@ -313,33 +313,6 @@ static bool deep_alone(const GemmArgs& g, GemmSplitPlan* plan) {
   return plan->deep && plan->splits == 1;
 }
 
-// The pair takes one launch where both products take the small-tile form by themselves, undivided (in fp32: 64 x 64 or 32 x 32 tiles): those
-// leave CUs idle or last little longer than a launch.  The results are the same bits.  (Larger tiles fill the chip alone.)
-bool gemm_pair_supported(const GemmArgs& w, const GemmArgs& d) {
-  if (w.dtype == FAX_F32) return d.dtype == FAX_F32 && gemm_f32_pair_supported(w, d);
-  GemmSplitPlan wp, dp;
-  return w.c_f32 && w.ta && !w.tb && w.colsum && !d.c_f32 && !d.ta && d.tb && !d.C2 && !d.R && !d.bias &&
-         (d.epi == EPI_NONE || d.epi == EPI_DGELU) && deep_alone(w, &wp) && deep_alone(d, &dp);
-}
-
-int gemm_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s) {
-  if (w.dtype == FAX_F32) {
-    if (!gemm_pair_supported(w, d)) {
-      set_error("gemm_pair: not two fp32 products of small tiles");
-      return FAX_ERR_UNSUPPORTED;
-    }
-    Timed t("gemm_f32_pair", WORK_FLOP, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, s);
-    return gemm_f32_pair(w, d, s);
-  }
-  GemmSplitPlan wp, dp;
-  if (!deep_alone(w, &wp) || !deep_alone(d, &dp)) {
-    set_error("gemm_pair: not two products of the small-tile form");
-    return FAX_ERR_UNSUPPORTED;
-  }
-  Timed t("gemm_mfma_pair", WORK_FLOP, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, s);
-  return gemm_mfma_deep_pair(w, epi_args(w, wp), wp, d, epi_args(d, dp), dp, s);
-}
-
 // Launch included; with scratch for a split where the form may have one.
 // small: whether (the bulk of) it takes the small-tile form.
 static double mfma_time_us(const GemmArgs& g, bool* small) {
@@ -366,6 +339,46 @@ static double mfma_time_us(const GemmArgs& g, bool* small) {
 double gemm_mfma_time_us(const GemmArgs& g) {
   bool small;
   return mfma_time_us(g, &small);
+}
+
+// The pair takes one launch where both products take the small-tile form by themselves, undivided (in fp32: 64 x 64 or 32 x 32 tiles): those
+// leave CUs idle or last little longer than a launch.  The results are the same bits.  (Larger tiles fill the chip alone.)  And where the 64 x 64 tiles
+// of both are no more than a round together and so take less than the launches that each would have by itself: forward and backward pass of
+// 41 tokens x 64 89 -> 69 us, of 415 x 64 95 -> 85.  Not where the weight gradient would have K ranges: 4096 x 64 123, 145 in pairs.
+static bool pair_plan(const GemmArgs& w, const GemmArgs& d, GemmSplitPlan* wp, GemmSplitPlan* dp) {
+  if (!(w.c_f32 && w.ta && !w.tb && w.colsum && !d.c_f32 && !d.ta && d.tb && !d.C2 && !d.R && !d.bias && (d.epi == EPI_NONE || d.epi == EPI_DGELU)))
+    return false;
+  if (deep_alone(w, wp) && deep_alone(d, dp)) return true;
+  if (w.path != PATH_AUTO || d.path != PATH_AUTO || !gemm_edge_supported(w) || !gemm_edge_supported(d)) return false;
+  const TileClass& tc = kTiles[sizeof(kTiles) / sizeof(kTiles[0]) - 1];
+  auto tiles = [&](const GemmArgs& g) { return (long long)((g.M + tc.m - 1) / tc.m) * ((g.N + tc.n - 1) / tc.n); };
+  if (tiles(w) + tiles(d) > kCUs || gemm_route(w, w.split_ws != nullptr).splits > 1) return false;
+  auto us = [&](const GemmArgs& g) { return tile_time_us(tc, g.M, g.N, g.K, g.c_f32, 1); };
+  *wp = *dp = GemmSplitPlan{tc.m, tc.n, 1, true};
+  return 3.0 + std::max(us(w), us(d)) < 0.95 * (gemm_mfma_time_us(w) + gemm_mfma_time_us(d));
+}
+bool gemm_pair_supported(const GemmArgs& w, const GemmArgs& d) {
+  if (w.dtype == FAX_F32) return d.dtype == FAX_F32 && gemm_f32_pair_supported(w, d);
+  GemmSplitPlan wp, dp;
+  return pair_plan(w, d, &wp, &dp);
+}
+
+int gemm_pair(const GemmArgs& w, const GemmArgs& d, hipStream_t s) {
+  if (w.dtype == FAX_F32) {
+    if (!gemm_pair_supported(w, d)) {
+      set_error("gemm_pair: not two fp32 products of small tiles");
+      return FAX_ERR_UNSUPPORTED;
+    }
+    Timed t("gemm_f32_pair", WORK_FLOP, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, s);
+    return gemm_f32_pair(w, d, s);
+  }
+  GemmSplitPlan wp, dp;
+  if (!pair_plan(w, d, &wp, &dp)) {
+    set_error("gemm_pair: not two products of the small-tile form");
+    return FAX_ERR_UNSUPPORTED;
+  }
+  Timed t("gemm_mfma_pair", WORK_FLOP, 2.0 * w.M * w.N * w.K + 2.0 * d.M * d.N * d.K, s);
+  return gemm_mfma_deep_pair(w, epi_args(w, wp), wp, d, epi_args(d, dp), dp, s);
 }
 
 // Weight gradients of one layer in one launch, whose tiles share the rounds: by themselves each ends in a partly filled one, takes tiles
