@@ -53,6 +53,15 @@ __device__ __forceinline__ float4 chunk_load(const float* __restrict__ p, int ld
   if (VEC) return *reinterpret_cast<const float4*>(q + min(row, rows - 4));
   return make_float4(q[min(row, rows - 1)], q[min(row + 1, rows - 1)], q[min(row + 2, rows - 1)], q[min(row + 3, rows - 1)]);
 }
+// The same for whole vectors, as bytes from the slab's first element (row r0, index k0): fixed but for the slab in which K ends, so that a load needs
+// a scalar address and this, where working the place out for each took as much of the vector unit as two thirds of the cutting: 4096 x 4096 x 4096
+// 742 -> 662 us with both operands [row][k], 2048 x 4096 x 1024 104 -> 97, [K, N] weights 107 -> 103.
+template <int ROWS, int BK, bool KC>
+__device__ __forceinline__ unsigned chunk_offset(int ld, int rows, int k_left, int c) {  // rows, k_left: how many there are from the slab's first
+  if (KC) return 4u * ((unsigned)min(c / (BK / 4), rows - 1) * (unsigned)ld + (unsigned)min(c % (BK / 4) * 4, k_left - 4));
+  return 4u * ((unsigned)min(c / (ROWS / 4), k_left - 1) * (unsigned)ld + (unsigned)min(c % (ROWS / 4) * 4, rows - 4));
+}
+static constexpr int CHUNK_MAX_LD = 1 << 22;  // 128 rows of it are 2^31 bytes
 template <int ROWS, int BK, bool KC, bool VEC>
 __device__ __forceinline__ float4 chunk_mask(float4 v, int K, int k0, int c) {
   if (KC) {
@@ -271,13 +280,33 @@ __device__ __forceinline__ void f32_product_tile(int block, int M, int N, int K,
     }
   } else {
     float4 ra[AHEAD][SA::CHUNKS], rb[AHEAD][SB::CHUNKS];  // slabs on their way from memory to LDS
+    // Not for weight gradients, whose two operands are both [k][row] (3072 x 1024 x 2048 81 us, 84 with it), and of the smaller tiles only where both are [row][k].
+    constexpr bool PLACES = VEC && !TA && (TB || BM + BN >= 192);
+    unsigned oa[SA::CHUNKS], ob[SB::CHUNKS];
+    auto places = [&](int k0) {
+#pragma unroll
+      for (int i = 0; i < SA::CHUNKS; i++) oa[i] = chunk_offset<BM, BK, !TA>(lda, a_rows - m0, a_k - k0, tid + i * 512);
+#pragma unroll
+      for (int i = 0; i < SB::CHUNKS; i++) ob[i] = chunk_offset<BN, BK, TB>(ldb, N - n0, K - k0, tid + i * 512);
+    };
+    if (PLACES) places(0);
     auto request = [&](auto set_c, int s) {
       constexpr int SET = decltype(set_c)::value;
       const int k0 = s * BK;
+      if constexpr (PLACES) {
+        if (s > 0 && s == ns - 1) places(k0);  // (no load in a branch)
+        const char* a = reinterpret_cast<const char*>(A + (TA ? (size_t)k0 * lda + m0 : (size_t)m0 * lda + k0));
+        const char* b = reinterpret_cast<const char*>(B + (TB ? (size_t)n0 * ldb + k0 : (size_t)k0 * ldb + n0));
 #pragma unroll
-      for (int i = 0; i < SA::CHUNKS; i++) ra[SET][i] = chunk_load<BM, BK, !TA, VEC>(A, lda, a_rows, a_k, m0, k0, tid + i * 512);
+        for (int i = 0; i < SA::CHUNKS; i++) ra[SET][i] = *reinterpret_cast<const float4*>(a + oa[i]);
 #pragma unroll
-      for (int i = 0; i < SB::CHUNKS; i++) rb[SET][i] = chunk_load<BN, BK, TB, VEC>(B, ldb, N, K, n0, k0, tid + i * 512);
+        for (int i = 0; i < SB::CHUNKS; i++) rb[SET][i] = *reinterpret_cast<const float4*>(b + ob[i]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < SA::CHUNKS; i++) ra[SET][i] = chunk_load<BM, BK, !TA, VEC>(A, lda, a_rows, a_k, m0, k0, tid + i * 512);
+#pragma unroll
+        for (int i = 0; i < SB::CHUNKS; i++) rb[SET][i] = chunk_load<BN, BK, TB, VEC>(B, ldb, N, K, n0, k0, tid + i * 512);
+      }
     };
     auto publish = [&](auto set_c, int s) {
       constexpr int SET = decltype(set_c)::value;
@@ -660,7 +689,7 @@ struct F32Operands {
   bool vec;
 };
 static F32Operands f32_operands(const GemmArgs& g) {
-  auto vec_ok = [](const void* p, int ld, int extent) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && ld % 4 == 0 && extent % 4 == 0; };
+  auto vec_ok = [](const void* p, int ld, int extent) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && ld % 4 == 0 && extent % 4 == 0 && ld < CHUNK_MAX_LD; };
   const int a_row = g.ta ? g.M : g.K, a_lim = g.a_padded ? (a_row + 3) / 4 * 4 : a_row;  // how far A's rows may be read
   F32Operands o{{g.bias, g.R, g.ldr, g.C, g.ldc, g.C2, g.ldc2, g.U, g.ldu, g.epi, g.gelu_form, 1, g.accumulate ? 1 : 0, g.colsum},
                 vec_ok(g.A, g.lda, a_lim) && vec_ok(g.B, g.ldb, g.tb ? g.K : g.N)};
