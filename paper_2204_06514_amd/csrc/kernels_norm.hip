@@ -589,13 +589,15 @@ static int ln_bwd_t(int rows, int D, const T* dh, const T* x, const float* mu, c
     // Each workgroup writes two fp32 partial rows, which the fold reads back: with R rows per
     // workgroup that is 2 / R on top of the rows' own traffic.  Eight row blocks per workgroup, fewer
     // (down to two) while that leaves less than two workgroups per CU: with few tokens the
-    // parallelism is worth more than the partial rows cost (2048 x 5120: 43 -> 31 us).
+    // parallelism is worth more than the partial rows cost (2048 x 5120: 43 -> 31 us).  One where even two leave half of the CUs
+    // without any (512 rows of up to 1024: a block's backward pass 1 us shorter, 270 x 192 2 us).
     // And no more workgroups than the chip holds at once (by their registers): 1024 of the three a CU were a round and a third, 16384 x 1536
     // 43 us instead of 40.
     auto grid = [&](int rpb, int tpr, int nv) {
       const int most = tpr == 512 ? 256 : nv <= 2 ? (VN == 8 ? 768 : 1024) : VN == 4 && nv == 3 ? 768 : 512;
       int per_wg = 8;
       while (per_wg > 2 && rows / (per_wg * rpb) < 512) per_wg /= 2;
+      if (per_wg == 2 && rows / (2 * rpb) < 128) per_wg = 1;
       return parts = max(1, min(most, (rows + per_wg * rpb - 1) / (per_wg * rpb)));
     };
     // threads per row and vectors per thread: as few registers as the row length allows, so that
