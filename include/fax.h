@@ -57,11 +57,11 @@ enum { FAX_GELU_TANH = 0, FAX_GELU_ERF = 1 };
 /* FaxBlockDims.flags */
 #define FAX_FLAG_TP_PARTIAL 1u /* also emit the pre-reduction partial sums (Sec. 3.2) */
 /* fax_block_bwd (and the backward pass inside fax_train_step) by default enqueues the four
- * weight-gradient products, some of them together in one launch, and the folds of the LayerNorm
- * parameter gradients on a stream of the library's own, forked from the caller's stream at the
- * point where the first of them can start and joined back into it before the call returns: they
- * depend on nothing later in the chain of input gradients and run beside it.  To the caller the call behaves as if everything were on its stream (ordered after
- * what was enqueued before, before what is enqueued after).  The stream and its events are
+ * weight-gradient products, some of them together in one launch, on a stream of the library's
+ * own, forked from the caller's stream at the point where the first of them can start and joined
+ * back into it before the call returns: they depend on nothing later in the chain of input
+ * gradients and run beside it.  To the caller the call behaves as if everything were on its stream
+ * (ordered after what was enqueued before, before what is enqueued after).  The stream and its events are
  * created once per device, on first use (not under stream capture: make one call before
  * capturing), and live until the process ends; no device memory is involved.  Host threads that
  * call into the library on the same device share that stream: their calls are enqueued one after

@@ -25,7 +25,7 @@ struct DeepLds {
 // MFMAs take 0.1) and the barrier; with many more by what the L2s deliver into the LDS, which is where larger tiles take over.
 // Operands from memory, us, against the best of the other classes: 3108 x 512 x 2048 17 (26 at 128 x 128), 2048 x 640 x 5120 39 (58),
 // 3108 x 512 x 32000 211 (327), weight gradients 512 x 512 x 3108 18 (33), 1024 x 1024 x 8192 44 (84, or 32 in four K ranges and a
-// fold), 512 x 256 x 1024 7.4 (11).  The other way round 3000 x 1200 x 4800: 60 at 128 x 64, 88 at 64 x 64, 52 at 128 x 128.
+// fold), 512 x 256 x 1024 7.4 (11).  From the caches: 3108 x 512 x 2048 13, 2048 x 640 x 5120 27, 512 x 512 x 3108 11, 512 x 256 x 1024 4.9.  The other way round 3000 x 1200 x 4800: 60 at 128 x 64, 88 at 64 x 64, 52 at 128 x 128.
 // 128 x 128 tiles in this form were slower than in the other at every size tried (16-24 waves' worth of LDS reads per slab
 // either way, and one workgroup per CU instead of two).
 template <int BM, int BN, bool A_KC, bool B_KC, int EM>
@@ -335,8 +335,8 @@ struct DeepProduct {
 };
 
 // Bound like gemm_deep_kernel; what it saves is a launch's ramp and tail, and the CUs that either product alone leaves idle.
-// 512 tokens x 256, F = 1024: 6.8 us a pair, where the two launches took 6 each and the gap between them; the block forward and
-// backward 132.2 -> 114.8 us.
+// 512 tokens x 256, F = 1024: 6 us a pair, where the two launches take 5 each and the gap between them; the block forward and
+// backward 132.2 -> 114.8 us (75 with what came after).
 template <int BM, int WEM, int DM, int DEM>
 __global__ __launch_bounds__(512) void gemm_deep_pair_kernel(DeepProduct w, DeepProduct d, int first) {
   const int block = blockIdx.x;

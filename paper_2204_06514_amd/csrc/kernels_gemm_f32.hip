@@ -141,12 +141,12 @@ __device__ __forceinline__ void f32_tile(int id, int tiles_m, int tiles_n, int& 
   tn = rest / gsz;
 }
 
-// Bound, with a full chip, by the matrix cores at the clock that their power leaves (4096 x 4096 x 4096: 185 to 202 TFLOP/s counted once, 1.1 to
-// 1.2 bf16 PFLOP/s), with one workgroup on a CU by the chain from barrier to barrier: loads, cutting, LDS and back, 24
+// Bound, with a full chip, by the matrix cores at the clock that their power leaves (4096 x 4096 x 4096: 199 to 208 TFLOP/s counted once, 1.2
+// to 1.25 bf16 PFLOP/s), with one workgroup on a CU by the chain from barrier to barrier: loads, cutting, LDS and back, 24
 // MFMAs.  In the block below the matrix cores are busy 37 to 59 % of the busy CUs' clocks, the vector unit, mostly with the cutting, 41 to 56 %, and
 // waits are 19 to 24 % of the waves' time.  v_mfma_f32_32x32x2_f32 sustains 154 from registers alone; the kernel on it that this one replaces, us: 2048 x 3072 x 1024 145, here
-// 95; 2048 x 1024 x 1024 52, 30; 2048 x 4096 x 1024 160, 98; 2048 x 1024 x 4096 172, 104; its block of 2048 tokens x 1024 wide,
-// forward and backward, 1625, 1165.
+// 91; 2048 x 1024 x 1024 52, 30; 2048 x 4096 x 1024 160, 92 to 96; 2048 x 1024 x 4096 172, 104; its block of 2048 tokens x 1024 wide,
+// forward and backward, 1625, 1150.
 // Phases the other way round in one or both waves of a SIMD, s_setprio around the cutting, requests further ahead: within 2 %.
 // Fragments requested before the slab is cut instead of where they are used: 3 %, 128 x 64 8 %.  128 x 64 as 64 x 32 per wave and slabs of 32: 6 % slower.
 template <int WM, int WN, int KS, int TM, int TN>
@@ -650,7 +650,7 @@ static int dispatch_f32_class(int cls, const GemmArgs& g, const EpiArgs& e, hipS
 
 // Tile class with the smallest predicted time: rounds of one workgroup per CU (workgroups that share a CU take turns on its
 // matrix cores), each slabs x slab time + a share of prologue and epilogue.  Measured, us, at 128 x 128, 128 x 64, 64 x 64 and 32 x 32 with its
-// K in eighths: 2048 x 4096 x 1024 98, 120, 124, 255; 2048 x 1024 x 4096 150, 103, 123, 215; 1024 x 1024 x 2048 72, 47, 37, 55; 1000 x 640 x
+// K in eighths: 2048 x 4096 x 1024 96, 120, 124, 255; 2048 x 1024 x 4096 150, 103, 123, 215; 1024 x 1024 x 2048 72, 47, 37, 55; 1000 x 640 x
 // 640 -, 19, 14, 18; 777 x 512 x 2048 -, 50, 37, 28; 512 x 512 x 512 -, 17, 12, 8.
 struct F32Class { int m, n, k; double slab_us, tile_us; };
 static constexpr F32Class kF32Classes[] = {{128, 128, 32, 1.35, 4.0}, {128, 64, 64, 1.7, 4.0}, {64, 64, 32, 0.48, 1.5}, {32, 32, 128, 0.85, 1.6}};
