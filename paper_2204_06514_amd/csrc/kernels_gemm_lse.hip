@@ -43,7 +43,8 @@ __global__ __launch_bounds__(64 * LSE_WAVES) void lse_row_loss_kernel(int M, int
   }
 }
 
-// Bulk and strip of the output projection: whole 256 x 256 tiles with the last 128 columns on 256 x 128 ones, or masked tiles.
+// Bulk and strip of the output projection: whole 256 x 256 tiles with the last 128 columns on 256 x 128 ones (128 columns: nothing but those), or
+// masked tiles.
 struct LsePlan { bool edge; int bulk, parts; };
 static LsePlan lse_plan(int M, int N, int K) {
   const bool edge = M % 256 || N % 128 || K % GK;
@@ -72,7 +73,7 @@ int lse_loss(int M, int N, int K, const void* hf, const void* emb, const int32_t
     if (plan.edge) {
       FAX_TRY((launch_mfma<256, 256, true, true, EK_LSE, true>(g, e, s)));
     } else {
-      FAX_TRY((launch_mfma<256, 256, true, true, EK_LSE>(g, e, s)));
+      if (plan.bulk) FAX_TRY((launch_mfma<256, 256, true, true, EK_LSE>(g, e, s)));
       if (plan.bulk < N) {
         g.N = N - plan.bulk;
         g.B = (const bf16_t*)emb + (size_t)plan.bulk * K;

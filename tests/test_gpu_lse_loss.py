@@ -61,6 +61,18 @@ def test_few_tiles_keep_the_stored_logits():
     assert not fused and got == run_train_step(ms, p, tok, lab, update=False)[0]
 
 
+# Few columns, whole tiles of them (a strip of 128 alone, one tile) and a part of one, at the fewest row tiles the line asks for and one less.
+@pytest.mark.parametrize("T,V,B,fused", [(49152, 128, 24, True), (48896, 128, 191, False), (49152, 256, 24, True), (49152, 72, 24, True), (49151, 101, 23, True),
+                                         (48896, 72, 191, False)])
+def test_few_columns(T, V, B, fused):
+    ms, p, tok, lab = _model(T, 64, V, 6, B)
+    lab[0, :2] = [0, V - 1]
+    got, was_fused = _eval(ms, p, tok, lab)
+    assert was_fused == fused
+    ref = run_train_step(ms, p, tok, lab, update=False)[0]
+    assert abs(got - ref) <= 2e-6 * abs(ref)
+
+
 @pytest.mark.parametrize("V", [4096, 4203])
 @pytest.mark.parametrize("what", ["dominant", "empty part", "minus inf everywhere else", "far below", "nan", "inf"])
 def test_extremes(what, V):
