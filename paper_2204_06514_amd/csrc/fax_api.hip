@@ -511,15 +511,15 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
   FAX_TRY(hand_over(&SideStream::dqkv));
   const bool with_input = group && (!dh1_out || apart(dh1, dy)) && gemm_group_input_supported(all, 4, dqkv1);
   if (with_input && !side) {
-    FAX_TRY(gemm_group_input(all, 4, dqkv1, false, s));
+    FAX_TRY(gemm_group_input(all, 4, dqkv1, PART_BOTH, s));
   } else if (group) {
-    FAX_TRY(gemm_group(all, 4, sw));
+    FAX_TRY(with_input ? gemm_group_input(all, 4, dqkv1, PART_WEIGHTS, sw) : gemm_group(all, 4, sw));
     if (side) FAX_HIP(hipEventRecord(side->w2_done, side->s));
   } else if (att) {
     FAX_TRY(gemm_group(all + 2, 2, sw));
   }
   if (!with_input) FAX_TRY(layer(wqkv, dqkv1, group || att));
-  else if (side) FAX_TRY(gemm_group_input(all, 4, dqkv1, true, s));
+  else if (side) FAX_TRY(gemm_group_input(all, 4, dqkv1, PART_INPUT, s));
   // LN1 and the residual branch: dx = dx1 + LN1'(dh1).  dx may be the buffer dy came in: the weight gradient that reads dy
   // (the first one, or all together) has to be through with it.
   if (side) {

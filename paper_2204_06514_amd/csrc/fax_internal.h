@@ -146,10 +146,11 @@ int gemm_group(const GemmArgs* g, int n, hipStream_t s);
 enum GemmGroup { GROUP_FFN = 1, GROUP_ATTENTION = 2, GROUP_ALL = 4 };
 int gemm_groups(const GemmArgs (&w)[4], const GemmArgs (&in)[4]);
 int gemm_mfma_group(const GemmArgs* g, int n, const EpiArgs* e, int tile, bool edge, hipStream_t s);
-// The same together with an input gradient that does not depend on them, on the CUs they leave over, in one launch; or that one `alone`, on as many
-// CUs, beside gemm_group on another stream.
+// The same together with an input gradient that does not depend on them, on the CUs they leave over, in one launch; or either part by itself, on its
+// share of the CUs, for two streams.
+enum GroupPart { PART_BOTH, PART_WEIGHTS, PART_INPUT };
 bool gemm_group_input_supported(const GemmArgs* w, int n, const GemmArgs& d);
-int gemm_group_input(const GemmArgs* w, int n, const GemmArgs& d, bool alone, hipStream_t s);
+int gemm_group_input(const GemmArgs* w, int n, const GemmArgs& d, GroupPart part, hipStream_t s);
 int gemm_mfma_group_input(const GemmArgs* g, int n, const EpiArgs* e, int first, int blocks, const GemmArgs& d, const EpiArgs& de, int tile_n, bool edge, hipStream_t s);
 // Whether the weight gradients are one round of tiles with that place left in it, and how long they take.
 bool gemm_group_input_pays(const GemmArgs* w, int n, const GemmArgs& d, double* group_us);

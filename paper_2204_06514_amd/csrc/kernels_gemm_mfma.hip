@@ -408,7 +408,11 @@ static bool group_plan(const GemmArgs* g, int n, GroupPlan* plan) {
 }
 
 // Weight gradients and an input gradient in one launch: as many workgroups for the former as share their tiles in no more rounds than the whole
-// chip would; the latter has the others, in tiles 256 or 128 columns wide, if it is through by then.
+// chip would; the latter has the others, in tiles 256 or 128 columns wide, if it is through by then.  On two streams each keeps to its CUs as
+// well: weight gradients on all 256 leave the input gradient none before their last round.  Several rounds, us, forward and backward, tokens x width x heads' width
+// x F: the two one after the other, the input gradient alone confined, both confined: 8192 x 1920 x 960 x 7680 1963, 2020, 1912; 15872 x 3456 x 640 x
+// 10880 7245, 8290, 7154; 12800 x 2176 x 1408 x 8704 4016, 4285, 3909; 17920 x 896 x 896 x 12544 3062, 3020, 3023.  On one stream, one after the other
+// and in one launch: the first 1978 and 1945, the last 3104 and 3076.
 struct GroupInputPlan { int rounds, first, blocks, tile_n; bool edge; };
 static bool group_input_plan(const GemmArgs* g, int n, const GemmArgs& d, GroupInputPlan* plan) {
   GroupPlan gp;
@@ -447,20 +451,21 @@ bool gemm_group_input_pays(const GemmArgs* w, int n, const GemmArgs& d, double* 
   *group_us = gp.us;
   return true;
 }
-int gemm_group_input(const GemmArgs* w, int n, const GemmArgs& d, bool alone, hipStream_t s) {
+int gemm_group_input(const GemmArgs* w, int n, const GemmArgs& d, GroupPart part, hipStream_t s) {
   GroupInputPlan plan;
   if (!group_input_plan(w, n, d, &plan)) {
     set_error("gemm_group_input: not products for one launch");
     return FAX_ERR_UNSUPPORTED;
   }
   EpiArgs e[GEMM_GROUP];
-  double work = 2.0 * d.M * d.N * d.K;
+  double work = part == PART_WEIGHTS ? 0.0 : 2.0 * d.M * d.N * d.K;
   for (int i = 0; i < n; i++) {
     e[i] = epi_args(w[i], GemmSplitPlan{256, 256, 1, false});
-    if (!alone) work += 2.0 * w[i].M * w[i].N * w[i].K;
+    if (part != PART_INPUT) work += 2.0 * w[i].M * w[i].N * w[i].K;
   }
-  if (alone) plan.first = 0;
-  Timed t(alone ? "gemm_mfma_Ak_Bk_store" : "gemm_mfma_group", WORK_FLOP, work, s);
+  if (part == PART_INPUT) plan.first = 0;
+  if (part == PART_WEIGHTS) plan.blocks = 0;
+  Timed t(part == PART_INPUT ? "gemm_mfma_group_input" : "gemm_mfma_group", WORK_FLOP, work, s);
   return gemm_mfma_group_input(w, n, e, plan.first, plan.blocks, d, epi_args(d, GemmSplitPlan{256, plan.tile_n, 1, false}), plan.tile_n, plan.edge, s);
 }
 

@@ -17,7 +17,12 @@ SHAPES = [
     (BlockShape(B=4, S=1024, D=2048, H=8, dh=64, F=2048, dtype="bf16", sigma_w=0.02), 2),    # a tensor-parallel share, 64 CUs for 128 tiles
     (BlockShape(B=3, S=2048, D=1024, H=16, dh=64, F=4096, dtype="bf16", sigma_w=0.02), 2),
     (BlockShape(B=5, S=1111, D=1000, H=10, dh=96, F=4000, dtype="bf16", sigma_w=0.02), 2),   # nothing a multiple of the tile
+    (BlockShape(B=7, S=146, D=1000, H=10, dh=64, F=4000, dtype="bf16", sigma_w=0.02), 1),    # 172 tiles: no multiple of the XCDs
+    (BlockShape(B=11, S=512, D=1024, H=1, dh=128, F=4096, dtype="bf16", sigma_w=0.02), 2),   # 140
+    (BlockShape(B=28, S=384, D=896, H=7, dh=128, F=10752, dtype="bf16", sigma_w=0.02), 2),   # 396 tiles: two rounds on 200 CUs
+    (BlockShape(B=12, S=512, D=2176, H=11, dh=128, F=8704, dtype="bf16", sigma_w=0.02), 2),  # 819 tiles: four on 208
 ]
+SEVERAL_ROUNDS = (6, 7)
 
 
 class _Pass:
@@ -54,8 +59,17 @@ class _Pass:
 def test_products(i, accumulate):
     sh, streams = SHAPES[i]
     assert fax.fax_block_bwd_streams(dims_of(sh)) == streams
-    s = _Pass(sh, i)
-    got = s.backward(accumulate=accumulate)
+    _check_products(sh, i, 0, accumulate)
+
+
+@pytest.mark.parametrize("i", SEVERAL_ROUNDS)
+def test_products_of_several_rounds_on_one_stream(i):
+    _check_products(SHAPES[i][0], i, fax.FAX_FLAG_SINGLE_STREAM, 1)
+
+
+def _check_products(sh, seed, flags, accumulate):
+    s = _Pass(sh, seed)
+    got = s.backward(flags, accumulate=accumulate)
     bl, D, Hd, F = fax.fax_block_bwd_layout(dims_of(sh)), sh.D, sh.Hd, sh.F
     dqkv, dx1, du = s.left(s.ws, bl.dqkv, 3 * Hd), s.left(s.ws, bl.dx1, D), s.left(s.ws, bl.du, F)
     dh1 = s.left(s.ws, bl.dh1, D)
@@ -87,7 +101,7 @@ def test_same_bits_on_one_and_two_streams_and_over_dy(i):
 
 @pytest.mark.parametrize("i", range(len(SHAPES)))
 def test_launches(i):
-    """One launch of all weight gradients; on one stream it does the input gradient's work too."""
+    """One launch of all weight gradients; on one stream it does the input gradient's work too, on two that has a launch on the CUs left over."""
     sh, streams = SHAPES[i]
     s = _Pass(sh, 20 + i)
     fax.fax_timing_enable(1)
@@ -97,6 +111,8 @@ def test_launches(i):
     finally:
         fax.fax_timing_enable(0)
     assert not any("f32out" in r for r in rows), rows
+    n, work = rows.get("gemm_mfma_group_input", (0, 0))
+    assert (n, work) == (streams - 1, (streams - 1) * 6.0 * sh.T * sh.D * sh.Hd)
     n, work = rows["gemm_mfma_group"]
     want = 2.0 * sh.T * sh.D * (4 * sh.Hd + 2 * sh.F + (3 * sh.Hd if streams == 1 else 0))
     assert n == 1 and abs(work - want) <= 1e-6 * want
