@@ -17,7 +17,8 @@ __global__ __launch_bounds__(64 * LSE_WAVES) void lse_row_loss_kernel(int M, int
   const int m0 = blockIdx.x * LSE_ROWS, m = min(m0 + lane, M - 1);
   auto join = [](float& top, float& sum, float2 p) {  // a part with -infinity has no elements, or none that count
     const float t = __builtin_elementwise_maximum(top, p.x);
-    sum = (top == -INFINITY ? 0.f : sum * __builtin_amdgcn_exp2f(top - t)) + (p.x == -INFINITY ? 0.f : p.y * __builtin_amdgcn_exp2f(p.x - t));
+    sum = (top == -INFINITY ? 0.f : sum * __builtin_amdgcn_exp2f((top - t) * LSE_LOG2E)) +
+          (p.x == -INFINITY ? 0.f : p.y * __builtin_amdgcn_exp2f((p.x - t) * LSE_LOG2E));
     top = t;
   };
   float top = -INFINITY, sum = 0.f;
@@ -39,7 +40,7 @@ __global__ __launch_bounds__(64 * LSE_WAVES) void lse_row_loss_kernel(int M, int
   __syncthreads();
   if (wave == 0 && m0 + lane < M) {
     for (int w = 1; w < LSE_WAVES; w++) join(top, sum, make_float2(tops[w][lane], sums[w][lane]));
-    row_loss[m0 + lane] = (top + __builtin_amdgcn_logf(sum)) * 0.6931471805599453f - label_logit[lane];  // v_log_f32 is log2
+    row_loss[m0 + lane] = (top - label_logit[lane]) + __builtin_amdgcn_logf(sum) * 0.6931471805599453f;  // v_log_f32 is log2
   }
 }
 

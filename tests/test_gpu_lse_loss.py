@@ -10,7 +10,7 @@ import torch
 import paper_2204_06514_amd as fax
 from helpers import DEV, dims_of
 from test_gpu_train import run_train_step, _dev_params
-from workloads import BlockShape, ModelShape, make_model_inputs
+from workloads import BlockShape, ModelShape, make_model_inputs, round_to_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -96,3 +96,27 @@ def test_extremes(what, V):
     top = z.max()
     ref = top + np.log(np.exp(z - top).sum()) - z[300]
     assert abs(got - ref) <= 2e-6 * max(abs(ref), abs(top))   # of the logits' size: what cancels in the difference
+
+
+@pytest.mark.parametrize("V", [4096, 4203])
+@pytest.mark.parametrize("what", ["largest", "least of all", "least but for one", "a part of the least", "2^29", "2^31", "1e12", "-1e12"])
+def test_ends_of_the_range(what, V):
+    """Logits of 2.5e38 and 3e38 either way, which log2(e) takes beyond fp32's range, and of sizes whose product with it is rounded by 64 and
+    more."""
+    T, D, big = 4096, 64, 3.0e38
+    ms, p, tok, lab = _model(T, D, V, 4, 4)
+    p["lnf_g"][:] = 0
+    p["lnf_b"][:] = 1   # every hidden state is one: the logits are the embedding's elements
+    tok, lab = np.full_like(tok, 300), np.full_like(lab, 300)
+    at = {"largest": {300: 2.5e38, 777: 2.5e38}, "least of all": {n: -big for n in range(V)},
+          "least but for one": {n: -big if n != 300 else -2.5e38 for n in range(V)}, "a part of the least": {n: -big for n in range(128, 256)},
+          "2^29": {n: 1.5 * 2.0 ** 29 for n in (300, 301, 777)}, "2^31": {n: 1.5 * 2.0 ** 31 for n in (300, 301, 777)},
+          "1e12": {n: 1.25e12 for n in (300, 301, 777)}, "-1e12": {n: -1.25e12 for n in range(V)}}[what]
+    at = {n: round_to_bf16(np.array([v]))[0] for n, v in at.items()}
+    z = p["tok_emb"].sum(1)
+    for n, v in at.items():
+        p["tok_emb"][n, n % D] = z[n] = v
+    got, fused = _eval(ms, p, tok, lab)
+    assert fused
+    ref = np.log(np.exp(z - z.max()).sum()) + (z.max() - z[300])
+    assert abs(got - ref) <= 2e-6 * max(1.0, abs(ref))
