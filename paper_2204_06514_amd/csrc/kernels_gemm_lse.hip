@@ -40,7 +40,9 @@ __global__ __launch_bounds__(64 * LSE_WAVES) void lse_row_loss_kernel(int M, int
   __syncthreads();
   if (wave == 0 && m0 + lane < M) {
     for (int w = 1; w < LSE_WAVES; w++) join(top, sum, make_float2(tops[w][lane], sums[w][lane]));
-    row_loss[m0 + lane] = (top - label_logit[lane]) + __builtin_amdgcn_logf(sum) * 0.6931471805599453f;  // v_log_f32 is log2
+    // The label's logit is summed in another order than the tiles' and may come out above the largest of them: no loss below zero.  v_log_f32 is log2.
+    const float loss = (top - label_logit[lane]) + __builtin_amdgcn_logf(sum) * 0.6931471805599453f;
+    row_loss[m0 + lane] = loss < 0.f ? 0.f : loss;
   }
 }
 

@@ -120,3 +120,16 @@ def test_ends_of_the_range(what, V):
     assert fused
     ref = np.log(np.exp(z - z.max()).sum()) + (z.max() - z[300])
     assert abs(got - ref) <= 2e-6 * max(1.0, abs(ref))
+
+
+@pytest.mark.parametrize("V", [4096, 4203])
+def test_dominant_labels_cost_nothing_below_zero(V):
+    """The label's logit some 300 above the others: its loss is zero whatever order the logits are summed in."""
+    T, D = 4096, 520
+    rng = np.random.default_rng(7)
+    for _ in range(6):
+        ms, p, tok, lab = _model(T, D, V, 4, 4)
+        p["lnf_g"][:] = 0
+        p["lnf_b"][:] = p["tok_emb"][300] = round_to_bf16(rng.standard_normal(D) * 0.8)
+        got, fused = _eval(ms, p, tok, np.full_like(lab, 300))
+        assert fused and 0.0 <= got <= 1e-4   # 300 in fp32, 2^-15, twice
