@@ -61,9 +61,10 @@ def test_few_tiles_keep_the_stored_logits():
     assert not fused and got == run_train_step(ms, p, tok, lab, update=False)[0]
 
 
-# Few columns, whole tiles of them (a strip of 128 alone, one tile) and a part of one, at the fewest row tiles the line asks for and one less.
+# Few columns, whole tiles of them (a strip of 128 alone, one tile) and a part of one, at the fewest row tiles the line asks for and one less; eight
+# and seven, whose parts take the logits' place and more.
 @pytest.mark.parametrize("T,V,B,fused", [(49152, 128, 24, True), (48896, 128, 191, False), (49152, 256, 24, True), (49152, 72, 24, True), (49151, 101, 23, True),
-                                         (48896, 72, 191, False)])
+                                         (48896, 72, 191, False), (49152, 8, 24, True), (49152, 7, 24, False)])
 def test_few_columns(T, V, B, fused):
     ms, p, tok, lab = _model(T, 64, V, 6, B)
     lab[0, :2] = [0, V - 1]
