@@ -32,3 +32,11 @@ def test_deep_gemm_assembly_blocks(tmp_path):
             slabs = {3 if "ILi128ELi64E" in name else 2}
         waits = re.findall(r"#ASMSTART\s+s_waitcnt vmcnt\((\d+)\)\s+s_barrier\s", k)
         assert set(waits) == {str(i * slab) for i in range(4) for slab in slabs}, waits
+
+
+def test_loss_gemm_loads_are_waited_for_and_nothing_goes_to_scratch(tmp_path):
+    text = _assembly(tmp_path, os.path.join(CSRC, "kernels_gemm_lse.hip"))
+    n, bad = scan(text)
+    assert n == 3, n   # whole and masked 256 x 256 tiles, the strip's 256 x 128
+    assert not bad, {k: v[:3] for k, v in bad.items()}
+    assert not re.search(r"^\s*scratch_", text, re.M)
