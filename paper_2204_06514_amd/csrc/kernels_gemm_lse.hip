@@ -47,10 +47,14 @@ __global__ __launch_bounds__(64 * LSE_WAVES) void lse_row_loss_kernel(int M, int
 }
 
 // Bulk and strip of the output projection: whole 256 x 256 tiles with the last 128 columns on 256 x 128 ones (128 columns: nothing but those), or
-// masked tiles.
+// masked tiles, also for those columns where their tiles find room in the others' last round.  The strip's launch takes as long as a round
+// of its tiles, us, strip and masked: 256 x 50304 x 2048 73 and 52, 4096 x 3200 x 768 37 and 27, 2048 x 16768 x 768 78 and 71; with a round more the other way, 4096 x
+// 4224 x 768 40 and 47, 8192 x 8320 x 768 108 and 117.
 struct LsePlan { bool edge; int bulk, parts; };
 static LsePlan lse_plan(int M, int N, int K) {
-  const bool edge = M % 256 || N % 128 || K % GK;
+  const int rows = (M + 255) / 256;
+  auto rounds = [&](int n) { return ((long long)rows * ((n + 255) / 256) + 255) / 256; };
+  const bool edge = M % 256 || N % 128 || K % GK || (N % 256 && rounds(N) == rounds(N / 256 * 256));
   const int bulk = edge ? N : N / 256 * 256;
   return LsePlan{edge, bulk, 2 * ((bulk + 255) / 256) + (bulk < N ? 2 : 0)};
 }

@@ -40,6 +40,7 @@ def _eval(ms, p, tok, lab):
 
 SIZES = [(4096, 64, 4096, 4),      # whole tiles, one slab
          (4096, 128, 4224, 4),     # and a strip
+         (4096, 64, 3200, 4),      # 128 columns beyond whole tiles whose tiles fit into the round
          (3000, 200, 8003, 3),     # nothing whole: rows, columns, contraction
          (4001, 72, 3329, 1),      # one column beyond a tile
          (3841, 520, 3200, 1)]     # one row beyond, a part of 128 columns masked out
