@@ -112,6 +112,7 @@ size_t gemm_store_split_ws_bytes(int M, int N, int K);
 GemmSplitPlan gemm_plan_query(int M, int N, int K, bool f32_out, int* tail);
 int gemm_tile_walk_query(int M, int N, int K, bool f32_out, int* tm, int* tn, int capacity, int* count, int* group);
 double gemm_mfma_time_us(const GemmArgs& g);
+double gemm_tiles_us(int tile_m, int tile_n, int M, int N, int K);
 // The launch gemm() makes of a product (of its bulk, where the last 128 rows (tail 1) or columns (2) are one of their own), with or
 // without scratch for a split: form, whether in its small-tile kernel, tile, K ranges, and the grid and grouping of the tile walk (bf16 forms; -1: none).
 struct GemmRoute {
@@ -156,7 +157,7 @@ int gemm_mfma_group_input(const GemmArgs* g, int n, const EpiArgs* e, int first,
 bool gemm_group_input_pays(const GemmArgs* w, int n, const GemmArgs& d, double* group_us);
 
 // Loss of every row of hf emb^T (bf16, [M, K] and [N, K], densely stored) without storing the product.
-bool lse_loss_supported(int dtype, int M, int N, int K, const void* hf, const void* emb);
+bool lse_loss_supported(const GemmArgs& logits, int N);
 size_t lse_loss_ws_bytes(int M, int N, int K);
 int lse_loss(int M, int N, int K, const void* hf, const void* emb, const int32_t* labels, void* ws, float* row_loss, hipStream_t s);
 

@@ -59,13 +59,22 @@ static LsePlan lse_plan(int M, int N, int K) {
   return LsePlan{edge, bulk, 2 * ((bulk + 255) / 256) + (bulk < N ? 2 : 0)};
 }
 
-// hf [M, K], emb [N, K], both densely stored.  What it saves is the logits' way to memory and back: 16384 x 50304 x 768 1450 -> 1210 us.  From 192
-// tiles on, below which 256 x 256 ones leave too many CUs idle.  Validation steps, stored logits and this, us (tokens x vocabulary, width): 128 tiles
-// 1024 x 8192, 64 57 and 57;  200 2048 x 6400, 1024 155 and 150;  256 4096 x 4096, 1024 217 and 215;  400 2048 x 12800, 1024 191 and 179;  2000
-// 4096 x 32000, 1024 500 and 436, 4000 x 32003, 512 345 and 285, 3998 x 50257, 768 730 and 555.
-bool lse_loss_supported(int dtype, int M, int N, int K, const void* hf, const void* emb) {
-  const uintptr_t at = reinterpret_cast<uintptr_t>(hf) | reinterpret_cast<uintptr_t>(emb);
-  return dtype == FAX_BF16 && K % 8 == 0 && (at & 15) == 0 && (long long)((M + 255) / 256) * ((N + 255) / 256) >= 192;
+// hf [M, K], emb [N, K], both densely stored; `logits` the product with them stored.  What it saves is the logits' way to memory and back: 16384 x 50304 x
+// 768 1450 -> 1160 us.  From 192 tiles on, below which 256 x 256 ones leave too many CUs idle, and where the tiles and the rows' kernel (11 us and 2.7 for every 1000 of
+// width) are predicted to take less than the product in the tiles it takes by itself and the kernel over its rows (9 us, 0.27 a megabyte and 0.8 for every 1000 rows).
+// Validation steps of one narrow layer, stored logits and this, us (tokens x columns x width): 256 x 50304 x 768 75.2 and 72.5, 1024 x 12928 x 2048 121 and 118, 1024 x 21938 x
+// 1600 142.5 and 141.7, 4096 x 8448 x 768 153 and 141, 2048 x 13000 x 768 119 and 106, 4096 x 12672 x 2048 332 and 307;  on the other side,
+// where the product takes other tiles, 4096 x 8448 x 2048 239 and 241, 4096 x 8576 x 2048 246 and 255, 1111 x 16000 x 2048 164 and
+// 162, 4096 x 4224 x 2048 184.5 either way.
+bool lse_loss_supported(const GemmArgs& logits, int N) {
+  const int M = logits.M, K = logits.K;
+  const uintptr_t at = reinterpret_cast<uintptr_t>(logits.A) | reinterpret_cast<uintptr_t>(logits.B);
+  if (!(logits.dtype == FAX_BF16 && K % 8 == 0 && (at & 15) == 0 && (long long)((M + 255) / 256) * ((N + 255) / 256) >= 192)) return false;
+  const LsePlan plan = lse_plan(M, N, K);
+  double us = 11.0 + 2.7e-3 * K;
+  if (plan.bulk) us += 3.0 + gemm_tiles_us(256, 256, M, plan.bulk, K);
+  if (plan.bulk < N) us += 3.0 + gemm_tiles_us(256, 128, M, N - plan.bulk, K);
+  return us < 0.98 * (gemm_time_estimate_us(logits) + 9.0 + 0.27 * (2e-6 * M * N) + 0.8e-3 * M);
 }
 size_t lse_loss_ws_bytes(int M, int N, int K) { return (size_t)lse_plan(M, N, K).parts * M * sizeof(float2); }
 

@@ -342,6 +342,12 @@ double gemm_mfma_time_us(const GemmArgs& g) {
   bool small;
   return mfma_time_us(g, &small);
 }
+// Of a product with 16-bit outputs in tiles of one class, without the launch.
+double gemm_tiles_us(int tile_m, int tile_n, int M, int N, int K) {
+  for (const TileClass& tc : kTiles)
+    if (tc.m == tile_m && tc.n == tile_n) return tile_time_us(tc, M, N, K, false, 1);
+  return 0.0;
+}
 
 // The pair takes one launch where both products take the small-tile form by themselves, undivided (in fp32: 64 x 64 or 32 x 32 tiles): those
 // leave CUs idle or last little longer than a launch.  The results are the same bits.  (Larger tiles fill the chip alone.)  And where the 64 x 64 tiles

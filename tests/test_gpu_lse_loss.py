@@ -56,8 +56,9 @@ def test_loss_is_that_of_stored_logits(T, D, V, B):
     assert abs(got - ref) <= 2e-6 * abs(ref)
 
 
-def test_few_tiles_keep_the_stored_logits():
-    ms, p, tok, lab = _model(2048, 64, 2048, 5)
+@pytest.mark.parametrize("T,D,V", [(2048, 64, 2048), (4096, 2048, 8448)])   # 64 tiles; 528, a round of 16 and 32 slabs each
+def test_few_tiles_and_rounds_of_few_keep_the_stored_logits(T, D, V):
+    ms, p, tok, lab = _model(T, D, V, 5)
     got, fused = _eval(ms, p, tok, lab)
     assert not fused and got == run_train_step(ms, p, tok, lab, update=False)[0]
 
