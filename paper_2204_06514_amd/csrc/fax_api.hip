@@ -877,10 +877,8 @@ int fax_eval_step(const FaxModelDims* dims, const FaxModelTensors* params, const
                  (float*)(w + W.muf), (float*)(w + W.rstdf), s));
   // the parts go where the logits would: a thirty-second of them, more than they take where there are fewer than eight columns
   const GemmArgs logits = logits_product(*dims, w + W.hf, params->tok_emb, w + W.logits);
-  if (lse_loss_supported(logits, V) && lse_loss_ws_bytes(T, V, D) <= z.T * (size_t)V * z.es) {
-    FAX_TRY(lse_loss(T, V, D, w + W.hf, params->tok_emb, labels, w + W.logits, (float*)(w + W.row_loss), s));
-    return mean_loss(T, (const float*)(w + W.row_loss), loss_out, s);
-  }
+  if (lse_loss_supported(logits, V) && lse_loss_ws_bytes(T, V, D) <= z.T * (size_t)V * z.es)
+    return lse_loss(T, V, D, w + W.hf, params->tok_emb, labels, w + W.logits, (float*)(w + W.row_loss), loss_out, s);
   FAX_TRY(gemm(logits, s));
   return cross_entropy(d.dtype, T, V, ldl, w + W.logits, labels, nullptr, (float*)(w + W.row_loss), loss_out, 1.0f, s);
 }

@@ -156,10 +156,10 @@ int gemm_mfma_group_input(const GemmArgs* g, int n, const EpiArgs* e, int first,
 // Whether the weight gradients are one round of tiles with that place left in it, and how long they take.
 bool gemm_group_input_pays(const GemmArgs* w, int n, const GemmArgs& d, double* group_us);
 
-// Loss of every row of hf emb^T (bf16, [M, K] and [N, K], densely stored) without storing the product.
+// Loss of every row of hf emb^T (bf16, [M, K] and [N, K], densely stored) and their mean without storing the product.
 bool lse_loss_supported(const GemmArgs& logits, int N);
 size_t lse_loss_ws_bytes(int M, int N, int K);
-int lse_loss(int M, int N, int K, const void* hf, const void* emb, const int32_t* labels, void* ws, float* row_loss, hipStream_t s);
+int lse_loss(int M, int N, int K, const void* hf, const void* emb, const int32_t* labels, void* ws, float* row_loss, float* loss_out, hipStream_t s);
 
 // ---- LayerNorm, column sums ---------------------------------------------------------------
 int ln_fwd(int dtype, int rows, int D, const void* x, const void* gamma, const void* beta, float eps,

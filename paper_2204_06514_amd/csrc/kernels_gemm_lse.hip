@@ -78,7 +78,7 @@ bool lse_loss_supported(const GemmArgs& logits, int N) {
 }
 size_t lse_loss_ws_bytes(int M, int N, int K) { return (size_t)lse_plan(M, N, K).parts * M * sizeof(float2); }
 
-int lse_loss(int M, int N, int K, const void* hf, const void* emb, const int32_t* labels, void* ws, float* row_loss, hipStream_t s) {
+int lse_loss(int M, int N, int K, const void* hf, const void* emb, const int32_t* labels, void* ws, float* row_loss, float* loss_out, hipStream_t s) {
   const LsePlan plan = lse_plan(M, N, K);
   {
     Timed t("gemm_mfma_Ak_Bk_lse", WORK_FLOP, 2.0 * M * N * K, s);
@@ -98,10 +98,11 @@ int lse_loss(int M, int N, int K, const void* hf, const void* emb, const int32_t
       }
     }
   }
+  Timed t("lse_row_loss", WORK_BYTE, (double)plan.parts * M * sizeof(float2) + 4.0 * M * K, s);
   hipLaunchKernelGGL(lse_row_loss_kernel, dim3((M + LSE_ROWS - 1) / LSE_ROWS), dim3(64 * LSE_WAVES), 0, s, M, N, K, plan.parts, (const float2*)ws,
                      (const bf16_t*)hf, (const bf16_t*)emb, labels, row_loss);
   FAX_LAUNCH_CHECK("lse_row_loss");
-  return FAX_OK;
+  return mean_loss(M, row_loss, loss_out, s);
 }
 
 }  // namespace fax

@@ -655,6 +655,7 @@ int ln_bwd_fold(const LnFold& a, const LnFold* b, bool accumulate, hipStream_t s
   uintptr_t at = 0;
   for (float* p : f.out) at |= reinterpret_cast<uintptr_t>(p);
   const dim3 grid((a.D + 63) / 64, b ? 4 : 2);
+  Timed t("layernorm_bwd_fold", WORK_BYTE, 4.0 * grid.y * a.D * (a.parts + (accumulate ? 2.0 : 1.0)), s);
   if (a.D % 4 == 0 && (at & 15) == 0) hipLaunchKernelGGL(fold_partials4_kernel, grid, dim3(256), 0, s, a.parts, a.D, f, accumulate ? 1 : 0);
   else hipLaunchKernelGGL(fold_partials_kernel, grid, dim3(256), 0, s, a.parts, a.D, f, accumulate ? 1 : 0);
   FAX_LAUNCH_CHECK("ln_bwd_fold");

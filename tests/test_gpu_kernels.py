@@ -8,8 +8,8 @@ import torch
 
 import paper_2204_06514_amd as fax
 from oracle import transformer as orc
-from workloads import round_to_bf16
-from helpers import DEV, TDTYPE, CODE, to_dev, to_np, err, tol, rel_max, rel_fro
+from workloads import BlockShape, make_block_inputs, round_to_bf16
+from helpers import run_block, DEV, TDTYPE, CODE, to_dev, to_np, err, tol, rel_max, rel_fro
 
 pytestmark = pytest.mark.gpu
 
@@ -359,3 +359,29 @@ def test_timing_report_names_kernels_and_counts_their_work():
         assert fax.fax_timing_report(64) == []
     finally:
         fax.fax_timing_enable(0)
+
+
+def test_timing_report_has_the_folds_of_layernorm_gradients():
+    """Both LayerNorms of a block in one launch, outside of the rows' kernels; one fold to a call by itself."""
+    sh = BlockShape(B=2, S=256, D=256, H=4, dh=64, F=1024, dtype="bf16", sigma_w=0.02)
+    p, x, dy = make_block_inputs(sh, seed=1, generic=True)
+    D, rows = 64, 100
+    a = torch.zeros((rows, D), device=DEV)
+    v = torch.ones(rows, device=DEV)
+    wsb = fax.fax_layernorm_bwd_workspace_bytes(D)
+    ws = torch.empty(wsb, dtype=torch.uint8, device=DEV)
+
+    def report(call):
+        fax.fax_timing_enable(1)
+        try:
+            call()
+            torch.cuda.synchronize()
+            return {r["name"]: r for r in fax.fax_timing_report(64)}
+        finally:
+            fax.fax_timing_enable(0)
+
+    r = report(lambda: run_block(sh, p, x, dy))
+    assert r["layernorm_bwd"]["launches"] == 2 and r["layernorm_bwd_fold"]["launches"] == 1 and r["layernorm_bwd_fold"]["ms"] > 0
+    r = report(lambda: fax.fax_layernorm_bwd(fax.FAX_F32, rows, D, a, a, v, v, torch.ones(D, device=DEV), None, torch.empty_like(a),
+                                             torch.zeros(D, device=DEV), torch.zeros(D, device=DEV), 0, ws, wsb))
+    assert r["layernorm_bwd"]["launches"] == 1 and r["layernorm_bwd_fold"]["launches"] == 1

@@ -35,7 +35,9 @@ def _eval(ms, p, tok, lab):
         names = [r["name"] for r in fax.fax_timing_report(64)]
     finally:
         fax.fax_timing_enable(0)
-    return out[0].item(), "gemm_mfma_Ak_Bk_lse" in names
+    fused = "gemm_mfma_Ak_Bk_lse" in names
+    assert ("lse_row_loss" in names) == fused and ("cross_entropy" in names) == (not fused)   # every kernel of the loss is in the report
+    return out[0].item(), fused
 
 
 SIZES = [(4096, 64, 4096, 4),      # whole tiles, one slab
