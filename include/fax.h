@@ -254,7 +254,8 @@ int fax_block_fwd(const FaxBlockDims* dims, const FaxBlockTensors* params, const
  * dx: [B,S,D] gradient at x (may alias dy).
  * grads: twelve fp32 buffers; accumulate != 0 adds into them, 0 overwrites.
  * dh1_partial, dh2_partial: optional [B,S,D] outputs in dims.dtype (device, 16-byte aligned, not
- *   aliasing any other argument) for the gradients at the outputs of the two LayerNorms,
+ *   aliasing any other argument, except that dh1_partial may be the buffer dy came in where dx is
+ *   another) for the gradients at the outputs of the two LayerNorms,
  *   dh1 = dqkv Wqkv^T and dh2 = du W1^T: on a tensor-parallel rank these are the partial sums
  *   that are reduced over the model axis before the LayerNorm backward of the full model
  *   (Sec. 3.2).  NULL: they are left in the workspace instead, at the offsets of

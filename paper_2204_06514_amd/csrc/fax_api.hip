@@ -509,7 +509,9 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
                         dqkv, delta, PATH_AUTO, s));
   // QKV projection
   FAX_TRY(hand_over(&SideStream::dqkv));
-  const bool with_input = group && (!dh1_out || apart(dh1, dy)) && gemm_group_input_supported(all, 4, dqkv1);
+  // dh1 over dy, which the first weight gradient reads: not in one launch with it then, and behind it
+  const bool over_dy = dh1_out && !apart(dh1, dy);
+  const bool with_input = group && !over_dy && gemm_group_input_supported(all, 4, dqkv1);
   if (with_input && !side) {
     FAX_TRY(gemm_group_input(all, 4, dqkv1, PART_BOTH, s));
   } else if (group) {
@@ -518,6 +520,7 @@ static int block_bwd_impl(const FaxBlockDims& d, const FaxBlockTensors& p, const
   } else if (att) {
     FAX_TRY(gemm_group(all + 2, 2, sw));
   }
+  if (side && over_dy) FAX_HIP(hipStreamWaitEvent(s, side->w2_done, 0));
   if (!with_input) FAX_TRY(layer(wqkv, dqkv1, group || att));
   else if (side) FAX_TRY(gemm_group_input(all, 4, dqkv1, PART_INPUT, s));
   // LN1 and the residual branch: dx = dx1 + LN1'(dh1).  dx may be the buffer dy came in: the weight gradient that reads dy

@@ -99,6 +99,17 @@ def test_same_bits_on_one_and_two_streams_and_over_dy(i):
             assert torch.equal(got[k], want[k]), (k, flags, over, dh1)
 
 
+# dh1 may take dy's place on two streams too; attention's two weight gradients together or apart besides the shapes above
+@pytest.mark.parametrize("sh", [s for s, streams in SHAPES if streams == 2] + [
+    BlockShape(B=4, S=777, D=512, H=8, dh=64, F=2048, dtype="bf16", sigma_w=0.02), BlockShape(B=8, S=512, D=1024, H=16, dh=64, F=4096, dtype="bf16", sigma_w=0.02)])
+def test_dh1_over_dy_on_two_streams(sh):
+    assert fax.fax_block_bwd_streams(dims_of(sh)) == 2
+    s = _Pass(sh, 30)
+    want, got = s.backward(fax.FAX_FLAG_SINGLE_STREAM, dh1="dy"), s.backward(0, dh1="dy")
+    for k in want:
+        assert torch.equal(got[k], want[k]), k
+
+
 @pytest.mark.parametrize("i", range(len(SHAPES)))
 def test_launches(i):
     """One launch of all weight gradients; on one stream it does the input gradient's work too, on two that has a launch on the CUs left over."""
