@@ -1,14 +1,16 @@
 """fp32 weight and input gradient of a layer in one launch, and both LayerNorms' folds in one: blocks whose products take every
 pairing of the small tile classes, sizes at and beside tile edges, gradients added onto given ones.
 
-Bar: that of the fp32 block (max-norm relative 1e-5 per tensor); with gradients added, one fp32 rounding of the sum more."""
+Bar: that of the fp32 block (max-norm relative 1e-5 per tensor); with gradients added, one fp32 rounding of the sum more.  And the bits of the same
+products in launches of their own."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2204_06514_amd as fax
 from oracle import transformer as orc
 from workloads import BlockShape, make_block_inputs, PARAM_NAMES
-from helpers import run_block, err, dims_of
+from helpers import DEV, run_block, err, dims_of, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +60,30 @@ def test_block_gradients(i, accumulate):
             report["d" + k] = err(got, g[k], "f32")
     bad = {k: v for k, v in report.items() if not v <= 1e-5}
     assert not bad, (bad, report)
+
+
+def _product(ta, tb, a, b):
+    """float64 arrays of fp32 values -> their product by fax_gemm."""
+    (K, M), N = (a.shape, b.shape[1]) if ta else (a.shape[::-1], b.shape[0])
+    c = torch.empty((M, N), dtype=torch.float32, device=DEV)
+    fax.fax_gemm(fax.FAX_F32, ta, tb, M, N, K, to_dev(a, "f32"), a.shape[1], to_dev(b, "f32"), b.shape[1], c, N, c_f32=ta)
+    return to_np(c)
+
+
+@pytest.mark.parametrize("i", range(len(SHAPES)))
+def test_bits_of_the_products_by_themselves(i):
+    sh = SHAPES[i][0]
+    p, x, dy = make_block_inputs(sh, seed=i, generic=True)
+    fax.fax_timing_enable(1)
+    try:
+        out = run_block(sh, p, x, dy)
+        rows = {r["name"]: r["launches"] for r in fax.fax_timing_report(64)}
+    finally:
+        fax.fax_timing_enable(0)
+    assert rows.get("gemm_f32_pair", 0) == (0 if i == len(SHAPES) - 1 else 4), rows
+    s, b, g = out["saved"], out["bwd"], out["grads"]
+    dy = dy.reshape(sh.T, sh.D)
+    for name, act, grad in (("w2", s["a"], dy), ("w1", s["h2"], b["du"]), ("wo", s["ctx"], b["dx1"]), ("wqkv", s["h1"], b["dqkv"])):
+        assert np.array_equal(g[name], _product(1, 0, act, grad)), name
+    for name, grad, w in (("dh2", b["du"], "w1"), ("dctx", b["dx1"], "wo"), ("dh1", b["dqkv"], "wqkv")):
+        assert np.array_equal(b[name], _product(0, 1, grad, p[w])), name
