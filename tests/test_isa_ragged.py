@@ -40,3 +40,15 @@ def test_loss_gemm_loads_are_waited_for_and_nothing_goes_to_scratch(tmp_path):
     assert n == 3, n   # whole and masked 256 x 256 tiles, the strip's 256 x 128
     assert not bad, {k: v[:3] for k, v in bad.items()}
     assert not re.search(r"^\s*scratch_", text, re.M)
+
+
+def test_grouped_gemm_loads_are_waited_for(tmp_path):
+    text = _assembly(tmp_path, os.path.join(CSRC, "kernels_gemm_group.hip"))
+    n, bad = scan(text)
+    assert n == 8, n   # two tile classes, whole and masked, stored and added to
+    assert not bad, {k: v[:3] for k, v in bad.items()}
+    # the same with an input gradient: whatever its width, 256 rows of A in either part, which is what the name of the other kernel says
+    text = re.sub(r"_ZN3fax23gemm_group_input_kernelI(?!Li256ELi)", "_ZN3fax23gemm_group_input_kernelILi256ELi", text)
+    n, bad = scan(text, r"_ZN3fax23gemm_group_input_kernel")
+    assert n == 8, n   # two widths, whole and masked, stored and added to
+    assert not bad, {k: v[:3] for k, v in bad.items()}
