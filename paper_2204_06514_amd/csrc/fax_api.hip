@@ -409,8 +409,10 @@ static BwdPlan bwd_plan(const FaxBlockDims& d) {
   //   on one stream: 2048 tokens x 1024 293 and 272, with F 3072 279 and 248, an eighth's share of 2048 tokens x 2048 302 and 281, 8192 x 1024 820 and 787;
   //   on two, weight gradients of 140 to 350 us: 6144 x 1024 797 and 762, 7500 x 1024 1242 and 1167, 12288 x 1024 1183 and 1110,
   //     5555 x 1000 868 and 828, 8192 x 1024 with half the heads 713 and 666;  or the feed-forward's input gradients whole rounds: 4096 x 2048 with a
-  //     quarter of the heads, F 2048, 471 and 429, 16384 x 1024 1651 and 1588;  beyond the line within 2 %: 4096 x 1024 465 and 455, 3000 x 1000 495 and 492, 4096 x 768 with
-  //     F 6144 484 and 492.
+  //     quarter of the heads, F 2048, 471 and 429, 16384 x 1024 1651 and 1588;  shorter ones gain 2 % or lose it: 4096 x 1024 465 and 455, 3000 x 1000 495 and
+  //     492, 4096 x 768 with F 6144 484 and 492;  longer ones without whole rounds go either way, and nothing in the sizes says which: 15360 x 1024 with a
+  //     quarter of the heads 999 and 1029, 18432 x 1024 1329 and 1363, 64768 x 1024 with a sixteenth 3532 and 3834, but 29184 x 896 2687 and 2563, 18816 x 896 with F 3328
+  //     1984 and 1899.
   double group_us;
   const bool one_launch =
       gemm_group_input_pays(w, 4, in[3], &group_us) && (rounds || (group_us >= 140.0 && group_us < 350.0) || (gemm_fill(in[0]).rounds && gemm_fill(in[1]).rounds));

@@ -7,9 +7,9 @@ import paper_2204_06514_amd as fax
 
 @pytest.mark.parametrize("B,S,D,H,F,streams", [
     (8, 1024, 1024, 16, 4096, 1),    # weight gradients in one launch, input gradients 32 x 8 tiles of 256 x 128
-    (8, 2048, 1024, 8, 4096, 2),     # in four launches beside input gradients of 64 x 4 tiles of 256 x 256: 1649 us, in two on one stream 1701
+    (8, 2048, 1024, 8, 4096, 2),     # in one launch beside QKV's input gradient, those of the feed-forward 64 x 16 and 64 x 4 tiles of 256 x 256: 1588 us; four launches 1649, two on one stream 1701
     (8, 512, 1024, 16, 4096, 2),     # in two launches, smaller tiles, 312 us
-    (2, 1024, 1024, 8, 4096, 1),     # the same at half the tokens: under 200 us
+    (2, 1024, 1024, 8, 4096, 1),     # under 200 us, in one launch with QKV's input gradient
     (4, 777, 512, 8, 2048, 2),       # under 200 us, a fifth idle
     (4, 1024, 512, 8, 2048, 2),      # under 200 us, nothing idle, separate launches
     (8, 2048, 2048, 16, 8192, 2),    # whole rounds only without the weight gradients
