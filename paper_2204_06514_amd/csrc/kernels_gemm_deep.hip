@@ -24,9 +24,9 @@ struct DeepLds {
 // Bound, with one or two workgroups per CU, by the LDS (fragment reads and arriving slabs, about 0.3 us a slab at 128 x 64 where the
 // MFMAs take 0.1) and the barrier; with many more by what the L2s deliver into the LDS, which is where larger tiles take over.
 // Operands from memory, us, against the best of the other classes: 3108 x 512 x 2048 17 (26 at 128 x 128), 2048 x 640 x 5120 39 (58),
-// 3108 x 512 x 32000 211 (327), weight gradients 512 x 512 x 3108 18 (33), 1024 x 1024 x 8192 44 (84, or 32 in four K ranges and a
-// fold), 512 x 256 x 1024 7.4 (11).  From the caches: 3108 x 512 x 2048 13, 2048 x 640 x 5120 27, 512 x 512 x 3108 11, 512 x 256 x 1024 4.9.  The other way round 3000 x 1200 x 4800: 60 at 128 x 64, 88 at 64 x 64, 52 at 128 x 128.
-// 128 x 128 tiles in this form were slower than in the other at every size tried (16-24 waves' worth of LDS reads per slab
+// 3108 x 512 x 32000 225 (336), weight gradients 512 x 512 x 3108 18 (36), 1024 x 1024 x 8192 44 (86, or 32 in four K ranges and a
+// fold), 512 x 256 x 1024 6.2 (11).  From the caches: 3108 x 512 x 2048 13, 2048 x 640 x 5120 27, 512 x 512 x 3108 11, 512 x 256 x 1024 4.9.  The other way round 3000 x 1200 x 4800: 61 at 128 x 64, 81 at 64 x 64, 59 at 128 x 128.
+// 128 x 128 tiles in this form, with tests and cases still in the loop over slabs, were slower than in the other at every size tried (16-24 waves' worth of LDS reads per slab
 // either way, and one workgroup per CU instead of two).
 template <int BM, int BN, bool A_KC, bool B_KC, int EM>
 __device__ __forceinline__ void deep_tile(int block, int M, int N, int K, const bf16_t* __restrict__ A, int lda,

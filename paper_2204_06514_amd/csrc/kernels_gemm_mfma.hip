@@ -36,8 +36,9 @@ static constexpr int kCUs = 256;
 // the L2s' bandwidth, which is what bounds the 256 x 128 class on a full chip (13.7 TB/s into LDS
 // over all CUs: 0.90 us a slab on 256 CUs, 0.78 on 50).  The smaller the tile, the more LDS
 // fragment traffic per flop (4 + 4 fragments per 16 MFMAs at 256^2, 4 + 2 per 8 at 256 x 128,
-// 2 + 2 per 4 at 128^2).  Measured and predicted, us: 3108 x 512 x 2048 41 / 30 / 26 / 17 / 19 in the five classes' order,
-// predicted 43 / 29 / 24 / 17 / 28; 3000 x 1200 x 4800 87 / 63 / 53 / 68 / 88, predicted 90 / 63 / 53 / 65 / 116.
+// 2 + 2 per 4 at 128^2).  Measured and predicted, us, 256 x 192 left out: 3108 x 512 x 2048 40 / 30 / 26 / 17 / 19 in
+// that order, predicted 43 / 29 / 24 / 17 / 28; 3000 x 1200 x 4800 86 / 63 / 59 / 61 / 81, predicted 90 / 63 / 53 / 65 / 116.  From the caches the smaller classes gain more, 38 / 23 / 16 / 13
+// / 16 and 80 / 53 / 45 / 54 / 70: the prices are those of operands from memory.
 struct TileClass {
   int m, n;
   bool deep;  // kernels_gemm_deep.hip: any shape
