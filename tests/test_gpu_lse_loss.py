@@ -58,9 +58,14 @@ def test_loss_is_that_of_stored_logits(T, D, V, B):
     assert abs(got - ref) <= 2e-6 * abs(ref)
 
 
-@pytest.mark.parametrize("T,D,V", [(2048, 64, 2048), (4096, 2048, 8448)])   # 64 tiles; 528, a round of 16 and 32 slabs each
-def test_few_tiles_and_rounds_of_few_keep_the_stored_logits(T, D, V):
-    ms, p, tok, lab = _model(T, D, V, 5)
+def test_few_tiles_keep_the_stored_logits():
+    ms, p, tok, lab = _model(2048, 64, 2048, 5)
+    got, fused = _eval(ms, p, tok, lab)
+    assert not fused and got == run_train_step(ms, p, tok, lab, update=False)[0]
+
+
+def test_long_tiles_in_badly_filled_rounds_keep_the_stored_logits():
+    ms, p, tok, lab = _model(4096, 2048, 8448, 5)   # 528 tiles of 32 slabs, two rounds and 16
     got, fused = _eval(ms, p, tok, lab)
     assert not fused and got == run_train_step(ms, p, tok, lab, update=False)[0]
 
